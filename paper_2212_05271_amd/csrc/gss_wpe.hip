@@ -10,7 +10,7 @@
 //   solve  : R += 1e-10 tr(R)/N I,  G = R^-1 P
 //   apply  : x_t = y_t - G^H ytilde_t  (and lambda for the next iteration, or the complex64 output)
 //
-// Everything up to the output is fp64: R is built from strongly correlated delayed copies of one signal and
+// R and P are accumulated on the fp64 matrix cores.  Everything up to the output is fp64: R is built from strongly correlated delayed copies of one signal and
 // the solve amplifies rounding errors of the sums by its condition number.
 #include "gss_internal.h"
 
@@ -40,8 +40,8 @@ __device__ __forceinline__ void staged_copy(int first, int n, int stride, Load l
     }
   }
 }
+
 constexpr int kWpeTile = 64;                  // frames per LDS window of the covariance kernel
-constexpr int kWpeBlockDoubles = 32;          // a 4 x 4 complex block of R or P per lane
 constexpr double kWpeEpsPowerRel = 1e-10;
 constexpr double kWpeLoadRel = 1e-10;
 
@@ -103,170 +103,340 @@ __global__ __launch_bounds__(kWpeThreads) void wpe_power_kernel(const float2* __
   lam[sf * Tmax + t] = p / (double)D;
 }
 
-// Lane l of the covariance kernel owns one 4 x 4 block: the first nb(nb+1)/2 lanes the blocks (bi >= bj) of
-// the lower triangle of R (nb = ceil(N/4)), the next nb * nbd lanes the blocks of P (nbd = ceil(D/4)).
-__host__ __device__ inline void wpe_block(int l, int nb, int nbd, int& bi, int& bj, bool& is_p, bool& valid) {
-  const int nR = nb * (nb + 1) / 2;
-  valid = l < nR + nb * nbd;
-  if (l < nR) {                                          // row bi of the triangle holds bi + 1 blocks
-    bi = (int)((sqrtf(8.f * (float)l + 1.f) - 1.f) * 0.5f);
-    while (bi * (bi + 1) / 2 > l) --bi;
-    while ((bi + 1) * (bi + 2) / 2 <= l) ++bi;
-    bj = l - bi * (bi + 1) / 2;
-    is_p = false;
-  } else {
-    const int m = valid ? l - nR : 0;
-    bi = m / nbd;
-    bj = m % nbd;
-    is_p = true;
-  }
+// Tiles of the augmented matrix [R | P] (N rows of N + D entries): 16 x 16 complex tiles, nt = ceil(N / 16) tile rows;
+// row p holds the tiles of R from the diagonal on (columns p .. nt - 1; R is Hermitian) and then the ntd = ceil(D / 16)
+// tiles of P (columns nt .. nt + ntd - 1).  A tile is stored as 256 double2 in the order in which the lanes of a
+// wavefront hold it: entry (i, j) at 16 i + j.
+typedef double double4v __attribute__((ext_vector_type(4)));
+constexpr int kTileEntries = 256;
+__host__ __device__ inline int wpe_tile_base(int p, int nt, int ntd) { return p * (nt + ntd) - p * (p - 1) / 2; }
+__host__ __device__ inline int wpe_num_tiles(int nt, int ntd) { return wpe_tile_base(nt, nt, ntd); }
+
+// D += A B of 16 x 4 and 4 x 16 doubles.  Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], and D[l / 16 + 4 v][l % 16]
+// for v = 0..3: entry v of a tile's lane is entry 64 v + l of the tile's storage.
+__device__ __forceinline__ double4v mfma_f64(double a, double b, double4v c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Covariance accumulation.  A workgroup takes a chunk of 64-frame tiles of one (segment, frequency).  Per
-// tile the frames t0-Delta-L+1 .. t0+63 are staged in LDS in DESCENDING time order: then ytilde_t is the
-// contiguous run of N values that starts Delta frames after frame t, and the values of y_t itself sit right
-// before it, whatever D is.  Each lane keeps its 4 x 4 block in registers and adds, frame by frame,
-// (w_t a_i) conj(b_j) for its four row values a and four column values b.  Rows >= N and columns >= N (or
-// >= D) of the last blocks take whatever follows in the window; nothing ever reads them.
-// More than 256 blocks (large arrays): G workgroups per chunk, workgroup g of them takes the blocks
-// 256 g .. 256 g + 255 (blockIdx.x = chunk slot * G + g).
-// part[(blockIdx.x * 32 + j) * 256 + lane]: the 32 doubles (re, im of entry [i][j'], j = (i*4 + j')*2 + {0,1}).
-__global__ __launch_bounds__(kWpeThreads) void wpe_cov_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
-                                                              const double* __restrict__ lam, double* __restrict__ part,
-                                                              int F, int Tmax, int D, int taps, int delay, ChunkMap cmap,
-                                                              int win_elems, int G) {
+// LDS addresses as plain numbers: a read at a register plus a constant number of elements.
+typedef double double2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned lds_address(const void* p) {
+  unsigned a = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+  asm("" : "+v"(a));
+  return a;
+}
+template <class V>
+__device__ __forceinline__ V lds_at(unsigned address, int elem) {
+  return ((const __attribute__((address_space(3))) V*)(uintptr_t)address)[elem];
+}
+
+// Covariance accumulation on the fp64 matrix cores.  A workgroup takes a chunk of 64-frame windows of one (segment,
+// frequency).  Per window the frames t0-Delta-L+1 .. t0+63 are staged in LDS, converted to fp64 once, P >= D values
+// apart: component n = tau D + d of ytilde_t is value d of row t - Delta - tau, so a lane's operand is at a position of
+// its own plus a multiple of the frame.  A wavefront owns TPW tiles and adds, four frames at a time, the tile products
+// sum_t (w_t a_i(t)) conj(b_j(t)).  The complex product takes three real ones, S1 = sum w Re a Re b,
+// S2 = sum w Im a Im b and S3 = sum w (Re a + Im a)(Re b - Im b): the real part is S1 + S2, the imaginary part
+// S3 - S1 + S2.  Lanes of rows or columns >= N (or >= D) repeat the last one; nothing uses their results.
+// Few tiles (small D * taps): `split` wavefronts share their tiles, each takes a part of the window's frames and writes
+// partial sums of its own.  Many tiles (large arrays): G workgroups per chunk (blockIdx.x = chunk slot * G + g).
+// part[((chunk slot * split + part) * tiles + tile) * 256 ..]: the tile's entries.
+//
+// Bound: the fp64 matrix rate.  Vector instructions do not run beside a fp64 matrix instruction of the same SIMD (busy
+// times of the two add up), so the loop is written for few of them: Re - Im is kept in LDS beside the value, the
+// frame pitch is a compile-time constant (operand addresses are one register per tile plus constant offsets for four
+// steps), and the weighted left operand is formed once per tile row.  Measured, 10 taps: 513 x 1560 x 8 440 us (vector
+// FMAs on 4 x 4 blocks: 639 us), 513 x 1500 x 24 3.25 ms (5.42 ms); the matrix cores are busy 80 % of the time.
+template <int P, int TPW>
+__global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
+                                                                 const double* __restrict__ lam, double2* __restrict__ part,
+                                                                 int F, int Tmax, int D, int taps, int delay, ChunkMap cmap,
+                                                                 int G, int split) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  double2* __restrict__ sWin = reinterpret_cast<double2*>(lds_raw);
-  double* __restrict__ sWt = reinterpret_cast<double*>(lds_raw + (size_t)win_elems * sizeof(double2));
+  const int past = delay + taps - 1;
+  const int win_frames = kWpeTile + past;
+  double2* __restrict__ sWin = reinterpret_cast<double2*>(lds_raw);                    // [win_frames][P]
+  double* __restrict__ sDif = reinterpret_cast<double*>(sWin + (size_t)win_frames * P);   // [win_frames][P]: re - im
+  double* __restrict__ sWt = sDif + (size_t)win_frames * P;                               // [kWpeTile]
   double* __restrict__ sRed = sWt + kWpeTile;
 
+  const unsigned slot = blockIdx.x / (unsigned)G;
+  const int g = (int)(blockIdx.x % (unsigned)G);
   long sf;
   int chunk, tpc;
-  chunk_decode(cmap, blockIdx.x / (unsigned)G, sf, chunk, tpc);
+  chunk_decode(cmap, slot, sf, chunk, tpc);
   const int T = clamp_T(T_len, (int)(sf / F), Tmax);
   const int N = D * taps;
-  const int nb = (N + 3) / 4, nbd = (D + 3) / 4;
-  int bi, bj;
-  bool is_p, valid;
-  wpe_block((int)(blockIdx.x % (unsigned)G) * kWpeThreads + (int)threadIdx.x, nb, nbd, bi, bj, is_p, valid);
-  if (!valid) { bi = 0; bj = 0; is_p = false; }
-  const int aoff = delay * D + 4 * bi;
-  const int boff = is_p ? 4 * bj : delay * D + 4 * bj;
+  const int nt = (N + 15) / 16, ntd = (D + 15) / 16;
+  const int n_tiles = wpe_num_tiles(nt, ntd);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int part_of = wave % split;                      // which of the wavefronts on the same tiles
+  const int first = (g * (kWpeThreads / kWave / split) + wave / split) * TPW;   // the wavefront's first tile
+  const int steps = kWpeTile / 4 / split;                // groups of four frames per window (4, 8 or 16)
+
+  // Positions of the tiles' operands in the window: lane (k, i) = (l / 16, l % 16) holds component i of the tile at
+  // frame k of the group.  TPW <= 5 consecutive tiles lie in at most two tile rows (rows get shorter by one from 2 or 3
+  // tiles at the bottom up): the first n0 of them in row p0, the others in the next.
+  const int k4 = lane >> 4, li = lane & 15;
+  int apos0, apos1, n0 = TPW;
+  int bpos[TPW];
+  {
+    const int f0 = past + 4 * steps * part_of + k4;      // window row of the lane's first frame
+    auto delayed = [&](int tile) {
+      int n = 16 * tile + li;
+      n = n < N ? n : N - 1;
+      const int tau = n / D;
+      return (f0 - delay - tau) * P + (n - tau * D);
+    };
+    auto current = [&](int tile) {
+      const int d = 16 * tile + li;
+      return f0 * P + (d < D ? d : D - 1);
+    };
+    int p = 0;
+    while (p + 1 < nt && wpe_tile_base(p + 1, nt, ntd) <= first) ++p;
+    int c = p + first - wpe_tile_base(p, nt, ntd);
+    if (c >= nt + ntd) c = p;                            // (surplus tiles repeat the last row: in bounds, not stored)
+    apos0 = delayed(p);
+    apos1 = apos0;
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+      if (c >= nt + ntd) {                               // the next row of tiles
+        p = p + 1 < nt ? p + 1 : p;
+        c = p;
+        n0 = n0 == TPW ? q : n0;
+        apos1 = delayed(p);
+      }
+      bpos[q] = c < nt ? delayed(c) : current(c - nt);
+      ++c;
+    }
+  }
+  n0 = __builtin_amdgcn_readfirstlane(n0);
 
   const double* __restrict__ lrow = lam + sf * Tmax;
   const double floor_l = kWpeEpsPowerRel * block_max(lrow, T, sRed);
   const float2* __restrict__ Yrow = Y + sf * (long)Tmax * D;
 
-  double ar_[4][4], ai_[4][4];
+  double4v s1[TPW], s2[TPW], s3[TPW];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { ar_[i][j] = 0.0; ai_[i][j] = 0.0; }
+  for (int q = 0; q < TPW; ++q) {
+    s1[q] = double4v{0.0, 0.0, 0.0, 0.0};
+    s2[q] = double4v{0.0, 0.0, 0.0, 0.0};
+    s3[q] = double4v{0.0, 0.0, 0.0, 0.0};
+  }
 
   const int tile_end = (T + kWpeTile - 1) / kWpeTile;
   const int tile_lo = chunk * tpc;
   const int tile_hi = tile_lo + tpc < tile_end ? tile_lo + tpc : tile_end;
-  const int win_frames = kWpeTile + delay + taps - 1;
+  const unsigned n_valid = (unsigned)(T * D);            // (values of a row: always below 2^31, its bytes below 2^32)
+  // where the thread's first value of a window goes, and the step to its next one (kWpeThreads values further on)
+  const int r0 = (int)threadIdx.x / D, d0 = (int)threadIdx.x - r0 * D;
+  const int step_d = kWpeThreads % D, step_pos = kWpeThreads / D * P + step_d;
+  const char* __restrict__ Ybytes = reinterpret_cast<const char*>(Yrow);
+  // The power of the thread's frame of a window, requested one window ahead, and with it one value of every 128-byte line
+  // of the window's new frames, so that the staging loads find them in cache: the wavefronts of a compute unit tend to
+  // reach the staging together, and nothing hides a memory latency there.
+  auto power_of = [&](int t) { return threadIdx.x < kWpeTile && t < T ? lrow[t] : 0.0; };
+  double l_next = tile_lo < tile_hi ? power_of(tile_lo * kWpeTile + (int)threadIdx.x) : 0.0;
   for (int tile = tile_lo; tile < tile_hi; ++tile) {
     const int t0 = tile * kWpeTile;
-    const int tmax = t0 + kWpeTile - 1;
     __syncthreads();                                    // the previous tile's window is no longer read
-    staged_copy<4, float2>(
-        threadIdx.x, win_elems, kWpeThreads,
-        [&](int e) {
-          const int r = e / D, d = e - r * D;
-          const int t = tmax - r;
-          return (r < win_frames && t >= 0 && t < T) ? Yrow[(long)t * D + d] : make_float2(0.f, 0.f);
-        },
-        [&](int e, float2 v) { sWin[e] = make_double2((double)v.x, (double)v.y); });   // converted once here, not at every use
+    {
+      const unsigned g0 = (unsigned)((t0 - past) * D);  // the window's frames are one run of memory
+      int d = d0, pos = r0 * P + d0;
+      staged_copy<8, float2>(
+          threadIdx.x, win_frames * D, kWpeThreads,
+          [&](int m) {
+            const unsigned e = g0 + (unsigned)m;
+            return e < n_valid ? *reinterpret_cast<const float2*>(Ybytes + e * 8u) : make_float2(0.f, 0.f);
+          },
+          [&](int, float2 v) {
+            const double re = v.x, im = v.y;              // converted once here, not at every use
+            sWin[pos] = make_double2(re, im);
+            sDif[pos] = re - im;
+            d += step_d;
+            pos += step_pos;
+            if (d >= D) {
+              d -= D;
+              pos += P - D;
+            }
+          });
+    }
     if (threadIdx.x < kWpeTile) {
-      const int t = t0 + threadIdx.x;
       double w = 0.0;
-      if (t < T) {
-        const double l = fmax(lrow[t], floor_l);
+      if (t0 + (int)threadIdx.x < T) {
+        const double l = fmax(l_next, floor_l);
         w = l > 0.0 ? 1.0 / l : 0.0;                   // all-zero bin: no weight, R = 0, bin left unchanged
       }
       sWt[threadIdx.x] = w;
     }
-    __syncthreads();
-#pragma unroll 2
-    for (int tt = 0; tt < kWpeTile; ++tt) {
-      const int base = (kWpeTile - 1 - tt) * D;
-      const double w = sWt[tt];
-      double war[4], wai[4], br[4], bim[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double2 a = sWin[base + aoff + i];
-        const double2 b = sWin[base + boff + i];
-        war[i] = w * a.x;
-        wai[i] = w * a.y;
-        br[i] = b.x;
-        bim[i] = b.y;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {                   // a conj(b)
-          ar_[i][j] = fma(war[i], br[j], fma(wai[i], bim[j], ar_[i][j]));
-          ai_[i][j] = fma(wai[i], br[j], fma(-war[i], bim[j], ai_[i][j]));
-        }
+    l_next = power_of(t0 + kWpeTile + (int)threadIdx.x);
+    float touched = 0.f;
+    {
+      const unsigned e = (unsigned)((t0 + kWpeTile) * D) + threadIdx.x * 16u;
+      if ((int)threadIdx.x < kWpeTile * D / 16 && e < n_valid) touched = *reinterpret_cast<const float*>(Ybytes + e * 8u);
     }
+    __syncthreads();
+    // LDS addresses the compiler cannot take apart again (it would add the base at every use)
+    unsigned a0 = lds_address(sWin + apos0), a1 = lds_address(sWin + apos1), aw = lds_address(sWt + 4 * steps * part_of + k4);
+    unsigned ab[TPW], ad[TPW];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+      ab[q] = lds_address(sWin + bpos[q]);
+      ad[q] = lds_address(sDif + bpos[q]);
+    }
+    // The operands of the next group of four frames are requested between the matrix instructions of the current one,
+    // each tile's as soon as its own are used: two wavefronts that share a SIMD run in step, so reads issued in a
+    // block of their own would leave the matrix core idle in both.  (Behind the last group: that group's again.)
+    double w[2];
+    double2v x0[2], x1[2], b[TPW];
+    double bd[TPW];
+    auto fetch_row = [&](auto UI) {
+      constexpr int u = decltype(UI)::value;
+      w[u & 1] = lds_at<double>(aw, 4 * u);
+      x0[u & 1] = lds_at<double2v>(a0, 4 * P * u);
+      x1[u & 1] = lds_at<double2v>(a1, 4 * P * u);
+    };
+    auto fetch_col = [&](auto QI, auto UI) {
+      constexpr int q = decltype(QI)::value, u = decltype(UI)::value;
+      b[q] = lds_at<double2v>(ab[q], 4 * P * u);
+      bd[q] = lds_at<double>(ad[q], 4 * P * u);
+    };
+    fetch_row(std::integral_constant<int, 0>{});
+    static_for<0, TPW>([&](auto QI) { fetch_col(QI, std::integral_constant<int, 0>{}); });
+    for (int s = 0; s < steps; s += 4) {
+      const unsigned on = s + 4 < steps ? 1u : 0u;
+      static_for<0, 4>([&](auto UI) {
+        constexpr int u = UI.value;
+        constexpr std::integral_constant<int, (u + 1) & 3> next{};
+        double ar = w[u & 1] * x0[u & 1].x, ai = w[u & 1] * x0[u & 1].y, as = ar + ai;
+        double w1 = w[u & 1];
+        const double2v y1 = x1[u & 1];
+        static_for<0, TPW>([&](auto QI) {
+          constexpr int q = QI.value;
+          int row1 = n0;
+          asm volatile("" : "+s"(row1));                // (tested anew: kept as booleans the tests cost vector instructions)
+          if (q > 0 && q == row1) {                     // (wave-uniform) the next tile row's operand
+            asm volatile("" : "+v"(w1));                // (keeps this a branch: six selects at every tile otherwise)
+            ar = w1 * y1.x;
+            ai = w1 * y1.y;
+            as = ar + ai;
+          }
+          s1[q] = mfma_f64(ar, b[q].x, s1[q]);
+          s2[q] = mfma_f64(ai, b[q].y, s2[q]);
+          s3[q] = mfma_f64(as, bd[q], s3[q]);
+          if constexpr (u == 3) {
+            ab[q] += on * 16 * P * sizeof(double2);
+            ad[q] += on * 16 * P * sizeof(double);
+          }
+          fetch_col(QI, next);
+          if constexpr (q == 0) {
+            if constexpr (u == 3) {
+              aw += on * 16 * sizeof(double);
+              a0 += on * 16 * P * sizeof(double2);
+              a1 += on * 16 * P * sizeof(double2);
+            }
+            fetch_row(next);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      });
+    }
+    asm volatile("" ::"v"(touched));                    // (the load above is not dropped)
   }
-  double* __restrict__ out = part + (size_t)blockIdx.x * kWpeBlockDoubles * kWpeThreads + threadIdx.x;
+  double2* __restrict__ out = part + ((size_t)slot * split + part_of) * n_tiles * kTileEntries + lane;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int q = 0; q < TPW; ++q)
+    if (first + q < n_tiles) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      out[(size_t)((i * 4 + j) * 2 + 0) * kWpeThreads] = ar_[i][j];
-      out[(size_t)((i * 4 + j) * 2 + 1) * kWpeThreads] = ai_[i][j];
+      for (int v = 0; v < 4; ++v)
+        out[(size_t)(first + q) * kTileEntries + v * kWave] =
+            make_double2(s1[q][v] + s2[q][v], (s3[q][v] - s1[q][v]) + s2[q][v]);
     }
 }
 
-// Assemble.  Four workgroups per (segment, frequency), one per row of the 4 x 4 blocks: lane l sums row
-// blockIdx % 4 of its block over the chunks and writes the four entries, with the Hermitian mirror image,
-// into the augmented matrix A[sf] = [R | P] (N rows of N + D complex doubles) in global memory.  (Little
-// work per thread on purpose: the kernel is a gather and scatter that wants many wavefronts in flight; one
-// workgroup per bin took 85 us on 513 bins, four take 42 us, eight 47 us.)
-__global__ __launch_bounds__(kWpeThreads) void wpe_assemble_kernel(const double* __restrict__ part, double2* __restrict__ A,
-                                                                   int D, int taps, ChunkMap cmap, int G) {
-  const long sf = blockIdx.x / (unsigned)(4 * G);
-  const int i = blockIdx.x & 3;
-  const int g = (int)(blockIdx.x % (unsigned)(4 * G)) >> 2;      // group of 256 blocks (large arrays: G > 1)
-  const int N = D * taps;
-  const int W = N + D;
-  const int nb = (N + 3) / 4, nbd = (D + 3) / 4;
-  int count;
-  const long wg0 = chunk_base(cmap, sf, count);
-  double2* __restrict__ M = A + sf * (long)N * W;
+// Workgroups per compute unit that the chunks are planned for: two wavefronts per SIMD keep its matrix core busy, and
+// finer chunks would only add partial sums (more workgroups may be resident).
+constexpr int kWpeCovPerCu = 2;
 
-  int bi, bj;
-  bool is_p, valid;
-  wpe_block(g * kWpeThreads + (int)threadIdx.x, nb, nbd, bi, bj, is_p, valid);
-  if (!valid) return;
-  double v[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = 0.0;
-  for (int c = 0; c < count; ++c) {
-    const double* __restrict__ src =
-        part + (((size_t)(wg0 + c) * G + g) * kWpeBlockDoubles + (size_t)i * 8) * kWpeThreads + threadIdx.x;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] += src[(size_t)q * kWpeThreads];
-  }
-  const int a = 4 * bi + i;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int b = 4 * bj + j;
-    const double re = v[2 * j], im = v[2 * j + 1];
-    if (is_p) {
-      if (a < N && b < D) M[(long)a * W + N + b] = make_double2(re, im);
-    } else if (a < N && b < N) {
-      if (bi != bj || i > j) {                           // below the diagonal: the entry and its mirror image
-        M[(long)a * W + b] = make_double2(re, im);
-        M[(long)b * W + a] = make_double2(re, -im);
-      } else if (i == j) {
-        M[(long)a * W + a] = make_double2(re, 0.0);
-      }
+// Tiles per wavefront (1..5), wavefronts that share the same tiles, workgroups per chunk.
+struct WpeTiling { int tpw, split, groups; };
+// Chosen by the time of one 64-frame window: TPW tiles of 48 matrix instructions of 64 cycles each in every wavefront,
+// divided among the wavefronts that share them, plus about 1500 cycles of staging, for each of the groups.
+inline WpeTiling wpe_tiling(int n_tiles) {
+  WpeTiling best{1, 1, 1};
+  long best_cost = -1;
+  for (int tpw = 5; tpw >= 1; --tpw) {
+    const int waves = (n_tiles + tpw - 1) / tpw;
+    const int split = waves == 1 ? 4 : waves == 2 ? 2 : 1;
+    const int groups = waves <= 2 ? 1 : (waves + 3) / 4;
+    const long cost = (long)groups * (tpw * 3072 / split + 1500);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = WpeTiling{tpw, split, groups};
     }
+  }
+  return best;
+}
+typedef void (*wpe_cov_fn)(const float2*, const int32_t*, const double*, double2*, int, int, int, int, int, ChunkMap, int, int);
+template <int P>
+inline wpe_cov_fn wpe_cov_tpw(int tpw) {
+  switch (tpw) {
+    case 1: return wpe_cov_kernel<P, 1>;
+    case 2: return wpe_cov_kernel<P, 2>;
+    case 3: return wpe_cov_kernel<P, 3>;
+    case 4: return wpe_cov_kernel<P, 4>;
+    default: return wpe_cov_kernel<P, 5>;
+  }
+}
+// The kernel for D channels and its frame pitch.
+inline wpe_cov_fn wpe_cov_of(int D, int tpw, int& pitch) {
+  pitch = D <= 2 ? 2 : D <= 4 ? 4 : (D + 7) / 8 * 8;
+  switch (pitch) {
+    case 2: return wpe_cov_tpw<2>(tpw);
+    case 4: return wpe_cov_tpw<4>(tpw);
+    case 8: return wpe_cov_tpw<8>(tpw);
+    case 16: return wpe_cov_tpw<16>(tpw);
+    case 24: return wpe_cov_tpw<24>(tpw);
+    default: return wpe_cov_tpw<32>(tpw);
+  }
+}
+inline int wpe_cov_lds(int pitch, int taps, int delay) {
+  return (kWpeTile + delay + taps - 1) * pitch * 3 * (int)sizeof(double) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double);
+}
+// Largest window accepted (64 KB for the values and the weights).
+inline bool wpe_window_fits(int D, int taps, int delay) {
+  return ((kWpeTile + delay + taps) * D + 8) * (int)sizeof(double2) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double) <=
+         64 * 1024;
+}
+
+// Assemble.  One workgroup per tile: sums it over the chunks and writes its entries, with the Hermitian mirror image,
+// into the augmented matrix A[sf] = [R | P] (N rows of N + D complex doubles) in global memory.
+__global__ __launch_bounds__(kWpeThreads) void wpe_assemble_kernel(const double2* __restrict__ part, double2* __restrict__ A,
+                                                                   int D, int taps, ChunkMap cmap, int split, int n_tiles) {
+  const long sf = blockIdx.x / (unsigned)n_tiles;
+  const int tile = (int)(blockIdx.x % (unsigned)n_tiles);
+  const int N = D * taps, W = N + D;
+  const int nt = (N + 15) / 16, ntd = (D + 15) / 16;
+  int p = 0;
+  while (p + 1 < nt && wpe_tile_base(p + 1, nt, ntd) <= tile) ++p;
+  const int c = p + tile - wpe_tile_base(p, nt, ntd);
+  int count;
+  const long slot0 = chunk_base(cmap, sf, count) * split;
+  count *= split;
+  double2 v = make_double2(0.0, 0.0);
+  for (int q = 0; q < count; ++q) {
+    const double2 x = part[((size_t)(slot0 + q) * n_tiles + tile) * kTileEntries + threadIdx.x];
+    v.x += x.x;
+    v.y += x.y;
+  }
+  double2* __restrict__ M = A + sf * (long)N * W;
+  const int a = 16 * p + (int)(threadIdx.x >> 4);
+  const int b = 16 * (c < nt ? c : c - nt) + (int)(threadIdx.x & 15);
+  if (c >= nt) {
+    if (a < N && b < D) M[(long)a * W + N + b] = v;
+  } else if (a < N && b < N && a <= b) {
+    M[(long)a * W + b] = a == b ? make_double2(v.x, 0.0) : v;
+    if (a < b) M[(long)b * W + a] = make_double2(v.x, -v.y);
   }
 }
 
@@ -867,46 +1037,48 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
   const int N = D * taps;
   const int W = N + D;
   const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
-  const int nb = (N + 3) / 4, nbd = (D + 3) / 4;
-  const int G = (nb * (nb + 1) / 2 + nb * nbd + kWpeThreads - 1) / kWpeThreads;
-  const int win_elems = (kWpeTile + delay + taps) * D + 8;
-  const int cov_lds = (int)(win_elems * sizeof(double2) + (kWpeTile + kWpeThreads / kWave) * sizeof(double));
+  const int n_tiles = wpe_num_tiles((N + 15) / 16, (D + 15) / 16);
+  const WpeTiling til = wpe_tiling(n_tiles);
+  int pitch;
+  const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
+  const int G = til.groups;
+  const int cov_lds = wpe_cov_lds(pitch, taps, delay);
   const int fb_apply = D > 24 ? 128 : 256, fb_power = 64;
   const int apitch = D | 1;
   const int apply_lds = (int)((size_t)(fb_apply + delay + taps - 1) * apitch * sizeof(float2));
   const int solve_lds = (int)(((size_t)(N + D) * kLsPitch + (size_t)kLsNB * D) * sizeof(double2));
-  if (apply_lds > 64 * 1024 || cov_lds > 64 * 1024 || solve_lds > 64 * 1024) return GSS_EUNSUPPORTED;
+  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay) || solve_lds > 64 * 1024) return GSS_EUNSUPPORTED;
   if (hipFuncSetAttribute((const void*)wpe_solve_large_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, solve_lds) !=
           hipSuccess ||
       hipFuncSetAttribute((const void*)wpe_apply_large_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           apply_lds) != hipSuccess ||
       hipFuncSetAttribute((const void*)wpe_apply_large_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           apply_lds) != hipSuccess ||
-      hipFuncSetAttribute((const void*)wpe_cov_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, cov_lds) != hipSuccess)
+      hipFuncSetAttribute((const void*)cov, hipFuncAttributeMaxDynamicSharedMemorySize, cov_lds) != hipSuccess)
     return GSS_EHIP;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, wpe_cov_kernel, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
   // G workgroups per chunk: the chunks are planned for a G-th of the resident workgroups
-  long slots = (long)ctx->num_cu * per_cu / G;
+  long slots = (long)ctx->num_cu * (per_cu < kWpeCovPerCu ? per_cu : kWpeCovPerCu) / G;
   if (slots < 1) slots = 1;
   const ChunkMap cmap = plan_chunk_map(slots, n_sf, tiles, 1, 0, true);
   const long wgs = chunk_map_wgs(cmap, n_sf);
   const long bps_apply = (Tmax + fb_apply - 1) / fb_apply, bps_power = (Tmax + fb_power - 1) / fb_power;
-  if (wgs * G > 0x7fffffffL || n_sf * bps_power + 8 > 0x7fffffffL || n_sf * 4 * G > 0x7fffffffL) return GSS_EUNSUPPORTED;
+  if (wgs * G > 0x7fffffffL || n_sf * bps_power + 8 > 0x7fffffffL || n_sf * n_tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
 
   size_t o = 0;
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
   const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 1024, 256);   // + read-ahead padding
-  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * G * kWpeBlockDoubles * kWpeThreads * sizeof(double), 256);
+  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
   const size_t off_a = o;    o = gss_align_up(o + (size_t)n_sf * N * W * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   double* lam = (double*)(base + off_lam);
   double2* Gc = (double2*)(base + off_g);
-  double* part = (double*)(base + off_part);
+  double2* part = (double2*)(base + off_part);
   double2* A = (double2*)(base + off_a);
 
   const dim3 block(kWpeThreads);
@@ -916,10 +1088,11 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
                      (int)bps_power, nb_power, px_power, fb_power);
   for (int it = 0; it < iters; ++it) {
     gss_profile_begin(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_cov_kernel, dim3((unsigned)(wgs * G)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps,
-                       delay, cmap, win_elems, G);
+    hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * G)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay, cmap,
+                       G, til.split);
     gss_profile_end(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * 4 * G)), block, 0, st, part, A, D, taps, cmap, G);
+    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * n_tiles)), block, 0, st, part, A, D, taps, cmap, til.split,
+                       n_tiles);
     hipLaunchKernelGGL(wpe_solve_large_kernel, dim3((unsigned)n_sf), dim3(kLsThreads), solve_lds, st, A, Gc, ctx->status, D,
                        taps);
     if (it + 1 < iters)
@@ -940,33 +1113,36 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   const int N = D * taps;
   const int W = N + D;
   const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
-  // covariance kernel: window of 64 + delay + taps - 1 frames, plus room for the overrun of the last blocks
-  const int win_elems = (kWpeTile + delay + taps) * D + 8;
-  const int cov_lds = (int)(win_elems * sizeof(double2) + (kWpeTile + kWpeThreads / kWave) * sizeof(double));
+  const int n_tiles = wpe_num_tiles((N + 15) / 16, (D + 15) / 16);
+  const WpeTiling til = wpe_tiling(n_tiles);
+  int pitch;
+  const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
+  const int cov_lds = wpe_cov_lds(pitch, taps, delay);
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, wpe_cov_kernel, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
-  const ChunkMap cmap = plan_chunk_map((long)ctx->num_cu * per_cu, n_sf, tiles, 1, 0, true);
+  const ChunkMap cmap = plan_chunk_map((long)ctx->num_cu * (per_cu < kWpeCovPerCu ? per_cu : kWpeCovPerCu) / til.groups,
+                                       n_sf, tiles, 1, 0, true);
   const long wgs = chunk_map_wgs(cmap, n_sf);
   const long blocks_per_sf = (Tmax + kWpeThreads - 1) / kWpeThreads;
-  if (wgs > 0x7fffffffL || n_sf * blocks_per_sf + 8 > 0x7fffffffL || n_sf * 4 > 0x7fffffffL) return GSS_EUNSUPPORTED;
+  if (wgs > 0x7fffffffL || n_sf * blocks_per_sf + 8 > 0x7fffffffL || n_sf * n_tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
   // apply kernel: row pitch odd for even D
   const int apitch = D | 1;
   const int apply_lds = (int)((size_t)(kWpeThreads + delay + taps - 1) * apitch * sizeof(float2));
-  if (apply_lds > 64 * 1024 || cov_lds > 64 * 1024) return GSS_EUNSUPPORTED;
+  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
 
   size_t o = 0;
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
   const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 256, 256);   // + read-ahead padding
-  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * kWpeBlockDoubles * kWpeThreads * sizeof(double), 256);
+  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
   const size_t off_a = o;    o = gss_align_up(o + (size_t)n_sf * N * W * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   double* lam = (double*)(base + off_lam);
   double2* Gc = (double2*)(base + off_g);
-  double* part = (double*)(base + off_part);
+  double2* part = (double2*)(base + off_part);
   double2* A = (double2*)(base + off_a);
 
   const dim3 block(kWpeThreads);
@@ -976,10 +1152,11 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
                      per_xcd, kWpeThreads);
   for (int it = 0; it < iters; ++it) {
     gss_profile_begin(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_cov_kernel, dim3((unsigned)wgs), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay,
-                       cmap, win_elems, 1);
+    hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * til.groups)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay,
+                       cmap, til.groups, til.split);
     gss_profile_end(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * 4)), block, 0, st, part, A, D, taps, cmap, 1);
+    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * n_tiles)), block, 0, st, part, A, D, taps, cmap, til.split,
+                       n_tiles);
     hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, A, Gc, ctx->status, D, taps);
     if (it + 1 < iters)
       hipLaunchKernelGGL((wpe_apply_kernel<D, false>), frame_grid, block, apply_lds, st, Y, T_len, Gc, lam, X, F, Tmax, taps,
@@ -999,11 +1176,7 @@ extern "C" int gss_wpe(gss_ctx* ctx, const float* Y, const int32_t* T_len, int S
   if (!ctx || !Y || !X || Y == X) return GSS_EINVAL;
   if (S <= 0 || F <= 0 || Tmax <= 0 || D <= 0 || taps <= 0 || delay <= 0 || iters < 0) return GSS_EINVAL;
   if (D > GSS_WPE_LARGE_MAX_D || (long)D * taps > GSS_WPE_LARGE_MAX_N || delay > 64) return GSS_EUNSUPPORTED;
-  bool small = D <= GSS_WPE_MAX_D && (long)D * taps <= GSS_WPE_MAX_N;
-  if (small) {
-    const int N = D * taps, nb = (N + 3) / 4, nbd = (D + 3) / 4;
-    if (nb * (nb + 1) / 2 + nb * nbd > kWpeThreads) small = false;               // more than one block per lane
-  }
+  const bool small = D <= GSS_WPE_MAX_D && (long)D * taps <= GSS_WPE_MAX_N;
   if (hipSetDevice(ctx->device) != hipSuccess) return GSS_EHIP;
   hipStream_t st = (hipStream_t)stream;
   const float2* Yc = (const float2*)Y;

@@ -136,6 +136,19 @@ def test_wpe_large_ragged_and_degenerate(env):
     _check(env, Y, np.array([0, 5], dtype=np.int32), 6, 2, 3)
 
 
+@pytest.mark.parametrize("D,taps,delay,T", [(1, 16, 1, 150), (1, 17, 64, 190), (2, 16, 3, 129), (3, 11, 2, 128), (2, 24, 2, 191),
+                                             (7, 7, 1, 192), (4, 16, 2, 193), (5, 13, 2, 260), (8, 8, 2, 200), (16, 5, 2, 200),
+                                             (17, 1, 1, 130), (17, 2, 2, 200), (24, 2, 2, 200), (25, 4, 2, 300), (1, 97, 2, 330),
+                                             (11, 9, 2, 330), (32, 1, 1, 150)])
+def test_wpe_tile_edges(env, D, taps, delay, T):
+    """Unknowns around the multiples of the 16 x 16 tiles (D * taps = 16, 17, 32, 33, 48, ...), one and two column tiles
+    of the right-hand side, wavefronts that share their tiles, frame pitches wider than D, and lengths around the
+    multiples of the 64-frame window."""
+    Y, _, _ = env["synth"].reverberant_stft(F=3, T=T, D=D, order=min(taps, 6), delay=min(delay, 3), seed=D * 100 + taps)
+    _check(env, Y[None], None, taps, delay, 2)
+    assert env["ctx"].get_status() == 0
+
+
 def test_wpe_config3_shape_sampled_bins(env):
     """24 channels at configuration 3's size (513 x 1500 x 24, 10 taps, delay 2, 3 iterations): all bins on the
     GPU, a sample of them on the oracle."""
