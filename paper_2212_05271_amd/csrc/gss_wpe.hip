@@ -409,162 +409,345 @@ inline bool wpe_window_fits(int D, int taps, int delay) {
          64 * 1024;
 }
 
-// Assemble.  One workgroup per tile: sums it over the chunks and writes its entries, with the Hermitian mirror image,
-// into the augmented matrix A[sf] = [R | P] (N rows of N + D complex doubles) in global memory.
-__global__ __launch_bounds__(kWpeThreads) void wpe_assemble_kernel(const double2* __restrict__ part, double2* __restrict__ A,
-                                                                   int D, int taps, ChunkMap cmap, int split, int n_tiles) {
-  const long sf = blockIdx.x / (unsigned)n_tiles;
-  const int tile = (int)(blockIdx.x % (unsigned)n_tiles);
-  const int N = D * taps, W = N + D;
-  const int nt = (N + 15) / 16, ntd = (D + 15) / 16;
-  int p = 0;
-  while (p + 1 < nt && wpe_tile_base(p + 1, nt, ntd) <= tile) ++p;
-  const int c = p + tile - wpe_tile_base(p, nt, ntd);
+// ----------------------------------------------------------------------------------------------
+// Solve R G = P (R loaded on its diagonal), one workgroup of four wavefronts per (segment, frequency).
+//
+// Blocked Cholesky factorisation R = U^H U on the 16 x 16 tiles, left-looking by tile rows, the tiles of P carried along
+// as further columns: for tile row p
+//   S(p, i) = A(p, i) - sum_{j < p} U(j, p)^H U(j, i)   for every column i >= p,
+//   V = U(p, p)^-1 from S(p, p) = U(p, p)^H U(p, p)     (one wavefront),
+//   U(p, i) = V^H S(p, i)                               for i > p,
+// which leaves Z = U^-H P in the columns of P; then the back substitution G(p) = V_p Z(p), Z(i) -= U(i, p) G(p) for
+// i < p.  A tile in a wavefront's registers, as the matrix instructions leave it (entry (l / 16 + 4 v, l % 16) in lane l),
+// is at once the left operand of X^H Y and the right operand of X Y, so the factorisation needs no transposition; the
+// back substitution reads the tiles transposed.
+// Without pivoting (R is Hermitian positive definite; a pivot <= 1e-300 is floored and flagged).  Rows and columns >= N
+// of the last tile row are the identity's.
+// part: the covariance kernel's tiles; chunks are added up as they are read, and the first chunk's tiles are overwritten (a
+// workgroup's tiles stay in L2).  Out: Gc[sf][a][d] = conj(G[a][d]).
+//
+// Bound: for small systems the chain of the 16 sweeps per tile row (LDS round trip and reciprocal, about 400 cycles each),
+// for large ones the tile products.  Three workgroups per compute unit (two: 40 % more time).  Measured, 513 bins: 63 us for
+// 80 unknowns and 8 right-hand sides, 0.79 ms for 240 and 24 (assembled matrix and Gauss-Jordan in the registers of a
+// workgroup: 228 us; 8-column Cholesky in global memory: 4.0 ms).
+// ----------------------------------------------------------------------------------------------
+constexpr int kSolveThreads = 256;
+constexpr int kSolveMaxSlots = 4;             // partial sums per problem that the solve kernel adds up itself
+
+// Problems with many partial sums (the ones left over after the last full round of workgroups are cut into small chunks):
+// their tiles are added up here, one workgroup per tile, into the first chunk's.  (One workgroup of the solve kernel
+// would read all of them alone: 24 chunks of the last of 513 bins took 1.4 ms at 24 channels, everything else 0.65 ms.)
+__global__ __launch_bounds__(kTileEntries) void wpe_sum_chunks_kernel(double2* __restrict__ part, ChunkMap cmap, long sf0,
+                                                                      int split, int n_tiles) {
+  const long sf = sf0 + blockIdx.x / (unsigned)n_tiles;
   int count;
   const long slot0 = chunk_base(cmap, sf, count) * split;
   count *= split;
-  double2 v = make_double2(0.0, 0.0);
-  for (int q = 0; q < count; ++q) {
-    const double2 x = part[((size_t)(slot0 + q) * n_tiles + tile) * kTileEntries + threadIdx.x];
-    v.x += x.x;
-    v.y += x.y;
+  const size_t stride = (size_t)n_tiles * kTileEntries;
+  double2* __restrict__ t = part + (size_t)slot0 * stride + (size_t)(blockIdx.x % (unsigned)n_tiles) * kTileEntries + threadIdx.x;
+  double2 sum = t[0];
+  for (int q0 = 1; q0 < count; q0 += 4) {
+    double2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = q0 + u < count ? t[(q0 + u) * stride] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      sum.x += v[u].x;
+      sum.y += v[u].y;
+    }
   }
-  double2* __restrict__ M = A + sf * (long)N * W;
-  const int a = 16 * p + (int)(threadIdx.x >> 4);
-  const int b = 16 * (c < nt ? c : c - nt) + (int)(threadIdx.x & 15);
-  if (c >= nt) {
-    if (a < N && b < D) M[(long)a * W + N + b] = v;
-  } else if (a < N && b < N && a <= b) {
-    M[(long)a * W + b] = a == b ? make_double2(v.x, 0.0) : v;
-    if (a < b) M[(long)b * W + a] = make_double2(v.x, -v.y);
-  }
+  t[0] = sum;
 }
 
-// Solve.  One workgroup of 16 x 32 threads per (segment, frequency) keeps the whole augmented matrix in
-// registers: thread (i, j) owns rows i, i+16, ... and columns j, j+32, j+64.  Gauss-Jordan elimination without
-// pivoting (R + loading is Hermitian positive definite) and without scaling the pivot rows: after sweep p
-// column p is never touched again, so at the end row a of the right-hand part divided by pivot a is row a of
-// G.  Per sweep the owners publish the pivot row and the pivot column of the NEXT sweep in LDS (two
-// buffers, one barrier per sweep); every thread reads the values for its rows and columns from there.
-// Out: Gc[sf][a][d] = conj(G[a][d]), the coefficient that multiplies ytilde_a in the prediction of y_d.
-constexpr int kSolveTR = 16, kSolveTC = 32;
-constexpr int kSolveThreads = kSolveTR * kSolveTC;
-constexpr int kSolveKR = (GSS_WPE_MAX_N + kSolveTR - 1) / kSolveTR;                      // rows per thread
-constexpr int kSolveMC = (GSS_WPE_MAX_N + GSS_WPE_MAX_D + kSolveTC - 1) / kSolveTC;      // columns per thread
-constexpr int kSolveRowBuf = kSolveMC * kSolveTC, kSolveColBuf = kSolveKR * kSolveTR;
+struct CTile {                                            // the lane's entries of a complex tile
+  double4v re, im;
+};
+__device__ __forceinline__ CTile tile_load(const double2* __restrict__ t, int lane) {
+  CTile c;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double2 x = t[lane + kWave * v];
+    c.re[v] = x.x;
+    c.im[v] = x.y;
+  }
+  return c;
+}
+__device__ __forceinline__ CTile tile_load_transposed(const double2* __restrict__ t, int lane) {
+  CTile c;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double2 x = t[16 * (lane & 15) + (lane >> 4) + 4 * v];
+    c.re[v] = x.x;
+    c.im[v] = x.y;
+  }
+  return c;
+}
+__device__ __forceinline__ void tile_store(double2* __restrict__ t, const CTile& c, int lane) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) t[lane + kWave * v] = make_double2(c.re[v], c.im[v]);
+}
+// s +- conj(x) y over the tiles' common rows (x as loaded: X^H Y)
+template <bool SUB>
+__device__ __forceinline__ void tile_xhy(CTile& s, const CTile& x, const CTile& y) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double xr = SUB ? -x.re[k] : x.re[k], xi = SUB ? -x.im[k] : x.im[k];
+    s.re = mfma_f64(xr, y.re[k], s.re);
+    s.im = mfma_f64(xr, y.im[k], s.im);
+    s.re = mfma_f64(xi, y.im[k], s.re);
+    s.im = mfma_f64(-xi, y.re[k], s.im);
+  }
+}
+// s +- x y with x loaded transposed (X Y)
+template <bool SUB>
+__device__ __forceinline__ void tile_xy(CTile& s, const CTile& x, const CTile& y) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double xr = SUB ? -x.re[k] : x.re[k], xi = SUB ? -x.im[k] : x.im[k];
+    s.re = mfma_f64(xr, y.re[k], s.re);
+    s.im = mfma_f64(xr, y.im[k], s.im);
+    s.re = mfma_f64(-xi, y.im[k], s.re);
+    s.im = mfma_f64(xi, y.re[k], s.im);
+  }
+}
+__device__ __forceinline__ CTile tile_zero() {
+  const double4v z = {0.0, 0.0, 0.0, 0.0};
+  return CTile{z, z};
+}
 
-__global__ __launch_bounds__(kSolveThreads) void wpe_solve_kernel(const double2* __restrict__ A, double2* __restrict__ Gc,
-                                                                uint32_t* __restrict__ status, int D, int taps) {
-  __shared__ double2 sRow[2][kSolveRowBuf];
-  __shared__ double2 sCol[2][kSolveColBuf];
-  __shared__ double sPiv[kSolveColBuf];
+__global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __restrict__ part, double2* __restrict__ Gc,
+                                                                     uint32_t* __restrict__ status, int D, int taps,
+                                                                     ChunkMap cmap, int split) {
+  __shared__ double2 sG[2][(GSS_WPE_LARGE_MAX_D + 15) / 16][kTileEntries];
+  __shared__ double2 sRow[16];
+  __shared__ double sPiv[16];
+  __shared__ double sRed[kSolveThreads / kWave];
   const long sf = blockIdx.x;
   const int N = D * taps;
-  const int W = N + D;
-  const int j = threadIdx.x % kSolveTC, i = threadIdx.x / kSolveTC;
+  const int nt = (N + 15) / 16, ntd = (D + 15) / 16, nc = nt + ntd;
+  const int n_tiles = wpe_num_tiles(nt, ntd);
+  int count;
+  const long slot0 = chunk_base(cmap, sf, count) * split;
+  count *= split;
+  if (count > kSolveMaxSlots) count = 1;                   // (wpe_sum_chunks_kernel has added them up)
+  double2* __restrict__ A = part + (size_t)slot0 * n_tiles * kTileEntries;       // the tiles of the first chunk
+  const size_t slot_stride = (size_t)n_tiles * kTileEntries;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int k4 = lane >> 4, li = lane & 15;
   double2* __restrict__ out = Gc + sf * (long)N * D;
-  const double2* __restrict__ M = A + sf * (long)N * W;
-  double tre[kSolveKR][kSolveMC], tim[kSolveKR][kSolveMC];
+  // tile (p, i) of [A | P], later [U | Z]
+  auto tile_at = [&](int p, int i) { return A + (size_t)(wpe_tile_base(p, nt, ntd) + i - p) * kTileEntries; };
+
+  // trace of R
   double tr = 0.0;
-#pragma unroll
-  for (int k = 0; k < kSolveKR; ++k)
-#pragma unroll
-    for (int m = 0; m < kSolveMC; ++m) {
-      const int r = i + kSolveTR * k, c = j + kSolveTC * m;
-      double2 v = make_double2(0.0, 0.0);
-      if (r < N && c < W) v = M[r * W + c];
-      if (r == c && r < N) tr += v.x;
-      tre[k][m] = v.x;
-      tim[k][m] = v.y;
-    }
-  // trace of R: every diagonal entry is held by exactly one thread
+  for (int a = threadIdx.x; a < N; a += kSolveThreads) {
+    const double2* __restrict__ t = tile_at(a >> 4, a >> 4) + 17 * (a & 15);
+    for (int q = 0; q < count; ++q) tr += t[q * slot_stride].x;
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
-  if ((threadIdx.x & (kWave - 1)) == 0) sPiv[threadIdx.x / kWave] = tr;
+  if (lane == 0) sRed[wave] = tr;
   __syncthreads();
   tr = 0.0;
-  for (int w = 0; w < kSolveThreads / kWave; ++w) tr += sPiv[w];
-  __syncthreads();                                       // sPiv is reused for the pivots
-  if (!(tr > 0.0)) {                                     // no frame has a past (or silence): G = 0
+#pragma unroll
+  for (int w = 0; w < kSolveThreads / kWave; ++w) tr += sRed[w];
+  if (!(tr > 0.0)) {                                       // no frame has a past (or silence): G = 0
     for (int e = threadIdx.x; e < N * D; e += kSolveThreads) out[e] = make_double2(0.0, 0.0);
     return;
   }
   const double load = kWpeLoadRel * tr / (double)N;
-#pragma unroll
-  for (int k = 0; k < kSolveKR; ++k)
-#pragma unroll
-    for (int m = 0; m < kSolveMC; ++m)
-      if (i + kSolveTR * k == j + kSolveTC * m) tre[k][m] += load;
-  // Row q lives in register row q / TR of the threads with i == q % TR, column q in register column q / TC
-  // of the threads with j == q % TC: the register index is the same for the whole workgroup, so it is
-  // picked with scalar branches and only the lane test is a vector operation.
-  auto publish = [&](int q, int buf) {                   // row q and column q of the current matrix
-    const int kq = q / kSolveTR, mq = q / kSolveTC;
-    const bool row_owner = i == q % kSolveTR, col_owner = j == q % kSolveTC;
-#pragma unroll
-    for (int k = 0; k < kSolveKR; ++k)
-      if (k == kq && row_owner) {
-#pragma unroll
-        for (int m = 0; m < kSolveMC; ++m) sRow[buf][j + kSolveTC * m] = make_double2(tre[k][m], tim[k][m]);
-      }
-#pragma unroll
-    for (int m = 0; m < kSolveMC; ++m)
-      if (m == mq && col_owner) {
-#pragma unroll
-        for (int k = 0; k < kSolveKR; ++k) sCol[buf][i + kSolveTR * k] = make_double2(tre[k][m], tim[k][m]);
-      }
-  };
-  publish(0, 0);
-  __syncthreads();
   const double tiny = 1e-300;
-  for (int p = 0; p < N; ++p) {
-    const int buf = p & 1;
-    double piv = sRow[buf][p].x;
-    if (!(piv > tiny)) {
-      if (threadIdx.x == 0) atomicOr(status, GSS_STATUS_NONPD_WPE);
-      piv = tiny;
-    }
-    if (threadIdx.x == 0) sPiv[p] = piv;
-    const double inv = rcp_f64(piv);
-    double fr[kSolveKR], fi[kSolveKR];
-    const int kp = p / kSolveTR;
-    const double keep = i == p % kSolveTR ? 0.0 : inv;   // the pivot row itself stays
-#pragma unroll
-    for (int k = 0; k < kSolveKR; ++k) {
-      const double2 v = sCol[buf][i + kSolveTR * k];     // rows >= N hold zeros, and so does their column entry
-      const double sc = k == kp ? keep : inv;
-      fr[k] = v.x * sc;
-      fi[k] = v.y * sc;
+
+  // A(p, i): the chunks' sum, loaded and completed to the identity
+  auto load_a = [&](int p, int i) {
+    CTile c = tile_load(tile_at(p, i), lane);
+    for (int q = 1; q < count; ++q) {
+      const CTile x = tile_load(tile_at(p, i) + q * slot_stride, lane);
+      c.re += x.re;
+      c.im += x.im;
     }
 #pragma unroll
-    for (int m = 0; m < kSolveMC; ++m) {
-      const int c = j + kSolveTC * m;
-      if (c > p && c < W) {
-        const double2 pc = sRow[buf][c];
-#pragma unroll
-        for (int k = 0; k < kSolveKR; ++k) {             // row r -= f_r * row p
-          tre[k][m] = fma(-fr[k], pc.x, fma(fi[k], pc.y, tre[k][m]));
-          tim[k][m] = fma(-fr[k], pc.y, fma(-fi[k], pc.x, tim[k][m]));
-        }
+    for (int v = 0; v < 4; ++v) {
+      const int a = 16 * p + k4 + 4 * v, b = 16 * i + li;
+      const bool in = a < N && (i >= nt || b < N);
+      if (i == p && a == b) {
+        c.re[v] = in ? c.re[v] + load : 1.0;
+        c.im[v] = 0.0;
+      } else if (!in) {
+        c.re[v] = 0.0;
+        c.im[v] = 0.0;
       }
     }
-    if (p + 1 < N) publish(p + 1, buf ^ 1);
+    return c;
+  };
+  // S[c] -= sum over j < n of U(j, p)^H U(j, i0 + c), c = 0 and 1 (PAIR: they share the left operands)
+  auto update = [&](int p, int i0, int n, auto PAIR, CTile (&S)[2]) {
+    constexpr bool pair = decltype(PAIR)::value;
+    if (n <= 0) return;
+    CTile x = tile_load(tile_at(0, p), lane), y0 = tile_load(tile_at(0, i0), lane), y1 = tile_zero();
+    if constexpr (pair) y1 = tile_load(tile_at(0, i0 + 1), lane);
+    for (int j = 0; j < n; ++j) {
+      CTile xn = x, yn0 = y0, yn1 = y1;
+      if (j + 1 < n) {                                    // the next operands are requested ahead
+        xn = tile_load(tile_at(j + 1, p), lane);
+        yn0 = tile_load(tile_at(j + 1, i0), lane);
+        if constexpr (pair) yn1 = tile_load(tile_at(j + 1, i0 + 1), lane);
+      }
+      tile_xhy<true>(S[0], x, y0);
+      if constexpr (pair) tile_xhy<true>(S[1], x, y1);
+      x = xn;
+      y0 = yn0;
+      if constexpr (pair) y1 = yn1;
+    }
+  };
+  constexpr std::integral_constant<bool, false> one{};
+  constexpr std::integral_constant<bool, true> two{};
+
+  CTile diag = tile_zero();                               // (wavefront 0) S(p, p)
+  if (wave == 0) diag = load_a(0, 0);
+  for (int p = 0; p < nt; ++p) {
+    // Wavefront 0 factorises S(p, p); the others form S(p, i) for the columns behind the diagonal, and the next diagonal
+    // tile up to the terms that exist already.  As far as the factorisation (about five tile products long) leaves
+    // time, wavefront 0 takes columns too.
+    const int m = nc - p - 1;
+    int m0 = p > 0 ? (p * (m - 3) - 20) / (4 * p) : 0;
+    m0 = m0 < 0 ? 0 : m0;
+    int lo = nc - m0, hi = nc;
+    if (wave > 0) {
+      lo = p + 1 + (m - m0) * (wave - 1) / 3;
+      hi = p + 1 + (m - m0) * wave / 3;
+    }
+    if (wave == 0) {
+      CTile S = diag;
+      // S = U^H U by elimination in place: after sweep r, row r of S is row r of the unscaled U from the diagonal on, and
+      // the entries below the diagonal of columns <= r hold the inverse of the unit lower factor.  Row r goes through LDS;
+      // column r is its conjugate.
+      static_for<0, 16>([&](auto RI) {
+        constexpr int r = RI.value, vr = r >> 2;
+        if (k4 == (r & 3)) sRow[li] = make_double2(S.re[vr], S.im[vr]);
+        wave_lds_sync();
+        double piv = sRow[r].x;
+        const double2 rj = sRow[li];
+        double2 ri[4];
+#pragma unroll
+        for (int v = vr; v < 4; ++v) ri[v] = sRow[k4 + 4 * v];
+        wave_lds_sync();
+        if (!(piv > tiny)) {
+          if (lane == 0) atomicOr(status, GSS_STATUS_NONPD_WPE);
+          piv = tiny;
+        }
+        if (lane == 0) sPiv[r] = piv;
+        const double inv = rcp_f64(piv);
+        const double cr = rj.x * inv, ci = rj.y * inv;     // row r over the pivot
+        const bool col = li == r;
+#pragma unroll
+        for (int v = vr; v < 4; ++v) {
+          // rows below r: S(i, j) -= conj(S(r, i)) S(r, j) / pivot, and -conj(S(r, i)) / pivot in column r
+          const double nr = col ? -inv * ri[v].x : fma(-ri[v].x, cr, fma(-ri[v].y, ci, S.re[v]));
+          const double ni = col ? inv * ri[v].y : fma(-ri[v].x, ci, fma(ri[v].y, cr, S.im[v]));
+          if (v > vr || k4 > (r & 3)) {
+            S.re[v] = nr;
+            S.im[v] = ni;
+          }
+        }
+      });
+      wave_lds_sync();
+      // V = U^-1: the inverse of the unit lower factor, rows scaled by pivot^-1/2, conjugated and transposed
+      double2* __restrict__ dst = tile_at(p, p);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = k4 + 4 * v;
+        const double isq = 1.0 / sqrt(sPiv[i]);
+        const double wr = li < i ? S.re[v] : li == i ? 1.0 : 0.0, wi = li < i ? S.im[v] : 0.0;
+        dst[16 * li + i] = make_double2(wr * isq, -wi * isq);
+      }
+    }
+    if (wave == 3 && p + 1 < nt) {
+      CTile S[2] = {load_a(p + 1, p + 1), tile_zero()};
+      update(p + 1, p + 1, p, one, S);
+      tile_store(tile_at(p + 1, p + 1), S[0], lane);
+    }
+    for (int i = lo; i < hi; i += 2) {
+      CTile S[2] = {load_a(p, i), tile_zero()};
+      if (i + 1 < hi) {
+        S[1] = load_a(p, i + 1);
+        update(p, i, p, two, S);
+        tile_store(tile_at(p, i + 1), S[1], lane);
+      } else {
+        update(p, i, p, one, S);
+      }
+      tile_store(tile_at(p, i), S[0], lane);
+    }
+    __syncthreads();
+    {
+      const CTile V = tile_load(tile_at(p, p), lane);
+      const int i0 = p + 1 + wave;
+      CTile S = i0 < nc ? tile_load(tile_at(p, i0), lane) : tile_zero();
+      if (wave == 0 && p + 1 < nt) diag = tile_load(tile_at(p + 1, p + 1), lane);
+      for (int i = i0; i < nc; i += 4) {
+        CTile Sn = S;
+        if (i + 4 < nc) Sn = tile_load(tile_at(p, i + 4), lane);
+        CTile U = tile_zero();
+        tile_xhy<false>(U, V, S);
+        tile_store(tile_at(p, i), U, lane);
+        if (i == p + 1 && i < nt) tile_xhy<true>(diag, U, U);   // (wavefront 0) the last term of the next diagonal tile
+        S = Sn;
+      }
+    }
     __syncthreads();
   }
+
+  // Back substitution.  Wavefront i mod 4 owns tile row i of Z: it subtracts U(i, p) G(p) for every p > i, and forms G(i) as
+  // soon as the last of them is in; G goes to the others through LDS (two buffers, one barrier per tile row).
+  auto finish = [&](int p, int c, const CTile& V, const CTile& Z) {
+    CTile G = tile_zero();
+    tile_xy<false>(G, V, Z);
+    tile_store(sG[p & 1][c], G, lane);
 #pragma unroll
-  for (int m = 0; m < kSolveMC; ++m) {
-    const int c = j + kSolveTC * m;
-    if (c >= N && c < W) {
-#pragma unroll
-      for (int k = 0; k < kSolveKR; ++k) {
-        const int r = i + kSolveTR * k;
-        if (r < N) {
-          const double inv = rcp_f64(sPiv[r]);
-          out[r * D + (c - N)] = make_double2(tre[k][m] * inv, -tim[k][m] * inv);
+    for (int v = 0; v < 4; ++v) {
+      const int a = 16 * p + k4 + 4 * v, d = 16 * c + li;
+      if (a < N && d < D) out[(long)a * D + d] = make_double2(G.re[v], -G.im[v]);
+    }
+  };
+  if (wave == ((nt - 1) & 3)) {
+    const CTile V = tile_load_transposed(tile_at(nt - 1, nt - 1), lane);
+    for (int c = 0; c < ntd; ++c) finish(nt - 1, c, V, tile_load(tile_at(nt - 1, nt + c), lane));
+  }
+  __syncthreads();
+  for (int p = nt - 1; p > 0; --p) {
+    const int i0 = p - 1 - ((p - 1 - wave) & 3);          // the wavefront's last row above p (negative: none)
+    for (int c = 0; c < ntd && i0 >= 0; ++c) {
+      const CTile G = tile_load(sG[p & 1][c], lane);
+      CTile V = tile_zero();
+      if (i0 == p - 1) V = tile_load_transposed(tile_at(i0, i0), lane);
+      CTile X = tile_load_transposed(tile_at(i0, p), lane), Z = tile_load(tile_at(i0, nt + c), lane);
+      for (int i = i0; i >= 0; i -= 4) {
+        CTile Xn = X, Zn = Z;
+        if (i >= 4) {                                     // the next operands are requested ahead
+          Xn = tile_load_transposed(tile_at(i - 4, p), lane);
+          Zn = tile_load(tile_at(i - 4, nt + c), lane);
         }
+        tile_xy<true>(Z, X, G);
+        if (i == p - 1) finish(i, c, V, Z);
+        else tile_store(tile_at(i, nt + c), Z, lane);
+        X = Xn;
+        Z = Zn;
       }
     }
+    __syncthreads();
   }
+}
+
+inline void wpe_launch_solve(double2* part, double2* Gc, uint32_t* status, long n_sf, int D, int taps, const ChunkMap& cmap,
+                             int split, hipStream_t st) {
+  const int n_tiles = wpe_num_tiles((D * taps + 15) / 16, (D + 15) / 16);
+  const bool all = cmap.c_main * split > kSolveMaxSlots;
+  const long sf0 = all ? 0 : cmap.n_main;
+  if ((all || cmap.c_tail * split > kSolveMaxSlots) && sf0 < n_sf)
+    hipLaunchKernelGGL(wpe_sum_chunks_kernel, dim3((unsigned)((n_sf - sf0) * n_tiles)), dim3(kTileEntries), 0, st, part, cmap, sf0,
+                       split, n_tiles);
+  hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, part, Gc, status, D, taps, cmap, split);
 }
 
 // Apply: lane = frame.  The frames t0-Delta-L+1 .. t0+255 of the bin are staged in LDS (row pitch odd in
@@ -711,231 +894,9 @@ __global__ __launch_bounds__(kWpeThreads) void wpe_copy_kernel(const float2* __r
 }
 
 // ----------------------------------------------------------------------------------------------
-// Large arrays (D > 8 or D * taps > 80; up to D = 32, D * taps = 320).  The covariance, assemble and power
-// kernels above serve them too (several groups of 256 blocks); the linear system no longer fits the
-// registers of a workgroup, so it is solved in global memory, and the prediction is applied by a kernel
-// with a run-time channel count.
+// Large arrays (D > 8 or D * taps > 80; up to D = 32, D * taps = 320).  The covariance, solve and power kernels above serve
+// them too; the prediction is applied by a kernel with a run-time channel count.
 // ----------------------------------------------------------------------------------------------
-constexpr int kLsNB = 8;                      // columns per panel of the blocked factorisation
-constexpr int kLsPitch = kLsNB + 1;           // LDS row pitch of a panel (in double2)
-constexpr int kLsThreads = 256;
-
-__device__ __forceinline__ double2 cmul_conj(double2 a, double2 b) {          // a conj(b)
-  return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
-
-// Solve for large systems: one workgroup per (segment, frequency), the augmented matrix [R | P] stays in
-// global memory (it is L2-resident while its workgroup runs).  Blocked right-looking Cholesky factorisation
-// R + loading = L L^H, panels of 8 columns staged in LDS; the right-hand side rides along as D extra rows of
-// the virtual lower-triangular matrix V (row N + d of V is column d of P, conjugated: V = [R ; P^H]), so that
-// after the last panel the storage of P holds L^-1 P.  Then a blocked back substitution L^H G = L^-1 P.
-// No pivoting (the matrix is Hermitian positive definite; a pivot <= 1e-300 is floored and flagged).
-// Out: Gc[sf][a][d] = conj(G[a][d]).
-__global__ __launch_bounds__(kLsThreads) void wpe_solve_large_kernel(double2* __restrict__ A, double2* __restrict__ Gc,
-                                                                     uint32_t* __restrict__ status, int D, int taps) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  const int N = D * taps;
-  const int W = N + D;
-  const int R = N + D;                                    // rows of V
-  double2* __restrict__ sPanel = reinterpret_cast<double2*>(lds_raw);         // [R][kLsPitch]: V(r, k0 + c)
-  double2* __restrict__ sRhs = sPanel + (size_t)R * kLsPitch;                 // [kLsNB][D]: back substitution
-  __shared__ double sRed[kLsThreads / kWave];
-  const long sf = blockIdx.x;
-  double2* __restrict__ M = A + sf * (long)N * W;
-  double2* __restrict__ out = Gc + sf * (long)N * D;
-  const int tid = threadIdx.x;
-  // V(r, c), c < N: r < N: M[r][c]; r >= N: conj(M[c][N + r - N])
-  auto ldv = [&](int r, int c) -> double2 {
-    if (r < N) return M[(long)r * W + c];
-    double2 v = M[(long)c * W + N + (r - N)];
-    v.y = -v.y;
-    return v;
-  };
-  auto stv = [&](int r, int c, double2 v) {
-    if (r < N) {
-      M[(long)r * W + c] = v;
-    } else {
-      v.y = -v.y;
-      M[(long)c * W + N + (r - N)] = v;
-    }
-  };
-
-  double tr = 0.0;
-  for (int a = tid; a < N; a += kLsThreads) tr += M[(long)a * W + a].x;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
-  if ((tid & (kWave - 1)) == 0) sRed[tid / kWave] = tr;
-  __syncthreads();
-  tr = 0.0;
-  for (int w = 0; w < kLsThreads / kWave; ++w) tr += sRed[w];
-  if (!(tr > 0.0)) {                                     // no frame has a past (or silence): G = 0
-    for (int e = tid; e < N * D; e += kLsThreads) out[e] = make_double2(0.0, 0.0);
-    return;
-  }
-  const double load = kWpeLoadRel * tr / (double)N;
-  const double tiny = 1e-300;
-
-  for (int k0 = 0; k0 < N; k0 += kLsNB) {
-    const int bs = N - k0 < kLsNB ? N - k0 : kLsNB;
-    // the panel: rows k0 .. R-1, columns k0 .. k0+bs-1 (of the diagonal block only the lower triangle is used)
-    for (int e = tid; e < (R - k0) * bs; e += kLsThreads) {
-      const int r = k0 + e / bs, c = e % bs;
-      double2 v = make_double2(0.0, 0.0);
-      if (r >= k0 + c) v = ldv(r, k0 + c);
-      if (r == k0 + c) { v.x += load; v.y = 0.0; }
-      sPanel[r * kLsPitch + c] = v;
-    }
-    __syncthreads();
-    // Cholesky of the diagonal block, thread (i, j) of the first 64
-    {
-      const int i = tid >> 3, j = tid & 7;
-      const bool on = tid < 64 && i < bs && j < bs;
-      for (int p = 0; p < bs; ++p) {
-        if (tid == 0) {
-          double d = sPanel[(k0 + p) * kLsPitch + p].x;
-          if (!(d > tiny)) {
-            d = tiny;
-            atomicOr(status, GSS_STATUS_NONPD_WPE);
-          }
-          sPanel[(k0 + p) * kLsPitch + p] = make_double2(sqrt(d), 0.0);
-        }
-        __syncthreads();
-        if (on && j == p && i > p) {
-          const double inv = 1.0 / sPanel[(k0 + p) * kLsPitch + p].x;
-          double2 v = sPanel[(k0 + i) * kLsPitch + p];
-          sPanel[(k0 + i) * kLsPitch + p] = make_double2(v.x * inv, v.y * inv);
-        }
-        __syncthreads();
-        if (on && j > p && i >= j) {
-          const double2 a = sPanel[(k0 + i) * kLsPitch + p], b = sPanel[(k0 + j) * kLsPitch + p];
-          const double2 m = cmul_conj(a, b);
-          double2 v = sPanel[(k0 + i) * kLsPitch + j];
-          sPanel[(k0 + i) * kLsPitch + j] = make_double2(v.x - m.x, v.y - m.y);
-        }
-        __syncthreads();
-      }
-    }
-    // rows below the block: x L_kk^H = a, one row per thread; the factor goes back to memory
-    for (int r = k0 + tid; r < R; r += kLsThreads) {
-      if (r < k0 + bs) {
-        for (int c = 0; c <= r - k0; ++c) stv(r, k0 + c, sPanel[r * kLsPitch + c]);
-        continue;
-      }
-      double2 x[kLsNB];
-#pragma unroll
-      for (int c = 0; c < kLsNB; ++c) {
-        if (c < bs) {
-          double2 acc = sPanel[r * kLsPitch + c];
-#pragma unroll
-          for (int m = 0; m < kLsNB; ++m)
-            if (m < c) {
-              const double2 t = cmul_conj(x[m], sPanel[(k0 + c) * kLsPitch + m]);
-              acc.x -= t.x;
-              acc.y -= t.y;
-            }
-          const double inv = 1.0 / sPanel[(k0 + c) * kLsPitch + c].x;
-          x[c] = make_double2(acc.x * inv, acc.y * inv);
-        } else {
-          x[c] = make_double2(0.0, 0.0);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < kLsNB; ++c)
-        if (c < bs) {
-          sPanel[r * kLsPitch + c] = x[c];
-          stv(r, k0 + c, x[c]);
-        }
-    }
-    __syncthreads();
-    // trailing update: V(r, c) -= sum_m L(r, m) conj(L(c, m)) for k0+bs <= c < N, c <= r < R
-    const int c_lo = k0 + bs;
-    const int ncols = N - c_lo;
-    if (ncols > 0) {
-      const int nrows = R - c_lo;
-      // four entries per thread and step: their loads are issued together (the entries of different threads and
-      // steps are distinct, which the compiler cannot know)
-      constexpr int U = 4;
-      for (int e0 = tid; e0 < nrows * ncols; e0 += U * kLsThreads) {
-        int rr[U], cc[U];
-        bool on[U];
-        double2 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int e = e0 + u * kLsThreads;
-          rr[u] = c_lo + e / ncols;
-          cc[u] = c_lo + e % ncols;
-          on[u] = e < nrows * ncols && cc[u] <= rr[u];
-          v[u] = make_double2(0.0, 0.0);
-          if (on[u]) v[u] = ldv(rr[u], cc[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (!on[u]) continue;
-          double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-          for (int m = 0; m < kLsNB; ++m)
-            if (m < bs) {
-              const double2 t = cmul_conj(sPanel[rr[u] * kLsPitch + m], sPanel[cc[u] * kLsPitch + m]);
-              acc.x += t.x;
-              acc.y += t.y;
-            }
-          v[u].x -= acc.x;
-          v[u].y -= acc.y;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (on[u]) stv(rr[u], cc[u], v[u]);
-      }
-    }
-    __syncthreads();
-  }
-
-  // back substitution L^H G = Z with Z = L^-1 P in the storage of P (M[c][N + d]); G overwrites it
-  const int last = (N - 1) / kLsNB * kLsNB;
-  for (int k0 = last; k0 >= 0; k0 -= kLsNB) {
-    const int bs = N - k0 < kLsNB ? N - k0 : kLsNB;
-    for (int e = tid; e < bs * bs; e += kLsThreads) {     // L_kk (lower triangle)
-      const int i = e / bs, j = e % bs;
-      if (j <= i) sPanel[i * kLsPitch + j] = M[(long)(k0 + i) * W + k0 + j];
-    }
-    for (int e = tid; e < bs * D; e += kLsThreads) sRhs[e] = M[(long)(k0 + e / D) * W + N + e % D];
-    __syncthreads();
-    if (tid < D) {                                         // one right-hand side per thread
-      for (int c = bs - 1; c >= 0; --c) {
-        double2 acc = sRhs[c * D + tid];
-        for (int m = c + 1; m < bs; ++m) {                 // conj(L(m, c)) g_m
-          const double2 lmc = sPanel[m * kLsPitch + c], g = sRhs[m * D + tid];
-          acc.x -= lmc.x * g.x + lmc.y * g.y;
-          acc.y -= lmc.x * g.y - lmc.y * g.x;
-        }
-        const double inv = 1.0 / sPanel[c * kLsPitch + c].x;
-        acc.x *= inv;
-        acc.y *= inv;
-        sRhs[c * D + tid] = acc;
-        M[(long)(k0 + c) * W + N + tid] = acc;
-      }
-    }
-    __syncthreads();
-    // rows above the block: Z(r, d) -= sum_m conj(L(k0 + m, r)) G(k0 + m, d)
-    for (int e = tid; e < k0 * D; e += kLsThreads) {
-      const int r = e % k0, d = e / k0;
-      double2 acc = make_double2(0.0, 0.0);
-      for (int m = 0; m < bs; ++m) {
-        const double2 lmr = M[(long)(k0 + m) * W + r], g = sRhs[m * D + d];
-        acc.x += lmr.x * g.x + lmr.y * g.y;
-        acc.y += lmr.x * g.y - lmr.y * g.x;
-      }
-      double2 z = M[(long)r * W + N + d];
-      M[(long)r * W + N + d] = make_double2(z.x - acc.x, z.y - acc.y);
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < N * D; e += kLsThreads) {
-    const double2 g = M[(long)(e / D) * W + N + e % D];
-    out[e] = make_double2(g.x, -g.y);
-  }
-}
-
 // Apply for large arrays: lane = frame, fb frames per workgroup (+ the needed past) staged in LDS as they
 // came; a lane holds all D outputs (up to 32) and walks the D * taps components of ytilde_t; the
 // coefficients are the same for all lanes and come through the scalar path, 8 outputs at a time.  A row of
@@ -1035,7 +996,6 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
                   int iters, float2* X, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int N = D * taps;
-  const int W = N + D;
   const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
   const int n_tiles = wpe_num_tiles((N + 15) / 16, (D + 15) / 16);
   const WpeTiling til = wpe_tiling(n_tiles);
@@ -1046,11 +1006,8 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
   const int fb_apply = D > 24 ? 128 : 256, fb_power = 64;
   const int apitch = D | 1;
   const int apply_lds = (int)((size_t)(fb_apply + delay + taps - 1) * apitch * sizeof(float2));
-  const int solve_lds = (int)(((size_t)(N + D) * kLsPitch + (size_t)kLsNB * D) * sizeof(double2));
-  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay) || solve_lds > 64 * 1024) return GSS_EUNSUPPORTED;
-  if (hipFuncSetAttribute((const void*)wpe_solve_large_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, solve_lds) !=
-          hipSuccess ||
-      hipFuncSetAttribute((const void*)wpe_apply_large_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
+  if (hipFuncSetAttribute((const void*)wpe_apply_large_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           apply_lds) != hipSuccess ||
       hipFuncSetAttribute((const void*)wpe_apply_large_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           apply_lds) != hipSuccess ||
@@ -1072,14 +1029,12 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
   const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 1024, 256);   // + read-ahead padding
   const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
-  const size_t off_a = o;    o = gss_align_up(o + (size_t)n_sf * N * W * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   double* lam = (double*)(base + off_lam);
   double2* Gc = (double2*)(base + off_g);
   double2* part = (double2*)(base + off_part);
-  double2* A = (double2*)(base + off_a);
 
   const dim3 block(kWpeThreads);
   const long nb_power = n_sf * bps_power, px_power = (nb_power + 7) / 8;
@@ -1091,10 +1046,7 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
     hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * G)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay, cmap,
                        G, til.split);
     gss_profile_end(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * n_tiles)), block, 0, st, part, A, D, taps, cmap, til.split,
-                       n_tiles);
-    hipLaunchKernelGGL(wpe_solve_large_kernel, dim3((unsigned)n_sf), dim3(kLsThreads), solve_lds, st, A, Gc, ctx->status, D,
-                       taps);
+    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, st);
     if (it + 1 < iters)
       hipLaunchKernelGGL((wpe_apply_large_kernel<false>), dim3((unsigned)(8 * px_apply)), block, apply_lds, st, Y, T_len, Gc,
                          lam, X, F, Tmax, D, taps, delay, (int)bps_apply, apitch, fb_apply, nb_apply, px_apply);
@@ -1111,7 +1063,6 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
             float2* X, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int N = D * taps;
-  const int W = N + D;
   const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
   const int n_tiles = wpe_num_tiles((N + 15) / 16, (D + 15) / 16);
   const WpeTiling til = wpe_tiling(n_tiles);
@@ -1136,14 +1087,12 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
   const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 256, 256);   // + read-ahead padding
   const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
-  const size_t off_a = o;    o = gss_align_up(o + (size_t)n_sf * N * W * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   double* lam = (double*)(base + off_lam);
   double2* Gc = (double2*)(base + off_g);
   double2* part = (double2*)(base + off_part);
-  double2* A = (double2*)(base + off_a);
 
   const dim3 block(kWpeThreads);
   const long n_blocks = n_sf * blocks_per_sf, per_xcd = (n_blocks + 7) / 8;
@@ -1155,9 +1104,7 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
     hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * til.groups)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay,
                        cmap, til.groups, til.split);
     gss_profile_end(ctx, 2, st);
-    hipLaunchKernelGGL(wpe_assemble_kernel, dim3((unsigned)(n_sf * n_tiles)), block, 0, st, part, A, D, taps, cmap, til.split,
-                       n_tiles);
-    hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, A, Gc, ctx->status, D, taps);
+    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, st);
     if (it + 1 < iters)
       hipLaunchKernelGGL((wpe_apply_kernel<D, false>), frame_grid, block, apply_lds, st, Y, T_len, Gc, lam, X, F, Tmax, taps,
                          delay, (int)blocks_per_sf, apitch, n_blocks, per_xcd);
