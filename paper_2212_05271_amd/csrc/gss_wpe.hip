@@ -424,7 +424,8 @@ inline bool wpe_window_fits(int D, int taps, int delay) {
 // Without pivoting (R is Hermitian positive definite; a pivot <= 1e-300 is floored and flagged).  Rows and columns >= N
 // of the last tile row are the identity's.
 // part: the covariance kernel's tiles; chunks are added up as they are read, and the first chunk's tiles are overwritten (a
-// workgroup's tiles stay in L2).  Out: Gc[sf][a][d] = conj(G[a][d]).
+// workgroup's tiles stay in L2).  Out: the coefficients as the apply kernels read them: rt > 0 tiles of 8 channels:
+// wpe_apply_coef; rt = 0: Gc[sf][a][d] = conj(G[a][d]).
 //
 // Bound: for small systems the chain of the 16 sweeps per tile row (LDS round trip and reciprocal, about 400 cycles each),
 // for large ones the tile products.  Three workgroups per compute unit (two: 40 % more time).  Measured, 513 bins: 63 us for
@@ -432,6 +433,14 @@ inline bool wpe_window_fits(int D, int taps, int delay) {
 // workgroup: 228 us; 8-column Cholesky in global memory: 4.0 ms).
 // ----------------------------------------------------------------------------------------------
 constexpr int kSolveThreads = 256;
+
+constexpr int kApplyFewMaxD = 4;              // channels up to which the prediction is applied by the vector kernel
+__host__ __device__ inline int wpe_apply_groups(int N) { return (N + 3) / 4; }        // groups of four components
+// Entry of the coefficient array for component n, channel d and part (0: the row that yields Re x_d, 1: Im x_d).
+__host__ __device__ inline int wpe_apply_coef(int n, int d, int part, int rt) {
+  return ((n >> 2) * rt + (d >> 3)) * kWave + (n & 3) * 16 + (d & 3) + 8 * ((d >> 2) & 1) + 4 * part;
+}
+
 constexpr int kSolveMaxSlots = 4;             // partial sums per problem that the solve kernel adds up itself
 
 // Problems with many partial sums (the ones left over after the last full round of workgroups are cut into small chunks):
@@ -517,7 +526,7 @@ __device__ __forceinline__ CTile tile_zero() {
 
 __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __restrict__ part, double2* __restrict__ Gc,
                                                                      uint32_t* __restrict__ status, int D, int taps,
-                                                                     ChunkMap cmap, int split) {
+                                                                     ChunkMap cmap, int split, int rt) {
   __shared__ double2 sG[2][(GSS_WPE_LARGE_MAX_D + 15) / 16][kTileEntries];
   __shared__ double2 sRow[16];
   __shared__ double sPiv[16];
@@ -535,7 +544,8 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int k4 = lane >> 4, li = lane & 15;
-  double2* __restrict__ out = Gc + sf * (long)N * D;
+  const int n_coef = rt ? wpe_apply_groups(N) * rt * kWave : N * D;
+  double2* __restrict__ out = Gc + sf * (long)n_coef;
   // tile (p, i) of [A | P], later [U | Z]
   auto tile_at = [&](int p, int i) { return A + (size_t)(wpe_tile_base(p, nt, ntd) + i - p) * kTileEntries; };
 
@@ -553,7 +563,7 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
 #pragma unroll
   for (int w = 0; w < kSolveThreads / kWave; ++w) tr += sRed[w];
   if (!(tr > 0.0)) {                                       // no frame has a past (or silence): G = 0
-    for (int e = threadIdx.x; e < N * D; e += kSolveThreads) out[e] = make_double2(0.0, 0.0);
+    for (int e = threadIdx.x; e < n_coef; e += kSolveThreads) out[e] = make_double2(0.0, 0.0);
     return;
   }
   const double load = kWpeLoadRel * tr / (double)N;
@@ -707,7 +717,15 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int a = 16 * p + k4 + 4 * v, d = 16 * c + li;
-      if (a < N && d < D) out[(long)a * D + d] = make_double2(G.re[v], -G.im[v]);
+      if (rt == 0) {
+        if (a < N && d < D) out[a * D + d] = make_double2(G.re[v], -G.im[v]);
+      } else if (a < 4 * wpe_apply_groups(N) && d < 8 * rt) {
+        // Re x -= Re G Re ytilde + Im G Im ytilde, Im x -= Re G Im ytilde - Im G Re ytilde; zero for what is padding
+        const bool in = a < N && d < D;
+        const double gr = in ? G.re[v] : 0.0, gi = in ? G.im[v] : 0.0;
+        out[wpe_apply_coef(a, d, 0, rt)] = make_double2(-gr, -gi);
+        out[wpe_apply_coef(a, d, 1, rt)] = make_double2(gi, -gr);
+      }
     }
   };
   if (wave == ((nt - 1) & 3)) {
@@ -740,23 +758,25 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
 }
 
 inline void wpe_launch_solve(double2* part, double2* Gc, uint32_t* status, long n_sf, int D, int taps, const ChunkMap& cmap,
-                             int split, hipStream_t st) {
+                             int split, int rt, hipStream_t st) {
   const int n_tiles = wpe_num_tiles((D * taps + 15) / 16, (D + 15) / 16);
   const bool all = cmap.c_main * split > kSolveMaxSlots;
   const long sf0 = all ? 0 : cmap.n_main;
   if ((all || cmap.c_tail * split > kSolveMaxSlots) && sf0 < n_sf)
     hipLaunchKernelGGL(wpe_sum_chunks_kernel, dim3((unsigned)((n_sf - sf0) * n_tiles)), dim3(kTileEntries), 0, st, part, cmap, sf0,
                        split, n_tiles);
-  hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, part, Gc, status, D, taps, cmap, split);
+  hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, part, Gc, status, D, taps, cmap, split,
+                     rt);
 }
 
-// Apply: lane = frame.  The frames t0-Delta-L+1 .. t0+255 of the bin are staged in LDS (row pitch odd in
+// Apply for up to kApplyFewMaxD channels: lane = frame.  (A tile of the matrix cores has 16 rows, Re and Im of 8 channels:
+// mostly padding here.)  The frames t0-Delta-L+1 .. t0+255 of the bin are staged in LDS (row pitch odd in
 // 8-byte units for even D, so that the lanes' rows start in different banks); every lane then subtracts
 // the prediction, walking the N components of ytilde_t while the N x D coefficients, which are the same for
 // all lanes, come through the scalar path.  FINAL: writes the complex64 output (zero at t >= T); otherwise
 // writes lambda_t of the new estimate for the next iteration.
 template <int D, bool FINAL>
-__global__ __launch_bounds__(kWpeThreads) void wpe_apply_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
+__global__ __launch_bounds__(kWpeThreads) void wpe_apply_few_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
                                                                 const double2* __restrict__ Gc, double* __restrict__ lam,
                                                                 float2* __restrict__ X, int F, int Tmax, int taps, int delay,
                                                                 int blocks_per_sf, int pitch, long n_blocks, long per_xcd) {
@@ -893,107 +913,206 @@ __global__ __launch_bounds__(kWpeThreads) void wpe_copy_kernel(const float2* __r
   X[i] = t < clamp_T(T_len, s, Tmax) ? Y[i] : make_float2(0.f, 0.f);
 }
 
-// ----------------------------------------------------------------------------------------------
-// Large arrays (D > 8 or D * taps > 80; up to D = 32, D * taps = 320).  The covariance, solve and power kernels above serve
-// them too; the prediction is applied by a kernel with a run-time channel count.
-// ----------------------------------------------------------------------------------------------
-// Apply for large arrays: lane = frame, fb frames per workgroup (+ the needed past) staged in LDS as they
-// came; a lane holds all D outputs (up to 32) and walks the D * taps components of ytilde_t; the
-// coefficients are the same for all lanes and come through the scalar path, 8 outputs at a time.  A row of
-// coefficients is read in whole groups of 8: the last group of a row may reach into the next row (or, at the
-// very end of the array, into its padding); those values only enter accumulators that are never stored.
-template <bool FINAL>
-__global__ __launch_bounds__(kWpeThreads) void wpe_apply_large_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
-                                                                      const double2* __restrict__ Gc, double* __restrict__ lam,
-                                                                      float2* __restrict__ X, int F, int Tmax, int D, int taps,
-                                                                      int delay, int blocks_per_sf, int pitch, int fb,
-                                                                      long n_blocks, long per_xcd) {
+// Apply on the fp64 matrix cores: x_t = y_t - G^H ytilde_t as a product of real matrices, 16 rows (Re and Im of 8 channels)
+// by 4 components of ytilde by 16 frames at a time, once for their real and once for their imaginary parts, added up on
+// top of y_t.  RT tiles of 8 channels (8 RT >= D > 8 (RT - 1)); a wavefront owns CT groups of 16 frames.  The frames
+// t0-Delta-L+1 .. t0+64 CT-1 are staged in LDS as they came, 8 RT + 1 values apart (odd: the lanes' frames start in
+// different banks).  Row i = k + 4 v of a tile is part v & 1 (Re, Im) of channel k + 4 (v >> 1), so that a lane ends up
+// with whole complex values.  The coefficients come from memory in the order of the operands (wpe_apply_coef), two groups
+// of components ahead.  FINAL: writes the complex64 output (zero at t >= T); otherwise lambda_t of the new estimate.
+//
+// Bound: the fp64 matrix rate (no padding where D is a multiple of 8).  Measured, 10 taps: 94 us at 513 x 1560 x 8 (one frame
+// per lane with the coefficients through the scalar path: 102 us), 0.63 ms at 513 x 1500 x 24 (1.40 ms).
+constexpr int kApplyAhead = 4;                // groups of components whose coefficients are in flight (even)
+
+// A value of the window: as it came, or, where only one tile of channels would use each conversion, converted once (each value
+// is read `taps` times).
+template <int RT>
+struct ApplyWindow {
+  using type = float2;
+  static __device__ __forceinline__ type make(float2 v) { return v; }
+};
+template <>
+struct ApplyWindow<1> {
+  using type = double2;
+  static __device__ __forceinline__ type make(float2 v) { return make_double2((double)v.x, (double)v.y); }
+};
+
+template <int RT, int CT, bool FINAL>
+__global__ __launch_bounds__(kWpeThreads, 2) void wpe_apply_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
+                                                                   const double2* __restrict__ Gc, double* __restrict__ lam,
+                                                                   float2* __restrict__ X, int F, int Tmax, int D, int taps,
+                                                                   int delay, int blocks_per_sf, long n_blocks, long per_xcd) {
+  constexpr int P = 8 * RT + 1, fb = kWpeThreads / kWave * 16 * CT;
+  using Win = ApplyWindow<RT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  float2* __restrict__ sWin = reinterpret_cast<float2*>(lds_raw);
+  typename Win::type* __restrict__ sWin = reinterpret_cast<typename Win::type*>(lds_raw);
   const long blk = xcd_block(blockIdx.x, per_xcd);
   if (blk >= n_blocks) return;
-  const long sf = blk / blocks_per_sf;
-  const int t0 = (int)(blk % blocks_per_sf) * fb;
-  const int T = clamp_T(T_len, (int)(sf / F), Tmax);
-  const int t = t0 + threadIdx.x;
-  const bool mine_on = (int)threadIdx.x < fb && t < Tmax;
+  const unsigned sfu = (unsigned)blk / (unsigned)blocks_per_sf;         // (fewer than 2^31 blocks)
+  const int t0 = (int)((unsigned)blk - sfu * (unsigned)blocks_per_sf) * fb;
+  const long sf = (long)sfu;
+  const int T = clamp_T(T_len, (int)(sfu / (unsigned)F), Tmax);
   const int N = D * taps;
   if (t0 >= T) {                                         // nothing valid in this block
-    if (mine_on) {
-      if constexpr (FINAL) {
-        for (int d = 0; d < D; ++d) X[(sf * Tmax + t) * D + d] = make_float2(0.f, 0.f);
-      } else {
-        lam[sf * Tmax + t] = 0.0;
-      }
+    const int n = Tmax - t0 < fb ? Tmax - t0 : fb;
+    if constexpr (FINAL) {
+      for (int e = threadIdx.x; e < n * D; e += kWpeThreads) X[(sf * Tmax + t0) * D + e] = make_float2(0.f, 0.f);
+    } else {
+      for (int e = threadIdx.x; e < n; e += kWpeThreads) lam[sf * Tmax + t0 + e] = 0.0;
     }
     return;
   }
   const int past = delay + taps - 1;
   const int rows = fb + past;
   const float2* __restrict__ Yrow = Y + sf * (long)Tmax * D;
-  staged_copy<6, float2>(
-      threadIdx.x, rows * D, kWpeThreads,
-      [&](int e) {
-        const int r = e / D, d = e - r * D;
-        const int tt = t0 - past + r;
-        return (tt >= 0 && tt < T) ? Yrow[(long)tt * D + d] : make_float2(0.f, 0.f);
-      },
-      [&](int e, float2 v) {
-        const int r = e / D, d = e - r * D;
-        sWin[r * pitch + d] = v;
-      });
-  __syncthreads();
-  if ((int)threadIdx.x >= fb) return;
-  constexpr int DM = 32;
-  double xr[DM], xi[DM];
-  const float2* __restrict__ mine = sWin + (threadIdx.x + past) * pitch;
-#pragma unroll
-  for (int d = 0; d < DM; ++d) {
-    xr[d] = 0.0;
-    xi[d] = 0.0;
-    if (d < D) {
-      xr[d] = (double)mine[d].x;
-      xi[d] = (double)mine[d].y;
-    }
-  }
-  typedef const __attribute__((address_space(4))) double* cptr_t;
-  const cptr_t g4 = (cptr_t)(uintptr_t)(Gc + sf * (long)N * D);
-  for (int tau = 0; tau < taps; ++tau) {
-    const float2* __restrict__ src = mine - (delay + tau) * pitch;
-    for (int dp = 0; dp < D; ++dp) {
-      const float2 v = src[dp];
-      const double vr = (double)v.x, vi = (double)v.y;
-      const cptr_t c = g4 + ((long)(tau * D + dp) * D) * 2;
-      static_for<0, DM / 8>([&](auto GI) {
-        constexpr int g = GI.value;
-        if (8 * g < D) {
-#pragma unroll
-          for (int d = 0; d < 8; ++d) {                  // x_d -= c[d] * v
-            const double cr = c[2 * (8 * g + d)], ci = c[2 * (8 * g + d) + 1];
-            xr[8 * g + d] = fma(-cr, vr, fma(ci, vi, xr[8 * g + d]));
-            xi[8 * g + d] = fma(-cr, vi, fma(-ci, vr, xi[8 * g + d]));
+  {
+    const unsigned n_valid = (unsigned)(T * D), g0 = (unsigned)((t0 - past) * D);      // (one run of memory)
+    const int step_r = kWpeThreads / D, step_d = kWpeThreads - step_r * D, step_pos = step_r * P + step_d;
+    const int r0 = (int)((unsigned)threadIdx.x / (unsigned)D);
+    int d = (int)threadIdx.x - r0 * D, pos = r0 * P + d;
+    staged_copy<8, float2>(
+        threadIdx.x, rows * D, kWpeThreads,
+        [&](int m) {
+          const unsigned e = g0 + (unsigned)m;
+          return e < n_valid ? Yrow[e] : make_float2(0.f, 0.f);
+        },
+        [&](int, float2 v) {
+          sWin[pos] = Win::make(v);
+          d += step_d;
+          pos += step_pos;
+          if (d >= D) {
+            d -= D;
+            pos += P - D;
           }
-        }
-      });
-    }
+        });
   }
-  if (t >= Tmax) return;
-  if constexpr (FINAL) {
-    float2* __restrict__ o = X + (sf * Tmax + t) * D;
+  __syncthreads();
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int k4 = lane >> 4, li = lane & 15;
+  const int f0 = wave * 16 * CT + li;                    // the lane's frame within the block, first group
+  double4v acc[RT][CT];
 #pragma unroll
-    for (int d = 0; d < DM; ++d)
-      if (d < D) o[d] = t < T ? make_float2((float)xr[d], (float)xi[d]) : make_float2(0.f, 0.f);
-  } else {
-    double p = 0.0;
+  for (int r = 0; r < RT; ++r)
 #pragma unroll
-    for (int d = 0; d < DM; ++d)
-      if (d < D) p += xr[d] * xr[d] + xi[d] * xi[d];
-    lam[sf * Tmax + t] = t < T ? p / (double)D : 0.0;
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int d = 8 * r + 4 * h + k4;
+        const typename Win::type y = sWin[(f0 + 16 * c + past) * P + (d < D ? d : 0)];
+        acc[r][c][2 * h] = d < D ? (double)y.x : 0.0;
+        acc[r][c][2 * h + 1] = d < D ? (double)y.y : 0.0;
+      }
+  // component n = 4 s + k4 of ytilde_t: value d of the frame Delta + tau before t (components >= N, which have zero
+  // coefficients, repeat the last one)
+  const int groups = wpe_apply_groups(N);
+  const int n_steps = t0 + wave * 16 * CT < T ? groups : 0;   // (none where no frame of the wavefront is valid)
+  const double2* __restrict__ g = Gc + (size_t)sf * groups * RT * kWave + lane;
+  int n = k4, d = k4;                                     // (D > 4)
+  int pos = (f0 + past - delay) * P + d;
+  auto step = [&]() {
+    n += 4;
+    const bool wrap = d + 4 >= D;
+    const int to = wrap ? 4 - D - P : 4, dd = wrap ? 4 - D : 4;
+    pos += n < N ? to : 0;
+    d += dd;
+  };
+  auto coef = [&](double2 (&a)[RT], int s) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) a[r] = g[(s * RT + r) * kWave];
+  };
+  auto frames = [&](typename Win::type (&v)[CT]) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) v[c] = sWin[pos + 16 * P * c];
+    step();
+  };
+  // (The buffers of the requested operands are picked at compile time: moving them along would wait for the loads.)
+  double2 a[kApplyAhead][RT];
+  typename Win::type v[2][CT];
+  static_for<0, kApplyAhead>([&](auto UI) { coef(a[UI.value], UI.value < groups ? UI.value : 0); });
+  frames(v[0]);
+  for (int s0 = 0; s0 < n_steps; s0 += kApplyAhead) {
+    static_for<0, kApplyAhead>([&](auto UI) {
+      constexpr int u = UI.value;
+      if (s0 + u < n_steps) {
+        double br[CT], bi[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          br[c] = (double)v[u & 1][c].x;
+          bi[c] = (double)v[u & 1][c].y;
+        }
+        frames(v[(u + 1) & 1]);                           // (behind the last group: read, not used)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[r][c] = mfma_f64(a[u][r].x, br[c], acc[r][c]);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[r][c] = mfma_f64(a[u][r].y, bi[c], acc[r][c]);
+        if (s0 + u + kApplyAhead < n_steps) coef(a[u], s0 + u + kApplyAhead);
+      }
+    });
+  }
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int t = t0 + f0 + 16 * c;
+    if constexpr (FINAL) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int dd = 8 * r + 4 * h + k4;
+          if (t < Tmax && dd < D)
+            X[(sf * Tmax + t) * D + dd] =
+                t < T ? make_float2((float)acc[r][c][2 * h], (float)acc[r][c][2 * h + 1]) : make_float2(0.f, 0.f);
+        }
+    } else {
+      double p = 0.0;
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (8 * r + 4 * h + k4 < D) p += acc[r][c][2 * h] * acc[r][c][2 * h] + acc[r][c][2 * h + 1] * acc[r][c][2 * h + 1];
+      p += __shfl_xor(p, 16);
+      p += __shfl_xor(p, 32);
+      if (k4 == 0 && t < Tmax) lam[sf * Tmax + t] = t < T ? p / (double)D : 0.0;
+    }
   }
 }
 
-int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, int Tmax, int D, int taps, int delay,
-                  int iters, float2* X, hipStream_t st) {
+// ----------------------------------------------------------------------------------------------
+// Host side
+// ----------------------------------------------------------------------------------------------
+struct WpeApply {
+  int fb, lds, rt;                                       // frames per workgroup, LDS bytes, tiles of 8 channels (0: few channels)
+  const void* fn[2];                                     // the kernel without and with the output
+};
+// Up to 4 channels the vector kernel (of the 16 rows of a matrix tile at most half would be used: gss_wpe on 513 x 1000 x 4,
+// 10 taps, 3 iterations 636 us against 646; from 5 channels on the matrix kernel is the faster one).  More than 24 channels: half as many frames per workgroup (registers, LDS).
+inline WpeApply wpe_apply_of(int D, int taps, int delay) {
+  WpeApply a;
+  a.fb = D > 24 ? 128 : 256;
+  a.rt = D <= kApplyFewMaxD ? 0 : (D + 7) / 8;
+  const int pitch = a.rt ? 8 * a.rt + 1 : D | 1;
+  a.lds = (a.fb + delay + taps - 1) * pitch * (int)(a.rt == 1 ? sizeof(double2) : sizeof(float2));
+#define GSS_APPLY(...) { a.fn[0] = (const void*)__VA_ARGS__, false>; a.fn[1] = (const void*)__VA_ARGS__, true>; }
+  switch (a.rt ? a.rt + kApplyFewMaxD : D) {
+    case 1: GSS_APPLY(wpe_apply_few_kernel<1) break;
+    case 2: GSS_APPLY(wpe_apply_few_kernel<2) break;
+    case 3: GSS_APPLY(wpe_apply_few_kernel<3) break;
+    case 4: GSS_APPLY(wpe_apply_few_kernel<4) break;
+    case 5: GSS_APPLY(wpe_apply_kernel<1, 4) break;
+    case 6: GSS_APPLY(wpe_apply_kernel<2, 4) break;
+    case 7: GSS_APPLY(wpe_apply_kernel<3, 4) break;
+    default: GSS_APPLY(wpe_apply_kernel<4, 2) break;
+  }
+#undef GSS_APPLY
+  return a;
+}
+
+int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, int Tmax, int D, int taps, int delay, int iters,
+            float2* X, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int N = D * taps;
   const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
@@ -1001,33 +1120,33 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
   const WpeTiling til = wpe_tiling(n_tiles);
   int pitch;
   const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
-  const int G = til.groups;
   const int cov_lds = wpe_cov_lds(pitch, taps, delay);
-  const int fb_apply = D > 24 ? 128 : 256, fb_power = 64;
-  const int apitch = D | 1;
-  const int apply_lds = (int)((size_t)(fb_apply + delay + taps - 1) * apitch * sizeof(float2));
-  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
-  if (hipFuncSetAttribute((const void*)wpe_apply_large_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          apply_lds) != hipSuccess ||
-      hipFuncSetAttribute((const void*)wpe_apply_large_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          apply_lds) != hipSuccess ||
+  const WpeApply ap = wpe_apply_of(D, taps, delay);
+  const int fb_power = D > GSS_WPE_MAX_D ? 64 : 256;
+  // (windows of at most 64 KB, in the apply kernel at the smallest odd frame pitch)
+  if ((ap.fb + delay + taps - 1) * (D | 1) * (int)sizeof(float2) > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
+  if (hipFuncSetAttribute(ap.fn[0], hipFuncAttributeMaxDynamicSharedMemorySize, ap.lds) != hipSuccess ||
+      hipFuncSetAttribute(ap.fn[1], hipFuncAttributeMaxDynamicSharedMemorySize, ap.lds) != hipSuccess ||
       hipFuncSetAttribute((const void*)cov, hipFuncAttributeMaxDynamicSharedMemorySize, cov_lds) != hipSuccess)
     return GSS_EHIP;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
-      per_cu < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess || per_cu < 1)
     per_cu = 1;
-  // G workgroups per chunk: the chunks are planned for a G-th of the resident workgroups
-  long slots = (long)ctx->num_cu * (per_cu < kWpeCovPerCu ? per_cu : kWpeCovPerCu) / G;
+  // several workgroups per chunk: the chunks are planned for that part of the resident workgroups
+  long slots = (long)ctx->num_cu * (per_cu < kWpeCovPerCu ? per_cu : kWpeCovPerCu) / til.groups;
   if (slots < 1) slots = 1;
   const ChunkMap cmap = plan_chunk_map(slots, n_sf, tiles, 1, 0, true);
   const long wgs = chunk_map_wgs(cmap, n_sf);
-  const long bps_apply = (Tmax + fb_apply - 1) / fb_apply, bps_power = (Tmax + fb_power - 1) / fb_power;
-  if (wgs * G > 0x7fffffffL || n_sf * bps_power + 8 > 0x7fffffffL || n_sf * n_tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
+  const long bps_apply = (Tmax + ap.fb - 1) / ap.fb, bps_power = (Tmax + fb_power - 1) / fb_power;
+  if (wgs * til.groups > 0x7fffffffL || n_sf * bps_power + 8 > 0x7fffffffL || n_sf * n_tiles > 0x7fffffffL)
+    return GSS_EUNSUPPORTED;
 
+  // coefficients: as the apply kernel reads them; the vector kernel's are followed by room for its read-ahead
+  const size_t coef_bytes = ap.rt ? (size_t)n_sf * wpe_apply_groups(N) * ap.rt * kWave * sizeof(double2)
+                                  : (size_t)n_sf * N * D * sizeof(double2) + 256;
   size_t o = 0;
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
-  const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 1024, 256);   // + read-ahead padding
+  const size_t off_g = o;    o = gss_align_up(o + coef_bytes, 256);
   const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
@@ -1038,79 +1157,22 @@ int run_wpe_large(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, in
 
   const dim3 block(kWpeThreads);
   const long nb_power = n_sf * bps_power, px_power = (nb_power + 7) / 8;
-  const long nb_apply = n_sf * bps_apply, px_apply = (nb_apply + 7) / 8;
+  long nb_apply = n_sf * bps_apply, px_apply = (nb_apply + 7) / 8;
   hipLaunchKernelGGL(wpe_power_kernel, dim3((unsigned)(8 * px_power)), block, 0, st, Y, T_len, lam, F, Tmax, D,
                      (int)bps_power, nb_power, px_power, fb_power);
-  for (int it = 0; it < iters; ++it) {
-    gss_profile_begin(ctx, 2, st);
-    hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * G)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay, cmap,
-                       G, til.split);
-    gss_profile_end(ctx, 2, st);
-    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, st);
-    if (it + 1 < iters)
-      hipLaunchKernelGGL((wpe_apply_large_kernel<false>), dim3((unsigned)(8 * px_apply)), block, apply_lds, st, Y, T_len, Gc,
-                         lam, X, F, Tmax, D, taps, delay, (int)bps_apply, apitch, fb_apply, nb_apply, px_apply);
-    else
-      hipLaunchKernelGGL((wpe_apply_large_kernel<true>), dim3((unsigned)(8 * px_apply)), block, apply_lds, st, Y, T_len, Gc,
-                         lam, X, F, Tmax, D, taps, delay, (int)bps_apply, apitch, fb_apply, nb_apply, px_apply);
-  }
-  if (hipGetLastError() != hipSuccess) return GSS_EHIP;
-  return GSS_OK;
-}
-
-template <int D>
-int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, int Tmax, int taps, int delay, int iters,
-            float2* X, hipStream_t st) {
-  const long n_sf = (long)S * F;
-  const int N = D * taps;
-  const int tiles = (Tmax + kWpeTile - 1) / kWpeTile;
-  const int n_tiles = wpe_num_tiles((N + 15) / 16, (D + 15) / 16);
-  const WpeTiling til = wpe_tiling(n_tiles);
-  int pitch;
-  const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
-  const int cov_lds = wpe_cov_lds(pitch, taps, delay);
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
-  const ChunkMap cmap = plan_chunk_map((long)ctx->num_cu * (per_cu < kWpeCovPerCu ? per_cu : kWpeCovPerCu) / til.groups,
-                                       n_sf, tiles, 1, 0, true);
-  const long wgs = chunk_map_wgs(cmap, n_sf);
-  const long blocks_per_sf = (Tmax + kWpeThreads - 1) / kWpeThreads;
-  if (wgs > 0x7fffffffL || n_sf * blocks_per_sf + 8 > 0x7fffffffL || n_sf * n_tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  // apply kernel: row pitch odd for even D
-  const int apitch = D | 1;
-  const int apply_lds = (int)((size_t)(kWpeThreads + delay + taps - 1) * apitch * sizeof(float2));
-  if (apply_lds > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
-
-  size_t o = 0;
-  const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
-  const size_t off_g = o;    o = gss_align_up(o + (size_t)n_sf * N * D * sizeof(double2) + 256, 256);   // + read-ahead padding
-  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
-  const int rc = gss_ensure_scratch(ctx, o);
-  if (rc != GSS_OK) return rc;
-  char* base = (char*)ctx->scratch;
-  double* lam = (double*)(base + off_lam);
-  double2* Gc = (double2*)(base + off_g);
-  double2* part = (double2*)(base + off_part);
-
-  const dim3 block(kWpeThreads);
-  const long n_blocks = n_sf * blocks_per_sf, per_xcd = (n_blocks + 7) / 8;
-  const dim3 frame_grid((unsigned)(8 * per_xcd));
-  hipLaunchKernelGGL(wpe_power_kernel, frame_grid, block, 0, st, Y, T_len, lam, F, Tmax, D, (int)blocks_per_sf, n_blocks,
-                     per_xcd, kWpeThreads);
   for (int it = 0; it < iters; ++it) {
     gss_profile_begin(ctx, 2, st);
     hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * til.groups)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay,
                        cmap, til.groups, til.split);
     gss_profile_end(ctx, 2, st);
-    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, st);
-    if (it + 1 < iters)
-      hipLaunchKernelGGL((wpe_apply_kernel<D, false>), frame_grid, block, apply_lds, st, Y, T_len, Gc, lam, X, F, Tmax, taps,
-                         delay, (int)blocks_per_sf, apitch, n_blocks, per_xcd);
-    else
-      hipLaunchKernelGGL((wpe_apply_kernel<D, true>), frame_grid, block, apply_lds, st, Y, T_len, Gc, lam, X, F, Tmax, taps,
-                         delay, (int)blocks_per_sf, apitch, n_blocks, per_xcd);
+    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, ap.rt, st);
+    int bps = (int)bps_apply;
+    int apitch = D | 1;
+    void* few[] = {&Y, &T_len, &Gc, &lam, &X, &F, &Tmax, &taps, &delay, &bps, &apitch, &nb_apply, &px_apply};
+    void* mat[] = {&Y, &T_len, &Gc, &lam, &X, &F, &Tmax, &D, &taps, &delay, &bps, &nb_apply, &px_apply};
+    if (hipLaunchKernel(ap.fn[it + 1 < iters ? 0 : 1], dim3((unsigned)(8 * px_apply)), block, ap.rt ? mat : few, (size_t)ap.lds, st) !=
+        hipSuccess)
+      return GSS_EHIP;
   }
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
@@ -1123,7 +1185,6 @@ extern "C" int gss_wpe(gss_ctx* ctx, const float* Y, const int32_t* T_len, int S
   if (!ctx || !Y || !X || Y == X) return GSS_EINVAL;
   if (S <= 0 || F <= 0 || Tmax <= 0 || D <= 0 || taps <= 0 || delay <= 0 || iters < 0) return GSS_EINVAL;
   if (D > GSS_WPE_LARGE_MAX_D || (long)D * taps > GSS_WPE_LARGE_MAX_N || delay > 64) return GSS_EUNSUPPORTED;
-  const bool small = D <= GSS_WPE_MAX_D && (long)D * taps <= GSS_WPE_MAX_N;
   if (hipSetDevice(ctx->device) != hipSuccess) return GSS_EHIP;
   hipStream_t st = (hipStream_t)stream;
   const float2* Yc = (const float2*)Y;
@@ -1135,12 +1196,5 @@ extern "C" int gss_wpe(gss_ctx* ctx, const float* Y, const int32_t* T_len, int S
     hipLaunchKernelGGL(wpe_copy_kernel, dim3((unsigned)blocks), dim3(kWpeThreads), 0, st, Yc, T_len, Xc, F, Tmax, D, n);
     return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
   }
-  if (!small) return run_wpe_large(ctx, Yc, T_len, S, F, Tmax, D, taps, delay, iters, Xc, st);
-  switch (D) {
-#define GSS_CASE_D(DD) \
-  case DD: return run_wpe<DD>(ctx, Yc, T_len, S, F, Tmax, taps, delay, iters, Xc, st);
-    GSS_CASE_D(1) GSS_CASE_D(2) GSS_CASE_D(3) GSS_CASE_D(4) GSS_CASE_D(5) GSS_CASE_D(6) GSS_CASE_D(7) GSS_CASE_D(8)
-#undef GSS_CASE_D
-    default: return GSS_EUNSUPPORTED;
-  }
+  return run_wpe(ctx, Yc, T_len, S, F, Tmax, D, taps, delay, iters, Xc, st);
 }
