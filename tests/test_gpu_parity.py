@@ -490,6 +490,18 @@ def test_mvdr_target_class_and_literal_normalised_input(env):
 # ---------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("S,D,N", [(1, 2, 5000), (2, 3, 4096), (1, 9, 2500), (1, 1, 255)])
 def test_stft_istft(env, S, D, N):
+    _check_stft_istft(env, S, D, N)
+
+
+@pytest.mark.parametrize("S,D,N", [(3, 1, 256 * 13), (2, 4, 257 * 7), (3, 5, 1281), (2, 8, 256 * 5 + 1), (1, 16, 2047), (2, 17, 1500),
+                                   (1, 32, 300), (700, 1, 1), (350, 1, 256 * 61), (330, 1, 256 * 90 + 3), (1, 8, 256 * 1100 + 9)])
+def test_stft_istft_edges(env, S, D, N):
+    """Steps of several frames that end with a segment or with the items of an XCD, channel groups of 8 and 16 with a rest,
+    and inverse transforms of one and of several steps of eight frames per workgroup, with a last block that is cut."""
+    _check_stft_istft(env, S, D, N)
+
+
+def _check_stft_istft(env, S, D, N):
     t, o, gss = env["torch"], env["o"], env["gss"]
     rng = np.random.default_rng(N + D)
     x = rng.standard_normal((S, D, N)).astype(np.float32)
