@@ -151,80 +151,132 @@ __device__ __forceinline__ float2 hann_pair(const float2* tw, int n) {
   return make_float2(0.5f - 0.5f * tw[i0 <= kH ? i0 : kN - i0].x, 0.5f - 0.5f * tw[i1 <= kH ? i1 : kN - i1].x);
 }
 
+// Items of workgroup w of `wgs`: an even, contiguous share of n.
+__device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (long)((unsigned long)w * (unsigned long)n / (unsigned long)wgs); }
+
 // ----------------------------------------------------------------------------------------------
-// STFT: one workgroup per (segment, frame); its wavefronts take the channels in turn, eight channels
-// at a time are staged in LDS as [bin][channel] and written out as 64-byte runs.
+// STFT.  A workgroup takes several steps of (segment, frame) items; a step is two units of 8 transforms, one per
+// wavefront: a unit is all channels of a frame (of 8 / D consecutive frames with fewer than 5 channels), or 8 channels of
+// a frame with more than 8.  The samples of the next unit are requested before the current transforms.  The spectrum
+// replaces the transform in the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and
+// X[512 - k]), and the workgroup writes a bin's values of both units as one run of memory (128 bytes for 8 channels).
+//
+// Bound: memory (samples read once per overlapping frame from L2, the spectrum written once).  Two workgroups per compute
+// unit (LDS); the twiddles of a lane are set up once per workgroup.  Ten minutes of 8 channels: 548 us = 2.8 TB/s (one
+// workgroup per frame, 64-byte runs: 722 us; an even share of consecutive frames per workgroup instead of turns: 583 us).
 // ----------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64 * kFftWaves) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
-                                                             const float2* __restrict__ table, int D, long N, int T,
-                                                             long n_items) {
+constexpr int kStftWgsPerCu = 2, kStftShares = 1;          // workgroups: up to kStftShares rounds of the resident ones
+// Row pitch: 1 modulo 16, so that sixteen rows are read at one bin without bank conflicts.
+constexpr int kStftRow = 577;
+static_assert(kStftRow >= 8 * kExStride && kStftRow >= kBins && kStftRow % 16 == 1, "row pitch of the transforms in LDS");
+struct __attribute__((packed, aligned(4))) PairUnaligned { float a, b; };
+__global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
+                                                                const float2* __restrict__ table, int D, long N, int T,
+                                                                long n_items) {
   __shared__ float2 tw[kH + 1];
-  __shared__ float2 buf[kFftWaves][kRow];
-  __shared__ float2 stage[kBins][8];
+  __shared__ float2 rows[2 * kFftWaves][kStftRow];
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const long item = xcd_contiguous(blockIdx.x, n_items);
-  if (item < 0) return;
-  const int t = (int)(item % T);
-  const int s = (int)(item / T);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Every XCD has an even, contiguous share of the items, which its workgroups take step by step in turn: at any time they
+  // write neighbouring frames.
+  const int xcd = (int)(blockIdx.x % kXcds);
+  const long j = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
+  const bool by_frame = D <= 8;                            // the units of a step: frames, or groups of eight channels
+  const int per_unit = D <= 4 ? 8 / D : 1;                 // frames per unit
+  const int per_step = by_frame ? 2 * per_unit : 1;        // frames per step
+  const long item1 = share_begin(xcd + 1, kXcds, n_items);
+  long i = share_begin(xcd, kXcds, n_items) + j * per_step, block_end = i + per_step;
+  if (i >= item1) return;
   fill_twiddles(tw, table);
   __syncthreads();
   FftLane fc;
   fft_lane_init(fc, tw, lane);
-  // periodic Hann window at the lane's samples 2n, 2n + 1, n = 64 m + lane
-  float w0[8], w1[8];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const int i0 = 2 * (lane + 64 * m), i1 = i0 + 1;
-    w0[m] = 0.5f - 0.5f * tw[i0 <= kH ? i0 : kN - i0].x;     // cos(2 pi i / 1024) is even around 512
-    w1[m] = 0.5f - 0.5f * tw[i1 <= kH ? i1 : kN - i1].x;
-  }
 
-  const long start = (long)t * kHop - kPad;      // first sample of the frame (may be negative)
-  for (int d0 = 0; d0 < D; d0 += 8) {
-    for (int dd = wave; dd < 8; dd += kFftWaves) {
-      const int d = d0 + dd;
-      if (d < D) {
-        const float* __restrict__ xs = x + ((long)s * D + d) * N;
-        float2* Z = buf[wave];
-        // windowed frame, even/odd packed: z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1]
-        float2 v[8];
+  const int my_frame = D <= 4 ? wave / D : 0, my_chan = D <= 4 ? wave % D : wave;
+  // this wavefront's samples of unit u of the step at item i, channels from d0 on
+  float2 raw[8];
+  auto request = [&](long i, int d0, int u) {
+    const int s = (int)((unsigned)i / (unsigned)T);        // (fewer than 2^31 items)
+    const int fr = by_frame ? u * per_unit + my_frame : 0, d = d0 + my_chan + (by_frame ? 0 : 8 * u);
+    const int t = (int)i - s * T + fr;
+    const long start = (long)t * kHop - kPad;              // first sample of the frame (may be negative)
+    const bool on = my_frame < per_unit && t < T && i + fr < item1 && d < D;
+    const float* __restrict__ xs = x + ((long)s * D + (on ? d : 0)) * N;
+    if (on && start >= 0 && start + kN <= N) {
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int n = lane + 64 * m;           // 0 .. 511
-          const long p0 = start + 2 * n, p1 = p0 + 1;
-          const float x0 = (p0 >= 0 && p0 < N) ? xs[p0] : 0.f;
-          const float x1 = (p1 >= 0 && p1 < N) ? xs[p1] : 0.f;
-          v[m] = make_float2(w0[m] * x0, w1[m] * x1);
-        }
+      for (int m = 0; m < 8; ++m) {
+        const PairUnaligned v = *reinterpret_cast<const PairUnaligned*>(xs + start + 2 * (lane + 64 * m));   // (4-byte aligned)
+        raw[m] = make_float2(v.a, v.b);
+      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const long p0 = start + 2 * (lane + 64 * m), p1 = p0 + 1;
+        raw[m].x = on && p0 >= 0 && p0 < N ? xs[p0] : 0.f;
+        raw[m].y = on && p1 >= 0 && p1 < N ? xs[p1] : 0.f;
+      }
+    }
+  };
+  int d0 = 0;
+  request(i, 0, 0);
+  while (i < item1) {
+    const int s = (int)((unsigned)i / (unsigned)T), t = (int)i - s * T;
+    const long end = block_end < item1 ? block_end : item1;
+    int nf = (int)(end - i);                               // frames of this step that are in the same segment
+    nf = T - t < nf ? T - t : nf;
+    const int nd = by_frame ? D : (D - d0 < 16 ? D - d0 : 16);
+    const bool more = !by_frame && d0 + 16 < D;            // the frame has channels left
+    long in = more ? i : i + nf;
+    if (in >= block_end) {                                 // the workgroup's next block of frames
+      in = block_end + (per_xcd - 1) * per_step;
+      block_end = in + per_step;
+    }
+    const int dn = more ? d0 + 16 : 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      // windowed frame, even/odd packed: z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1]
+      float2 v[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const float2 w = hann_pair(tw, lane + 64 * m);
+        v[m] = make_float2(w.x * raw[m].x, w.y * raw[m].y);
+      }
+      if (u == 0) request(i, d0, 1);
+      else if (in < item1) request(in, dn, 0);
+      const int fr = by_frame ? u * per_unit + my_frame : 0, dd = my_chan + (by_frame ? 0 : 8 * u);
+      if (my_frame < per_unit && fr < nf && dd < nd) {
+        float2* __restrict__ Z = rows[u * kFftWaves + wave];
         fft512(v, Z, fc, lane);
-        // split: X[k] = (Z[k] + conj Z[512-k]) / 2 - i w^k (Z[k] - conj Z[512-k]) / 2, Z[512] = Z[0]
-        for (int k = lane; k <= kH; k += 64) {
-          const float2 zk = Z[k & (kH - 1)];
+        // split: with e = (Z[k] + conj Z[512-k]) / 2, o = (Z[k] - conj Z[512-k]) / 2, Z[512] = Z[0]:
+        // X[k] = e - i w^k o, X[512-k] = conj(e + i w^k o)
+        for (int k = lane; k <= kH / 2; k += 64) {
+          const float2 zk = Z[k];
           const float2 zc = Z[(kH - k) & (kH - 1)];
           const float2 e = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y - zc.y));
           const float2 o = make_float2(0.5f * (zk.x - zc.x), 0.5f * (zk.y + zc.y));
-          const float2 wo = cmul(tw[k], o);      // w^k * o
-          stage[k][dd] = make_float2(e.x + wo.y, e.y - wo.x);   // e - i * wo
+          const float2 wo = cmul(tw[k], o);
+          Z[k] = make_float2(e.x + wo.y, e.y - wo.x);
+          if (k < kH / 2) Z[kH - k] = make_float2(e.x - wo.y, -(e.y + wo.x));
         }
-        wave_sync();                             // Z is reused by this wavefront's next transform
       }
     }
     __syncthreads();
-    const int nd = (D - d0) < 8 ? (D - d0) : 8;
-    if (nd == 8) {
-      for (int i = threadIdx.x; i < kBins * 8; i += blockDim.x) {
-        const int k = i >> 3, dd = i & 7;
-        Y[(((long)s * kBins + k) * T + t) * D + d0 + dd] = stage[k][dd];
-      }
+    // bin k: the step's nf frames x nd channels, one run of memory (several frames: all their channels)
+    const int nr = nf * nd, q = by_frame ? per_unit * D : kFftWaves;     // values per bin, of the first unit
+    float2* __restrict__ out = Y + ((long)s * kBins * T + t) * D + d0;
+    const long pitch = (long)T * D;
+    if (nr == 16) {
+      for (int e = threadIdx.x; e < kBins * 16; e += 64 * kFftWaves) out[(e >> 4) * pitch + (e & 15)] = rows[e & 15][e >> 4];
     } else {
-      for (int i = threadIdx.x; i < kBins * nd; i += blockDim.x) {
-        const int k = i / nd, dd = i % nd;
-        Y[(((long)s * kBins + k) * T + t) * D + d0 + dd] = stage[k][dd];
+      for (int e = threadIdx.x; e < kBins * nr; e += 64 * kFftWaves) {
+        const int k = (int)((unsigned)e / (unsigned)nr), r = e - k * nr;
+        out[k * pitch + r] = rows[r < q ? r : kFftWaves + r - q][k];
       }
     }
     __syncthreads();
+    i = in;
+    d0 = dn;
   }
 }
 
@@ -370,7 +422,9 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   const int rc = get_twiddles(ctx, (hipStream_t)stream, &table);
   if (rc != GSS_OK) return rc;
   const long n_items = (long)S * T;
-  const long grid = (n_items + kXcds - 1) / kXcds * kXcds;
+  const long per_step = D <= 4 ? 2 * (8 / D) : D <= 8 ? 2 : 1;
+  const long steps = (n_items + per_step - 1) / per_step, most = (long)ctx->num_cu * kStftWgsPerCu * kStftShares;
+  const long grid = ((steps < most ? steps : most) + kXcds - 1) / kXcds * kXcds;
   hipLaunchKernelGGL(stft_kernel, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, (hipStream_t)stream, x, (float2*)Y,
                      table, D, (long)N, T, n_items);
   return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
