@@ -343,8 +343,11 @@ constexpr SlotTable make_slot_table() {
 }
 
 // Phase 2 of a tile: lane (tg, eg) accumulates acc[n][k] += w_k[r] * (slot n of lane type eg)[r] over its 8
-// frames r = tg, tg + 8, ... of the 64-frame tile in LDS.  sY: [64][kYStride] doubles (8 complex channels
-// per frame, zero beyond D), sW: [64][WS] doubles (KW weights per frame).
+// frames r = 8 tg, 8 tg + 1, ... of the 64-frame tile in LDS.  Rows of neighbouring frame groups are then 8 * 208 bytes apart,
+// 128 modulo the 256 bytes that LDS delivers per cycle, and a 16-byte read of the wavefront's 8 rows takes 4 cycles; with
+// frames tg, tg + 8, ... (rows 208 bytes apart, overlapping halves) it took 9.  Whole-EM kernel -1.7 to -2.7 %, chunked EM
+// -2.5 %, mvdr_cov_small -6 %.  sY: [64][kYStride] doubles (8 complex channels per frame, zero beyond D), sW: [64][WS]
+// doubles (KW weights per frame).
 template <int KW, int WS, int UNROLL = 2>
 __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, const double* __restrict__ sW,
                                                 int tg, int eg, double (&acc)[8][KW]) {
@@ -352,7 +355,7 @@ __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, c
   const int c4 = eg < 4 ? 2 * (eg + 4) : kYTurned + 2 * (eg - 4);
 #pragma unroll UNROLL
   for (int j = 0; j < 8; ++j) {
-    const int r = tg + 8 * j;              // rows of the 8 frame groups are adjacent: distinct LDS banks
+    const int r = 8 * tg + j;
     double w[KW];
 #pragma unroll
     for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
@@ -385,23 +388,23 @@ __device__ __forceinline__ void accumulate_tile_masked(const double* __restrict_
                                                        int tg, int eg, unsigned mask, double (&acc)[8][KW]) {
   // five row pointers and one weight pointer per lane; every access below is one of them plus a constant
   // (the constant goes into the offset field of the LDS instruction)
-  const double* __restrict__ p0 = sY + tg * kYStride + 2 * eg;
-  const double* __restrict__ p1 = sY + tg * kYStride + 2 * ((eg + 1) & 7);
-  const double* __restrict__ p2 = sY + tg * kYStride + 2 * ((eg + 2) & 7);
-  const double* __restrict__ p3 = sY + tg * kYStride + 2 * ((eg + 3) & 7);
-  const double* __restrict__ p4 = sY + tg * kYStride + (eg < 4 ? 2 * (eg + 4) : kYTurned + 2 * (eg - 4));
-  const double* __restrict__ pw = sW + tg * WS;
+  const double* __restrict__ p0 = sY + 8 * tg * kYStride + 2 * eg;
+  const double* __restrict__ p1 = sY + 8 * tg * kYStride + 2 * ((eg + 1) & 7);
+  const double* __restrict__ p2 = sY + 8 * tg * kYStride + 2 * ((eg + 2) & 7);
+  const double* __restrict__ p3 = sY + 8 * tg * kYStride + 2 * ((eg + 3) & 7);
+  const double* __restrict__ p4 = sY + 8 * tg * kYStride + (eg < 4 ? 2 * (eg + 4) : kYTurned + 2 * (eg - 4));
+  const double* __restrict__ pw = sW + 8 * tg * WS;
   double2 y[5];
   double w[KW];
   auto fetch = [&](auto JF) {
-    constexpr int o = 8 * JF.value * kYStride;     // rows of the 8 frame groups are adjacent: distinct LDS banks
+    constexpr int o = JF.value * kYStride;
     y[0] = *reinterpret_cast<const double2*>(p0 + o);
     y[1] = *reinterpret_cast<const double2*>(p1 + o);
     y[2] = *reinterpret_cast<const double2*>(p2 + o);
     y[3] = *reinterpret_cast<const double2*>(p3 + o);
     y[4] = *reinterpret_cast<const double2*>(p4 + o);
 #pragma unroll
-    for (int k = 0; k < KW; ++k) w[k] = pw[8 * JF.value * WS + k];
+    for (int k = 0; k < KW; ++k) w[k] = pw[JF.value * WS + k];
   };
   fetch(std::integral_constant<int, 0>{});
   static_for<0, 8>([&](auto JI) {

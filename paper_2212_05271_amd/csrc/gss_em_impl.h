@@ -72,7 +72,7 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // Phase 1 (lane = frame): the Hermitian outer product is generated 16 entries at a time in fp64, and
 //   q_k = <coef_k, y y^H> takes 16 row-broadcast FMAs per live class and block; posterior over the active
 //   classes; weights w_k = gamma_k / q_k.  y (as fp64) and w go to the wavefront's LDS tile.
-// Phase 2 (lane = (frame group tg, channel eg), 8 x 8; frames tg, tg+8, ... of the tile): lane type eg = i
+// Phase 2 (lane = (frame group tg, channel eg), 8 x 8; frames 8 tg .. 8 tg + 7 of the tile): lane type eg = i
 //   owns the entries y_i conj(y_b) for b = i+1, i+2, i+3 (mod 8), and either the pair (i, i+4) (i < 4) or
 //   the real diagonal entries of channels i and i-4 (i >= 4): 8 real entries per lane, all 64 of the packed
 //   Hermitian 8 x 8 matrix over the 8 lane types, the same instructions for every lane except the last two
