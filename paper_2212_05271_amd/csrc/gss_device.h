@@ -512,6 +512,20 @@ __device__ __forceinline__ void reduce_and_store_partials(double (&acc)[8][KW], 
   }
 }
 
+// Sum of n values src[0], src[stride], ... in their order, eight loads in flight (in a plain loop every one waits out a memory
+// latency before the next goes out; the problems of a launch's tail have the most chunks, and everything waits for them).
+__device__ __forceinline__ double sum_chunks(const double* __restrict__ src, long stride, int n) {
+  double sum = 0.0;
+  for (int c0 = 0; c0 < n; c0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = c0 + u < n ? src[(c0 + u) * stride] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += v[u];
+  }
+  return sum;
+}
+
 // Workgroups of `threads` threads of kernel `kern` that one compute unit holds at a time (`dflt` if the
 // runtime cannot say).
 template <typename Kern>

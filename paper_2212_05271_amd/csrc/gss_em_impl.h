@@ -576,14 +576,10 @@ __global__ __launch_bounds__(kWave * K) void em_factor_small(
   const long slot0 = chunk_base(cmap, sf, C);
 
   if (l < E) {
-    double r = 0.0;
-    for (int c = 0; c < C; ++c) r += part[((slot0 + c) * K + k) * (long)E + l];
-    sR[k][l] = r;
+    sR[k][l] = sum_chunks(part + (slot0 * K + k) * (long)E + l, (long)K * E, C);
   }
   if (l == 0) {
-    double n = 0.0;
-    for (int c = 0; c < C; ++c) n += npart[(slot0 + c) * K + k];
-    sN[k] = n;
+    sN[k] = sum_chunks(npart + slot0 * K + k, K, C);
   }
   __syncthreads();
 

@@ -472,8 +472,7 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
 
   // class counts: lane l < K adds the chunks' counts of class l (in chunk order)
   double nl = 0.0;
-  if (lane < K)
-    for (int c = 0; c < C; ++c) nl += npart[(slot0 + c) * K + lane];
+  if (lane < K) nl = sum_chunks(npart + slot0 * K + lane, K, C);
   const double Nk = __shfl(nl, k, kWave);
   double Ntot = 0.0;
   for (int kk = 0; kk < K; ++kk) Ntot += __shfl(nl, kk, kWave);

@@ -127,13 +127,8 @@ __global__ __launch_bounds__(kWave) void mvdr_solve_small(
   const int i = l / D, j = l % D;
 
   if (on) {
-    double a = 0.0, b = 0.0;
-    for (int c = 0; c < C; ++c) {
-      a += part[((sf * C + c) * 2 + 0) * (long)E + l];
-      b += part[((sf * C + c) * 2 + 1) * (long)E + l];
-    }
-    sR[0][l] = a;
-    sR[1][l] = b;
+    sR[0][l] = sum_chunks(part + sf * C * 2 * (long)E + l, 2L * E, C);
+    sR[1][l] = sum_chunks(part + (sf * C * 2 + 1) * (long)E + l, 2L * E, C);
   }
   __syncthreads();
   double trb = 0.0, trk = 0.0;
