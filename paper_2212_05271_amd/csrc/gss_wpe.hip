@@ -227,11 +227,9 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* _
   const int tile_end = (T + kWpeTile - 1) / kWpeTile;
   const int tile_lo = chunk * tpc;
   const int tile_hi = tile_lo + tpc < tile_end ? tile_lo + tpc : tile_end;
-  const unsigned n_valid = (unsigned)(T * D);            // (values of a row: always below 2^31, its bytes below 2^32)
   // where the thread's first value of a window goes, and the step to its next one (kWpeThreads values further on)
   const int r0 = (int)threadIdx.x / D, d0 = (int)threadIdx.x - r0 * D;
   const int step_d = kWpeThreads % D, step_pos = kWpeThreads / D * P + step_d;
-  const char* __restrict__ Ybytes = reinterpret_cast<const char*>(Yrow);
   // The power of the thread's frame of a window, requested one window ahead, and with it one value of every 128-byte line
   // of the window's new frames, so that the staging loads find them in cache: the wavefronts of a compute unit tend to
   // reach the staging together, and nothing hides a memory latency there.
@@ -239,15 +237,20 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* _
   double l_next = tile_lo < tile_hi ? power_of(tile_lo * kWpeTile + (int)threadIdx.x) : 0.0;
   for (int tile = tile_lo; tile < tile_hi; ++tile) {
     const int t0 = tile * kWpeTile;
+    // The window's frames and the next window's new ones, as far as they exist, are one run of n_run values.  Its start
+    // takes 64 bits (a row may be longer than 2^32 values), positions inside it 32 (those before it wrap around).
+    const int t_run = t0 > past ? t0 - past : 0;
+    const char* __restrict__ Yrun = reinterpret_cast<const char*>(Yrow + (long)t_run * D);
+    const unsigned n_run = (unsigned)((t0 - t_run + (T - t0 < 2 * kWpeTile ? T - t0 : 2 * kWpeTile)) * D);
     __syncthreads();                                    // the previous tile's window is no longer read
     {
-      const unsigned g0 = (unsigned)((t0 - past) * D);  // the window's frames are one run of memory
+      const unsigned g0 = (unsigned)((t0 - past - t_run) * D);
       int d = d0, pos = r0 * P + d0;
       staged_copy<8, float2>(
           threadIdx.x, win_frames * D, kWpeThreads,
           [&](int m) {
             const unsigned e = g0 + (unsigned)m;
-            return e < n_valid ? *reinterpret_cast<const float2*>(Ybytes + e * 8u) : make_float2(0.f, 0.f);
+            return e < n_run ? *reinterpret_cast<const float2*>(Yrun + e * 8u) : make_float2(0.f, 0.f);
           },
           [&](int, float2 v) {
             const double re = v.x, im = v.y;              // converted once here, not at every use
@@ -272,8 +275,8 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* _
     l_next = power_of(t0 + kWpeTile + (int)threadIdx.x);
     float touched = 0.f;
     {
-      const unsigned e = (unsigned)((t0 + kWpeTile) * D) + threadIdx.x * 16u;
-      if ((int)threadIdx.x < kWpeTile * D / 16 && e < n_valid) touched = *reinterpret_cast<const float*>(Ybytes + e * 8u);
+      const unsigned e = (unsigned)((t0 + kWpeTile - t_run) * D) + threadIdx.x * 16u;
+      if ((int)threadIdx.x < kWpeTile * D / 16 && e < n_run) touched = *reinterpret_cast<const float*>(Yrun + e * 8u);
     }
     __syncthreads();
     // LDS addresses the compiler cannot take apart again (it would add the base at every use)
@@ -967,7 +970,10 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_apply_kernel(const float2*
   const int rows = fb + past;
   const float2* __restrict__ Yrow = Y + sf * (long)Tmax * D;
   {
-    const unsigned n_valid = (unsigned)(T * D), g0 = (unsigned)((t0 - past) * D);      // (one run of memory)
+    // the window's frames that exist are one run of n_run values: its start takes 64 bits, positions inside it 32
+    const int t_run = t0 > past ? t0 - past : 0;
+    const float2* __restrict__ Yrun = Yrow + (long)t_run * D;
+    const unsigned n_run = (unsigned)((t0 - t_run + (T - t0 < fb ? T - t0 : fb)) * D), g0 = (unsigned)((t0 - past - t_run) * D);
     const int step_r = kWpeThreads / D, step_d = kWpeThreads - step_r * D, step_pos = step_r * P + step_d;
     const int r0 = (int)((unsigned)threadIdx.x / (unsigned)D);
     int d = (int)threadIdx.x - r0 * D, pos = r0 * P + d;
@@ -975,7 +981,7 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_apply_kernel(const float2*
         threadIdx.x, rows * D, kWpeThreads,
         [&](int m) {
           const unsigned e = g0 + (unsigned)m;
-          return e < n_valid ? Yrow[e] : make_float2(0.f, 0.f);
+          return e < n_run ? Yrun[e] : make_float2(0.f, 0.f);
         },
         [&](int, float2 v) {
           sWin[pos] = Win::make(v);

@@ -161,3 +161,26 @@ def test_wpe_full_size_sampled_bins(env):
     GPU, a sample of them on the oracle."""
     Y, _, _ = env["synth"].reverberant_stft(F=513, T=1560, D=8, seed=0)
     _check(env, Y[None], None, 10, 2, 3, fsel=[0, 1, 100, 255, 256, 511, 512])
+
+
+@pytest.mark.parametrize("D,taps,T", [(8, 2, 2 ** 26 + 500), (32, 1, 2 ** 27 + 500)])
+def test_wpe_long_rows(env, D, taps, T):
+    """Rows of more than 2^32 bytes and of more than 2^32 values: silence, then 1000 frames of signal across the value
+    2^29 (2^32) of the row.  The silence is nobody's past, so the result is that of the signal alone."""
+    t, gss = env["torch"], env["gss"]
+    if t.cuda.mem_get_info()[0] < 2.5 * 8 * T * D:
+        pytest.skip("not enough device memory")
+    n = 1000
+    y, _, _ = env["synth"].reverberant_stft(F=1, T=n, D=D, order=taps, delay=2, seed=D)
+    Y = t.zeros((1, 1, T, D), dtype=t.complex64, device="cuda")
+    Y[0, 0, T - n:] = t.from_numpy(y[0]).cuda()
+    ctx = gss.Context(0)
+    X = gss.gss_wpe(ctx, Y, None, taps, 2, 2)
+    tail = X[0, 0, T - n:].cpu().numpy()
+    silent = not bool(t.any(t.view_as_real(X[0, 0, :T - n]) != 0))
+    ctx.close()
+    del X, Y
+    t.cuda.empty_cache()
+    want = env["w"].wpe(y.astype(np.complex128), taps, 2, 2)[0]
+    assert _rel(tail, want) <= TOL_X
+    assert silent
