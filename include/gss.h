@@ -132,9 +132,14 @@ int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, int n_fft, i
  *   taps >= 1, delay >= 1, iters >= 0 (0 copies the input); the usual setting is 10, 2, 3
  *   X      [S][F][Tmax][D] complex64 out, must not overlap Y; exact 0 at t >= T_len[s].  A bin that is
  *          silent, or too short for any frame to have a past, comes back unchanged.
- * Limits: D <= GSS_WPE_LARGE_MAX_D, D * taps <= GSS_WPE_LARGE_MAX_N, delay <= 64.  Scratch per segment and frequency, with
- * n = ceil(D taps / 16) and m = ceil(D / 16): about 4096 * (n (n + 1) / 2 + n m) bytes for the linear system (times the
- * chunks of frames where few problems are cut over several workgroups).  Arithmetic: fp64 throughout.
+ * Limits: D <= GSS_WPE_LARGE_MAX_D, D * taps <= GSS_WPE_LARGE_MAX_N, delay <= 64.  Arithmetic: fp64 throughout.
+ * Scratch, in bytes per segment and frequency, with N = D taps, n = ceil(N / 16) and m = ceil(D / 16) (the context rounds a
+ * growth up by an eighth and to a MiB):
+ *     8 Tmax                            lambda
+ *   + 16 N D (D <= 4) or 1024 ceil(N / 4) ceil(D / 8)     prediction coefficients
+ *   + 4096 (n (n + 1) / 2 + n m)        linear system, for every chunk of frames: one chunk; where S F is below 1024 the
+ *                                       problems, and in larger batches the last ones, are cut into several, at most
+ *                                       2000 (Tmax <= 6400) or 4000 (Tmax <= 100000) more altogether
  */
 int gss_wpe(gss_ctx* ctx, const float* Y, const int32_t* T_len, int S, int F, int Tmax, int D,
             int taps, int delay, int iters, float* X, void* stream);

@@ -137,9 +137,9 @@ __device__ __forceinline__ V lds_at(unsigned address, int elem) {
 // sum_t (w_t a_i(t)) conj(b_j(t)).  The complex product takes three real ones, S1 = sum w Re a Re b,
 // S2 = sum w Im a Im b and S3 = sum w (Re a + Im a)(Re b - Im b): the real part is S1 + S2, the imaginary part
 // S3 - S1 + S2.  Lanes of rows or columns >= N (or >= D) repeat the last one; nothing uses their results.
-// Few tiles (small D * taps): `split` wavefronts share their tiles, each takes a part of the window's frames and writes
-// partial sums of its own.  Many tiles (large arrays): G workgroups per chunk (blockIdx.x = chunk slot * G + g).
-// part[((chunk slot * split + part) * tiles + tile) * 256 ..]: the tile's entries.
+// Few tiles (small D * taps): `split` wavefronts share their tiles, each takes a part of the window's frames; their sums
+// meet in LDS at the end.  Many tiles (large arrays): G workgroups per chunk (blockIdx.x = chunk slot * G + g).
+// part[(chunk slot * tiles + tile) * 256 ..]: the tile's entries.
 //
 // Bound: the fp64 matrix rate.  Vector instructions do not run beside a fp64 matrix instruction of the same SIMD (busy
 // times of the two add up), so the loop is written for few of them: Re - Im is kept in LDS beside the value, the
@@ -346,16 +346,41 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* _
     }
     asm volatile("" ::"v"(touched));                    // (the load above is not dropped)
   }
-  double2* __restrict__ out = part + ((size_t)slot * split + part_of) * n_tiles * kTileEntries + lane;
+  double2* __restrict__ out = part + (size_t)slot * n_tiles * kTileEntries + lane;
+  // A tile of every wavefront that is not the first on its tiles, in the window's place (kWpeCovSumBytes): one set of tiles
+  // per chunk is written, whatever `split` is.
+  double2* __restrict__ sSum = reinterpret_cast<double2*>(lds_raw) + lane;
 #pragma unroll
-  for (int q = 0; q < TPW; ++q)
-    if (first + q < n_tiles) {
+  for (int q = 0; q < TPW; ++q) {
+    double2 x[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        out[(size_t)(first + q) * kTileEntries + v * kWave] =
-            make_double2(s1[q][v] + s2[q][v], (s3[q][v] - s1[q][v]) + s2[q][v]);
+    for (int v = 0; v < 4; ++v) x[v] = make_double2(s1[q][v] + s2[q][v], (s3[q][v] - s1[q][v]) + s2[q][v]);
+    if (split > 1) {
+      __syncthreads();                                  // the window, or the tile before, is no longer read
+      if (part_of > 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sSum[(wave - 1 - wave / split) * kTileEntries + v * kWave] = x[v];
+      }
+      __syncthreads();
+      if (part_of == 0)
+        for (int u = 0; u < split - 1; ++u) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double2 y = sSum[(wave / split * (split - 1) + u) * kTileEntries + v * kWave];
+            x[v].x += y.x;
+            x[v].y += y.y;
+          }
+        }
     }
+    if (part_of == 0 && first + q < n_tiles) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(size_t)(first + q) * kTileEntries + v * kWave] = x[v];
+    }
+  }
 }
+
+// LDS in which the wavefronts that share their tiles add them up: one tile of at most 3 of the 4.
+constexpr int kWpeCovSumBytes = 3 * kTileEntries * (int)sizeof(double2);
 
 // Workgroups per compute unit that the chunks are planned for: two wavefronts per SIMD keep its matrix core busy, and
 // finer chunks would only add partial sums (more workgroups may be resident).
@@ -403,8 +428,10 @@ inline wpe_cov_fn wpe_cov_of(int D, int tpw, int& pitch) {
     default: return wpe_cov_tpw<32>(tpw);
   }
 }
-inline int wpe_cov_lds(int pitch, int taps, int delay) {
-  return (kWpeTile + delay + taps - 1) * pitch * 3 * (int)sizeof(double) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double);
+inline int wpe_cov_lds(int pitch, int taps, int delay, int split) {
+  const int window =
+      (kWpeTile + delay + taps - 1) * pitch * 3 * (int)sizeof(double) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double);
+  return split > 1 && window < kWpeCovSumBytes ? kWpeCovSumBytes : window;
 }
 // Largest window accepted (64 KB for the values and the weights).
 inline bool wpe_window_fits(int D, int taps, int delay) {
@@ -450,11 +477,10 @@ constexpr int kSolveMaxSlots = 4;             // partial sums per problem that t
 // their tiles are added up here, one workgroup per tile, into the first chunk's.  (One workgroup of the solve kernel
 // would read all of them alone: 24 chunks of the last of 513 bins took 1.4 ms at 24 channels, everything else 0.65 ms.)
 __global__ __launch_bounds__(kTileEntries) void wpe_sum_chunks_kernel(double2* __restrict__ part, ChunkMap cmap, long sf0,
-                                                                      int split, int n_tiles) {
+                                                                      int n_tiles) {
   const long sf = sf0 + blockIdx.x / (unsigned)n_tiles;
   int count;
-  const long slot0 = chunk_base(cmap, sf, count) * split;
-  count *= split;
+  const long slot0 = chunk_base(cmap, sf, count);
   const size_t stride = (size_t)n_tiles * kTileEntries;
   double2* __restrict__ t = part + (size_t)slot0 * stride + (size_t)(blockIdx.x % (unsigned)n_tiles) * kTileEntries + threadIdx.x;
   double2 sum = t[0];
@@ -529,7 +555,7 @@ __device__ __forceinline__ CTile tile_zero() {
 
 __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __restrict__ part, double2* __restrict__ Gc,
                                                                      uint32_t* __restrict__ status, int D, int taps,
-                                                                     ChunkMap cmap, int split, int rt) {
+                                                                     ChunkMap cmap, int rt) {
   __shared__ double2 sG[2][(GSS_WPE_LARGE_MAX_D + 15) / 16][kTileEntries];
   __shared__ double2 sRow[16];
   __shared__ double sPiv[16];
@@ -539,8 +565,7 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
   const int nt = (N + 15) / 16, ntd = (D + 15) / 16, nc = nt + ntd;
   const int n_tiles = wpe_num_tiles(nt, ntd);
   int count;
-  const long slot0 = chunk_base(cmap, sf, count) * split;
-  count *= split;
+  const long slot0 = chunk_base(cmap, sf, count);
   if (count > kSolveMaxSlots) count = 1;                   // (wpe_sum_chunks_kernel has added them up)
   double2* __restrict__ A = part + (size_t)slot0 * n_tiles * kTileEntries;       // the tiles of the first chunk
   const size_t slot_stride = (size_t)n_tiles * kTileEntries;
@@ -761,15 +786,14 @@ __global__ __launch_bounds__(kSolveThreads, 3) void wpe_solve_kernel(double2* __
 }
 
 inline void wpe_launch_solve(double2* part, double2* Gc, uint32_t* status, long n_sf, int D, int taps, const ChunkMap& cmap,
-                             int split, int rt, hipStream_t st) {
+                             int rt, hipStream_t st) {
   const int n_tiles = wpe_num_tiles((D * taps + 15) / 16, (D + 15) / 16);
-  const bool all = cmap.c_main * split > kSolveMaxSlots;
+  const bool all = cmap.c_main > kSolveMaxSlots;
   const long sf0 = all ? 0 : cmap.n_main;
-  if ((all || cmap.c_tail * split > kSolveMaxSlots) && sf0 < n_sf)
+  if ((all || cmap.c_tail > kSolveMaxSlots) && sf0 < n_sf)
     hipLaunchKernelGGL(wpe_sum_chunks_kernel, dim3((unsigned)((n_sf - sf0) * n_tiles)), dim3(kTileEntries), 0, st, part, cmap, sf0,
-                       split, n_tiles);
-  hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, part, Gc, status, D, taps, cmap, split,
-                     rt);
+                       n_tiles);
+  hipLaunchKernelGGL(wpe_solve_kernel, dim3((unsigned)n_sf), dim3(kSolveThreads), 0, st, part, Gc, status, D, taps, cmap, rt);
 }
 
 // Apply for up to kApplyFewMaxD channels: lane = frame.  (A tile of the matrix cores has 16 rows, Re and Im of 8 channels:
@@ -1126,7 +1150,7 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   const WpeTiling til = wpe_tiling(n_tiles);
   int pitch;
   const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
-  const int cov_lds = wpe_cov_lds(pitch, taps, delay);
+  const int cov_lds = wpe_cov_lds(pitch, taps, delay, til.split);
   const WpeApply ap = wpe_apply_of(D, taps, delay);
   const int fb_power = D > GSS_WPE_MAX_D ? 64 : 256;
   // (windows of at most 64 KB, in the apply kernel at the smallest odd frame pitch)
@@ -1153,7 +1177,7 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   size_t o = 0;
   const size_t off_lam = o;  o = gss_align_up(o + (size_t)n_sf * Tmax * sizeof(double), 256);
   const size_t off_g = o;    o = gss_align_up(o + coef_bytes, 256);
-  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * til.split * n_tiles * kTileEntries * sizeof(double2), 256);
+  const size_t off_part = o; o = gss_align_up(o + (size_t)wgs * n_tiles * kTileEntries * sizeof(double2), 256);
   const int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
@@ -1171,7 +1195,7 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
     hipLaunchKernelGGL(cov, dim3((unsigned)(wgs * til.groups)), block, cov_lds, st, Y, T_len, lam, part, F, Tmax, D, taps, delay,
                        cmap, til.groups, til.split);
     gss_profile_end(ctx, 2, st);
-    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, til.split, ap.rt, st);
+    wpe_launch_solve(part, Gc, ctx->status, n_sf, D, taps, cmap, ap.rt, st);
     int bps = (int)bps_apply;
     int apitch = D | 1;
     void* few[] = {&Y, &T_len, &Gc, &lam, &X, &F, &Tmax, &taps, &delay, &bps, &apitch, &nb_apply, &px_apply};

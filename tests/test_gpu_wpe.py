@@ -184,3 +184,20 @@ def test_wpe_long_rows(env, D, taps, T):
     want = env["w"].wpe(y.astype(np.complex128), taps, 2, 2)[0]
     assert _rel(tail, want) <= TOL_X
     assert silent
+
+
+@pytest.mark.parametrize("S,D,taps", [(8, 1, 16), (8, 2, 10), (8, 4, 8), (8, 6, 8), (4, 12, 3), (4, 8, 10)])
+def test_wpe_scratch_is_what_the_header_states(env, S, D, taps):
+    """One set of 16 x 16 tiles per problem, also where several wavefronts share the tiles of a small system."""
+    t, gss = env["torch"], env["gss"]
+    F, T, N = 513, 70, D * taps
+    n, m = -(-N // 16), -(-D // 16)
+    tiles = 4096 * (n * (n + 1) // 2 + n * m)
+    coef = 16 * N * D if D <= 4 else 1024 * -(-N // 4) * -(-D // 8)
+    ctx = gss.Context(0)
+    Y = t.randn((S, F, T, D), dtype=t.complex64, device="cuda")
+    gss.gss_wpe(ctx, Y, None, taps, 2, 1)
+    held = ctx.scratch_bytes()
+    t.cuda.synchronize()
+    ctx.close()
+    assert held <= 1.125 * (S * F * (8 * T + coef + tiles) + 500 * tiles) + (1 << 21)
