@@ -241,7 +241,8 @@ int gss_mvdr_ex(gss_ctx* ctx, const float* Y, int64_t Trec, const int64_t* frame
  * Inverse STFT matching gss_stft: inverse real FFT, synthesis window w / sum_shifts(w^2), overlap-add,
  * padding stripped.
  *   X  [S][F][T] complex64   (F = n_fft/2 + 1)
- *   x  [S][N] float32 out, with ceil(N / hop) + 3 == T
+ *   x  [S][N] float32 out, with ceil(N / hop) + 3 == T; may share memory with X (the call then works on a copy of X in
+ *      the context's scratch memory)
  */
 int gss_istft(gss_ctx* ctx, const float* X, int S, int T, int n_fft, int hop,
               float* x, int64_t N, void* stream);

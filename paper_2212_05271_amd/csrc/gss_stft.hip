@@ -393,6 +393,11 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* 
   }
 }
 
+// A copy of a spectrum that shares memory with the output (gss_istft).
+__global__ void copy_spectrum_kernel(const float2* __restrict__ X, float2* __restrict__ copy, long n) {
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) copy[i] = X[i];
+}
+
 // The context's twiddle table, created on first use; the fill is ordered before the caller's kernels on `st`.
 int get_twiddles(gss_ctx* ctx, hipStream_t st, const float2** out) {
   if (!ctx->twiddles) {
@@ -440,8 +445,17 @@ extern "C" int gss_istft(gss_ctx* ctx, const float* X, int S, int T, int n_fft, 
   if ((long)S * ((T + 7) / 8) > 0x7fffffffL) return GSS_EUNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;
   const float2* table = nullptr;
-  const int rc = get_twiddles(ctx, st, &table);
+  int rc = get_twiddles(ctx, st, &table);
   if (rc != GSS_OK) return rc;
+  // Output over the input: workgroups write samples while others still read frames, so these are read from a copy.
+  const long n_spec = (long)S * kBins * T;
+  const uintptr_t in0 = (uintptr_t)X, in1 = in0 + n_spec * sizeof(float2), out0 = (uintptr_t)x, out1 = out0 + (size_t)S * N * sizeof(float);
+  if (in0 < out1 && out0 < in1) {
+    rc = gss_ensure_scratch(ctx, n_spec * sizeof(float2));
+    if (rc != GSS_OK) return rc;
+    hipLaunchKernelGGL(copy_spectrum_kernel, dim3(ctx->num_cu * 8), dim3(256), 0, st, (const float2*)X, (float2*)ctx->scratch, n_spec);
+    X = (const float*)ctx->scratch;
+  }
   // Steps of eight frames per workgroup: long runs (three of the frames are done twice) as long as the workgroups fill the
   // compute units a few times over, single steps for small calls.
   const long blocks = (long)S * (T - 3), want = (long)ctx->num_cu * 6;

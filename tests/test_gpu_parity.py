@@ -518,6 +518,18 @@ def _check_stft_istft(env, S, D, N):
     assert np.linalg.norm(back - x[:, 0]) <= TOL_STFT * np.linalg.norm(x[:, 0])
 
 
+@pytest.mark.parametrize("S,N,shift", [(40, 256 * 600, 0), (3, 256 * 90 + 7, 4096), (70, 5000, 1)])
+def test_istft_output_over_its_input(env, S, N, shift):
+    t, gss = env["torch"], env["gss"]
+    T = -(-N // 256) + 3
+    X = t.randn((S, 513, T), dtype=t.complex64, device="cuda")
+    want = gss.gss_istft(env["ctx"], X, N)
+    out = t.view_as_real(X).reshape(-1)[shift:shift + S * N].view(S, N)
+    assert out.data_ptr() == X.data_ptr() + 4 * shift
+    got = gss.gss_istft(env["ctx"], X, N, out=out)
+    assert t.equal(got, want)
+
+
 def test_full_chain_time_domain(env):
     """x -> STFT -> EM -> MVDR -> iSTFT on the GPU against the same chain in the oracle (the oracle's STFT
     is rounded to complex64, the type of the boundary between the stages)."""
