@@ -433,6 +433,7 @@ inline int wpe_cov_lds(int pitch, int taps, int delay, int split) {
       (kWpeTile + delay + taps - 1) * pitch * 3 * (int)sizeof(double) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double);
   return split > 1 && window < kWpeCovSumBytes ? kWpeCovSumBytes : window;
 }
+constexpr int kWpeLdsLimit = 160 * 1024;      // LDS of a compute unit
 // Largest window accepted (64 KB for the values and the weights).
 inline bool wpe_window_fits(int D, int taps, int delay) {
   return ((kWpeTile + delay + taps) * D + 8) * (int)sizeof(double2) + (kWpeTile + kWpeThreads / kWave) * (int)sizeof(double) <=
@@ -1155,10 +1156,10 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   const int fb_power = D > GSS_WPE_MAX_D ? 64 : 256;
   // (windows of at most 64 KB, in the apply kernel at the smallest odd frame pitch)
   if ((ap.fb + delay + taps - 1) * (D | 1) * (int)sizeof(float2) > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
-  if (hipFuncSetAttribute(ap.fn[0], hipFuncAttributeMaxDynamicSharedMemorySize, ap.lds) != hipSuccess ||
-      hipFuncSetAttribute(ap.fn[1], hipFuncAttributeMaxDynamicSharedMemorySize, ap.lds) != hipSuccess ||
-      hipFuncSetAttribute((const void*)cov, hipFuncAttributeMaxDynamicSharedMemorySize, cov_lds) != hipSuccess)
-    return GSS_EHIP;
+  // (the attribute belongs to the process: every call sets the same value, so that one thread's call cannot lower the limit
+  // between another's setting it and its launch)
+  for (const void* fn : {ap.fn[0], ap.fn[1], (const void*)cov})
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kWpeLdsLimit) != hipSuccess) return GSS_EHIP;
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cov, kWpeThreads, (size_t)cov_lds) != hipSuccess || per_cu < 1)
     per_cu = 1;

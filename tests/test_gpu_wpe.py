@@ -201,3 +201,31 @@ def test_wpe_scratch_is_what_the_header_states(env, S, D, taps):
     t.cuda.synchronize()
     ctx.close()
     assert held <= 1.125 * (S * F * (8 * T + coef + tiles) + 500 * tiles) + (1 << 21)
+
+
+def test_wpe_two_threads(env):
+    """Two threads with a context and a stream of their own, on the same kernels with windows of different sizes."""
+    import threading
+    t, gss = env["torch"], env["gss"]
+    Y = t.randn((1, 16, 260, 8), dtype=t.complex64, device="cuda")
+    want = {delay: gss.gss_wpe(env["ctx"], Y, None, 10, delay, 1) for delay in (2, 64)}
+    t.cuda.synchronize()
+    errors = []
+
+    def work(delay):
+        try:
+            with gss.Context(0) as ctx, t.cuda.stream(t.cuda.Stream()):
+                for _ in range(200):
+                    X = gss.gss_wpe(ctx, Y, None, 10, delay, 1)
+                t.cuda.current_stream().synchronize()
+                assert t.equal(X, want[delay])
+                t.cuda.current_stream().synchronize()
+        except Exception as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(d,)) for d in want]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not errors, errors
