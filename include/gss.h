@@ -49,10 +49,10 @@ typedef enum gss_status {
 /* Limits of the kernels in this build. */
 #define GSS_MAX_D 32
 #define GSS_MAX_K 8
-#define GSS_WPE_MAX_D 8  /* gss_wpe: channels                                   */
-#define GSS_WPE_MAX_N 80 /* gss_wpe: channels x taps (size of the linear system) */
-#define GSS_WPE_LARGE_MAX_D 32  /* gss_wpe, large arrays: channels                  */
-#define GSS_WPE_LARGE_MAX_N 320 /* gss_wpe, large arrays: channels x taps           */
+#define GSS_WPE_LARGE_MAX_D 32  /* gss_wpe: channels                                   */
+#define GSS_WPE_LARGE_MAX_N 320 /* gss_wpe: channels x taps (size of the linear system) */
+#define GSS_WPE_MAX_D 8         /* no limit of any call: kept for programs that name them */
+#define GSS_WPE_MAX_N 80
 #define GSS_STATIC_SCRATCH_BYTES (64u << 20) /* gss_cacgmm_em_noalloc: size of the static scratch array per GPU */
 
 /* Bits of the device status word (gss_get_status). */
@@ -240,7 +240,7 @@ int gss_mvdr_ex(gss_ctx* ctx, const float* Y, int64_t Trec, const int64_t* frame
 /*
  * Inverse STFT matching gss_stft: inverse real FFT, synthesis window w / sum_shifts(w^2), overlap-add,
  * padding stripped.
- *   X  [S][F][T] complex64   (F = n_fft/2 + 1)
+ *   X  [S][F][T] complex64   (F = n_fft/2 + 1), S <= 65535
  *   x  [S][N] float32 out, with ceil(N / hop) + 3 == T; may share memory with X (the call then works on a copy of X in
  *      the context's scratch memory)
  */

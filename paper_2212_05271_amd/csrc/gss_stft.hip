@@ -165,7 +165,7 @@ __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (
 // unit (LDS); the twiddles of a lane are set up once per workgroup.  Ten minutes of 8 channels: 548 us = 2.8 TB/s (one
 // workgroup per frame, 64-byte runs: 722 us; an even share of consecutive frames per workgroup instead of turns: 583 us).
 // ----------------------------------------------------------------------------------------------
-constexpr int kStftWgsPerCu = 2, kStftShares = 1;          // workgroups: up to kStftShares rounds of the resident ones
+constexpr int kStftWgsPerCu = 2;                           // resident workgroups; no more are launched
 // Row pitch: 1 modulo 16, so that sixteen rows are read at one bin without bank conflicts.
 constexpr int kStftRow = 577;
 static_assert(kStftRow >= 8 * kExStride && kStftRow >= kBins && kStftRow % 16 == 1, "row pitch of the transforms in LDS");
@@ -428,7 +428,7 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   if (rc != GSS_OK) return rc;
   const long n_items = (long)S * T;
   const long per_step = D <= 4 ? 2 * (8 / D) : D <= 8 ? 2 : 1;
-  const long steps = (n_items + per_step - 1) / per_step, most = (long)ctx->num_cu * kStftWgsPerCu * kStftShares;
+  const long steps = (n_items + per_step - 1) / per_step, most = (long)ctx->num_cu * kStftWgsPerCu;
   const long grid = ((steps < most ? steps : most) + kXcds - 1) / kXcds * kXcds;
   hipLaunchKernelGGL(stft_kernel, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, (hipStream_t)stream, x, (float2*)Y,
                      table, D, (long)N, T, n_items);
@@ -440,7 +440,7 @@ extern "C" int gss_istft(gss_ctx* ctx, const float* X, int S, int T, int n_fft, 
   if (!ctx || !X || !x || S <= 0 || T <= 0 || N <= 0) return GSS_EINVAL;
   if (n_fft != kN || hop != kHop) return GSS_EUNSUPPORTED;
   if ((N + hop - 1) / hop + 3 != T) return GSS_EINVAL;
-  if (S > 65535) return GSS_EUNSUPPORTED;
+  if (S > 65535) return GSS_EUNSUPPORTED;                  // (a limit of the call, not of the kernel)
   if (hipSetDevice(ctx->device) != hipSuccess) return GSS_EHIP;
   if ((long)S * ((T + 7) / 8) > 0x7fffffffL) return GSS_EUNSUPPORTED;
   hipStream_t st = (hipStream_t)stream;

@@ -10,8 +10,8 @@
 //   solve  : R += 1e-10 tr(R)/N I,  G = R^-1 P
 //   apply  : x_t = y_t - G^H ytilde_t  (and lambda for the next iteration, or the complex64 output)
 //
-// R and P are accumulated on the fp64 matrix cores.  Everything up to the output is fp64: R is built from strongly correlated delayed copies of one signal and
-// the solve amplifies rounding errors of the sums by its condition number.
+// R and P are accumulated on the fp64 matrix cores.  Everything up to the output is fp64: R is built from strongly
+// correlated delayed copies of one signal and the solve amplifies rounding errors of the sums by its condition number.
 #include "gss_internal.h"
 
 #include "gss_device.h"
@@ -74,11 +74,12 @@ __device__ __forceinline__ long xcd_block(unsigned b, long per_xcd) { return (lo
 
 // lambda of the observation itself (first iteration).  The block's frames are read as one contiguous run
 // (coalesced), |y|^2 per component goes to LDS, then thread = frame sums its D values in channel order.
-// fb = frames per block (256 for D <= 8, 64 for larger arrays: fb * (D | 1) doubles of LDS).
+// fb = frames per block (256 for D <= kPowerMaxD, 64 for larger arrays: fb * (D | 1) doubles of LDS).
+constexpr int kPowerMaxD = 8;
 __global__ __launch_bounds__(kWpeThreads) void wpe_power_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
                                                                 double* __restrict__ lam, int F, int Tmax, int D,
                                                                 int blocks_per_sf, long n_blocks, long per_xcd, int fb) {
-  __shared__ double sP[kWpeThreads * (GSS_WPE_MAX_D + 1)];
+  __shared__ double sP[kWpeThreads * (kPowerMaxD + 1)];
   const long blk = xcd_block(blockIdx.x, per_xcd);
   if (blk >= n_blocks) return;
   const long sf = blk / blocks_per_sf;
@@ -109,8 +110,8 @@ __global__ __launch_bounds__(kWpeThreads) void wpe_power_kernel(const float2* __
 // wavefront hold it: entry (i, j) at 16 i + j.
 typedef double double4v __attribute__((ext_vector_type(4)));
 constexpr int kTileEntries = 256;
-__host__ __device__ inline int wpe_tile_base(int p, int nt, int ntd) { return p * (nt + ntd) - p * (p - 1) / 2; }
-__host__ __device__ inline int wpe_num_tiles(int nt, int ntd) { return wpe_tile_base(nt, nt, ntd); }
+__host__ __device__ constexpr int wpe_tile_base(int p, int nt, int ntd) { return p * (nt + ntd) - p * (p - 1) / 2; }
+__host__ __device__ constexpr int wpe_num_tiles(int nt, int ntd) { return wpe_tile_base(nt, nt, ntd); }
 
 // D += A B of 16 x 4 and 4 x 16 doubles.  Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], and D[l / 16 + 4 v][l % 16]
 // for v = 0..3: entry v of a tile's lane is entry 64 v + l of the tile's storage.
@@ -175,8 +176,8 @@ __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* _
   const int steps = kWpeTile / 4 / split;                // groups of four frames per window (4, 8 or 16)
 
   // Positions of the tiles' operands in the window: lane (k, i) = (l / 16, l % 16) holds component i of the tile at
-  // frame k of the group.  TPW <= 5 consecutive tiles lie in at most two tile rows (rows get shorter by one from 2 or 3
-  // tiles at the bottom up): the first n0 of them in row p0, the others in the next.
+  // frame k of the group.  The TPW consecutive tiles of a wavefront lie in at most two tile rows (wpe_tiling_fits): the
+  // first n0 of them in row p0, the others in the next.
   const int k4 = lane >> 4, li = lane & 15;
   int apos0, apos1, n0 = TPW;
   int bpos[TPW];
@@ -386,14 +387,14 @@ constexpr int kWpeCovSumBytes = 3 * kTileEntries * (int)sizeof(double2);
 // finer chunks would only add partial sums (more workgroups may be resident).
 constexpr int kWpeCovPerCu = 2;
 
-// Tiles per wavefront (1..5), wavefronts that share the same tiles, workgroups per chunk.
+// Tiles per wavefront (2..5), wavefronts that share the same tiles, workgroups per chunk.
 struct WpeTiling { int tpw, split, groups; };
 // Chosen by the time of one 64-frame window: TPW tiles of 48 matrix instructions of 64 cycles each in every wavefront,
 // divided among the wavefronts that share them, plus about 1500 cycles of staging, for each of the groups.
-inline WpeTiling wpe_tiling(int n_tiles) {
-  WpeTiling best{1, 1, 1};
+constexpr WpeTiling wpe_tiling(int n_tiles) {
+  WpeTiling best{5, 1, 1};
   long best_cost = -1;
-  for (int tpw = 5; tpw >= 1; --tpw) {
+  for (int tpw = 5; tpw >= 2; --tpw) {
     const int waves = (n_tiles + tpw - 1) / tpw;
     const int split = waves == 1 ? 4 : waves == 2 ? 2 : 1;
     const int groups = waves <= 2 ? 1 : (waves + 3) / 4;
@@ -405,12 +406,31 @@ inline WpeTiling wpe_tiling(int n_tiles) {
   }
   return best;
 }
+// What the covariance kernel takes for granted of every legal system (nt tile rows, ntd column tiles of P; D > 16 has
+// nt >= 2): no wavefront's tiles touch three tile rows, and with two column tiles there are three tiles per wavefront or
+// more.  The rows get shorter by one down to 1 + ntd tiles, so five tiles from the last one of a row of 4 on (ntd = 1) would
+// touch three; a wavefront starts at a multiple of 5, and none of the sizes puts that tile there.
+constexpr bool wpe_tiling_fits() {
+  for (int ntd = 1; ntd <= (GSS_WPE_LARGE_MAX_D + 15) / 16; ++ntd)
+    for (int nt = ntd; nt <= (GSS_WPE_LARGE_MAX_N + 15) / 16; ++nt) {
+      const int n_tiles = wpe_num_tiles(nt, ntd), tpw = wpe_tiling(n_tiles).tpw;
+      if (tpw < 1 + ntd) return false;
+      for (int first = 0, p = 0; first < n_tiles; first += tpw) {
+        while (p + 1 < nt && wpe_tile_base(p + 1, nt, ntd) <= first) ++p;
+        const int last = first + tpw < n_tiles ? first + tpw - 1 : n_tiles - 1;
+        if (p + 2 < nt && wpe_tile_base(p + 2, nt, ntd) <= last) return false;
+      }
+    }
+  return true;
+}
+static_assert(wpe_tiling_fits(), "a wavefront of the covariance kernel has one left operand for each of two tile rows");
+
 typedef void (*wpe_cov_fn)(const float2*, const int32_t*, const double*, double2*, int, int, int, int, int, ChunkMap, int, int);
 template <int P>
 inline wpe_cov_fn wpe_cov_tpw(int tpw) {
+  if constexpr (P <= 16)
+    if (tpw == 2) return wpe_cov_kernel<P, 2>;
   switch (tpw) {
-    case 1: return wpe_cov_kernel<P, 1>;
-    case 2: return wpe_cov_kernel<P, 2>;
     case 3: return wpe_cov_kernel<P, 3>;
     case 4: return wpe_cov_kernel<P, 4>;
     default: return wpe_cov_kernel<P, 5>;
@@ -1153,7 +1173,7 @@ int run_wpe(gss_ctx* ctx, const float2* Y, const int32_t* T_len, int S, int F, i
   const wpe_cov_fn cov = wpe_cov_of(D, til.tpw, pitch);
   const int cov_lds = wpe_cov_lds(pitch, taps, delay, til.split);
   const WpeApply ap = wpe_apply_of(D, taps, delay);
-  const int fb_power = D > GSS_WPE_MAX_D ? 64 : 256;
+  const int fb_power = D > kPowerMaxD ? 64 : 256;
   // (windows of at most 64 KB, in the apply kernel at the smallest odd frame pitch)
   if ((ap.fb + delay + taps - 1) * (D | 1) * (int)sizeof(float2) > 64 * 1024 || !wpe_window_fits(D, taps, delay)) return GSS_EUNSUPPORTED;
   // (the attribute belongs to the process: every call sets the same value, so that one thread's call cannot lower the limit
