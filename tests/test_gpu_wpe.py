@@ -1,7 +1,7 @@
 """GPU parity of gss_wpe (through the C ABI) against the float64 WPE oracle on the same seeded inputs.
-Tolerance: relative L2 error of the dereverberated STFT <= 1e-4 per frequency bin (the bar of the
-beamformed STFT; both sides compute in fp64 and the output is rounded to complex64, so the measured error
-is the fp32 rounding, ~4e-8); structural zeros (t >= T_len) bit-exact."""
+Tolerance: relative L2 error of the dereverberated STFT per frequency bin: the rounding of the output to complex64 and the
+amplification of both sides' fp64 rounding by the condition of the last iteration's correlation matrix (_tolerance), and
+at most 1e-4 (the bar of the beamformed STFT); structural zeros (t >= T_len) bit-exact."""
 
 import numpy as np
 import pytest
@@ -9,6 +9,22 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 TOL_X = 1e-4
+
+
+def _tolerance(env, y, taps, delay, iters):
+    """Bound on the relative error of a bin y [T, D].  Rounding the output costs 2^-24 (2^-23 allowed).  Solving a system of
+    condition c in fp64 costs c 2^-53 times a modest factor on either side; measured against extended precision the
+    factor is 0.05 or less (c = 1.9e11: 9e-7 on either side), so c 2^-52 leaves room for both sides."""
+    w = env["w"]
+    tol = 2.0 ** -23
+    if iters > 0 and y.shape[0] > 0:
+        lam = w.variance(w.wpe_bin(y, taps, delay, iters - 1))
+        yt = w.stack_delayed(y, taps, delay)
+        if lam.max() > 0.0 and np.any(yt):
+            R = (yt.T / lam) @ yt.conj()
+            R += (w.LOAD_REL * np.real(np.trace(R)) / R.shape[0]) * np.eye(R.shape[0])
+            tol += 2.0 ** -52 * np.linalg.cond(R)
+    return min(TOL_X, tol)
 
 
 @pytest.fixture(scope="module")
@@ -51,8 +67,9 @@ def _check(env, Y, T_len, taps, delay, iters, fsel=None):
             if np.linalg.norm(want[i]) == 0.0:
                 assert np.array_equal(X[s, f], np.zeros_like(X[s, f]))
                 continue
-            worst = max(worst, _rel(X[s, f], want[i]))
-    assert worst <= TOL_X, worst
+            err, tol = _rel(X[s, f], want[i]), _tolerance(env, Y[s, f, :Tv].astype(np.complex128), taps, delay, iters)
+            assert err <= tol, (s, f, err, tol)
+            worst = max(worst, err)
     return worst
 
 
@@ -117,8 +134,8 @@ def test_wpe_rejects_unsupported_shapes(env):
 @pytest.mark.parametrize("D,taps,delay,T", [(9, 3, 2, 200), (12, 5, 2, 300), (16, 10, 2, 500), (24, 10, 2, 700),
                                              (32, 10, 1, 800), (8, 12, 2, 400), (10, 1, 1, 130), (13, 7, 3, 450)])
 def test_wpe_large_arrays(env, D, taps, delay, T):
-    """More than 8 channels, or more than 80 unknowns per channel: several groups of covariance blocks, the
-    blocked factorisation in global memory, the run-time-D apply kernel."""
+    """More than 8 channels, or more than 80 unknowns: several workgroups per chunk in the covariance, many tile rows in the
+    factorisation, two and more tiles of channels in the prediction."""
     Y, _, _ = env["synth"].reverberant_stft(F=3, T=T, D=D, order=min(taps, 6), delay=delay, seed=D * 100 + taps)
     _check(env, Y[None], None, taps, delay, 3)
     assert env["ctx"].get_status() == 0
@@ -182,7 +199,7 @@ def test_wpe_long_rows(env, D, taps, T):
     del X, Y
     t.cuda.empty_cache()
     want = env["w"].wpe(y.astype(np.complex128), taps, 2, 2)[0]
-    assert _rel(tail, want) <= TOL_X
+    assert _rel(tail, want) <= _tolerance(env, y[0].astype(np.complex128), taps, 2, 2)
     assert silent
 
 
