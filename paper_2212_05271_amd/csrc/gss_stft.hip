@@ -155,26 +155,31 @@ __device__ __forceinline__ float2 hann_pair(const float2* tw, int n) {
 __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (long)((unsigned long)w * (unsigned long)n / (unsigned long)wgs); }
 
 // ----------------------------------------------------------------------------------------------
-// STFT.  A workgroup takes several steps of (segment, frame) items; a step is two units of 8 transforms, one per
-// wavefront: a unit is all channels of a frame (of 8 / D consecutive frames with fewer than 5 channels), or 8 channels of
-// a frame with more than 8.  The samples of the next unit are requested before the current transforms.  The spectrum
-// replaces the transform in the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and
-// X[512 - k]), and the workgroup writes a bin's values of both units as one run of memory (128 bytes for 8 channels).
+// STFT.  A workgroup takes steps of (segment, frame) items; a step is UNITS units of 8 transforms, one per wavefront: a unit
+// is all channels of a frame (of 8 / D consecutive frames with fewer than 5 channels), or 8 channels of a frame with more
+// than 8.  The samples of the next unit are requested before the current transforms.  The spectrum replaces the transform in
+// the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and X[512 - k]), and the workgroup
+// writes a bin's values of the step as one run of memory (128 bytes for two units of 8 channels).
 //
-// Bound: memory (samples read once per overlapping frame from L2, the spectrum written once).  Two workgroups per compute
-// unit (LDS); the twiddles of a lane are set up once per workgroup.  Ten minutes of 8 channels: 548 us = 2.8 TB/s (one
-// workgroup per frame, 64-byte runs: 722 us; an even share of consecutive frames per workgroup instead of turns: 583 us).
+// Bound: latency.  Two workgroups per compute unit are resident, held there by 128 registers and, for two units, by LDS; each
+// has one unit of samples in flight.  At 128 registers 20 (two units) or 14 (one) are spilled to scratch memory, 84 or 60 bytes
+// per lane.  Ten minutes of 8 channels: 548 us = 2.8 TB/s (one workgroup per frame, 64-byte runs: 722 us; an even share of
+// consecutive frames per workgroup instead of turns: 583 us).
+//
+// One unit per step for short calls (gss_stft): 8 channels 7.7, 10.7, 17.2 us at 130, 510, 1020 frames (two units 11.0, 12.5,
+// 17.0; one workgroup per frame 8.1, 11.2, 20.6).
 // ----------------------------------------------------------------------------------------------
 constexpr int kStftWgsPerCu = 2;                           // resident workgroups; no more are launched
-// Row pitch: 1 modulo 16, so that sixteen rows are read at one bin without bank conflicts.
+// Row pitch: at least 8 * kExStride (the exchange) and 513 (a spectrum).
 constexpr int kStftRow = 577;
-static_assert(kStftRow >= 8 * kExStride && kStftRow >= kBins && kStftRow % 16 == 1, "row pitch of the transforms in LDS");
+static_assert(kStftRow >= 8 * kExStride && kStftRow >= kBins, "row pitch of the transforms in LDS");
 struct __attribute__((packed, aligned(4))) PairUnaligned { float a, b; };
+template <int UNITS>
 __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
                                                                 const float2* __restrict__ table, int D, long N, int T,
                                                                 long n_items) {
   __shared__ float2 tw[kH + 1];
-  __shared__ float2 rows[2 * kFftWaves][kStftRow];
+  __shared__ float2 rows[UNITS * kFftWaves][kStftRow];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -184,7 +189,8 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
   const long j = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
   const bool by_frame = D <= 8;                            // the units of a step: frames, or groups of eight channels
   const int per_unit = D <= 4 ? 8 / D : 1;                 // frames per unit
-  const int per_step = by_frame ? 2 * per_unit : 1;        // frames per step
+  const int per_step = by_frame ? UNITS * per_unit : 1;    // frames per step
+  constexpr int kChans = 8 * UNITS;                        // more than 8 channels: channels per step
   const long item1 = share_begin(xcd + 1, kXcds, n_items);
   long i = share_begin(xcd, kXcds, n_items) + j * per_step, block_end = i + per_step;
   if (i >= item1) return;
@@ -225,16 +231,16 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
     const long end = block_end < item1 ? block_end : item1;
     int nf = (int)(end - i);                               // frames of this step that are in the same segment
     nf = T - t < nf ? T - t : nf;
-    const int nd = by_frame ? D : (D - d0 < 16 ? D - d0 : 16);
-    const bool more = !by_frame && d0 + 16 < D;            // the frame has channels left
+    const int nd = by_frame ? D : (D - d0 < kChans ? D - d0 : kChans);
+    const bool more = !by_frame && d0 + kChans < D;        // the frame has channels left
     long in = more ? i : i + nf;
     if (in >= block_end) {                                 // the workgroup's next block of frames
       in = block_end + (per_xcd - 1) * per_step;
       block_end = in + per_step;
     }
-    const int dn = more ? d0 + 16 : 0;
+    const int dn = more ? d0 + kChans : 0;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < UNITS; ++u) {
       // windowed frame, even/odd packed: z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1]
       float2 v[8];
 #pragma unroll
@@ -242,7 +248,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
         const float2 w = hann_pair(tw, lane + 64 * m);
         v[m] = make_float2(w.x * raw[m].x, w.y * raw[m].y);
       }
-      if (u == 0) request(i, d0, 1);
+      if (u + 1 < UNITS) request(i, d0, u + 1);
       else if (in < item1) request(in, dn, 0);
       const int fr = by_frame ? u * per_unit + my_frame : 0, dd = my_chan + (by_frame ? 0 : 8 * u);
       if (my_frame < per_unit && fr < nf && dd < nd) {
@@ -266,8 +272,10 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
     const int nr = nf * nd, q = by_frame ? per_unit * D : kFftWaves;     // values per bin, of the first unit
     float2* __restrict__ out = Y + ((long)s * kBins * T + t) * D + d0;
     const long pitch = (long)T * D;
-    if (nr == 16) {
-      for (int e = threadIdx.x; e < kBins * 16; e += 64 * kFftWaves) out[(e >> 4) * pitch + (e & 15)] = rows[e & 15][e >> 4];
+    constexpr int kFull = 8 * UNITS, kShift = UNITS == 1 ? 3 : 4;        // (a full step: the first unit has 8 values)
+    if (nr == kFull) {
+      for (int e = threadIdx.x; e < kBins * kFull; e += 64 * kFftWaves)
+        out[(e >> kShift) * pitch + (e & (kFull - 1))] = rows[e & (kFull - 1)][e >> kShift];
     } else {
       for (int e = threadIdx.x; e < kBins * nr; e += 64 * kFftWaves) {
         const int k = (int)((unsigned)e / (unsigned)nr), r = e - k * nr;
@@ -426,12 +434,18 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   const float2* table = nullptr;
   const int rc = get_twiddles(ctx, (hipStream_t)stream, &table);
   if (rc != GSS_OK) return rc;
-  const long n_items = (long)S * T;
-  const long per_step = D <= 4 ? 2 * (8 / D) : D <= 8 ? 2 : 1;
-  const long steps = (n_items + per_step - 1) / per_step, most = (long)ctx->num_cu * kStftWgsPerCu;
+  const long n_items = (long)S * T, most = (long)ctx->num_cu * kStftWgsPerCu;
+  const int per_unit = D <= 4 ? 8 / D : 1;
+  const long steps1 = (n_items + per_unit - 1) / per_unit;
+  // Short calls take steps of one unit: the chip is not full otherwise, and each workgroup would do two units in a row.  The line
+  // lies at four rounds of the resident workgroups (8 channels, one / two units: 510 frames, one round, 10.7 / 12.5 us; 2040, four
+  // rounds, 29.9 / 31.1; 3000 37.9 / 38.1; 6000 79.8 / 68.7).  24 channels are three units per frame, of which pairs leave one
+  // alone (510 frames 24.2 / 27.1, 6000 frames 275 / 288); other counts beyond 8 gain nothing from single units.
+  const int units = (D <= 8 ? steps1 <= 4 * most : D % 16 == 8) ? 1 : 2;
+  const long per_step = D <= 8 ? units * per_unit : 1, steps = (n_items + per_step - 1) / per_step;
   const long grid = ((steps < most ? steps : most) + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL(stft_kernel, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, (hipStream_t)stream, x, (float2*)Y,
-                     table, D, (long)N, T, n_items);
+  hipLaunchKernelGGL(units == 1 ? stft_kernel<1> : stft_kernel<2>, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, (hipStream_t)stream,
+                     x, (float2*)Y, table, D, (long)N, T, n_items);
   return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
 }
 

@@ -501,6 +501,15 @@ def test_stft_istft_edges(env, S, D, N):
     _check_stft_istft(env, S, D, N)
 
 
+@pytest.mark.parametrize("S,D,N", [(700, 1, 256 * 21), (9, 2, 256 * 1000 + 1), (61, 3, 256 * 75 + 255), (41, 4, 256 * 101), (30, 5, 256 * 70),
+                                   (1, 7, 256 * 2047), (3, 8, 256 * 700 + 9), (2, 9, 256 * 260), (5, 16, 256 * 101 + 7), (2, 17, 256 * 255),
+                                   (1, 24, 256 * 600), (7, 32, 256 * 73 + 1)])
+def test_stft_istft_long_calls(env, S, D, N):
+    """Calls with more frames than the workgroups take in the first rounds: steps of two units for every kind of channel
+    count, ending with a segment or with the items of an XCD, and 24 channels (one unit)."""
+    _check_stft_istft(env, S, D, N)
+
+
 def _check_stft_istft(env, S, D, N):
     t, o, gss = env["torch"], env["o"], env["gss"]
     rng = np.random.default_rng(N + D)
