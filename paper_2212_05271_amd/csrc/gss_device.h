@@ -345,8 +345,9 @@ constexpr SlotTable make_slot_table() {
 // Phase 2 of a tile: lane (tg, eg) accumulates acc[n][k] += w_k[r] * (slot n of lane type eg)[r] over its 8
 // frames r = 8 tg, 8 tg + 1, ... of the 64-frame tile in LDS.  Rows of neighbouring frame groups are then 8 * 208 bytes apart,
 // 128 modulo the 256 bytes that LDS delivers per cycle, and a 16-byte read of the wavefront's 8 rows takes 4 cycles; with
-// frames tg, tg + 8, ... (rows 208 bytes apart, overlapping halves) it took 9.  Whole-EM kernel -1.7 to -2.7 %, chunked EM
-// -2.5 %, mvdr_cov_small -6 %.  sY: [64][kYStride] doubles (8 complex channels per frame, zero beyond D), sW: [64][WS]
+// frames tg, tg + 8, ... (rows 208 bytes apart, overlapping halves) it took 9.  Calls of 5 to 8 channels, 2 to 8 classes: one
+// segment of 1500 frames 1 to 9 % less time, three of 700 and twelve of 900 frames 0.5 to 5 %, the beamformer 3 to 8 % (one
+// segment of 200 frames: no change; two runs of a side differ by up to 0.7 %).  sY: [64][kYStride] doubles (8 complex channels per frame, zero beyond D), sW: [64][WS]
 // doubles (KW weights per frame).
 template <int KW, int WS, int UNROLL = 2>
 __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, const double* __restrict__ sW,

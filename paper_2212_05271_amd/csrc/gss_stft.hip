@@ -294,8 +294,9 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
 // 64-byte runs of X[bin][frame] and requested a step ahead.  The windowed frames stay in LDS; block th is the sum of
 // its four frames, oldest first, and the three blocks that the next step completes are carried over as partial sums.
 //
-// Bound: memory (X read once, x written once; through frames in memory this took 1.9 GB instead of 0.74 GB for 128 segments
-// of 18 s: 618 us, now 290).  The spectrum, the transform and the windowed frame share one LDS row per wavefront.
+// Bound: latency.  Two workgroups per compute unit, held there by 128 registers (2 of them spilled; the 44 KB of LDS would let
+// a third in), each with one step requested ahead: 128 segments of 18 s 290 us = 2.5 TB/s, X read once and x written once
+// (through frames in memory 1.9 GB instead of 0.74 GB: 618 us).  The spectrum, the transform and the windowed frame share one LDS row per wavefront.
 // ----------------------------------------------------------------------------------------------
 constexpr int kIstftMaxSteps = 8;
 __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* __restrict__ X, float* __restrict__ x,

@@ -479,7 +479,8 @@ inline bool wpe_window_fits(int D, int taps, int delay) {
 // wpe_apply_coef; rt = 0: Gc[sf][a][d] = conj(G[a][d]).
 //
 // Bound: for small systems the chain of the 16 sweeps per tile row (LDS round trip and reciprocal, about 400 cycles each),
-// for large ones the tile products.  Three workgroups per compute unit (two: 40 % more time).  Measured, 513 bins: 63 us for
+// for large ones the tile products.  Three workgroups per compute unit (two: 40 % more time), which leaves 168 registers: 16
+// vector registers (60 bytes per lane) and 42 scalar ones are spilled.  Measured, 513 bins: 63 us for
 // 80 unknowns and 8 right-hand sides, 0.79 ms for 240 and 24 (assembled matrix and Gauss-Jordan in the registers of a
 // workgroup: 228 us; 8-column Cholesky in global memory: 4.0 ms).
 // ----------------------------------------------------------------------------------------------
