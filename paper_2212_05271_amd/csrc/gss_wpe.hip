@@ -146,7 +146,7 @@ __device__ __forceinline__ V lds_at(unsigned address, int elem) {
 // times of the two add up), so the loop is written for few of them: Re - Im is kept in LDS beside the value, the
 // frame pitch is a compile-time constant (operand addresses are one register per tile plus constant offsets for four
 // steps), and the weighted left operand is formed once per tile row.  Measured, 10 taps: 513 x 1560 x 8 440 us (vector
-// FMAs on 4 x 4 blocks: 639 us), 513 x 1500 x 24 3.25 ms (5.42 ms); the matrix cores are busy 80 % of the time.
+// FMAs on 4 x 4 blocks: 639 us), 513 x 1500 x 24 3.25 ms (5.42 ms); the matrix cores are busy 82 % of the time.
 template <int P, int TPW>
 __global__ __launch_bounds__(kWpeThreads, 2) void wpe_cov_kernel(const float2* __restrict__ Y, const int32_t* __restrict__ T_len,
                                                                  const double* __restrict__ lam, double2* __restrict__ part,
@@ -1141,7 +1141,8 @@ struct WpeApply {
   const void* fn[2];                                     // the kernel without and with the output
 };
 // Up to 4 channels the vector kernel (of the 16 rows of a matrix tile at most half would be used: gss_wpe on 513 x 1000 x 4,
-// 10 taps, 3 iterations 636 us against 646; from 5 channels on the matrix kernel is the faster one).  More than 24 channels: half as many frames per workgroup (registers, LDS).
+// 10 taps, 3 iterations 616 us against 627; from 5 channels on the matrix kernel is the faster one).  More than 24 channels:
+// half as many frames per workgroup (registers, LDS).
 inline WpeApply wpe_apply_of(int D, int taps, int delay) {
   WpeApply a;
   a.fb = D > 24 ? 128 : 256;
