@@ -228,6 +228,41 @@ __device__ __forceinline__ void fma_bcast(double& acc, double c, double p) {
     asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(c), "v"(p), "n"(N));
 }
 
+// q[e mod 3] += c[lane e of the row] * P[e] for e = 0 .. NG - 1 (16, or what is left of D * D entries: 9, 4, 1), the FMAs of
+// fma_bcast in one statement: between separate statements the compiler puts an idle state in front of every third FMA, which
+// costs a wavefront an issue slot like any other instruction.  With three accumulators in turn each is read two issue slots
+// after it was written, and the two idle states in front separate the first FMA from the last write of its registers.
+template <int NG>
+__device__ __forceinline__ void fma_bcast_chain(double (&q)[3], double c, const double (&P)[NG]) {
+  static_assert(NG == 16 || NG == 9 || NG == 4 || NG == 1, "entries of a block of 16");
+#define GSS_BCAST_FMA(acc, e) "v_fmac_f64_dpp %[" #acc "], %[c], %[p" #e "] row_newbcast:" #e " row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (NG == 16)
+    asm("s_nop 1\n\t"
+        GSS_BCAST_FMA(q0, 0) GSS_BCAST_FMA(q1, 1) GSS_BCAST_FMA(q2, 2) GSS_BCAST_FMA(q0, 3)
+        GSS_BCAST_FMA(q1, 4) GSS_BCAST_FMA(q2, 5) GSS_BCAST_FMA(q0, 6) GSS_BCAST_FMA(q1, 7)
+        GSS_BCAST_FMA(q2, 8) GSS_BCAST_FMA(q0, 9) GSS_BCAST_FMA(q1, 10) GSS_BCAST_FMA(q2, 11)
+        GSS_BCAST_FMA(q0, 12) GSS_BCAST_FMA(q1, 13) GSS_BCAST_FMA(q2, 14) GSS_BCAST_FMA(q0, 15)
+        : [q0] "+v"(q[0]), [q1] "+v"(q[1]), [q2] "+v"(q[2])
+        : [c] "v"(c), [p0] "v"(P[0]), [p1] "v"(P[1]), [p2] "v"(P[2]), [p3] "v"(P[3]), [p4] "v"(P[4]), [p5] "v"(P[5]),
+          [p6] "v"(P[6]), [p7] "v"(P[7]), [p8] "v"(P[8]), [p9] "v"(P[9]), [p10] "v"(P[10]), [p11] "v"(P[11]),
+          [p12] "v"(P[12]), [p13] "v"(P[13]), [p14] "v"(P[14]), [p15] "v"(P[15]));
+  else if constexpr (NG == 9)
+    asm("s_nop 1\n\t"
+        GSS_BCAST_FMA(q0, 0) GSS_BCAST_FMA(q1, 1) GSS_BCAST_FMA(q2, 2) GSS_BCAST_FMA(q0, 3) GSS_BCAST_FMA(q1, 4)
+        GSS_BCAST_FMA(q2, 5) GSS_BCAST_FMA(q0, 6) GSS_BCAST_FMA(q1, 7) GSS_BCAST_FMA(q2, 8)
+        : [q0] "+v"(q[0]), [q1] "+v"(q[1]), [q2] "+v"(q[2])
+        : [c] "v"(c), [p0] "v"(P[0]), [p1] "v"(P[1]), [p2] "v"(P[2]), [p3] "v"(P[3]), [p4] "v"(P[4]), [p5] "v"(P[5]),
+          [p6] "v"(P[6]), [p7] "v"(P[7]), [p8] "v"(P[8]));
+  else if constexpr (NG == 4)
+    asm("s_nop 1\n\t"
+        GSS_BCAST_FMA(q0, 0) GSS_BCAST_FMA(q1, 1) GSS_BCAST_FMA(q2, 2) GSS_BCAST_FMA(q0, 3)
+        : [q0] "+v"(q[0]), [q1] "+v"(q[1]), [q2] "+v"(q[2])
+        : [c] "v"(c), [p0] "v"(P[0]), [p1] "v"(P[1]), [p2] "v"(P[2]), [p3] "v"(P[3]));
+  else
+    asm("s_nop 1\n\t" GSS_BCAST_FMA(q0, 0) : [q0] "+v"(q[0]) : [c] "v"(c), [p0] "v"(P[0]));
+#undef GSS_BCAST_FMA
+}
+
 // q0 += sum over u < n of c[2 u] re[u] and q1 += sum over u < n of c[2 u + 1] im[u], 1 <= n (8 and more: all 8
 // items), c[x] being the value that `c` holds in lane x of the lane's row of 16.  n must be the same in every lane.
 // The items run from the last to the first, and a shorter run enters the chain further down, so each accumulator
@@ -283,177 +318,243 @@ __device__ __forceinline__ bool class_on(unsigned mask, int k) {
 
 // Tile geometry shared by the kernels that accumulate weighted outer products: a workgroup is
 // kPassWaves wavefronts, each wavefront owns whole tiles of 64 frames and a private LDS region.
+//
+// Phase 2 of a tile: lane = (frame group tg, lane type i), D lane types and 64 / D frame groups (lanes left over idle along).
+// Lane type i owns D of the D * D reals of the packed Hermitian matrix: Re and Im of y_i conj(y_b), b = (i + d) mod D, for the
+// circular distances d = 1 .. (D - 1) / 2, the real diagonal entry |y_i|^2, and for even D one half of the pair at distance
+// D / 2: Re of y_i conj(y_(i + D/2)) for i < D / 2 and Im of y_(i - D/2) conj(y_i) otherwise.  Both halves are
+// y_i.re * a + y_i.im * b of a second operand (a, b) = y_(i + D/2) or -i y_(i - D/2), which the lane reads from the tile (a
+// row carries the turned copies of the lower half), so every lane type runs the same instructions.  The pairs at circular
+// distances up to D / 2 are all pairs once; where b < i the slot holds the conjugate of the stored (upper-triangle) entry,
+// i.e. its imaginary part with the opposite sign.
+//
+// A row is D complex channels, then the turned copies, in 16-byte units.  D = 8: 12 units and one of padding, a group takes 8
+// consecutive frames: LDS delivers 256 bytes per cycle, rows 8 * 208 bytes apart are 128 modulo 256, and a 16-byte read of the
+// wavefront's 8 rows takes 4 cycles (frames tg, tg + 8, ...: 9 cycles; calls of one segment 1 to 9 % slower).  D < 8: frames
+// tg, tg + 64 / D, ..., no padding: the rows read together are one run of memory (odd D) or start at an odd multiple of 16
+// bytes (D = 2 and 6).  Measured against 8 lane types whatever D (zero channels up to 8), 10 iterations: 48 segments of up to
+// 1000 frames and 4 classes 5 channels 3.41 -> 2.33 ms, 6 channels 3.75 -> 3.37, 7 channels 4.23 -> 4.00; 8 classes: 4
+// channels, 24 segments 3.05 -> 1.54, 32 segments of 5 channels 4.85 -> 2.70 ms (the accumulators no longer spill).
 constexpr int kPassWaves = 4;
-// Doubles per frame row of the y tile: the 8 complex channels, then -i y_c for the channels c < 4 (the lanes that
-// pair a channel with the one four below it read that copy, see slot_entry), then 2 of padding (16-byte units: 13
-// per row, odd, so that the rows of adjacent frames start in different banks).
-constexpr int kYStride = 26;
-constexpr int kYTurned = 16;   // offset of the turned copies within a row
-static_assert(kYStride == kYTurned + 8 + 2, "a row is 8 channels, 4 turned copies and two padding entries");
+template <int D>
+struct TileLayout {
+  static_assert(D >= 1 && D <= 8, "channels of the tile kernels");
+  static constexpr bool even = D % 2 == 0;
+  static constexpr int full = (D - 1) / 2;                  // circular distances whose pairs a lane type owns in full
+  static constexpr int reads = 1 + full + (even ? 1 : 0);   // channels that a lane reads per frame
+  static constexpr int turned = 2 * D;                      // offset of the turned copies within a row (doubles)
+  static constexpr int pad = D == 8 ? 2 : 0;
+  static constexpr int row = 2 * D + (even ? D : 0) + pad;  // doubles per frame row
+  static constexpr int groups = kWave / D;
+  static constexpr int steps = kWave / groups;              // frames that every group has
+  static constexpr int rest = kWave - groups * steps;       // groups that have one more
+  static constexpr bool blocked = D == 8;                   // a group's frames: consecutive, or `groups` apart
+  __host__ __device__ static constexpr int first(int tg) { return blocked ? steps * tg : tg; }
+  static constexpr int next = blocked ? 1 : groups;         // rows from one frame of a group to its next
+  static_assert(!blocked || rest == 0, "consecutive frames need equal groups");
+};
 
-// Writes one frame row of the y tile: channel d at 2 d (zero beyond D) and the turned copies of channels 0..3.
+// Writes one frame row of the y tile: channel d at 2 d and the turned copies of the lower half of the channels.
 template <int D>
 __device__ __forceinline__ void store_tile_row(double* __restrict__ row, const double (&yr)[D], const double (&yi)[D]) {
+  using L = TileLayout<D>;
 #pragma unroll
-  for (int d = 0; d < 8; ++d) {
-    double2 yv = make_double2(0.0, 0.0);
-    if (d < D) yv = make_double2(yr[d < D ? d : 0], yi[d < D ? d : 0]);
-    *reinterpret_cast<double2*>(&row[2 * d]) = yv;
-    if (d < 4) *reinterpret_cast<double2*>(&row[kYTurned + 2 * d]) = make_double2(yv.y, -yv.x);
+  for (int d = 0; d < D; ++d) {
+    *reinterpret_cast<double2*>(&row[2 * d]) = make_double2(yr[d], yi[d]);
+    if (L::even && d < D / 2) *reinterpret_cast<double2*>(&row[L::turned + 2 * d]) = make_double2(yi[d], -yr[d]);
   }
 }
 
+// Offsets within a row of the channels that lane type i reads: itself, i + 1, ..., and for even D the second operand of the
+// pair at distance D / 2.
+template <int D>
+__device__ __forceinline__ int tile_operand(int i, int n) {
+  using L = TileLayout<D>;
+  if (n <= L::full) return 2 * (i + n < D ? i + n : i + n - D);
+  return i < D / 2 ? 2 * (i + D / 2) : L::turned + 2 * (i - D / 2);
+}
+// The lane type's D entries of a frame from the operands it has read.
+template <int D>
+__device__ __forceinline__ void tile_entries(const double2 (&y)[TileLayout<D>::reads], double (&e)[D]) {
+  using L = TileLayout<D>;
+  const double2 x = y[0];
+#pragma unroll
+  for (int d = 0; d < L::full; ++d) {
+    const double2 b = y[1 + d];
+    e[2 * d] = x.x * b.x + x.y * b.y;
+    e[2 * d + 1] = x.y * b.x - x.x * b.y;
+  }
+  e[2 * L::full] = x.x * x.x + x.y * x.y;
+  if constexpr (L::even) e[D - 1] = x.x * y[L::reads - 1].x + x.y * y[L::reads - 1].y;
+}
 
-// Phase-2 lane type eg = channel i.  Its 8 accumulator slots: n = 0..5 are Re and Im of y_i conj(y_b),
-// b = (i + d) mod 8 for d = 1, 2, 3; n = 6 is the real diagonal entry |y_i|^2; n = 7 is one half of the pair at
-// distance 4: Re of y_i conj(y_(i+4)) for i < 4 and Im of y_(i-4) conj(y_i) for i >= 4.  Both halves are
-// y_i.re * a + y_i.im * b of a second operand (a, b) = y_(i+4) or -i y_(i-4), which the lane reads from the tile
-// (the row holds the turned copies), so every lane type runs the same instructions.  The pairs at circular
-// distance 1..4 are all 28 pairs once; where b < i the slot holds the conjugate of the stored (upper-triangle)
-// entry, i.e. its imaginary part with the opposite sign.
 struct SlotEntry { int i, j, part, sign; };     // part: 0 real diagonal, 1 Re, 2 Im
-__host__ __device__ constexpr SlotEntry slot_entry(int eg, int n) {
-  if (n < 6) {
-    const int d = n / 2 + 1;
-    const int part = 1 + (n & 1);
-    const int a = eg, b = (eg + d) % 8;
-    if (a < b) return SlotEntry{a, b, part, 1};
-    return SlotEntry{b, a, part, part == 2 ? -1 : 1};
+__host__ __device__ constexpr SlotEntry slot_entry(int i, int n, int D) {
+  const int full = (D - 1) / 2;
+  if (n < 2 * full) {
+    const int part = 1 + (n & 1), b = (i + n / 2 + 1) % D;
+    if (i < b) return SlotEntry{i, b, part, 1};
+    return SlotEntry{b, i, part, part == 2 ? -1 : 1};
   }
-  if (n == 6) return SlotEntry{eg, eg, 0, 1};
-  return eg < 4 ? SlotEntry{eg, eg + 4, 1, 1} : SlotEntry{eg - 4, eg, 2, 1};
+  if (n == 2 * full) return SlotEntry{i, i, 0, 1};
+  return i < D / 2 ? SlotEntry{i, i + D / 2, 1, 1} : SlotEntry{i - D / 2, i, 2, 1};
 }
-
-// Packed index (gss_packed_row order, matrix size D) of accumulator slot n of lane type eg, or -1 if the
-// slot lies in the zero padding.
-__host__ __device__ constexpr int slot_packed_index(int eg, int n, int D) {
-  const SlotEntry e = slot_entry(eg, n);
-  if (e.i >= D || e.j >= D) return -1;
-  return e.part == 0 ? gss_packed_row(e.i, D) : gss_packed_row(e.i, D) + 1 + 2 * (e.j - e.i - 1) + (e.part - 1);
-}
-
-// slot_packed_index for every matrix size 1..8 and slot eg * 8 + n, and the slot's sign, as tables.
-struct SlotTable { short v[9][64]; signed char sign[64]; };
-constexpr SlotTable make_slot_table() {
-  SlotTable t{};
-  for (int d = 0; d <= 8; ++d)
-    for (int sl = 0; sl < 64; ++sl) t.v[d][sl] = d == 0 ? (short)-1 : (short)slot_packed_index(sl / 8, sl % 8, d);
-  for (int sl = 0; sl < 64; ++sl) t.sign[sl] = (signed char)slot_entry(sl / 8, sl % 8).sign;
+// Packed index (gss_packed_row order) and sign of slot n of lane type i, at [n * D + i].
+template <int D>
+struct SlotTable { short index[kWave]; signed char sign[kWave]; };
+template <int D>
+constexpr SlotTable<D> make_slot_table() {
+  SlotTable<D> t{};
+  for (int o = 0; o < kWave; ++o) { t.index[o] = -1; t.sign[o] = 1; }
+  for (int o = 0; o < D * D; ++o) {
+    const SlotEntry e = slot_entry(o % D, o / D, D);
+    t.index[o] = (short)(gss_packed_row(e.i, D) + (e.part == 0 ? 0 : 1 + 2 * (e.j - e.i - 1) + (e.part - 1)));
+    t.sign[o] = (signed char)e.sign;
+  }
   return t;
 }
 
-// Phase 2 of a tile: lane (tg, eg) accumulates acc[n][k] += w_k[r] * (slot n of lane type eg)[r] over its 8
-// frames r = 8 tg, 8 tg + 1, ... of the 64-frame tile in LDS.  Rows of neighbouring frame groups are then 8 * 208 bytes apart,
-// 128 modulo the 256 bytes that LDS delivers per cycle, and a 16-byte read of the wavefront's 8 rows takes 4 cycles; with
-// frames tg, tg + 8, ... (rows 208 bytes apart, overlapping halves) it took 9.  Calls of 5 to 8 channels, 2 to 8 classes: one
-// segment of 1500 frames 1 to 9 % less time, three of 700 and twelve of 900 frames 0.5 to 5 %, the beamformer 3 to 8 % (one
-// segment of 200 frames: no change; two runs of a side differ by up to 0.7 %).  sY: [64][kYStride] doubles (8 complex channels per frame, zero beyond D), sW: [64][WS]
-// doubles (KW weights per frame).
-template <int KW, int WS, int UNROLL = 2>
+// Phase 2 of a tile: lane (tg, i) accumulates acc[n][k] += w_k[r] * (slot n of lane type i)[r] over the frames r of its group.
+// sY: [64][TileLayout<D>::row] doubles, sW: [64][WS] doubles (KW weights per frame).
+template <int D, int KW, int WS, int UNROLL = 2>
 __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, const double* __restrict__ sW,
-                                                int tg, int eg, double (&acc)[8][KW]) {
-  const int c1 = 2 * ((eg + 1) & 7), c2 = 2 * ((eg + 2) & 7), c3 = 2 * ((eg + 3) & 7);
-  const int c4 = eg < 4 ? 2 * (eg + 4) : kYTurned + 2 * (eg - 4);
-#pragma unroll UNROLL
-  for (int j = 0; j < 8; ++j) {
-    const int r = 8 * tg + j;
-    double w[KW];
+                                                int tg, int i, double (&acc)[D][KW]) {
+  using L = TileLayout<D>;
+  int o[L::reads];
+#pragma unroll
+  for (int n = 0; n < L::reads; ++n) o[n] = tile_operand<D>(i, n);
+  auto frame = [&](int r) {
+    double w[KW], e[D];
+    double2 y[L::reads];
 #pragma unroll
     for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
-    const double* __restrict__ row = sY + r * kYStride;
-    const double2 x = *reinterpret_cast<const double2*>(&row[2 * eg]);
-    const double2 y1 = *reinterpret_cast<const double2*>(&row[c1]);
-    const double2 y2 = *reinterpret_cast<const double2*>(&row[c2]);
-    const double2 y3 = *reinterpret_cast<const double2*>(&row[c3]);
-    const double2 y4 = *reinterpret_cast<const double2*>(&row[c4]);
-    double e[8];
-    e[0] = x.x * y1.x + x.y * y1.y;  e[1] = x.y * y1.x - x.x * y1.y;
-    e[2] = x.x * y2.x + x.y * y2.y;  e[3] = x.y * y2.x - x.x * y2.y;
-    e[4] = x.x * y3.x + x.y * y3.y;  e[5] = x.y * y3.x - x.x * y3.y;
-    e[6] = x.x * x.x + x.y * x.y;    e[7] = x.x * y4.x + x.y * y4.y;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < L::reads; ++n) y[n] = *reinterpret_cast<const double2*>(&sY[r * L::row + o[n]]);
+    tile_entries<D>(y, e);
+#pragma unroll
+    for (int n = 0; n < D; ++n)
 #pragma unroll
       for (int k = 0; k < KW; ++k) acc[n][k] = fma(w[k], e[n], acc[n][k]);
-    }
+  };
+#pragma unroll UNROLL
+  for (int j = 0; j < L::steps; ++j) frame(L::first(tg) + j * L::next);
+  if constexpr (L::rest > 0) {
+    if (tg < L::rest) frame(tg + L::steps * L::next);
   }
 }
 
 // The same for the classes of `mask` only (wave-uniform): the weights of the other classes are zero in every
-// frame of the tile (their columns of sW hold stale values that are read and never used).  One frame per
-// step: its entries are formed, the row and weights of the next frame are requested from LDS, and then each
-// class of the mask adds its 8 products under one uniform branch, so the LDS latency is covered by the
-// previous frame's arithmetic.
-template <int KW, int WS>
+// frame of the tile (their columns of sW hold stale values that are read and never used).  A step takes the entries of NF
+// frames, requests the rows of the next step from LDS, and then each class of the mask adds its products under one uniform
+// branch, so the LDS latency is covered by the current step's arithmetic.  Two frames per step where their entries fit into
+// registers beside up to 40 accumulators: a test is three scalar instructions and a branch, and a wavefront issues one
+// instruction in five cycles whatever its kind.  Ten minutes of 8 channels, 200 segments: 62.7 -> 61.4 ms.
+template <int D, int KW, int WS>
 __device__ __forceinline__ void accumulate_tile_masked(const double* __restrict__ sY, const double* __restrict__ sW,
-                                                       int tg, int eg, unsigned mask, double (&acc)[8][KW]) {
-  // five row pointers and one weight pointer per lane; every access below is one of them plus a constant
+                                                       int tg, int i, unsigned mask, double (&acc)[D][KW]) {
+  using L = TileLayout<D>;
+  constexpr int NF = D * KW <= 40 ? 2 : 1;
+  // a row pointer per operand and one weight pointer; every access of a full step is one of them plus a constant
   // (the constant goes into the offset field of the LDS instruction)
-  const double* __restrict__ p0 = sY + 8 * tg * kYStride + 2 * eg;
-  const double* __restrict__ p1 = sY + 8 * tg * kYStride + 2 * ((eg + 1) & 7);
-  const double* __restrict__ p2 = sY + 8 * tg * kYStride + 2 * ((eg + 2) & 7);
-  const double* __restrict__ p3 = sY + 8 * tg * kYStride + 2 * ((eg + 3) & 7);
-  const double* __restrict__ p4 = sY + 8 * tg * kYStride + (eg < 4 ? 2 * (eg + 4) : kYTurned + 2 * (eg - 4));
-  const double* __restrict__ pw = sW + 8 * tg * WS;
-  double2 y[5];
-  double w[KW];
-  auto fetch = [&](auto JF) {
-    constexpr int o = JF.value * kYStride;
-    y[0] = *reinterpret_cast<const double2*>(p0 + o);
-    y[1] = *reinterpret_cast<const double2*>(p1 + o);
-    y[2] = *reinterpret_cast<const double2*>(p2 + o);
-    y[3] = *reinterpret_cast<const double2*>(p3 + o);
-    y[4] = *reinterpret_cast<const double2*>(p4 + o);
+  const double* __restrict__ py[L::reads];
 #pragma unroll
-    for (int k = 0; k < KW; ++k) w[k] = pw[JF.value * WS + k];
-  };
-  fetch(std::integral_constant<int, 0>{});
-  static_for<0, 8>([&](auto JI) {
-    constexpr int j = JI.value;
-    double e[8], wc[KW];
-    {
-      const double2 x = y[0], y1 = y[1], y2 = y[2], y3 = y[3], y4 = y[4];
-      e[0] = x.x * y1.x + x.y * y1.y;  e[1] = x.y * y1.x - x.x * y1.y;
-      e[2] = x.x * y2.x + x.y * y2.y;  e[3] = x.y * y2.x - x.x * y2.y;
-      e[4] = x.x * y3.x + x.y * y3.y;  e[5] = x.y * y3.x - x.x * y3.y;
-      e[6] = x.x * x.x + x.y * x.y;    e[7] = x.x * y4.x + x.y * y4.y;
+  for (int n = 0; n < L::reads; ++n) py[n] = sY + L::first(tg) * L::row + tile_operand<D>(i, n);
+  const double* __restrict__ pw = sW + L::first(tg) * WS;
+  double2 y[NF][L::reads];
+  auto fetch = [&](auto JF, auto CNT) {                      // the rows of frames j .. j + cnt - 1 of the group
+    static_for<0, decltype(CNT)::value>([&](auto UI) {
+      constexpr int u = UI.value, o = (decltype(JF)::value + u) * L::next * L::row;
 #pragma unroll
-      for (int k = 0; k < KW; ++k) wc[k] = w[k];
-    }
-    if constexpr (j < 7) fetch(std::integral_constant<int, j + 1>{});
-    static_for<0, KW>([&](auto KI) {
-      constexpr int k = KI.value;
-      unsigned m = mask;
-      asm volatile("" : "+s"(m));           // re-test the one mask register instead of keeping KW booleans
-      if ((m >> k) & 1u) {
-#pragma unroll
-        for (int n = 0; n < 8; ++n) acc[n][k] = fma(wc[k], e[n], acc[n][k]);
-      }
+      for (int n = 0; n < L::reads; ++n) y[u][n] = *reinterpret_cast<const double2*>(py[n] + o);
     });
+  };
+  // a group without a frame in the last step reads its first row there, and adds nothing
+  const int last = tg < L::rest ? L::steps * L::next : 0;
+  auto step = [&](auto JI, auto CNT, auto REST) {
+    constexpr int j = decltype(JI)::value, cnt = decltype(CNT)::value;
+    constexpr bool rest = decltype(REST)::value;
+    double e[cnt][D], w[cnt][KW];
+    static_for<0, cnt>([&](auto UI) {
+      constexpr int u = UI.value;
+#pragma unroll
+      for (int k = 0; k < KW; ++k) w[u][k] = pw[(rest ? last : (j + u) * L::next) * WS + k];
+      tile_entries<D>(y[u], e[u]);
+    });
+    constexpr int j2 = j + cnt, left = L::steps - j2;
+    if constexpr (!rest && left > 0) {
+      fetch(std::integral_constant<int, j2>{}, std::integral_constant<int, (left < NF ? left : NF)>{});
+    } else if constexpr (!rest && L::rest > 0) {
+#pragma unroll
+      for (int n = 0; n < L::reads; ++n) y[0][n] = *reinterpret_cast<const double2*>(py[n] + last * L::row);
+    }
+    if (!rest || tg < L::rest) {
+      static_for<0, KW>([&](auto KI) {
+        constexpr int k = KI.value;
+        if (class_on(mask, k)) {
+#pragma unroll
+          for (int u = 0; u < cnt; ++u)
+#pragma unroll
+            for (int n = 0; n < D; ++n) acc[n][k] = fma(w[u][k], e[u][n], acc[n][k]);
+        }
+      });
+    }
+  };
+  constexpr int nfull = L::steps / NF, odd = L::steps % NF;
+  fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, (L::steps < NF ? L::steps : NF)>{});
+  static_for<0, nfull>([&](auto SI) {
+    step(std::integral_constant<int, NF * SI.value>{}, std::integral_constant<int, NF>{}, std::false_type{});
   });
+  if constexpr (odd > 0) step(std::integral_constant<int, NF * nfull>{}, std::integral_constant<int, odd>{}, std::false_type{});
+  if constexpr (L::rest > 0) step(std::integral_constant<int, L::steps>{}, std::integral_constant<int, 1>{}, std::true_type{});
 }
 
 // Reduction of the per-lane accumulators of a workgroup of kPassWaves wavefronts into packed partial
 // sums: out[k * E + packed index] for k < KW, matrix size D.  Sums are taken in a fixed order (frame
 // groups ascending, then wavefronts ascending).
-//   wbuf: LDS private to the calling wavefront, kReduceWaveDoubles doubles (its tile region);
+//   wbuf: LDS private to the calling wavefront, reduce_wave_doubles(D) doubles (its tile region);
 //   red:  LDS scratch of the workgroup, kPassWaves * (64 * KW + KW) doubles, may overlap the wbuf regions.
 // WITH_N: nvals[k] is one more per-lane partial sum per class (lane = frame layout), summed over all lanes and
 // wavefronts into nout[k].
 // The function starts with a barrier (every wavefront is done with its tiles).  First every wavefront
-// sums over its 8 frame groups through its own LDS region, two classes at a time: entry n of all lanes
-// goes out as one contiguous row (lane = 8 tg + eg), and lane o = 8 n + eg reads the 8 values of slot
-// (eg, n) back.  Then the wavefronts' sums meet in `red`.
+// sums over its frame groups through its own LDS region, two classes at a time: entry n of all lanes
+// goes out as one contiguous row (lane = D tg + i), and lane o = D n + i reads the values of slot
+// (i, n) back.  Then the wavefronts' sums meet in `red`.
 constexpr int kReduceRow = 72;                         // doubles per row of 64 (+ 8: spreads the banks)
-constexpr int kReduceWaveDoubles = 2 * 8 * kReduceRow;
-static_assert(kReduceWaveDoubles <= kWave * kYStride, "the y tile of a wavefront must hold its reduction rows");
+__host__ __device__ constexpr int reduce_wave_doubles(int D) { return 2 * D * kReduceRow; }
+// The wavefront's sums over the frame groups of the classes k0 and k0 + 1 (as far as they exist): S[c] of lane o = D n + i is
+// slot (i, n) of class k0 + c (lanes from D * D on: a copy of the last slot).
+template <int D, int KW>
+__device__ __forceinline__ void sum_frame_groups(const double (&acc)[D][KW], int k0, double* __restrict__ wbuf, int lane,
+                                                 double (&S)[2]) {
+  using L = TileLayout<D>;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (k0 + c < KW) {
+#pragma unroll
+      for (int n = 0; n < D; ++n) wbuf[(c * D + n) * kReduceRow + lane] = acc[n][k0 + c < KW ? k0 + c : 0];
+    }
+  }
+  wave_lds_sync();
+  const int o = lane < D * D ? lane : D * D - 1;
+  const int n = o / D, i = o - n * D;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    double sum = 0.0;
+    if (k0 + c < KW) {
+#pragma unroll
+      for (int tg = 0; tg < L::groups; ++tg) sum += wbuf[(c * D + n) * kReduceRow + tg * D + i];
+    }
+    S[c] = sum;
+  }
+  wave_lds_sync();
+}
 
 template <int D, int KW, bool WITH_N>
-__device__ __forceinline__ void reduce_and_store_partials(double (&acc)[8][KW], double (&nvals)[KW], double* wbuf,
+__device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], double (&nvals)[KW], double* wbuf,
                                                           double* red, double* __restrict__ out,
                                                           double* __restrict__ nout, int lane, int wave) {
   constexpr int E = D * D;
-  double S[KW];
+  double S[KW + 1];
   if constexpr (WITH_N) {                    // per-lane scalars (one per class): summed over the wavefront
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
@@ -464,29 +565,15 @@ __device__ __forceinline__ void reduce_and_store_partials(double (&acc)[8][KW], 
   __syncthreads();
 #pragma unroll
   for (int k0 = 0; k0 < KW; k0 += 2) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      if (k0 + c < KW) {
-#pragma unroll
-        for (int n = 0; n < 8; ++n) wbuf[(c * 8 + n) * kReduceRow + lane] = acc[n][k0 + c];
-      }
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      if (k0 + c < KW) {
-        double sum = 0.0;
-#pragma unroll
-        for (int tg = 0; tg < 8; ++tg) sum += wbuf[(c * 8 + (lane >> 3)) * kReduceRow + tg * 8 + (lane & 7)];
-        S[k0 + c] = sum;
-      }
-    }
-    wave_lds_sync();
+    double S2[2];
+    sum_frame_groups<D, KW>(acc, k0, wbuf, lane, S2);
+    S[k0] = S2[0];
+    S[k0 + 1] = S2[1];
   }
   __syncthreads();                           // the private regions are free: `red` may overlap them
   double* redn = red + kPassWaves * 64 * KW;
 #pragma unroll
-  for (int k = 0; k < KW; ++k) red[(wave * KW + k) * 64 + (lane & 7) * 8 + (lane >> 3)] = S[k];
+  for (int k = 0; k < KW; ++k) red[(wave * KW + k) * 64 + lane] = S[k];
   if constexpr (WITH_N) {
     if (lane == 0) {
 #pragma unroll
@@ -499,9 +586,8 @@ __device__ __forceinline__ void reduce_and_store_partials(double (&acc)[8][KW], 
     double sum = 0.0;
 #pragma unroll
     for (int w = 0; w < kPassWaves; ++w) sum += red[(w * KW + k) * 64 + slot];
-    static constexpr SlotTable kSlotTable = make_slot_table();
-    const int pidx = kSlotTable.v[D][slot];   // slot -> packed index for matrix size D; padding slots are dropped
-    if (pidx >= 0) out[k * E + pidx] = kSlotTable.sign[slot] < 0 ? -sum : sum;
+    static constexpr SlotTable<D> kSlots = make_slot_table<D>();
+    if (slot < E) out[k * E + kSlots.index[slot]] = kSlots.sign[slot] < 0 ? -sum : sum;
   }
   if constexpr (WITH_N) {
     if (threadIdx.x < KW) {

@@ -72,19 +72,24 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // Phase 1 (lane = frame): the Hermitian outer product is generated 16 entries at a time in fp64, and
 //   q_k = <coef_k, y y^H> takes 16 row-broadcast FMAs per live class and block; posterior over the active
 //   classes; weights w_k = gamma_k / q_k.  y (as fp64) and w go to the wavefront's LDS tile.
-// Phase 2 (lane = (frame group tg, channel eg), 8 x 8; frames 8 tg .. 8 tg + 7 of the tile): lane type eg = i
-//   owns the entries y_i conj(y_b) for b = i+1, i+2, i+3 (mod 8), and either the pair (i, i+4) (i < 4) or
-//   the real diagonal entries of channels i and i-4 (i >= 4): 8 real entries per lane, all 64 of the packed
-//   Hermitian 8 x 8 matrix over the 8 lane types, the same instructions for every lane except the last two
-//   entries.  For its 8 frames per tile a lane reads 5 channels of y and the weights, forms its 8
-//   entries exactly and accumulates R_k[e] += w_k * P[e] in fp64.  Channels >= D are zero padding.
-//   The accumulators stay in registers across the tiles of the chunk.
+// Phase 2 (lane = (frame group, lane type), TileLayout): a lane reads the channels of its type and the weights for the frames
+//   of its group, forms its D entries exactly and accumulates R_k[e] += w_k * P[e] in fp64.  The accumulators stay in
+//   registers across the tiles of the chunk.  The frames of the next live tile are requested from memory before phase 2
+//   (stream_tiles): a wavefront used to wait 1300 of the 9700 cycles of a tile for them (8 channels, 5 classes, two
+//   wavefronts per SIMD); 200 segments of 8 channels 64.2 -> 62.7 ms.
 //
 // Grid: blockIdx.x = chunk + C * (f + F * s).  A chunk is `tiles_per_chunk` tiles of 64 frames.
 // ----------------------------------------------------------------------------------------------
 
 // Doubles per frame row of the weight tile in LDS (odd: spreads the rows over the banks).
 __host__ __device__ constexpr int weight_stride(int K) { return K | 1; }
+// Doubles of a wavefront's LDS region: the tile of 64 frame rows and its weights, or the rows of the reduction over the frame
+// groups that use the same memory after the last tile.
+template <int D>
+__host__ __device__ constexpr int tile_region_doubles(int WS) {
+  const int tile = kWave * TileLayout<D>::row + kWave * WS, red = reduce_wave_doubles(D);
+  return ((tile > red ? tile : red) + 1) / 2 * 2;
+}
 
 // Registers (pairs) of 16 coefficients per class, and how many of them a wavefront keeps resident.
 __host__ __device__ constexpr int coef_regs(int D) { return (D * D + 15) / 16; }
@@ -92,7 +97,7 @@ constexpr int kResidentRegs = 20;
 
 // Few channels: the lane that owns a frame in phase 1 has all D * D entries of its outer product in registers
 // anyway (one block of at most 16), so it adds w_k * P[e] to K * D * D accumulators of its own, and there is no
-// LDS tile and no phase 2 (whose 8 x 8 lane layout would run mostly on zero padding below 5 channels).  Used
+// LDS tile and no phase 2.  Used
 // when the accumulators fit in registers beside phase 1.  The accumulators are acc[k][e] then (packed order)
 // instead of acc[slot n][k], and the sums over the lanes are taken at the end of the pass (transpose_reduce).
 constexpr int kDirectMaxAcc = 80;
@@ -101,7 +106,7 @@ __host__ __device__ constexpr bool direct_layout(int D, int K) { return D <= 4 &
 template <int D, int K>
 struct PassAcc {
   static constexpr bool direct = direct_layout(D, K);
-  static constexpr int rows = direct ? K : 8, cols = direct ? D * D : K;
+  static constexpr int rows = direct ? K : D, cols = direct ? D * D : K;
   using type = double[rows][cols];
 };
 template <int A, int B>
@@ -137,19 +142,22 @@ __device__ __forceinline__ void load_tile_regs(TileRegs<D>& r, const float2* __r
 //   creg : the resident coefficient registers [K * coef_regs(D)] (used when RESIDENT)
 //   sC   : LDS copy of the coefficients, [K * coef_regs(D)][16] doubles (used otherwise)
 //   cc   : class constants pi_k / det B_k (wave-uniform)
-//   pre  : PRE: the lane's frame, loaded by the caller (nothing is read from Yrow / abrow)
-template <int D, int K, bool FINAL, bool RESIDENT, bool PRE = false>
+//   cur  : the lane's frame, loaded by the caller (nothing is read from Yrow / abrow): TILE_KEEP leaves it as it is;
+//          TILE_STREAM replaces it by the lane's frame of the tile at next_t0, requested before phase 2, when the
+//          posterior's registers are free, and wants a mask that is not empty.
+enum TileSource { TILE_LOAD, TILE_KEEP, TILE_STREAM };
+template <int D, int K, bool FINAL, bool RESIDENT, TileSource SRC = TILE_LOAD>
 __device__ __forceinline__ void pass_tile(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, const double (&creg)[RESIDENT ? K * coef_regs(D) : 1],
     const double* __restrict__ sC, const double (&cc)[K], float* __restrict__ gamma_row /* + k*F*Tmax */,
     uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int t0, int lane, unsigned tmask,
     double* __restrict__ sY, double* __restrict__ sW, typename PassAcc<D, K>::type& acc, double (&nacc)[K],
-    const TileRegs<D>* pre = nullptr) {
+    TileRegs<D>* cur = nullptr, int next_t0 = 0) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr int WS = weight_stride(K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;
-  const int tg = lane >> 3, eg = lane & 7;
+  const int tg = lane / D, eg = lane - tg * D;
   tmask &= (1u << K) - 1u;
   const int t = t0 + lane;
   if constexpr (FINAL) {
@@ -161,7 +169,9 @@ __device__ __forceinline__ void pass_tile(
       }
     });
   }
-  if (tmask == 0u) return;                    // no frame of the tile has an active class
+  if constexpr (SRC != TILE_STREAM) {
+    if (tmask == 0u) return;                  // no frame of the tile has an active class
+  }
 
   // ---- phase 1: load y ----
   // A lane whose frame lies beyond T reads frame 0 instead (it exists whenever a tile is processed at all, or is
@@ -169,13 +179,15 @@ __device__ __forceinline__ void pass_tile(
   const bool valid = t < T;
   double yr[D], yi[D];
   unsigned abits;
-  if constexpr (PRE) {
+  if constexpr (SRC != TILE_LOAD) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      yr[d] = (double)pre->y[d].x;
-      yi[d] = (double)pre->y[d].y;
+      float2 v = cur->y[d];
+      if constexpr (SRC == TILE_STREAM) asm volatile("" : "+v"(v.x), "+v"(v.y));   // (held in 32 bits up to here)
+      yr[d] = (double)v.x;
+      yi[d] = (double)v.y;
     }
-    abits = valid ? pre->abits : 0u;
+    abits = valid ? cur->abits : 0u;
   } else {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -216,10 +228,14 @@ __device__ __forceinline__ void pass_tile(
       if (class_on(tmask, k)) {
         double ck;
         if constexpr (RESIDENT) ck = creg[k * R + r]; else ck = c[k];
-        static_for<0, ng>([&](auto EI) {
-          constexpr int e = EI.value;
-          fma_bcast<e, e == 0>(q[k][e % NQ], ck, P[e]);
-        });
+        if constexpr (NQ == 3) {
+          fma_bcast_chain<ng>(q[k], ck, P);
+        } else {
+          static_for<0, ng>([&](auto EI) {
+            constexpr int e = EI.value;
+            fma_bcast<e, e == 0>(q[k][e % NQ], ck, P[e]);
+          });
+        }
       }
     });
   });
@@ -265,7 +281,7 @@ __device__ __forceinline__ void pass_tile(
     });
   } else {
     // this tile's y and weights go to LDS, then phase 2 runs over it
-    store_tile_row<D>(sY + lane * kYStride, yr, yi);
+    store_tile_row<D>(sY + lane * TileLayout<D>::row, yr, yi);
     static_for<0, K>([&](auto KI) {
       constexpr int k = KI.value;
       if (class_on(tmask, k)) {
@@ -274,11 +290,41 @@ __device__ __forceinline__ void pass_tile(
         sW[lane * WS + k] = g * rq[k];
       }
     });
+    if constexpr (SRC == TILE_STREAM) load_tile_regs<D>(*cur, Yrow, abrow, next_t0, lane, T);
     wave_lds_sync();
 
     // ---- phase 2 ----
-    accumulate_tile_masked<K, WS>(sY, sW, tg, eg, tmask, acc);
+    accumulate_tile_masked<D, K, WS>(sY, sW, tg, eg, tmask, acc);
     wave_lds_sync();
+  }
+}
+
+// The accumulating pass over tiles lo .. hi - 1 with the LDS tile: every live tile's frames are requested while the live
+// tile before it is in phase 2.
+template <int D, int K, bool RESIDENT, class MaskPtr>
+__device__ __forceinline__ void stream_tiles(
+    const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
+    const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K], int T,
+    int Tmax, int lo, int hi, int lane, double* __restrict__ sY, double* __restrict__ sW,
+    typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
+  constexpr unsigned kmask = (1u << K) - 1u;
+  int tile = lo;
+  unsigned m = 0u;
+  while (tile < hi && (m = tmrow[tile] & kmask) == 0u) ++tile;
+  if (tile >= hi) return;
+  TileRegs<D> cur;
+  load_tile_regs<D>(cur, Yrow, abrow, tile * kWave, lane, T);
+  for (;;) {
+    int next = tile + 1;
+    unsigned mn = 0u;
+    while (next < hi && (mn = tmrow[next] & kmask) == 0u) ++next;
+    const bool last = next >= hi;
+    // (after the last live tile its own frames are requested again, so that the load needs no branch)
+    pass_tile<D, K, false, RESIDENT, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
+                                           sW, acc, nacc, &cur, (last ? tile : next) * kWave);
+    if (last) break;
+    tile = next;
+    m = mn;
   }
 }
 
@@ -324,7 +370,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   constexpr bool RESIDENT = K * R <= kResidentRegs;
   constexpr int WS = weight_stride(K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;        // no tiles in LDS then
-  constexpr int kTileDoubles = DIRECT ? 0 : kWave * kYStride + kWave * WS;
+  constexpr int kTileDoubles = DIRECT ? 0 : tile_region_doubles<D>(WS);
   constexpr int kCoefDoubles = RESIDENT ? 0 : K * R * 16;
   // per-wavefront tiles (+ the coefficient copy); the tiles are reused at the end for the cross-wavefront
   // reduction (needs kPassWaves * (64 * K + K); DIRECT: kPassWaves * (K * E + K))
@@ -345,7 +391,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
 
   const double* __restrict__ cf = coef + sf * (long)(K * E);
   double* __restrict__ sY = lds + (FINAL ? 0 : wave * kTileDoubles);
-  double* __restrict__ sW = sY + (FINAL ? 0 : kWave * kYStride);
+  double* __restrict__ sW = sY + (FINAL ? 0 : kWave * TileLayout<D>::row);
   double* __restrict__ sC = lds + kTilesDoubles;
 
   // The class coefficients: register r of class k holds entries 16 r .. 16 r + 15 of its packed coefficients,
@@ -399,10 +445,12 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   const int n_tiles = tile_hi > tile_lo ? tile_hi - tile_lo : 0;
   const int my_lo = tile_lo + (n_tiles * wave) / kPassWaves;
   const int my_hi = tile_lo + (n_tiles * (wave + 1)) / kPassWaves;
-  for (int tile = my_lo; tile < my_hi; ++tile) {
-    pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
-                                     lane, tmrow[tile], sY, sW, acc, nacc
-                                     );
+  if constexpr (DIRECT || FINAL) {
+    for (int tile = my_lo; tile < my_hi; ++tile)
+      pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
+                                       lane, tmrow[tile], sY, sW, acc, nacc);
+  } else {
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, lane, sY, sW, acc, nacc);
   }
   if (FINAL) return;
 
@@ -419,7 +467,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
       else npart[(long)blockIdx.x * K + (x - K * E)] = sum;
     }
   } else {
-    // Reduce over the 8 frame groups and over the wavefronts; write the chunk's packed partial sums and counts.
+    // Reduce over the frame groups and over the wavefronts; write the chunk's packed partial sums and counts.
     reduce_and_store_partials<D, K, true>(acc, nacc, sY, lds, part + (long)blockIdx.x * (K * E),
                                           npart + (long)blockIdx.x * K, lane, wave);
   }
@@ -702,12 +750,12 @@ __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
-    bool resident_tiles, int wave, int lane, unsigned my_mask, const TileRegs<D>& pre, double* __restrict__ sY,
+    bool resident_tiles, int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY,
     double* __restrict__ sW, typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
   if constexpr (NW > 1) {
     if (resident_tiles) {
       if (wave < tile_end)
-        pass_tile<D, K, FINAL, RESIDENT, true>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+        pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                                wave * kWave, lane, my_mask, sY, sW, acc, nacc, &pre);
       return;
     }
@@ -730,23 +778,25 @@ __device__ __forceinline__ void whole_pass(
         if (mn != 0u) load_tile_regs<D>(nxt, Yrow, abrow, next * kWave, lane, T);
       }
       // (the mask is the same in every lane; the compiler has to be told after the loop-carried copy)
-      pass_tile<D, K, FINAL, RESIDENT, true>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+      pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              tile * kWave, lane, __builtin_amdgcn_readfirstlane(m), sY, sW, acc, nacc,
                                              &cur);
       cur = nxt;
       m = mn;
       tile = next;
     }
-  } else {
+  } else if constexpr (PassAcc<D, K>::direct || FINAL || NW > 1) {
     for (int tile = wave; tile < tile_end; tile += NW)
       pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, sW, acc, nacc);
+  } else {
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, 0, tile_end, lane, sY, sW, acc, nacc);
   }
 }
 
 // ----------------------------------------------------------------------------------------------
 // Whole-EM kernel: a workgroup of NW wavefronts owns one (segment, frequency) for all iterations.  Per
-// iteration every wavefront walks its tiles (pass_tile above), sums its accumulators over the 8 frame groups
+// iteration every wavefront walks its tiles (pass_tile above), sums its accumulators over the frame groups
 // through LDS, and factorises the K class matrices itself, so that the coefficients of the next iteration go
 // from LDS straight back into its registers: no partial sums in memory, no second kernel, no launch per
 // iteration, and the same fixed summation order on every run.
@@ -774,7 +824,6 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   constexpr bool RESIDENT = K * R <= kResidentRegs;
   constexpr int WS = weight_stride(K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;       // no tiles in LDS then
-  constexpr int kTileDoubles = DIRECT ? 0 : kWave * kYStride + kWave * WS;
   constexpr int kCoefDoubles = K * R * 16;             // packed coefficients, padded to whole registers
   constexpr int kSumDoubles = K * E + K;               // packed weighted scatter sums, then the class counts
   // The sums, counts and class constants of the M-step live only between the last tile of a pass and the first
@@ -783,8 +832,9 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   // pass reads them from LDS and they keep a place of their own behind the tile).
   constexpr bool SHARED_MSTEP = !DIRECT;
   constexpr int kSharedDoubles = kSumDoubles + K + (RESIDENT ? kCoefDoubles : 0);
-  static_assert(!SHARED_MSTEP || kReduceWaveDoubles + kSharedDoubles <= kTileDoubles,
-                "the M-step's buffers must fit behind the reduction rows inside the tile region");
+  constexpr int kTileOnly = DIRECT ? 0 : tile_region_doubles<D>(WS);
+  constexpr int kMstepDoubles = SHARED_MSTEP ? (reduce_wave_doubles(D) + kSharedDoubles + 1) / 2 * 2 : 0;
+  constexpr int kTileDoubles = kTileOnly > kMstepDoubles ? kTileOnly : kMstepDoubles;
   constexpr int kWaveDoubles = !SHARED_MSTEP ? (kTileDoubles + kCoefDoubles + kSumDoubles + K + 1) / 2 * 2
                                : RESIDENT    ? kTileDoubles
                                              : (kTileDoubles + kCoefDoubles + 1) / 2 * 2;
@@ -794,9 +844,9 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0;
   double* __restrict__ sY = lds + wave * kWaveDoubles;
-  double* __restrict__ sW = sY + kWave * kYStride;
-  double* __restrict__ sC = sY + (SHARED_MSTEP && RESIDENT ? kReduceWaveDoubles : kTileDoubles);   // [K][R * 16] coefficients of B^-1 for the next pass
-  double* __restrict__ sR = SHARED_MSTEP && !RESIDENT ? sY + kReduceWaveDoubles : sC + kCoefDoubles;   // [K][E] packed weighted scatter sums
+  double* __restrict__ sW = sY + kWave * TileLayout<D>::row;
+  double* __restrict__ sC = sY + (SHARED_MSTEP && RESIDENT ? reduce_wave_doubles(D) : kTileDoubles);   // [K][R * 16] coefficients of B^-1 for the next pass
+  double* __restrict__ sR = SHARED_MSTEP && !RESIDENT ? sY + reduce_wave_doubles(D) : sC + kCoefDoubles;   // [K][E] packed weighted scatter sums
   double* __restrict__ sN = sR + K * E;                // [K] class counts
   double* __restrict__ sCC = sN + K;                   // [K] class constants pi / det B
   double* __restrict__ sShare = lds + NW * kWaveDoubles;   // [2][NW][kShareRows][kSumDoubles] sums of the wavefronts (NW > 1)
@@ -864,10 +914,9 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   // live across the tile loop, where there is no register for them, and come back from scratch memory one
   // dependent load at a time.
   if constexpr (!DIRECT) {
-    static constexpr SlotTable kSlots = make_slot_table();
-    const int slot = (lane & 7) * 8 + (lane >> 3);     // lane o = 8 n + eg reads back slot (eg, n)
-    const int pi0 = kSlots.v[D][slot];
-    sSlot[lane] = (pi0 < 0 ? 0x4000 : pi0) | (kSlots.sign[slot] < 0 ? 0x8000 : 0);
+    static constexpr SlotTable<D> kSlots = make_slot_table<D>();
+    const int pi0 = kSlots.index[lane];                // lane o = D n + i reads back slot (i, n)
+    sSlot[lane] = (pi0 < 0 ? 0x4000 : pi0) | (kSlots.sign[lane] < 0 ? 0x8000 : 0);
   }
   wave_lds_sync();
   for (int it = 0; it < iters; ++it) {
@@ -881,7 +930,7 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
 
     int le = lane;                                      // the lane number again, opaque
     asm volatile("" : "+v"(le));
-    // ---- sums over the 8 frame groups -> packed sR[k][e]; class counts over the lanes -> sN[k] ----
+    // ---- sums over the frame groups -> packed sR[k][e]; class counts over the lanes -> sN[k] ----
     // (NW > 1: into this wavefront's slot of the shared buffer of this iteration)
     double* __restrict__ sOut = NW > 1 ? sShare + ((it & 1) * NW + wave) * (kShareRows * kSumDoubles) : sR;
     if constexpr (DIRECT) {
@@ -898,23 +947,13 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
     }
 #pragma unroll
     for (int k0 = 0; k0 < K; k0 += 2) {
+      double S[2];
+      sum_frame_groups<D, K>(acc, k0, sY, le, S);
 #pragma unroll
       for (int c = 0; c < 2; ++c)
-        if (k0 + c < K) {
-#pragma unroll
-          for (int n = 0; n < 8; ++n) sY[(c * 8 + n) * kReduceRow + le] = acc[n][k0 + c];
-        }
-      wave_lds_sync();
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        if (k0 + c < K) {
-          double sum = 0.0;
-#pragma unroll
-          for (int tg = 0; tg < 8; ++tg) sum += sY[(c * 8 + (le >> 3)) * kReduceRow + tg * 8 + (le & 7)];
-          if (pidx >= 0) sOut[(k0 + c) * E + pidx] = sgn * sum;
-        }
-      wave_lds_sync();
+        if (k0 + c < K && pidx >= 0) sOut[(k0 + c) * E + pidx] = sgn * S[c];
     }
+    wave_lds_sync();
     }
     if constexpr (NW > 1) {
       __syncthreads();                                  // every wavefront's sums of this iteration are in place

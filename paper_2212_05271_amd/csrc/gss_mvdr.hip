@@ -21,8 +21,8 @@ namespace {
 // ----------------------------------------------------------------------------------------------
 // Covariance accumulation for D <= 8.  Same tile machinery as the EM pass: a workgroup of kPassWaves
 // wavefronts per (segment, frequency, chunk); per tile, lane = frame loads y and the two weights into the
-// wavefront's LDS region, then lane = (frame group, channel i) accumulates the two weighted outer products
-// (lane type i owns y_i conj(y_b) at circular channel distance 1..4 plus its share of the diagonal).  Output: part[sf][chunk][2][E] packed (0: target, 1: background).
+// wavefront's LDS region, then lane = (frame group, lane type) accumulates the two weighted outer products (TileLayout).
+// Output: part[sf][chunk][2][E] packed (0: target, 1: background).
 // ----------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
@@ -30,10 +30,12 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
     const int32_t* __restrict__ target, double* __restrict__ part, uint32_t* __restrict__ status,
     int F, int Tmax, int K, int C, int tiles_per_chunk) {
   constexpr int E = D * D;
-  // the two weights of a frame sit in the two padding entries at the end of its row of the y tile (three
-  // workgroups per CU fit that way)
-  constexpr int WS = kYStride;
-  constexpr int kTileDoubles = kWave * kYStride;
+  // D = 8: the two weights of a frame sit in the two padding entries at the end of its row of the y tile (three workgroups
+  // per CU fit that way).  D < 8: rows without padding, the weights behind the tile.
+  using L = TileLayout<D>;
+  constexpr int WS = L::pad > 0 ? L::row : 2;
+  constexpr int kRows = kWave * L::row + (L::pad > 0 ? 0 : kWave * WS);
+  constexpr int kTileDoubles = kRows > reduce_wave_doubles(D) ? kRows : reduce_wave_doubles(D);
   constexpr int kRedDoubles = kPassWaves * 64 * 2;
   constexpr int kLdsDoubles = kPassWaves * kTileDoubles > kRedDoubles ? kPassWaves * kTileDoubles : kRedDoubles;
   __shared__ __attribute__((aligned(16))) double lds[kLdsDoubles];
@@ -53,11 +55,11 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
   }
 
   double* __restrict__ sY = lds + wave * kTileDoubles;
-  double* __restrict__ sW = sY + kYTurned + 8;
-  double acc[8][2];
+  double* __restrict__ sW = sY + (L::pad > 0 ? L::row - L::pad : kWave * L::row);
+  double acc[D][2];
 #pragma unroll
-  for (int n = 0; n < 8; ++n) { acc[n][0] = 0.0; acc[n][1] = 0.0; }
-  const int tg = lane >> 3, eg = lane & 7;
+  for (int n = 0; n < D; ++n) { acc[n][0] = 0.0; acc[n][1] = 0.0; }
+  const int tg = lane / D, eg = lane - tg * D;
 
   const float* __restrict__ grow = gamma + ((long)s * K * F + f) * Tmax;   // + k * F * Tmax + t
   const long gk = (long)F * Tmax;
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
       double yr[D], yi[D];
 #pragma unroll
       for (int d = 0; d < D; ++d) { yr[d] = (double)yraw[d].x; yi[d] = (double)yraw[d].y; }
-      store_tile_row<D>(sY + lane * kYStride, yr, yi);
+      store_tile_row<D>(sY + lane * L::row, yr, yi);
     }
     double wt = 0.0, wb = 0.0;
 #pragma unroll
@@ -98,7 +100,7 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
     sW[lane * WS + 1] = valid ? wb : 0.0;
     if (tile + kPassWaves < tile_hi) load_tile(tile + kPassWaves);
     wave_lds_sync();
-    accumulate_tile<2, WS>(sY, sW, tg, eg, acc);
+    accumulate_tile<D, 2, WS>(sY, sW, tg, eg, acc);
     wave_lds_sync();
   }
   double none[2] = {0.0, 0.0};

@@ -300,6 +300,29 @@ def test_rank_deficient_classes(env, D, mode):
     assert ctx.get_status() == 0
 
 
+@pytest.mark.parametrize("D,K", [(4, 6), (5, 4), (6, 5), (6, 8), (7, 4), (8, 6)])
+def test_tile_frame_groups(env, D, K):
+    """The lane layout of the accumulating passes: 64 frames over 64 / D frame groups, some of which have a frame more, and
+    tiles that are requested ahead past tiles without any active class.  Lengths around the group counts and the tile edge,
+    the one-wavefront kernel and the chunked kernels.  Tolerance of test_rank_deficient_classes (short lengths are that)."""
+    gss, ctx = env["gss"], env["ctx"]
+    for T in (3, 59, 61, 63, 64, 65, 131, 400):
+        rng = np.random.default_rng(1000 * D + T)
+        Y = (_cn(rng, (3, T, D)) * np.exp(rng.standard_normal((3, T, 1)))).astype(np.complex64)
+        act = (rng.random((K, T)) < 0.4).astype(np.uint8)
+        act[K - 1] = 1
+        act[:, 64:128] = 0
+        act[:, 192:320] = 0
+        go = env["o"].cacgmm_em(Y, act, 2)
+        for forced in (0, 1 << 40):
+            ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, forced)
+            try:
+                g = _gpu_em(env, Y[None], act[None], None, 2)[0]
+            finally:
+                ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, -1)
+            assert np.max(np.abs(g - go)) <= 1e-5, (T, forced)
+
+
 @pytest.mark.parametrize("D", [10, 20, 26, 32])
 def test_every_large_instantiation(env, D):
     """Every (class count, items-per-lane) instantiation of the large-array kernels: K = 1..8 at one channel
