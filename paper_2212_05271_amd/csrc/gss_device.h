@@ -195,8 +195,10 @@ __device__ __forceinline__ void wave_lds_sync() {
 // A class whose bit is clear in a tile's activity mask has posterior 0 in every frame of the tile and adds nothing
 // to any sum: the pass kernels skip its arithmetic for the whole tile under wave-uniform branches.
 // Activity in the form the pass kernels read: abyte[s][t] has bit k set when class k may be active in frame t
-// (a_{t,k} of Eq. (5); 0 at t >= T_len[s]), tmask[s][tile] is the OR of the bytes of the tile's 64 frames.
+// (a_{t,k} of Eq. (5); 0 at t >= T_len[s]), tmask[s][tile] is the OR of the bytes of the tile's 64 frames, or (GROUPS) four
+// bytes, those of its groups of 16 frames.
 // Grid: one wavefront per (segment, tile).
+template <bool GROUPS>
 __global__ __launch_bounds__(kWave) void em_pack_activity(
     gss_yview yv, const uint8_t* __restrict__ act, const int32_t* __restrict__ T_len, uint8_t* __restrict__ abyte,
     uint32_t* __restrict__ tmask, int K, int Tmax, int tiles) {
@@ -208,6 +210,7 @@ __global__ __launch_bounds__(kWave) void em_pack_activity(
   if (t < T)
     for (int k = 0; k < K; ++k) b |= (act[((long)s * K + k) * Tmax + t] != 0 ? 1u : 0u) << k;
   if (t < Tmax) abyte[(long)s * Tmax + t] = (uint8_t)b;
+  if constexpr (GROUPS) b <<= 8 * (lane >> 4);
 #pragma unroll
   for (int off = 1; off < kWave; off <<= 1) b |= (unsigned)__shfl_xor((int)b, off, kWave);
   if (lane == 0) tmask[(long)s * tiles + tile] = b;

@@ -1064,7 +1064,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
   if (p.wgs_acc > 0x7fffffffL || p.wgs_fin > 0x7fffffffL) return GSS_EUNSUPPORTED;
   const dim3 block(kWave * kPassWaves);
-  hipLaunchKernelGGL(em_pack_activity, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
+  hipLaunchKernelGGL(em_pack_activity<false>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
                      Tmax, tiles);
   // Many problems per resident wavefront: one wavefront runs the whole EM of a problem (no partial sums, no
   // factor launches).  Few problems: each one is cut into chunks over several workgroups, one pass and one

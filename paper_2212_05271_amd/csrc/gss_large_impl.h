@@ -1,19 +1,17 @@
 // EM and MVDR kernels for large arrays, 9 <= D <= 32 channels (e.g. multi-array set-ups with 24
 // microphones).  Same algorithm, same fp64 arithmetic and the same pass / factor structure as the D <= 8
-// kernels (arXiv 2212.05271, Section 2.2 and 2.3); what changes is the mapping:
+// kernels (arXiv 2212.05271, Section 2.2 and 2.3); what changes is the mapping: D is a run-time value, and both
+// contractions of a pass run on the fp64 matrix cores in real arithmetic.
 //
-//   * D is a run-time value; the Hermitian outer product has M = D (D + 1) / 2 "items" (i <= j), each a
-//     real diagonal entry or a complex off-diagonal one.  Coefficients are class-major, coef[sf][k][CP]
-//     (entries 2 m and 2 m + 1 multiply Re and Im of item m; CP = 2 M rounded up to whole groups of 16,
-//     zero padding); partial sums are item-major, part[workgroup][m][k][2].
-//   * The frames of a tile sit in LDS as fp32 (exactly as they came), because D * 16 bytes of fp64 per
-//     frame would not leave room for two workgroups per compute unit.
-//   * Phase 1 (lane = frame) walks the items 8 at a time in a run-time loop, reading y_i, y_j of its own
-//     frame from LDS; the 16 coefficients of a group sit in one register pair per class and reach the FMAs
-//     through the row-broadcast operand selector.
-//   * Phase 2 (lane = a few items, frames in sequence): each lane owns NR items m = lane, lane + 64, ...,
-//     forms them for every frame of the tile from LDS and accumulates K weighted sums per real part.
-//   * Classes that are inactive in all 64 frames of a tile are skipped in both phases.
+//   * A frame is the vector u of its 2 D reals (re, im of every channel, as in memory), padded to 16 NB entries,
+//     NB = ceil(D / 8).
+//   * E-step: the class matrix enters as W = the inverse of its Cholesky factor (B = L L^H, W = L^-1), and
+//     q = y^H B^-1 y = |W y|^2: a product of the real form of W (2 D x 2 D, block lower triangular, 16 x 16 tiles) with 16
+//     frames, then a sum of squares.  No cancellation beyond that of W y, whose entries are the square roots of those of
+//     B^-1: better conditioned than the quadratic form itself.
+//   * M-step sums: sum_t w_t u_t u_t^T by 16 x 16 tiles on and above the diagonal; the Hermitian sums are
+//     Re = (re re) + (im im), Im = (im re) - (re im) of them, formed once at the end.
+//   * A class that is inactive in a group of 16 frames is skipped for the group in both steps.
 #pragma once
 
 #include "gss_internal.h"
@@ -45,362 +43,535 @@ __device__ __forceinline__ double ipow_rt(double x, int n) {   // x^n, n >= 1
   return r;
 }
 
-// Coefficient layout for 9 <= D <= 32: class-major, coef[sf][k][CP], in groups of 16 doubles = (Re, Im) of 8 items.
-// The items (i, j), i <= j, of row i fill ceil((D - i) / 8) groups of their own, in the order of j; the last group
-// of a row is padded (the padding is zero and never used).  A group never spans two rows, so the pass kernel
-// walks a group with one y_i and consecutive y_j.
-__host__ __device__ inline int groups_of_lengths_up_to(int n) {      // sum over L = 1 .. n of ceil(L / 8)
-  const int q = n >> 3, r = n & 7;
-  return 4 * q * (q + 1) + r * (q + 1);
+
+// ----------------------------------------------------------------------------------------------
+// Geometry of the matrix-core kernels
+// ----------------------------------------------------------------------------------------------
+typedef double double4v __attribute__((ext_vector_type(4)));
+typedef double double2v __attribute__((ext_vector_type(2)));
+// D += A B of 16 x 4 and 4 x 16 doubles.  Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], and D[l / 16 + 4 v][l % 16]
+// for v = 0..3.
+__device__ __forceinline__ double4v mfma_f64(double a, double b, double4v c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-__host__ __device__ inline int coef_groups(int D) { return groups_of_lengths_up_to(D); }
-__host__ __device__ inline int coef_pitch(int D) { return 16 * coef_groups(D); }
-// first group of row i (rows 0 .. i - 1 have the lengths D, D - 1, ..., D - i + 1)
-__host__ __device__ inline int row_group(int i, int D) { return groups_of_lengths_up_to(D) - groups_of_lengths_up_to(D - i); }
-// position (in doubles) of the Re coefficient of item (i, j), i <= j; Im follows
-__host__ __device__ inline int coef_pos(int i, int j, int D) {
-  return 16 * (row_group(i, D) + ((j - i) >> 3)) + 2 * ((j - i) & 7);
+// Sum over the four rows of 16 lanes, in every lane.
+__device__ __forceinline__ double sum_rows_f64(double v) {
+  auto add = [](auto lo, auto hi) { return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]); };
+  v = add(__builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false),
+          __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false));
+  return add(__builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false),
+             __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false));
 }
 
-__global__ void em_init_coef_large(double* __restrict__ coef, double* __restrict__ cmant, int32_t* __restrict__ cexp,
-                                   int D, int K, long n_sf) {
-  const int CP = coef_pitch(D);
-  const long total = n_sf * K * CP;
-  for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < total; x += (long)gridDim.x * blockDim.x) {
-    const int c = (int)(x % CP);
-    double v = 0.0;
-    if ((c & 15) == 0) {                     // first entry of a group: 1 if the group opens a row (the diagonal item)
-      int g = c >> 4, r = 0;
-      while (r < D && g >= (D - r + 7) / 8) { g -= (D - r + 7) / 8; ++r; }
-      v = (r < D && g == 0) ? 1.0 : 0.0;
-    }
-    coef[x] = v;
-  }
-  const long nl = n_sf * K;
-  for (long x = blockIdx.x * (long)blockDim.x + threadIdx.x; x < nl; x += (long)gridDim.x * blockDim.x) {
-    cmant[x] = 0.5;
-    cexp[x] = 1;
-  }
+// Largest of the four lane rows' values, in every lane.
+__device__ __forceinline__ int max_rows_i32(int v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  const int m = (int)a[0] > (int)a[1] ? (int)a[0] : (int)a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  return (int)b[0] > (int)b[1] ? (int)b[0] : (int)b[1];
 }
 
-// Cooperative, coalesced copy of one tile of frames [t0, t0 + 64) of a (segment, frequency) row into the
-// wavefront's LDS tile sY[frame][D] (float2, row stride RS float2); frames at or beyond T become zero.
-// The tile is one contiguous run of 64 D values in memory; lane l copies values l, l + 64, ... (D of them).  Their
-// frame and channel are stepped without divisions, and the loads go out six at a time before the first of them
-// is stored (one at a time, every value would wait out a full memory latency).
-__device__ __forceinline__ void load_tile(const float2* __restrict__ Yrow, int t0, int T, int D, int RS,
-                                          float2* __restrict__ sY, int lane) {
-  constexpr int kBatch = 12;
-  const int rstep = kWave / D, cstep = kWave % D;          // frame and channel advance per 64 values
-  int r = lane / D, c = lane - r * D;
-  const float2* __restrict__ src = Yrow + (long)t0 * D + lane;
-  const int rows = T - t0;                                   // frames of the tile that exist (may exceed 64)
-  for (int i0 = 0; i0 < D; i0 += kBatch) {
-    float2 v[kBatch];
-    int off[kBatch];
+// Real entries per frame row in LDS: 16 NB and 4 more.  The operands of a tile product are rows 4 g + s of 16 frames (lane
+// row g, step s): four rows apart is 128 modulo the 256 bytes that LDS delivers per cycle, so such a read has no conflicts.
+__host__ __device__ constexpr int large_pitch(int NB) { return 16 * NB + 4; }
+// Tiles of W (block lower triangular, by rows) and the doubles of a class: lane l = 16 g + m of a tile (i, j) holds
+// W[16 i + m][16 j + 4 g + s], s = 0..3, the left operand of step s: as two pairs, [tile][s / 2][lane][s % 2].
+__host__ __device__ constexpr int large_tiles(int NB) { return NB * (NB + 1) / 2; }
+__host__ __device__ constexpr int large_coef(int NB) { return 256 * large_tiles(NB); }
+
+// Tiles of the weighted sums: which of the NB (NB + 1) / 2 tiles on and above the diagonal a wavefront of the workgroup adds
+// up, over which of the four groups of 16 frames of a tile of frames.  A wavefront has one left operand (row of tiles `left`)
+// and `count` right ones; left > right is the transposed tile.  Every wavefront gets the same number of products (3, 6 and
+// 10 of them in four: three, six and ten groups x tiles), with few accumulators: 8 count K registers.  The first `full` right
+// operands of every wavefront take all groups.  `phase`: when the wavefront's sums of the tile join the others' at the end
+// (0: they are the first).
+template <int NB>
+struct LargeShare;
+template <>
+struct LargeShare<2> {
+  static constexpr int count = 2;
+  static constexpr int left[4] = {0, 0, 1, 1};
+  static constexpr int right[4][2] = {{0, 1}, {0, 1}, {1, 0}, {1, 0}};
+  static constexpr int groups[4][2] = {{3, 1}, {12, 4}, {3, 2}, {12, 8}};
+  static constexpr int full = 0, phases = 4;
+  static constexpr int phase[4][2] = {{0, 0}, {1, 1}, {0, 2}, {1, 3}};
+};
+template <>
+struct LargeShare<3> {
+  static constexpr int count = 2;
+  static constexpr int left[4] = {0, 0, 1, 2};
+  static constexpr int right[4][2] = {{0, 1}, {2, 1}, {1, 2}, {2, 1}};
+  static constexpr int groups[4][2] = {{15, 3}, {15, 12}, {15, 3}, {15, 12}};
+  static constexpr int full = 1, phases = 2;
+  static constexpr int phase[4][2] = {{0, 0}, {0, 1}, {0, 0}, {0, 1}};
+};
+template <>
+struct LargeShare<4> {
+  static constexpr int count = 3;
+  static constexpr int left[4] = {0, 3, 1, 2};
+  static constexpr int right[4][3] = {{0, 1, 2}, {3, 0, 1}, {1, 2, 3}, {2, 3, 0}};
+  static constexpr int groups[4][3] = {{15, 15, 3}, {15, 15, 12}, {15, 15, 3}, {15, 15, 12}};
+  static constexpr int full = 2, phases = 2;
+  static constexpr int phase[4][3] = {{0, 0, 0}, {0, 0, 1}, {0, 0, 0}, {0, 0, 1}};
+};
+// A wavefront's share in registers (wave-uniform).
+template <int NB>
+struct LargeRole {
+  int left, right[LargeShare<NB>::count], groups[LargeShare<NB>::count], phase[LargeShare<NB>::count];
+  __device__ __forceinline__ explicit LargeRole(int wave) {
+    using S = LargeShare<NB>;
+    left = 0;
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      v[u] = make_float2(0.f, 0.f);
-      off[u] = r * RS + c;
-      if (i0 + u < D) {
-        if (r < rows) v[u] = src[(long)(i0 + u) * kWave];
-        c += cstep;
-        r += rstep;
-        if (c >= D) { c -= D; ++r; }
+    for (int w = 0; w < kLargeWaves; ++w)
+      if (wave == w) {
+        left = S::left[w];
+#pragma unroll
+        for (int r = 0; r < S::count; ++r) {
+          right[r] = S::right[w][r];
+          groups[r] = S::groups[w][r];
+          phase[r] = S::phase[w][r];
+        }
       }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (i0 + u < D) sY[off[u]] = v[u];
   }
-}
+};
 
-// Phase 2 for the lane's NR items over the 64 frames of the tile, for the classes of `mask` (wave-uniform; the
-// weights of the other classes are zero in every frame of the tile).
-template <int KW, int NR>
-__device__ __forceinline__ void accumulate_items(const float2* __restrict__ sY, const double* __restrict__ sW, int RS,
-                                                 int WS, const int (&oi)[NR], const int (&oj)[NR], unsigned mask,
-                                                 double (&acc)[NR][2][KW]) {
-#pragma unroll 1
-  for (int r = 0; r < kWave; ++r) {
-    double w[KW];
+// A wavefront's 16 frames of a tile: lane (g, n) = (lane / 16, lane % 16) has frame n's channels 8 b + 2 g and the one behind it
+// for every b < NB, which is the right operand of the E-step's products (entries 16 b + 4 g .. + 3 of u).  Channels from D on
+// and frames from T on are zero.
+template <int NB>
+struct LargeFrames {
+  float2 v[NB][2];
+  unsigned abits, mask;                                     // (mask: the masks of a tile further on, the same in every lane)
+  __device__ __forceinline__ void request(const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, int t, int T,
+                                          int D, int g) {
+    struct __attribute__((packed, aligned(8))) pair { float x0, y0, x1, y1; };
+    const bool valid = t < T;
+    const float2* __restrict__ src = Yrow + (long)(valid ? t : 0) * D + 2 * g;     // (frame 0 exists where a tile is live)
+    abits = abrow[valid ? t : 0];
 #pragma unroll
-    for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
-    double re[NR], im[NR];
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      const float2 a = sY[r * RS + oi[n]];
-      const float2 b = sY[r * RS + oj[n]];
-      const double ar = a.x, ai = a.y, br = b.x, bi = b.y;
-      re[n] = ar * br + ai * bi;          // Re(y_i conj(y_j)); |y_i|^2 on the diagonal
-      im[n] = ai * br - ar * bi;          // Im(y_i conj(y_j)); 0 on the diagonal
+    for (int b = 0; b + 1 < NB; ++b) {
+      const pair q = *reinterpret_cast<const pair*>(src + 8 * b);
+      v[b][0] = make_float2(q.x0, q.y0);
+      v[b][1] = make_float2(q.x1, q.y1);
     }
+    // the last block of channels may end inside: channel 0 or 1 of the block before in the place of one that is not there (no
+    // branch: a load under one is waited for where the branch ends)
+    constexpr int c = 8 * (NB - 1);
+    v[NB - 1][0] = src[c + 2 * g < D ? c : c - 8];
+    v[NB - 1][1] = src[c + 2 * g + 1 < D ? c + 1 : c - 7];
+  }
+  __device__ __forceinline__ void convert(double (&u)[NB][4], unsigned& bits, int t, int T, int D, int g) const {
+    const bool valid = t < T;
+    bits = valid ? abits : 0u;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        u[b][2 * e] = (double)v[b][e].x;
+        u[b][2 * e + 1] = (double)v[b][e].y;
+      }
+    // (both conditions are the same in every lane: hardly ever true, or never)
+    if (__builtin_amdgcn_readfirstlane(t - (t & 15)) + 16 > T || (D & 7) != 0) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[b][e] = valid && 8 * b + 2 * g + (e >> 1) < D ? u[b][e] : 0.0;
+    }
+  }
+};
+
+// Adds w_k u u^T over the tile's 64 frames to the wavefront's tiles, for the classes of each group of 16 frames (byte g of
+// `masks`).  sW: [KW][64] weights.  Step s of a group takes frames 4 g + s (lane row g): a lane's four weights are contiguous,
+// and the four products of a tile follow each other on the same accumulators (a product on other accumulators starts about
+// ten of its 64 cycles later).
+template <int NB, int KW>
+__device__ __forceinline__ void accumulate_large(const double* __restrict__ sY, const double* __restrict__ sW,
+                                                 const LargeRole<NB>& role, unsigned masks, int lane,
+                                                 double4v (&acc)[KW][LargeShare<NB>::count]) {
+  constexpr int P = large_pitch(NB), C = LargeShare<NB>::count;
+  const double* __restrict__ p = sY + 4 * (lane >> 4) * P + (lane & 15);
+  const double* __restrict__ pw = sW + 4 * (lane >> 4);
+  // Requested ahead of their use: the operands of the next group of frames and the weights of the next class, whatever the
+  // masks say (an unused read costs less than a wait; 4 x 4 tiles: the registers allow the weights only).
+  constexpr bool kAheadOps = NB < 4;
+  double l[2][4], b[2][C][4];
+  auto operands = [&](int slot, int g) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      l[slot][s] = p[(16 * g + s) * P + 16 * role.left];
+#pragma unroll
+      for (int r = 0; r < C; ++r) b[slot][r][s] = p[(16 * g + s) * P + 16 * role.right[r]];
+    }
+  };
+  if constexpr (kAheadOps) operands(0, 0);
+  static_for<0, 4>([&](auto GI) {
+    constexpr int g = GI.value, cur = kAheadOps ? g & 1 : 0;
+    if constexpr (!kAheadOps) operands(0, g);
+    double2 w[2][2];
+    w[0][0] = *reinterpret_cast<const double2*>(pw + 16 * g);
+    w[0][1] = *reinterpret_cast<const double2*>(pw + 16 * g + 2);
+    if constexpr (kAheadOps && g < 3) operands(cur ^ 1, g + 1);
+    unsigned mask = (masks >> (8 * g)) & 0xffu;
     static_for<0, KW>([&](auto KI) {
       constexpr int k = KI.value;
+      if constexpr (k + 1 < KW) {
+        w[(k + 1) & 1][0] = *reinterpret_cast<const double2*>(pw + (k + 1) * kWave + 16 * g);
+        w[(k + 1) & 1][1] = *reinterpret_cast<const double2*>(pw + (k + 1) * kWave + 16 * g + 2);
+      }
       if (class_on(mask, k)) {
+        const double2 w0 = w[k & 1][0], w1 = w[k & 1][1];
+        const double a[4] = {w0.x * l[cur][0], w0.y * l[cur][1], w1.x * l[cur][2], w1.y * l[cur][3]};
 #pragma unroll
-        for (int n = 0; n < NR; ++n) {
-          acc[n][0][k] = fma(w[k], re[n], acc[n][0][k]);
-          acc[n][1][k] = fma(w[k], im[n], acc[n][1][k]);
+        for (int r = 0; r < C; ++r) {
+          if (r < LargeShare<NB>::full || class_on((unsigned)role.groups[r], g)) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc[k][r] = mfma_f64(a[s], b[cur][r][s], acc[k][r]);
+          }
         }
       }
     });
-  }
+  });
 }
 
-// Sums the accumulators of the workgroup's wavefronts through LDS and writes out[m][k][2].
-template <int KW, int NR>
-__device__ __forceinline__ void reduce_items(double (&acc)[NR][2][KW], double* __restrict__ red, double* __restrict__ out,
-                                             int M, int lane, int wave) {
-  __syncthreads();
-  for (int w = 0; w < kLargeWaves; ++w) {
-    if (wave == w) {
+// The workgroup's sums as packed partial sums out[k][m][2] (m: item (i, j), i <= j): the wavefronts put their tiles into LDS, in
+// a fixed order where several have the same one, as many classes at a time as there is room for; then Re and Im of the items
+// are formed from them.  red: large_red_doubles.
+constexpr int kRedTile = 16 * 17;                           // a tile, rows 17 apart
+__host__ __device__ constexpr int large_red_classes(int K, int NB) {
+  const int room = 2 * (kWave * large_pitch(NB) + K * kWave) / (kRedTile * large_tiles(NB));
+  return room < K ? room : K;
+}
+__host__ __device__ constexpr int upper_tile(int i, int j, int NB) { return i * NB - i * (i - 1) / 2 + (j - i); }   // i <= j
+template <int NB, int KW, int BATCH>
+__device__ __forceinline__ void reduce_large(const double4v (&acc)[KW][LargeShare<NB>::count], const LargeRole<NB>& role,
+                                             double* __restrict__ red, double* __restrict__ out, int D, int lane) {
+  constexpr int C = LargeShare<NB>::count, kClass = kRedTile * large_tiles(NB);
+  const int row = lane >> 4, col = lane & 15, M = num_items(D);
 #pragma unroll
-      for (int n = 0; n < NR; ++n) {
-        const int m = lane + kWave * n;
-        if (m < M) {
+  for (int k0 = 0; k0 < KW; k0 += BATCH) {
+    __syncthreads();
 #pragma unroll
-          for (int k = 0; k < KW; ++k)
+    for (int ph = 0; ph < LargeShare<NB>::phases; ++ph) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-              double* dst = &red[((long)m * KW + k) * 2 + p];
-              *dst = (w == 0) ? acc[n][p][k] : *dst + acc[n][p][k];
+      for (int r = 0; r < C; ++r) {
+        if (role.phase[r] == ph) {
+          const bool turned = role.left > role.right[r];
+          const int tile = turned ? upper_tile(role.right[r], role.left, NB) : upper_tile(role.left, role.right[r], NB);
+          double* __restrict__ dst = red + kRedTile * tile + (turned ? 17 * col + row : 17 * row + col);
+          const int step = turned ? 4 : 4 * 17;
+#pragma unroll
+          for (int c = 0; c < BATCH; ++c)
+            if (k0 + c < KW) {
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const double x = acc[k0 + c < KW ? k0 + c : 0][r][v];
+                dst[c * kClass + v * step] = ph == 0 ? x : dst[c * kClass + v * step] + x;
+              }
             }
         }
       }
+      __syncthreads();
     }
-    __syncthreads();
+    for (int x = threadIdx.x; x < D * D; x += kWave * kLargeWaves) {
+      const int i = x / D, j = x - i * D;
+      if (i <= j) {
+        const double* __restrict__ e = red + kRedTile * upper_tile(i >> 3, j >> 3, NB) + 17 * 2 * (i & 7) + 2 * (j & 7);
+        double* __restrict__ o = out + ((long)k0 * M + item_index(i, j, D)) * 2;
+#pragma unroll
+        for (int c = 0; c < BATCH; ++c)
+          if (k0 + c < KW)
+            *reinterpret_cast<double2*>(o + (long)c * M * 2) =
+                make_double2(e[c * kClass] + e[c * kClass + 18], e[c * kClass + 17] - e[c * kClass + 1]);
+      }
+    }
   }
-  const int total = M * KW * 2;
-  for (int x = threadIdx.x; x < total; x += kWave * kLargeWaves) out[x] = red[x];
 }
 
 // ----------------------------------------------------------------------------------------------
-// EM pass, 9 <= D <= 32.  Grid: blockIdx.x = chunk + C * (f + F * s); the chunk's tiles are dealt to the
-// wavefronts round-robin.  Dynamic LDS: kLargeWaves * (64 * RS float2 + 64 * WS doubles), reused for the
-// final reduction (needs M * K * 2 doubles).
+// EM pass, 9 <= D <= 32.  Grid: blockIdx.x = chunk + C * (f + F * s).  The workgroup's four wavefronts share every tile of 64
+// frames: wavefront w has frames 16 w .. 16 w + 15 in the E-step, straight from memory (requested before the sums of the tile
+// before), puts them into LDS as fp64 and, with their weights in place, takes its share of the tiles of the sums
+// (LargeShare).  Two buffers for frames and weights, so one barrier per tile.  The final pass has no sums: no tile in LDS, no
+// barrier, and every wavefront walks the tiles on its own.
+//   coef : W of every class (large_coef doubles each), or null for B = I (first pass)
+//   masks: per tile four bytes, the classes that are active in each group of 16 frames
+// Dynamic LDS: large_lds_doubles, reused for the final reduction.
 //
-// Phase 1 (lane = frame) walks the items 8 at a time.  The 16 class coefficients of such a group (Re and Im
-// of 8 items) sit in one register pair, entry lane mod 16 in every lane, fetched from memory one group ahead
-// (a coalesced 128-byte read that the four rows of the wavefront share); the FMAs take them through the
-// row-broadcast selector of the fp64 FMA.  Classes outside the tile's activity mask are skipped.
+// Bound: the fp64 matrix rate (2 * 96 products of 64 cycles per class and tile at 24 channels: 144 us of a pass over 513 x 1500
+// frames, 5 classes, 2.3 of them active), and vector instructions, which do not run beside a matrix instruction of the same
+// SIMD: the wavefront that is between its products gets one in for every product of the other, so it runs at a raised
+// priority there, lane rows share the posterior's classes, and the lane rows' parts are added up by their reader.  That
+// pass takes 240 us (340 us with the products of frames formed on the vector units, item by item, in both steps); the final
+// pass 122 us (181).  Ways there: frames through LDS with two barriers per tile 274 us, every lane all classes; loads under a
+// branch (waited for at its end) 258; masks through the scalar path, W two tiles ahead, no priorities 249.
 // ----------------------------------------------------------------------------------------------
-// Wavefronts per SIMD that the register allocation of the pass kernel is held to: two where the 4 K NR registers
-// of the phase-2 accumulators leave room for most of the rest within 256 (some values then go to scratch memory,
-// which costs far less than the second wavefront brings: 20 to 36 % less time at 25 to 32 channels or 6 to 8
-// classes), one otherwise (beyond 180 accumulator registers the spills reach the inner loops and the kernel gets
-// two to three times slower than with one wavefront).
-constexpr int pass_waves_per_simd(int K, int NR) { return 4 * K * NR <= 180 ? 2 : 1; }
+constexpr int pass_waves_per_simd(int K, int NB) { return NB == 4 && K > 6 ? 1 : 2; }
+__host__ __device__ constexpr int large_lds_doubles(int K, int NB, bool final_pass) {
+  const int fixed = 2 * K + kWave * K;                      // constants and counts
+  return fixed + (final_pass ? 4 * (K + 1) * kWave : 2 * (kWave * large_pitch(NB) + K * kWave));
+}
 
-template <int K, int NR, bool FINAL>
-__global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NR)) void em_pass_large(
-    gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
+template <int K, int NB, bool FINAL>
+__global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) void em_pass_large(
+    gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ masks,
     const int32_t* __restrict__ T_len,
     const double* __restrict__ coef, const double* __restrict__ cmant, const int32_t* __restrict__ cexp,
     double* __restrict__ part, double* __restrict__ npart, float* __restrict__ gamma, uint32_t* __restrict__ status,
-    int F, int Tmax, int D, ChunkMap cmap, int RS, int tile_bytes) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  constexpr int WS = K | 1;
-  const int M = num_items(D);
-  const int CP = coef_pitch(D);
+    int F, int Tmax, int D, ChunkMap cmap) {
+  extern __shared__ __attribute__((aligned(16))) double lds_large[];
+  constexpr int P = large_pitch(NB), NT = large_tiles(NB), C = LargeShare<NB>::count;
+  constexpr int kBuf = FINAL ? 0 : kWave * P + K * kWave;   // one buffer: weights, then the tile
+  constexpr int kRows = (K + 3) / 4;                        // classes of a lane row in the posterior
+  constexpr unsigned kmask = (1u << K) - 1u;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int g = lane >> 4, n = lane & 15;
   long sf;
   int chunk, tiles_per_chunk;
   chunk_decode(cmap, blockIdx.x, sf, chunk, tiles_per_chunk);
-  const int s = (int)(sf / F);
-  const int f = (int)(sf % F);
+  const int s = (int)((unsigned)sf / (unsigned)F);
+  const int f = (int)((unsigned)sf % (unsigned)F);
   int T;
   const float2* __restrict__ Yrow = y_row(yv, T_len, s, f, D, Tmax, T);
   const int t_end = FINAL ? Tmax : T;
 
-  float2* __restrict__ sY = reinterpret_cast<float2*>(lds_raw + (size_t)wave * tile_bytes);
-  double* __restrict__ sW = reinterpret_cast<double*>(lds_raw + (size_t)wave * tile_bytes + (size_t)kWave * RS * sizeof(float2));
-
-  const double* __restrict__ cf = coef + sf * (long)K * CP + (lane & 15);   // + k * CP + 16 * group
-  const double* __restrict__ cm = cmant + sf * K;
-  const int32_t* __restrict__ ce = cexp + sf * K;
+  double2* __restrict__ sC = reinterpret_cast<double2*>(lds_large);    // [K] mantissa and exponent of pi_k / det B_k
+  double* __restrict__ sN = lds_large + 2 * K;              // [4][K][16] class counts of the wavefronts' frames
+  double* __restrict__ sBuf = sN + kWave * K;
+  const double* __restrict__ cf = coef ? coef + sf * (long)(K * large_coef(NB)) + 2 * lane : nullptr;
   const uint8_t* __restrict__ abrow = abyte + (long)s * Tmax;
   const int tiles_total = (Tmax + kWave - 1) / kWave;
   typedef const __attribute__((address_space(4))) uint32_t* mask_ptr_t;
-  const mask_ptr_t tmrow = (mask_ptr_t)(uintptr_t)(tmask + (long)s * tiles_total);
+  const mask_ptr_t mrow = (mask_ptr_t)(uintptr_t)(masks + (long)s * tiles_total);
+  const uint32_t* __restrict__ mvec = masks + (long)s * tiles_total + (lane >> 6);   // the same, through the vector path
+  float* __restrict__ grow = FINAL ? gamma + ((long)s * K * F + f) * Tmax : nullptr;
+  const long gk = (long)F * Tmax;
 
-  int oi[NR], oj[NR];
-  double acc[NR][2][K];
+  const LargeRole<NB> role(wave);
+  double4v acc[FINAL ? 1 : K][C];
 #pragma unroll
-  for (int n = 0; n < NR; ++n) {
-    int m = lane + kWave * n;
-    if (m >= M) m = 0;                       // idle slot: computes item 0, never written out
-    item_ij(m, D, oi[n], oj[n]);
+  for (int k = 0; k < (FINAL ? 1 : K); ++k)
 #pragma unroll
-    for (int k = 0; k < K; ++k) { acc[n][0][k] = 0.0; acc[n][1][k] = 0.0; }
-  }
-  double nacc[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) nacc[k] = 0.0;
+    for (int r = 0; r < C; ++r) acc[k][r] = double4v{0.0, 0.0, 0.0, 0.0};
+  for (int x = threadIdx.x; x < kWave * K; x += kWave * kLargeWaves) sN[x] = 0.0;
+  if (threadIdx.x < K)
+    sC[threadIdx.x] = cf ? make_double2(cmant[sf * K + threadIdx.x], (double)cexp[sf * K + threadIdx.x])
+                         : make_double2(0.5, 1.0);
 
-  const int groups = coef_groups(D);
   const int tile_lo = chunk * tiles_per_chunk;
   int tile_hi = tile_lo + tiles_per_chunk;
   const int tile_end = (t_end + kWave - 1) / kWave;
   tile_hi = tile_hi < tile_end ? tile_hi : tile_end;
-  for (int tile = tile_lo + wave; tile < tile_hi; tile += kLargeWaves) {
-    const int t0 = tile * kWave;
-    const int t = t0 + lane;
-    const bool valid = t < T;
-    const unsigned mask = tmrow[tile] & ((1u << K) - 1u);
-    if constexpr (FINAL) {
-      static_for<0, K>([&](auto KI) {
-        constexpr int k = KI.value;
-        if (!class_on(mask, k)) {
-          if (t < Tmax) gamma[(((long)s * K + k) * F + f) * Tmax + t] = 0.f;
-        }
-      });
+  if constexpr (FINAL) {
+    // zeros of the classes that are not active in a group of 16 frames
+    for (int tile = tile_lo; tile < tile_hi; ++tile) {
+      const unsigned live = (mrow[tile] >> (8 * wave)) & kmask;
+      const int t = tile * kWave + 16 * wave + n;
+      for (int k = g; k < K; k += 4)
+        if (((live >> k) & 1u) == 0u && t < Tmax) grow[k * gk + t] = 0.f;
     }
-    if (mask == 0u) continue;                // no frame of the tile has an active class
-    load_tile(Yrow, t0, T, D, RS, sY, lane);
-    unsigned abits = abrow[valid ? t : 0];
-    abits = valid ? abits : 0u;
-    wave_lds_sync();
+  }
+  __syncthreads();
 
-    // ---- phase 1: q_k = <coef_k, y y^H> for the lane's frame ----
-    double q[K][2];
-#pragma unroll
-    for (int k = 0; k < K; ++k) { q[k][0] = 0.0; q[k][1] = 0.0; }
-    double n2 = 0.0;
-    const float2* __restrict__ yrow = sY + lane * RS;
-    // Coefficient registers of this group and of the next one.  The fetches go out for every class, active or
-    // not, one group ahead of their use: a fetch under a branch would make every wait for a group's coefficients
-    // a wait for all fetches in flight, the next group's included.  The two register sets swap roles from group
-    // to group (the loop body handles two groups), so nothing is moved between them.
-    double ca[K], cb[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) ca[k] = cf[k * CP];
-    int ri = 0, j0 = 0;                      // wave-uniform: row and first column of the group
-    double ar, ai;
-    {
-      const float2 a = yrow[0];
-      ar = a.x;
-      ai = a.y;
-    }
-    auto group = [&](const double (&ccur)[K], double (&cnxt)[K], int g) {
-      const int gn = g + 1 < groups ? g + 1 : g;
-#pragma unroll
-      for (int k = 0; k < K; ++k) cnxt[k] = cf[k * CP + 16 * gn];
-      const float2* __restrict__ yb = yrow + j0;
-      const int cnt = __builtin_amdgcn_readfirstlane(D - j0);   // items of the group: 8, fewer at the end of a row
-      // The group's items (ri, j0 + u), u < cnt, against the row-broadcast coefficients 2 u and 2 u + 1.  All 8
-      // are formed, whatever cnt is: the reads beyond the row land in the rows of the following frames or, for
-      // the last frame, in the weights behind the tile, and what is formed from them is not used.  (Forming the
-      // upper four under a branch costs more than it saves: the compiler then clears their registers first.)
-      double re[8], im[8];
-      auto form = [&](int u) {
-        const float2 bq = yb[u];
-        const double br = bq.x, bi = bq.y;
-        re[u] = ar * br + ai * bi;
-        im[u] = ai * br - ar * bi;
-      };
-#pragma unroll
-      for (int u = 0; u < 8; ++u) form(u);
-      if (j0 == ri) n2 += re[0];               // the diagonal item: |y_i|^2
-      static_for<0, K>([&](auto KI) {
-        constexpr int k = decltype(KI)::value;
-        if (class_on(mask, k)) fma_bcast_run(q[k][0], q[k][1], ccur[k], re, im, cnt);
-      });
-      j0 += 8;
-      if (j0 >= D) {                           // next row
-        ++ri;
-        j0 = ri;
-        if (ri < D) {
-          const float2 a = yrow[ri];
-          ar = a.x;
-          ai = a.y;
-        }
-      }
+  // The masks of the tiles (final pass: those of this wavefront's frames), 0 behind the last; the one after the next live tile is
+  // requested with the frames of the next.  live_tile: from `tile` with mask m on, the first that has an active class.
+  auto mask_of = [&](int tile) {
+    const unsigned m = mrow[tile < tile_hi ? tile : tile_lo];
+    return tile >= tile_hi ? 0u : FINAL ? m & (0xffu << (8 * wave)) : m;
+  };
+  auto live_tile = [&](int tile, unsigned& m) {
+    while (m == 0u && tile < tile_hi) m = mask_of(++tile);
+    return tile;
+  };
+  unsigned mq = tile_lo < tile_hi ? mask_of(tile_lo) : 0u;
+  int tile = live_tile(tile_lo, mq);
+  if (tile < tile_hi) {
+    LargeFrames<NB> frames;
+    frames.request(Yrow, abrow, tile * kWave + 16 * wave + n, T, D, g);
+    // W comes from memory tile by tile, kRing tiles ahead of its use, across the classes (behind the last class: the same
+    // again) and from one tile of frames to the next: a register set is refilled when its products have been issued
+    constexpr int kRing = NB == 4 ? 5 : NB == 3 && K <= 6 && !FINAL ? 6 : 3;
+    static_assert(NT % kRing == 0, "a class starts with the first register set");
+    double2v w[kRing][2];
+    auto fetch = [&](double2v (&dst)[2], const double* __restrict__ c, int tl) {
+      dst[0] = *reinterpret_cast<const double2v*>(c + 256 * tl);
+      dst[1] = *reinterpret_cast<const double2v*>(c + 256 * tl + 128);
     };
-    {
-      int g = 0;
-      for (; g + 1 < groups; g += 2) {
-        group(ca, cb, g);
-        group(cb, ca, g + 1);
+    auto fetch_first = [&](unsigned m) {                    // the first tiles of the first class of this wavefront's frames
+      const unsigned own = (m >> (8 * wave)) & kmask;
+      const double* __restrict__ c = cf + (long)(own != 0u ? __builtin_ctz(own) : 0) * large_coef(NB);
+      static_for<0, kRing>([&](auto TI) { fetch(w[TI.value], c, TI.value); });
+    };
+    if (cf) fetch_first(mq);
+    int buf = 0;
+    unsigned mnext = mask_of(tile + 1);
+    for (;;) {
+      double* __restrict__ sW = sBuf + buf * kBuf;          // [K][64] weights
+      double* sT = sW + K * kWave;                          // [64][P]
+      // [K + 1][16 frames][4 lane rows]: the lane rows' parts of the q and (last) of |y|^2; where the wavefront's frames go after
+      static_assert((K + 1) * kWave <= 16 * P, "a wavefront's rows must hold the parts");
+      double* sQ = FINAL ? sBuf + wave * (K + 1) * kWave : sT + 16 * wave * P;
+      const int t = tile * kWave + 16 * wave + n;
+      const unsigned live = (mq >> (8 * wave)) & kmask;     // classes of this wavefront's 16 frames
+      const int next = live_tile(tile + 1, mnext);
+      double u[NB][4];
+      unsigned abits;
+      frames.convert(u, abits, t, T, D, g);
+      if constexpr (!FINAL) {
+        // the next tile's frames and the masks of the one after (behind the last tile: the same again, so that the loads need
+        // no branch)
+        frames.request(Yrow, abrow, (next < tile_hi ? next : tile) * kWave + 16 * wave + n, T, D, g);
+        frames.mask = mvec[next + 1 < tile_hi ? next + 1 : tile];
       }
-      if (g < groups) group(ca, cb, g);
-    }
-    // posterior over the active classes: pi_k / det B_k * q_k^-D, mantissa / exponent form
-    const double n2c = fmax(n2, GSS_EPS_NORM_SQ);
-    const double qfloor = GSS_EPS_Q * n2c;
-    double rq[K], mant[K];
-    int ex[K];
-    int emax = -(1 << 28);
-    static_for<0, K>([&](auto KI) {
-      constexpr int k = KI.value;
-      rq[k] = 0.0;
-      mant[k] = 0.0;
-      ex[k] = -(1 << 28);
-      if (class_on(mask, k)) {
-        const bool a = (abits >> k) & 1u;
-        rq[k] = rcp_f64(fmax(q[k][0] + q[k][1], qfloor));
-        const double u = rq[k] * n2c;
-        const double mu = __builtin_amdgcn_frexp_mant(u);
-        const int eu = __builtin_amdgcn_frexp_exp(u);
-        const double pw = ipow_rt(mu, D);            // >= 2^-32
-        mant[k] = cm[k] * __builtin_amdgcn_frexp_mant(pw);
-        ex[k] = a ? ce[k] + eu * D + __builtin_amdgcn_frexp_exp(pw) : -(1 << 28);
-        emax = ex[k] > emax ? ex[k] : emax;
-      }
-    });
-    double v[K], Z = 0.0;
+      double n2 = 0.0;
+      if (live != 0u) {
+        // ---- E-step: q_k = |W_k y|^2 of the lane's frame (the same in the four lane rows) ----
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      int de = ex[k] - emax;
-      de = de < -1100 ? -1100 : de;
-      v[k] = ((abits >> k) & 1u) ? ldexp(mant[k], de) : 0.0;
-      Z += v[k];
-    }
-    const double rz = Z > 0.0 ? rcp_f64(Z) : 0.0;
-    if (FINAL) {
-      if (valid && !(n2 >= GSS_EPS_NORM_SQ)) atomicOr(status, GSS_STATUS_ZERO_FRAME);
-      static_for<0, K>([&](auto KI) {
-        constexpr int k = KI.value;
-        if (class_on(mask, k)) {
-          if (t < Tmax) gamma[(((long)s * K + k) * F + f) * Tmax + t] = (float)(v[k] * rz);
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) n2 = fma(u[b][e], u[b][e], n2);
+        sQ[K * kWave + 4 * n + g] = n2;
+        if (cf) {
+          __builtin_amdgcn_s_setprio(0);
+          unsigned left = live;
+          int k = __builtin_ctz(left);
+          const double* __restrict__ ck = cf + (long)k * large_coef(NB);
+          while (left != 0u) {
+            left &= left - 1u;
+            const int kn = left != 0u ? __builtin_ctz(left) : k;
+            const double* __restrict__ cn = cf + (long)kn * large_coef(NB);
+            double qs = 0.0;
+            double4v z[2];
+            static_for<0, NB>([&](auto II) {
+              constexpr int i = II.value;
+              z[i & 1] = double4v{0.0, 0.0, 0.0, 0.0};
+              static_for<0, i + 1>([&](auto JI) {
+                constexpr int j = JI.value, tl = i * (i + 1) / 2 + j, ta = tl + kRing;
+                const double2v w0 = w[tl % kRing][0], w1 = w[tl % kRing][1];
+                z[i & 1] = mfma_f64(w0.x, u[j][0], z[i & 1]);
+                z[i & 1] = mfma_f64(w0.y, u[j][1], z[i & 1]);
+                z[i & 1] = mfma_f64(w1.x, u[j][2], z[i & 1]);
+                z[i & 1] = mfma_f64(w1.y, u[j][3], z[i & 1]);
+                __builtin_amdgcn_sched_barrier(0);          // (the scheduler would put all of a class's loads in one place)
+                fetch(w[tl % kRing], ta < NT ? ck : cn, ta < NT ? ta : ta - NT);
+                if constexpr (i > 0 && j == 0) {            // the row before: its products are done by now
+#pragma unroll
+                  for (int v = 0; v < 4; ++v) qs = fma(z[(i - 1) & 1][v], z[(i - 1) & 1][v], qs);
+                }
+              });
+            });
+#pragma unroll
+            for (int v = 0; v < 4; ++v) qs = fma(z[(NB - 1) & 1][v], z[(NB - 1) & 1][v], qs);
+            sQ[k * kWave + 4 * n + g] = qs;                 // (added up by the reader: no chain of lane permutes per class)
+            k = kn;
+            ck = cn;
+          }
+          __builtin_amdgcn_s_setprio(2);
         }
-      });
-      wave_lds_sync();                       // the tile is overwritten by the next iteration
-      continue;
+        wave_lds_sync();
+      }
+      if constexpr (FINAL) {
+        if (next < tile_hi) {
+          frames.request(Yrow, abrow, next * kWave + 16 * wave + n, T, D, g);
+          frames.mask = mvec[next + 1 < tile_hi ? next + 1 : next];
+          if (cf) fetch_first(mnext);
+        }
+      }
+      if (live != 0u) {
+        // ---- posterior over the active classes: pi_k / det B_k * q_k^-D, mantissa / exponent form.  Lane row g takes the
+        // live classes number g and g + 4; the largest exponent and the sum go over the lane rows. ----
+        auto parts = [&](int k) {
+          const double2 x0 = *reinterpret_cast<const double2*>(sQ + k * kWave + 4 * n);
+          const double2 x1 = *reinterpret_cast<const double2*>(sQ + k * kWave + 4 * n + 2);
+          return (x0.x + x0.y) + (x1.x + x1.y);
+        };
+        n2 = parts(K);
+        const double n2c = fmax(n2, GSS_EPS_NORM_SQ);
+        const double qfloor = GSS_EPS_Q * n2c;
+        double rq[kRows], v[kRows];
+        int kc[kRows], ex[kRows], emax = -(1 << 28);
+        unsigned left = live;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          const unsigned l1 = left & (left - 1u), l2 = l1 & (l1 - 1u), l3 = l2 & (l2 - 1u);
+          const unsigned mine = g == 0 ? left : g == 1 ? l1 : g == 2 ? l2 : l3;
+          kc[r] = mine != 0u ? __builtin_ctz(mine) : -1;
+          v[r] = 0.0;
+          rq[r] = 0.0;
+          ex[r] = -(1 << 28);
+          if (r == 0 || left != 0u) {
+            const int k = kc[r] < 0 ? 0 : kc[r];
+            const double2 c = sC[k];
+            const double q = cf ? parts(mine != 0u ? k : __builtin_ctz(live)) : n2;
+            rq[r] = rcp_f64(fmax(q, qfloor));
+            const double x = rq[r] * n2c;
+            const double mu = __builtin_amdgcn_frexp_mant(x);
+            const int eu = __builtin_amdgcn_frexp_exp(x);
+            const double pw = ipow_rt(mu, D);              // >= 2^-32
+            v[r] = c.x * __builtin_amdgcn_frexp_mant(pw);
+            const bool a = mine != 0u && ((abits >> k) & 1u);
+            ex[r] = a ? (int)c.y + eu * D + __builtin_amdgcn_frexp_exp(pw) : -(1 << 28);
+            emax = ex[r] > emax ? ex[r] : emax;
+          }
+          left = l3 & (l3 - 1u);
+        }
+        emax = max_rows_i32(emax);
+        double Z = 0.0;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          int de = ex[r] - emax;
+          de = de < -1100 ? -1100 : de;
+          v[r] = ex[r] > -(1 << 28) ? ldexp(v[r], de) : 0.0;
+          Z += v[r];
+        }
+        Z = sum_rows_f64(Z);
+        const double rz = Z > 0.0 ? rcp_f64(Z) : 0.0;
+        if constexpr (FINAL) {
+          if (g == 0 && t < T && !(n2 >= GSS_EPS_NORM_SQ)) atomicOr(status, GSS_STATUS_ZERO_FRAME);
+#pragma unroll
+          for (int r = 0; r < kRows; ++r)
+            if (kc[r] >= 0 && t < Tmax) grow[kc[r] * gk + t] = (float)(v[r] * rz);
+          wave_lds_sync();                               // the parts have been read
+        } else {
+#pragma unroll
+          for (int r = 0; r < kRows; ++r)
+            if (kc[r] >= 0) {
+              const double gm = v[r] * rz;
+              sN[(wave * K + kc[r]) * 16 + n] += gm;
+              sW[kc[r] * kWave + 16 * wave + n] = gm * rq[r];
+            }
+        }
+      }
+      if constexpr (!FINAL) {
+        wave_lds_sync();                                 // the parts have been read
+        double* dst = sT + (16 * wave + n) * P + 4 * g;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          *reinterpret_cast<double2*>(dst + 16 * b) = make_double2(u[b][0], u[b][1]);
+          *reinterpret_cast<double2*>(dst + 16 * b + 2) = make_double2(u[b][2], u[b][3]);
+        }
+        __syncthreads();                                 // every frame and its weights are in place
+        if (cf) fetch_first(next < tile_hi ? mnext : mq);
+        __builtin_amdgcn_s_setprio(0);
+        accumulate_large<NB, K>(sT, sW, role, mq, lane, acc);
+        __builtin_amdgcn_s_setprio(2);
+        buf ^= 1;
+      }
+      if (next >= tile_hi) break;
+      tile = next;
+      mq = mnext;
+      mnext = tile + 1 < tile_hi ? __builtin_amdgcn_readfirstlane(frames.mask) : 0u;
+      if constexpr (FINAL) mnext &= 0xffu << (8 * wave);
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const double g = v[k] * rz;
-      nacc[k] += g;
-      sW[lane * WS + k] = g * rq[k];
+  }
+  if constexpr (!FINAL) {
+    reduce_large<NB, K, large_red_classes(K, NB)>(acc, role, sBuf, part + (long)blockIdx.x * (2 * K) * num_items(D), D, lane);
+    // class counts: the 64 frame columns in their order (written before the barriers of the reduction)
+    if (threadIdx.x < K) {
+      double sum = 0.0;
+      for (int x = 0; x < kWave; ++x) sum += sN[((x >> 4) * K + threadIdx.x) * 16 + (x & 15)];
+      npart[(long)blockIdx.x * K + threadIdx.x] = sum;
     }
-    wave_lds_sync();
-    // ---- phase 2 ----
-    accumulate_items<K, NR>(sY, sW, RS, WS, oi, oj, mask, acc);
-    wave_lds_sync();
-  }
-  if (FINAL) return;
-
-  double* __restrict__ red = reinterpret_cast<double*>(lds_raw);
-  reduce_items<K, NR>(acc, red, part + (long)blockIdx.x * M * K * 2, M, lane, wave);
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double nv = nacc[k];
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) nv += __shfl_xor(nv, off, kWave);
-    nacc[k] = nv;
-  }
-  __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) red[wave * K + k] = nacc[k];
-  }
-  __syncthreads();
-  if (threadIdx.x < K) {
-    double sum = 0.0;
-    for (int w = 0; w < kLargeWaves; ++w) sum += red[w * K + threadIdx.x];
-    npart[(long)blockIdx.x * K + threadIdx.x] = sum;
   }
 }
 
@@ -444,9 +615,11 @@ __device__ __forceinline__ void gauss_jordan_large(double (*sMr)[33], double (*s
 // ----------------------------------------------------------------------------------------------
 // Factor kernel, 9 <= D <= 32: one wavefront per (segment, frequency, class), a workgroup = the K classes of a
 // (segment, frequency).  The D x D matrix sits in the registers of the wavefront: lane (a, b) = (lane / 8,
-// lane % 8) holds the BS x BS block of rows a BS .. and columns b BS .. (BS = ceil(D / 8); rows and columns
-// beyond D are those of the identity and stay so).  In-place Gauss-Jordan sweeps without pivoting (B is Hermitian
-// positive definite after the loading; the product of the pivots is det B): the lanes that hold pivot row p and
+// lane % 8) holds the BS x BS block of rows a BS .. and columns b BS .. (BS = ceil(D / 8) = NB; rows and columns
+// beyond D are those of the identity and stay so).  Elimination without pivoting (B is Hermitian positive definite after
+// the loading; the product of the pivots is det B), in place: sweep p subtracts row p times a_ip / pivot from the rows i > p
+// and leaves -a_ip / pivot in column p, so that the strictly lower triangle ends as that of M = the inverse of the unit
+// lower factor, and the diagonal holds the pivots d.  W = d^-1/2 M.  The lanes that hold pivot row p and
 // pivot column p publish them in the wavefront's LDS, every lane reads back the entries of its own columns and
 // rows.  Nothing is shared between wavefronts, so there is no workgroup barrier.
 // ----------------------------------------------------------------------------------------------
@@ -457,7 +630,7 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
     int D, int K, ChunkMap cmap, int weight_mode) {
   constexpr int W = 8 * BS;                                // padded matrix size
   __shared__ double sPiv[GSS_MAX_K][4][W];                 // per wavefront: pivot row (re, im), pivot column (re, im)
-  extern __shared__ __attribute__((aligned(16))) double sCoef[];   // per wavefront: the class's coef_pitch(D) coefficients
+  extern __shared__ __attribute__((aligned(16))) double sItems[];   // per wavefront: the class's packed sums, 2 M doubles
   const int lane = threadIdx.x & (kWave - 1);
   const int k = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const long sf = blockIdx.x;
@@ -477,29 +650,46 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
   double Ntot = 0.0;
   for (int kk = 0; kk < K; ++kk) Ntot += __shfl(nl, kk, kWave);
 
-  // the lane's block of R_k = sum over the chunks (in chunk order) of the packed partial sums; entry (i, j) with
-  // i > j is the conjugate of item (j, i)
+  // R_k = sum over the chunks (in chunk order) of the packed partial sums: as one contiguous run per chunk, kFly of them in
+  // flight, into the wavefront's LDS, then the lane's block from there; entry (i, j) with i > j is the conjugate of item (j, i)
   double mr[BS][BS], mi[BS][BS];
-  int item[BS][BS];
+  {
+    constexpr int kRun = (W * (W + 1) / 2 + kWave - 1) / kWave, kFly = BS == 4 ? 2 : 4;
+    double2* __restrict__ sP = reinterpret_cast<double2*>(sItems) + k * M;
+    const double2* __restrict__ pc = reinterpret_cast<const double2*>(part) + (slot0 * K + k) * (long)M;
+    double2 sum[kRun];
 #pragma unroll
-  for (int r = 0; r < BS; ++r)
+    for (int x = 0; x < kRun; ++x) sum[x] = make_double2(0.0, 0.0);
+    for (int c0 = 0; c0 < C; c0 += kFly) {
+      double2 v[kFly][kRun];
 #pragma unroll
-    for (int c = 0; c < BS; ++c) {
-      const int i = a * BS + r, j = b * BS + c;
-      const int lo = i < j ? i : j, hi = i < j ? j : i;
-      item[r][c] = (hi < D) ? item_index(lo, hi, D) : 0;
-      mr[r][c] = 0.0;
-      mi[r][c] = 0.0;
+      for (int c = 0; c < kFly; ++c)
+#pragma unroll
+        for (int x = 0; x < kRun; ++x) {
+          v[c][x] = make_double2(0.0, 0.0);
+          if (c0 + c < C && lane + kWave * x < M) v[c][x] = pc[(long)(c0 + c) * K * M + lane + kWave * x];
+        }
+#pragma unroll
+      for (int c = 0; c < kFly; ++c)
+#pragma unroll
+        for (int x = 0; x < kRun; ++x) {
+          sum[x].x += v[c][x].x;
+          sum[x].y += v[c][x].y;
+        }
     }
-  for (int ch = 0; ch < C; ++ch) {
-    const double* __restrict__ pc = part + ((slot0 + ch) * (long)M * K + k) * 2;
+#pragma unroll
+    for (int x = 0; x < kRun; ++x)
+      if (lane + kWave * x < M) sP[lane + kWave * x] = sum[x];
+    wave_lds_sync();
 #pragma unroll
     for (int r = 0; r < BS; ++r)
 #pragma unroll
       for (int c = 0; c < BS; ++c) {
-        const double2 v = *reinterpret_cast<const double2*>(pc + (long)item[r][c] * K * 2);
-        mr[r][c] += v.x;
-        mi[r][c] += v.y;
+        const int i = a * BS + r, j = b * BS + c;
+        const int lo = i < j ? i : j, hi = i < j ? j : i;
+        const double2 v = sP[hi < D ? item_index(lo, hi, D) : 0];
+        mr[r][c] = v.x;
+        mi[r][c] = v.y;
       }
   }
   double trl = 0.0;
@@ -568,75 +758,153 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
         dete += __builtin_amdgcn_frexp_exp(detm);
         detm = __builtin_amdgcn_frexp_mant(detm);
         const double rp = rcp_f64(piv);
-        // Every entry takes m - (column entry)(row entry) / pivot.  With pivot - 1 in place of the column entry
-        // of the pivot row this gives (row entry) / pivot there, and with pivot + 1 in place of the row entry of
-        // the pivot column it gives -(column entry) / pivot there; the pivot itself becomes 1 / pivot.
-        const bool prow = a == pg, pcol = b == pg;
-        cr[pp] = prow ? piv - 1.0 : cr[pp];
-        cim[pp] = prow ? 0.0 : cim[pp];
+        // The rows below the pivot take m - (column entry)(row entry) / pivot; with pivot + 1 in place of the row entry of
+        // the pivot column this leaves -(column entry) / pivot there.
+        const bool pcol = b == pg;
         pr[pp] = pcol ? piv + 1.0 : pr[pp];
         pim[pp] = pcol ? 0.0 : pim[pp];
+#pragma unroll
+        for (int r = 0; r < BS; ++r) {
+          const bool below = a > pg || (a == pg && r > pp);
+          cr[r] = below ? cr[r] * rp : 0.0;
+          cim[r] = below ? cim[r] * rp : 0.0;
+        }
 #pragma unroll
         for (int r = 0; r < BS; ++r)
 #pragma unroll
           for (int c = 0; c < BS; ++c) {
             const double air = cr[r], aii = cim[r], apr = pr[c], api = pim[c];
-            mr[r][c] -= (air * apr - aii * api) * rp;
-            mi[r][c] -= (air * api + aii * apr) * rp;
+            mr[r][c] -= air * apr - aii * api;
+            mi[r][c] -= air * api + aii * apr;
           }
-        if (prow && pcol) { mr[pp][pp] = rp; mi[pp][pp] = 0.0; }
       }
     });
   }
 
-  // coefficients of <A, y y^H> over the items, A = the Hermitian part of the computed inverse: the diagonal
-  // entry, and A_ij + conj(A_ji) for i < j (not 2 A_ij: rounding leaves the computed inverse slightly
-  // non-Hermitian, and for an ill-conditioned B, whose inverse has entries of 1e6, one triangle mirrored puts a
-  // relative error of up to 1e-4 into the quadratic forms of the class's own frames, the Hermitian part 1e-10).
-  // The two triangles meet in the wavefront's LDS: the owners of the upper triangle write, then the owners of the
-  // lower triangle add their conjugates, and the coefficients leave in the pass kernel's layout as one contiguous run.
-  const int CP = coef_pitch(D);
-  double* __restrict__ cf = coef + (sf * K + k) * (long)CP;
-  double* __restrict__ sCo = sCoef + (long)k * CP;
-  for (int x = lane; x < CP; x += kWave) sCo[x] = 0.0;     // the padding of the groups stays zero
+  // W in the pass kernel's layout: the entry (i, j) = w of a tile is [[re, -im], [im, re]] of its real form, and these four are
+  // neighbours there.  Zero above the diagonal and beyond D.
+  if (a == b) {
+#pragma unroll
+    for (int r = 0; r < BS; ++r) rowR[a * BS + r] = 1.0 / sqrt(fmax(mr[r][r], 1e-300));
+  }
   wave_lds_sync();
-  int cpos[BS][BS];
+  double* __restrict__ cf = coef + (sf * K + k) * (long)large_coef(BS);
 #pragma unroll
-  for (int r = 0; r < BS; ++r)
-#pragma unroll
-    for (int c = 0; c < BS; ++c) {
-      const int i = a * BS + r, j = b * BS + c;
-      const int lo = i < j ? i : j, hi = i < j ? j : i;
-      cpos[r][c] = (hi < D) ? coef_pos(lo, hi, D) : 0;
-    }
-#pragma unroll
-  for (int r = 0; r < BS; ++r)
+  for (int r = 0; r < BS; ++r) {
+    const int i = a * BS + r;
+    const double ds = rowR[i];
 #pragma unroll
     for (int c = 0; c < BS; ++c) {
-      const int i = a * BS + r, j = b * BS + c;
-      if (i <= j && j < D) *reinterpret_cast<double2*>(sCo + cpos[r][c]) = make_double2(mr[r][c], i == j ? 0.0 : mi[r][c]);
-    }
-  wave_lds_sync();
-#pragma unroll
-  for (int r = 0; r < BS; ++r)
-#pragma unroll
-    for (int c = 0; c < BS; ++c) {
-      const int i = a * BS + r, j = b * BS + c;
-      if (i > j && i < D) {                                // entry (i, j) of the lower triangle: item (j, i)
-        double2 v = *reinterpret_cast<double2*>(sCo + cpos[r][c]);
-        v.x += mr[r][c];
-        v.y -= mi[r][c];
-        *reinterpret_cast<double2*>(sCo + cpos[r][c]) = v;
+      const int j = b * BS + c;
+      const int bi = i >> 3, bj = j >> 3;
+      if (bj <= bi) {
+        const bool in = i < D && j <= i;
+        const double re = in ? (i == j ? ds : mr[r][c] * ds) : 0.0;
+        const double im = in && i != j ? mi[r][c] * ds : 0.0;
+        double* __restrict__ dst = cf + 256 * (bi * (bi + 1) / 2 + bj) + 128 * (j & 1) + 2 * (16 * ((j & 7) >> 1) + 2 * (i & 7));
+        *reinterpret_cast<double2*>(dst) = make_double2(re, -im);
+        *reinterpret_cast<double2*>(dst + 2) = make_double2(im, re);
       }
     }
-  wave_lds_sync();
-  for (int x = lane; x < CP; x += kWave) cf[x] = sCo[x];
+  }
   if (lane == 0) {
     const double pi = weight_mode == 1 ? Nk / fmax(Ntot, GSS_EPS_N) : 1.0 / (double)K;
     const double cst = fmax(pi, GSS_EPS_PI) / detm;
     cmant[sf * K + k] = __builtin_amdgcn_frexp_mant(cst);
     cexp[sf * K + k] = __builtin_amdgcn_frexp_exp(cst) - dete;
   }
+}
+
+// Cooperative, coalesced copy of one tile of frames [t0, t0 + 64) of a (segment, frequency) row into the
+// wavefront's LDS tile sY[frame][D] (float2, row stride RS float2); frames at or beyond T become zero.
+// The tile is one contiguous run of 64 D values in memory; lane l copies values l, l + 64, ... (D of them).  Their
+// frame and channel are stepped without divisions, and the loads go out six at a time before the first of them
+// is stored (one at a time, every value would wait out a full memory latency).
+__device__ __forceinline__ void load_tile(const float2* __restrict__ Yrow, int t0, int T, int D, int RS,
+                                          float2* __restrict__ sY, int lane) {
+  constexpr int kBatch = 12;
+  const int rstep = kWave / D, cstep = kWave % D;          // frame and channel advance per 64 values
+  int r = lane / D, c = lane - r * D;
+  const float2* __restrict__ src = Yrow + (long)t0 * D + lane;
+  const int rows = T - t0;                                   // frames of the tile that exist (may exceed 64)
+  for (int i0 = 0; i0 < D; i0 += kBatch) {
+    float2 v[kBatch];
+    int off[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      v[u] = make_float2(0.f, 0.f);
+      off[u] = r * RS + c;
+      if (i0 + u < D) {
+        if (r < rows) v[u] = src[(long)(i0 + u) * kWave];
+        c += cstep;
+        r += rstep;
+        if (c >= D) { c -= D; ++r; }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (i0 + u < D) sY[off[u]] = v[u];
+  }
+}
+
+// The weighted sums of the lane's NR items over the 64 frames of the tile, for the classes of `mask` (wave-uniform; the
+// weights of the other classes are zero in every frame of the tile).
+template <int KW, int NR>
+__device__ __forceinline__ void accumulate_items(const float2* __restrict__ sY, const double* __restrict__ sW, int RS,
+                                                 int WS, const int (&oi)[NR], const int (&oj)[NR], unsigned mask,
+                                                 double (&acc)[NR][2][KW]) {
+#pragma unroll 1
+  for (int r = 0; r < kWave; ++r) {
+    double w[KW];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
+    double re[NR], im[NR];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+      const float2 a = sY[r * RS + oi[n]];
+      const float2 b = sY[r * RS + oj[n]];
+      const double ar = a.x, ai = a.y, br = b.x, bi = b.y;
+      re[n] = ar * br + ai * bi;          // Re(y_i conj(y_j)); |y_i|^2 on the diagonal
+      im[n] = ai * br - ar * bi;          // Im(y_i conj(y_j)); 0 on the diagonal
+    }
+    static_for<0, KW>([&](auto KI) {
+      constexpr int k = KI.value;
+      if (class_on(mask, k)) {
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+          acc[n][0][k] = fma(w[k], re[n], acc[n][0][k]);
+          acc[n][1][k] = fma(w[k], im[n], acc[n][1][k]);
+        }
+      }
+    });
+  }
+}
+
+// Sums the accumulators of the workgroup's wavefronts through LDS and writes out[m][k][2].
+template <int KW, int NR>
+__device__ __forceinline__ void reduce_items(double (&acc)[NR][2][KW], double* __restrict__ red, double* __restrict__ out,
+                                             int M, int lane, int wave) {
+  __syncthreads();
+  for (int w = 0; w < kLargeWaves; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int n = 0; n < NR; ++n) {
+        const int m = lane + kWave * n;
+        if (m < M) {
+#pragma unroll
+          for (int k = 0; k < KW; ++k)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+              double* dst = &red[((long)m * KW + k) * 2 + p];
+              *dst = (w == 0) ? acc[n][p][k] : *dst + acc[n][p][k];
+            }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  const int total = M * KW * 2;
+  for (int x = threadIdx.x; x < total; x += kWave * kLargeWaves) out[x] = red[x];
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -844,83 +1112,72 @@ long large_slots(const gss_ctx* ctx, Kern kern, int lds_bytes) {
   return (long)ctx->num_cu * per_cu;
 }
 
-template <int K, int NR>
+template <int K, int NB>
 int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
                  int D, int iters, int weight_mode, float* gamma, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int M = num_items(D);
-  const LargePlan p = plan_large(D, K);
-  if (hipFuncSetAttribute((const void*)em_pass_large<K, NR, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          p.lds_bytes) != hipSuccess ||
-      hipFuncSetAttribute((const void*)em_pass_large<K, NR, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          p.lds_bytes) != hipSuccess)
+  constexpr int lds_acc = large_lds_doubles(K, NB, false) * (int)sizeof(double);
+  constexpr int lds_fin = large_lds_doubles(K, NB, true) * (int)sizeof(double);
+  if (hipFuncSetAttribute((const void*)em_pass_large<K, NB, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          lds_acc) != hipSuccess)
     return GSS_EHIP;
-  // the factor kernel stages every class's coefficients in LDS (up to 80 KB: 8 classes of 32 channels)
-  const int factor_lds = K * coef_pitch(D) * (int)sizeof(double);
-  const void* factor_kern = D <= 16 ? (const void*)em_factor_large<2> : D <= 24 ? (const void*)em_factor_large<3>
-                                                                                 : (const void*)em_factor_large<4>;
-  if (hipFuncSetAttribute(factor_kern, hipFuncAttributeMaxDynamicSharedMemorySize, factor_lds) != hipSuccess) return GSS_EHIP;
+  // the factor kernel adds the chunks of every class in LDS (up to 68 KB: 8 classes of 32 channels); one limit for every call
+  const int factor_lds = K * M * 2 * (int)sizeof(double);
+  constexpr int factor_max = K * (8 * NB) * (8 * NB + 1) * (int)sizeof(double);
+  if (hipFuncSetAttribute((const void*)em_factor_large<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, factor_max) != hipSuccess)
+    return GSS_EHIP;
   const int tiles = (Tmax + kWave - 1) / kWave;
-  const long slots = large_slots(ctx, em_pass_large<K, NR, false>, p.lds_bytes);
-  const ChunkMap acc_map = plan_chunk_map(slots, n_sf, tiles, kLargeWaves, 0, true);
-  const ChunkMap fin_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NR, true>, p.lds_bytes), n_sf, tiles,
-                                          kLargeWaves, 0, true);
+  const ChunkMap acc_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, false>, lds_acc), n_sf, tiles, 1, 0, true);
+  const ChunkMap fin_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, true>, lds_fin), n_sf, tiles, 1, 0, true);
   const long wgs_acc = chunk_map_wgs(acc_map, n_sf), wgs_fin = chunk_map_wgs(fin_map, n_sf);
   if (wgs_acc > 0x7fffffffL || wgs_fin > 0x7fffffffL || n_sf * K > 0x7fffffffL) return GSS_EUNSUPPORTED;
   size_t o = 0;
-  const size_t off_coef = o;  o = gss_align_up(o + (size_t)n_sf * K * coef_pitch(D) * sizeof(double), 256);
+  const size_t off_coef = o;  o = gss_align_up(o + (size_t)n_sf * K * large_coef(NB) * sizeof(double), 256);
   const size_t off_cm = o;    o = gss_align_up(o + (size_t)n_sf * K * sizeof(double), 256);
   const size_t off_ce = o;    o = gss_align_up(o + (size_t)n_sf * K * sizeof(int32_t), 256);
   const size_t off_part = o;  o = gss_align_up(o + (size_t)wgs_acc * M * K * 2 * sizeof(double), 256);
   const size_t off_npart = o; o = gss_align_up(o + (size_t)wgs_acc * K * sizeof(double), 256);
   const size_t off_abyte = o; o = gss_align_up(o + (size_t)S * Tmax, 256);
-  const size_t off_tmask = o; o = gss_align_up(o + (size_t)S * tiles * sizeof(uint32_t), 256);
+  const size_t off_masks = o; o = gss_align_up(o + (size_t)S * tiles * sizeof(uint32_t), 256);
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
   int rc = gss_ensure_scratch(ctx, o);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   uint8_t* abyte = (uint8_t*)(base + off_abyte);
-  uint32_t* tmask = (uint32_t*)(base + off_tmask);
+  uint32_t* masks = (uint32_t*)(base + off_masks);
   double* coef = (double*)(base + off_coef);
   double* cm = (double*)(base + off_cm);
   int32_t* ce = (int32_t*)(base + off_ce);
   double* part = (double*)(base + off_part);
   double* npart = (double*)(base + off_npart);
   const dim3 block(kWave * kLargeWaves);
-  hipLaunchKernelGGL(em_init_coef_large, dim3(1024), dim3(256), 0, st, coef, cm, ce, D, K, n_sf);
-  hipLaunchKernelGGL(em_pack_activity, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
+  hipLaunchKernelGGL(em_pack_activity<true>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, masks, K,
                      Tmax, tiles);
   for (int it = 0; it < iters; ++it) {
     gss_profile_begin(ctx, 0, st);
-    hipLaunchKernelGGL((em_pass_large<K, NR, false>), dim3((unsigned)wgs_acc), block, p.lds_bytes, st, Y, abyte, tmask, T_len,
-                       coef, cm, ce, part, npart, (float*)nullptr, ctx->status, F, Tmax, D, acc_map, p.RS, p.tile_bytes);
+    hipLaunchKernelGGL((em_pass_large<K, NB, false>), dim3((unsigned)wgs_acc), block, lds_acc, st, Y, abyte, masks, T_len,
+                       it == 0 ? (const double*)nullptr : coef, cm, ce, part, npart, (float*)nullptr, ctx->status, F, Tmax, D,
+                       acc_map);
     gss_profile_end(ctx, 0, st);
     gss_profile_begin(ctx, 1, st);
-    if (D <= 16)
-      hipLaunchKernelGGL(em_factor_large<2>, dim3((unsigned)n_sf), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
-                         ctx->status, D, K, acc_map, weight_mode);
-    else if (D <= 24)
-      hipLaunchKernelGGL(em_factor_large<3>, dim3((unsigned)n_sf), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
-                         ctx->status, D, K, acc_map, weight_mode);
-    else
-      hipLaunchKernelGGL(em_factor_large<4>, dim3((unsigned)n_sf), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
-                         ctx->status, D, K, acc_map, weight_mode);
+    hipLaunchKernelGGL(em_factor_large<NB>, dim3((unsigned)n_sf), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
+                       ctx->status, D, K, acc_map, weight_mode);
     gss_profile_end(ctx, 1, st);
   }
-  hipLaunchKernelGGL((em_pass_large<K, NR, true>), dim3((unsigned)wgs_fin), block, p.lds_bytes, st, Y, abyte, tmask, T_len, coef,
-                     cm, ce, (double*)nullptr, (double*)nullptr, gamma, ctx->status, F, Tmax, D, fin_map, p.RS, p.tile_bytes);
+  hipLaunchKernelGGL((em_pass_large<K, NB, true>), dim3((unsigned)wgs_fin), block, lds_fin, st, Y, abyte, masks, T_len,
+                     iters == 0 ? (const double*)nullptr : coef, cm, ce, (double*)nullptr, (double*)nullptr, gamma, ctx->status,
+                     F, Tmax, D, fin_map);
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
 }
 
 template <int K>
-int dispatch_nr(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
+int dispatch_nb(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
                 int D, int iters, int weight_mode, float* gamma, hipStream_t st) {
-  const int nr = (num_items(D) + kWave - 1) / kWave;       // 1 .. 9
-  if (nr <= 3) return run_em_large<K, 3>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
-  if (nr <= 5) return run_em_large<K, 5>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
-  if (nr <= 7) return run_em_large<K, 7>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
-  return run_em_large<K, 9>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
+  if (D <= 16) return run_em_large<K, 2>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
+  if (D <= 24) return run_em_large<K, 3>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
+  return run_em_large<K, 4>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
 }
 
 template <int NR>
