@@ -31,7 +31,7 @@ struct gss_ctx {
   uint32_t* status;       // device, one word
   int num_cu;
   int64_t em_whole_min_problems;   // GSS_OPT_EM_WHOLE_MIN_PROBLEMS (< 0: default)
-  void* twiddles;         // device: exp(-2 pi i k / 1024), k = 0..512 (float2), filled by the first STFT/iSTFT call
+  void* twiddles;         // device: exp(-2 pi i k / 1024), k = 0..512, and the window (float2), filled by the first STFT/iSTFT call
   // optional per-kernel timing with HIP events (gss_profile_enable / gss_profile_get)
   int profile;
   hipEvent_t ev_start[GSS_PROFILE_KERNELS][GSS_PROFILE_SLOTS], ev_stop[GSS_PROFILE_KERNELS][GSS_PROFILE_SLOTS];

@@ -9,8 +9,9 @@
 // split step.  The 512-point transform is 8 x 8 x 8: one wavefront per transform, eight values per lane,
 // three passes of 8-point butterflies in registers with two exchanges through LDS in between (a radix-2
 // transform that lives in LDS is bound by LDS bandwidth: it moves every value through LDS nine times).
-// Twiddles come from one table exp(-2 pi i k / 1024), k = 0..512, evaluated in fp64 and rounded once; the
-// table is computed on the device by the first call of a context and copied into LDS by every workgroup.
+// Twiddles come from one table exp(-2 pi i k / 1024), k = 0..512, and the window from another, both evaluated in fp64 and
+// rounded once; the tables are computed on the device by the first call of a context, and every workgroup copies what it
+// reads per transform into LDS.
 //
 // Workgroup order: consecutive workgroup ids go to different XCDs (each with its own L2), so the id is
 // remapped such that every XCD walks a contiguous range of frames: neighbouring frames share three quarters
@@ -32,18 +33,29 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 
 constexpr int kXcds = 8;
 
-// table[k] = exp(-2 pi i k / 1024), k = 0 .. 512.
+// table[k] = exp(-2 pi i k / 1024), k = 0 .. 512; table[513 + n] = the periodic Hann window at the samples 2n and 2n + 1.
+constexpr int kTableSize = kH + 1 + kH;
+__device__ __forceinline__ float2* window_of(float2* table) { return table + kH + 1; }
+__device__ __forceinline__ const float2* window_of(const float2* table) { return table + kH + 1; }
 __global__ void twiddle_table_kernel(float2* __restrict__ table) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k > kH) return;
   double sn, cs;
   sincospi(-2.0 * (double)k / (double)kN, &sn, &cs);
   table[k] = make_float2((float)cs, (float)sn);
+  if (k < kH)
+    window_of(table)[k] = make_float2((float)(0.5 - 0.5 * cospi(4.0 * (double)k / (double)kN)),
+                                      (float)(0.5 - 0.5 * cospi((4.0 * (double)k + 2.0) / (double)kN)));
 }
 
-// LDS copy of the table, by the whole workgroup (the caller synchronises).
-__device__ __forceinline__ void fill_twiddles(float2* tw, const float2* __restrict__ table) {
-  for (int k = threadIdx.x; k <= kH; k += blockDim.x) tw[k] = table[k];
+// LDS copies of the first n twiddles and of the window times `scale`, by the whole workgroup (the caller synchronises).  The
+// window as a table of pairs: from the cosines among the twiddles it took two reads with four-way bank conflicts per pair.
+__device__ __forceinline__ void fill_tables(float2* tw, int n, float2* win, float scale, const float2* __restrict__ table) {
+  for (int k = threadIdx.x; k < n; k += blockDim.x) tw[k] = table[k];
+  for (int k = threadIdx.x; k < kH; k += blockDim.x) {
+    const float2 w = window_of(table)[k];
+    win[k] = make_float2(w.x * scale, w.y * scale);
+  }
 }
 
 // Work item of workgroup `id` out of `n` when the grid has kXcds * ceil(n / kXcds) workgroups: XCD x = id % 8
@@ -114,8 +126,8 @@ __device__ __forceinline__ void fft_lane_init(FftLane& c, const float2* tw, int 
   }
 }
 
-// Forward 512-point complex FFT by one wavefront.  In: v[r] = x[64 r + lane].  Out: the transform in natural
-// order in ex[0..511] (visible to the whole wavefront on return).  With n = 64 n1 + n2, k = k1 + 8 k2:
+// Forward 512-point complex FFT by one wavefront.  In: v[r] = x[64 r + lane].  Out: v[p] = the transform at k =
+// fft_bin(lane) + 64 p; the exchange buffer is free on return.  With n = 64 n1 + n2, k = k1 + 8 k2:
 //   pass 1 (lane = n2):            8-point DFT over n1, times W_512^(n2 k1)
 //   exchange: rows k1, columns n2 = 8 m1 + m0;   pass 2 (lane = (k1, m0)): DFT over m1, times W_64^(m0 p1)
 //   exchange: [k1][p1][m0], 9-float2 pitch;      pass 3 (lane = (k1, p1)): DFT over m0 -> k = k1 + 8 p1 + 64 p0
@@ -140,16 +152,8 @@ __device__ __forceinline__ void fft512(float2 (&v)[8], float2* ex, const FftLane
   for (int m0 = 0; m0 < 8; ++m0) v[m0] = ex[hi * kExStride + 9 * lo + m0];
   wave_sync();
   dft8(v);
-#pragma unroll
-  for (int p0 = 0; p0 < 8; ++p0) ex[hi + 8 * lo + 64 * p0] = v[p0];
-  wave_sync();
 }
-
-// Periodic Hann window at the samples 2n and 2n + 1.
-__device__ __forceinline__ float2 hann_pair(const float2* tw, int n) {
-  const int i0 = 2 * n, i1 = i0 + 1;                       // cos(2 pi i / 1024) is even around 512
-  return make_float2(0.5f - 0.5f * tw[i0 <= kH ? i0 : kN - i0].x, 0.5f - 0.5f * tw[i1 <= kH ? i1 : kN - i1].x);
-}
+__device__ __forceinline__ int fft_bin(int lane) { return (lane >> 3) + 8 * (lane & 7); }
 
 // Items of workgroup w of `wgs`: an even, contiguous share of n.
 __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (long)((unsigned long)w * (unsigned long)n / (unsigned long)wgs); }
@@ -161,10 +165,13 @@ __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (
 // the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and X[512 - k]), and the workgroup
 // writes a bin's values of the step as one run of memory (128 bytes for two units of 8 channels).
 //
-// Bound: latency.  Two workgroups per compute unit are resident, held there by 128 registers and, for two units, by LDS; each
-// has one unit of samples in flight.  At 128 registers 20 (two units) or 14 (one) are spilled to scratch memory, 84 or 60 bytes
-// per lane.  Ten minutes of 8 channels: 548 us = 2.8 TB/s (one workgroup per frame, 64-byte runs: 722 us; an even share of
-// consecutive frames per workgroup instead of turns: 583 us).
+// Bound: latency, with the LDS busy for some 40 % of the time (484 cycles per transform, 209 of them bank conflicts, before the
+// window had a table).  Two workgroups per compute unit are resident, held there by 128 registers and, for two units, by LDS;
+// each has one unit of samples in flight.  At 128 registers 14 (two units) or 10 (one) are spilled to scratch memory.  Ten
+// minutes of 8 channels: 504 us = 3.0 TB/s (window from the cosine table, a fifth round of the split loop for bin 256 alone:
+// 530 us; before that an even share of consecutive frames per workgroup instead of turns 583 us, one workgroup per frame,
+// 64-byte runs 722 us).  6000 frames of 8 channels 73 -> 63 us, 3000 frames of 12 channels 64 -> 59.  Three workgroups per
+// compute unit at 80 registers: 55 to 70 spilled, twice as slow.
 //
 // One unit per step for short calls (gss_stft): 8 channels 7.7, 10.7, 17.2 us at 130, 510, 1020 frames (two units 11.0, 12.5,
 // 17.0; one workgroup per frame 8.1, 11.2, 20.6).
@@ -178,7 +185,11 @@ template <int UNITS>
 __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
                                                                 const float2* __restrict__ table, int D, long N, int T,
                                                                 long n_items) {
-  __shared__ float2 tw[kH + 1];
+  // (two units: the split's half of the table only, so that two workgroups fit into a compute unit; the lanes' constants come
+  // from memory, one more latency at the start)
+  constexpr int kTw = UNITS == 1 ? kH + 1 : kH / 2;
+  __shared__ float2 tw[kTw];
+  __shared__ float2 win[kH];
   __shared__ float2 rows[UNITS * kFftWaves][kStftRow];
 
   const int lane = threadIdx.x & 63;
@@ -194,10 +205,6 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
   const long item1 = share_begin(xcd + 1, kXcds, n_items);
   long i = share_begin(xcd, kXcds, n_items) + j * per_step, block_end = i + per_step;
   if (i >= item1) return;
-  fill_twiddles(tw, table);
-  __syncthreads();
-  FftLane fc;
-  fft_lane_init(fc, tw, lane);
 
   const int my_frame = D <= 4 ? wave / D : 0, my_chan = D <= 4 ? wave % D : wave;
   // this wavefront's samples of unit u of the step at item i, channels from d0 on
@@ -226,6 +233,11 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
   };
   int d0 = 0;
   request(i, 0, 0);
+  fill_tables(tw, kTw, win, 1.f, table);
+  FftLane fc;
+  if constexpr (UNITS > 1) fft_lane_init(fc, table, lane);
+  __syncthreads();
+  if constexpr (UNITS == 1) fft_lane_init(fc, tw, lane);
   while (i < item1) {
     const int s = (int)((unsigned)i / (unsigned)T), t = (int)i - s * T;
     const long end = block_end < item1 ? block_end : item1;
@@ -245,7 +257,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
       float2 v[8];
 #pragma unroll
       for (int m = 0; m < 8; ++m) {
-        const float2 w = hann_pair(tw, lane + 64 * m);
+        const float2 w = win[lane + 64 * m];
         v[m] = make_float2(w.x * raw[m].x, w.y * raw[m].y);
       }
       if (u + 1 < UNITS) request(i, d0, u + 1);
@@ -254,17 +266,24 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
       if (my_frame < per_unit && fr < nf && dd < nd) {
         float2* __restrict__ Z = rows[u * kFftWaves + wave];
         fft512(v, Z, fc, lane);
+        const int kb = fft_bin(lane);
+#pragma unroll
+        for (int p = 0; p < 8; ++p) Z[kb + 64 * p] = v[p];
+        wave_sync();
         // split: with e = (Z[k] + conj Z[512-k]) / 2, o = (Z[k] - conj Z[512-k]) / 2, Z[512] = Z[0]:
-        // X[k] = e - i w^k o, X[512-k] = conj(e + i w^k o)
-        for (int k = lane; k <= kH / 2; k += 64) {
+        // X[k] = e - i w^k o, X[512-k] = conj(e + i w^k o); X[256] = conj Z[256]
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const int k = lane + 64 * m;
           const float2 zk = Z[k];
           const float2 zc = Z[(kH - k) & (kH - 1)];
           const float2 e = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y - zc.y));
           const float2 o = make_float2(0.5f * (zk.x - zc.x), 0.5f * (zk.y + zc.y));
           const float2 wo = cmul(tw[k], o);
           Z[k] = make_float2(e.x + wo.y, e.y - wo.x);
-          if (k < kH / 2) Z[kH - k] = make_float2(e.x - wo.y, -(e.y + wo.x));
+          Z[kH - k] = make_float2(e.x - wo.y, -(e.y + wo.x));
         }
+        if (lane == 0) Z[kH / 2].y = -Z[kH / 2].y;
       }
     }
     __syncthreads();
@@ -294,15 +313,18 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
 // 64-byte runs of X[bin][frame] and requested a step ahead.  The windowed frames stay in LDS; block th is the sum of
 // its four frames, oldest first, and the three blocks that the next step completes are carried over as partial sums.
 //
-// Bound: latency.  Two workgroups per compute unit, held there by 128 registers (2 of them spilled; the 44 KB of LDS would let
-// a third in), each with one step requested ahead: 128 segments of 18 s 290 us = 2.5 TB/s, X read once and x written once
-// (through frames in memory 1.9 GB instead of 0.74 GB: 618 us).  The spectrum, the transform and the windowed frame share one LDS row per wavefront.
+// Bound: latency, with the LDS busy for half of the time.  Two workgroups per compute unit, held there by 124 registers (its 48
+// KB of LDS would let a third in), each with one step requested ahead: 128 segments of 18 s 270 us = 2.7 TB/s, X read once and x
+// written once (window from the cosine table in a pass of its own through LDS: 291 us; through frames in memory, 1.9 GB
+// instead of 0.74 GB: 618 us).  The spectrum, the transform and the windowed frame share one LDS row per wavefront; the last
+// pass's values are windowed in registers.
 // ----------------------------------------------------------------------------------------------
 constexpr int kIstftMaxSteps = 8;
 __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* __restrict__ X, float* __restrict__ x,
                                                               const float2* __restrict__ table, long N, int T, int steps,
                                                               long wgs) {
   __shared__ float2 tw[kH + 1];
+  __shared__ float2 win[kH];                               // window / 1.5, irfft's 1 / N
   __shared__ float2 rows[kFftWaves][kRow];
   __shared__ float carry[3][kHop];
 
@@ -328,7 +350,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* 
     }
   };
   request(b0 - 3);
-  fill_twiddles(tw, table);
+  fill_tables(tw, kH + 1, win, 1.0f / (1.5f * (float)kN), table);
   for (int c = threadIdx.x; c < 3 * kHop; c += 64 * kFftWaves) carry[c / kHop][c % kHop] = 0.f;
   __syncthreads();
   FftLane fc;
@@ -361,12 +383,12 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* 
     }
     wave_sync();
     fft512(v, z, fc, lane);
-    const float scale = 1.0f / (1.5f * (float)kN);            // irfft 1/N, synthesis window / 1.5
+    // x[2n] = Re, x[2n+1] = -Im (undo the conjugate), windowed on the way to the row
+    const int nb0 = fft_bin(lane);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const int n = lane + 64 * m;
-      const float2 r = z[n], w = hann_pair(tw, n);             // x[2n] = Re, x[2n+1] = -Im (undo the conjugate)
-      z[n] = make_float2(r.x * w.x * scale, -r.y * w.y * scale);
+    for (int p = 0; p < 8; ++p) {
+      const float2 w = win[nb0 + 64 * p];
+      z[nb0 + 64 * p] = make_float2(v[p].x * w.x, -v[p].y * w.y);
     }
     __syncthreads();
     // block f0 + j: frames f0 + j - 3 .. f0 + j, frame f0 + q being row q
@@ -411,7 +433,7 @@ __global__ void copy_spectrum_kernel(const float2* __restrict__ X, float2* __res
 int get_twiddles(gss_ctx* ctx, hipStream_t st, const float2** out) {
   if (!ctx->twiddles) {
     void* p = nullptr;
-    if (hipMalloc(&p, (kH + 1) * sizeof(float2)) != hipSuccess) return GSS_ENOMEM;
+    if (hipMalloc(&p, kTableSize * sizeof(float2)) != hipSuccess) return GSS_ENOMEM;
     hipLaunchKernelGGL(twiddle_table_kernel, dim3((kH + 256) / 256), dim3(256), 0, st, (float2*)p);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
       (void)hipFree(p);
