@@ -600,6 +600,115 @@ __device__ __forceinline__ void factor_classes_in_wave(const double* __restrict_
   }
 }
 
+// The same for few channels, every class in one lane: lane k mod 8 has the packed matrix of class k in registers and eliminates
+// it alone, B = L diag(d) L^H, M = L^-1, B^-1 = M^H diag(1 / d) M (Hermitian by construction).  Nothing crosses lanes between
+// the reads of the sums and the writes of the coefficients.  Up to 4 channels its chain of dependent instructions is shorter
+// than that of the sweeps with a row per lane: one segment of 200 frames, 10 iterations, 2 channels and 3 classes 36.8 -> 32.6
+// us, 3 channels and 5 classes 62.0 -> 56.4, 24 segments of up to 700 frames, 4 channels and 5 classes 857 -> 805 us.
+constexpr int kLaneFactorMaxD = 4;
+template <int D, int K>
+__device__ __forceinline__ void factor_class_in_lane(const double* __restrict__ sR, const double* __restrict__ sN,
+                                                     double* __restrict__ sC, double* __restrict__ sCC, int le,
+                                                     int weight_mode, uint32_t* __restrict__ status) {
+  constexpr int E = D * D;
+  constexpr int R = coef_regs(D);
+  const int k = (le & 7) < K ? (le & 7) : K - 1;
+  const bool on = le < K;
+  double h[E], n[K];
+#pragma unroll
+  for (int e = 0; e < E; ++e) h[e] = sR[k * E + e];
+#pragma unroll
+  for (int c = 0; c < K; ++c) n[c] = sN[c];
+  const double Nk = sN[k];
+  double tr = 0.0, Ntot = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) tr += h[gss_packed_row(d, D)];
+#pragma unroll
+  for (int c = 0; c < K; ++c) Ntot += n[c];
+  const bool dead = !((double)D * tr > GSS_EPS_N * fmax(Nk, GSS_EPS_N));
+  const double sc = dead ? 0.0 : (double)D * rcp_f64(tr);
+  // upper triangle: hr/hi[i][j] = entry (i, j), i <= j
+  double hr[D][D], hi[D][D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    const int p = gss_packed_row(i, D);
+    hr[i][i] = (dead ? 1.0 : h[p] * sc) + GSS_DELTA;
+#pragma unroll
+    for (int j = i + 1; j < D; ++j) {
+      hr[i][j] = dead ? 0.0 : h[p + 1 + 2 * (j - i - 1)] * sc;
+      hi[i][j] = dead ? 0.0 : h[p + 2 + 2 * (j - i - 1)] * sc;
+    }
+  }
+  double det = 1.0, rd[D];
+  double lr[D][D], li[D][D];                            // unit lower factor, i > p; then its inverse
+#pragma unroll
+  for (int p = 0; p < D; ++p) {
+    double piv = hr[p][p];
+    if (!(piv > 1e-300)) {
+      piv = 1e-300;
+      if (on) atomicOr(status, GSS_STATUS_NONPD_B);
+    }
+    det *= piv;
+    rd[p] = rcp_f64(piv);
+#pragma unroll
+    for (int i = p + 1; i < D; ++i) {
+      lr[i][p] = hr[p][i] * rd[p];                      // conj(H_pi) / d_p
+      li[i][p] = -hi[p][i] * rd[p];
+#pragma unroll
+      for (int j = i; j < D; ++j) {
+        hr[i][j] -= lr[i][p] * hr[p][j] - li[i][p] * hi[p][j];
+        if (j > i) hi[i][j] -= lr[i][p] * hi[p][j] + li[i][p] * hr[p][j];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < D; ++c)
+#pragma unroll
+    for (int i = c + 1; i < D; ++i) {
+      double mr = lr[i][c], mi = li[i][c];
+#pragma unroll
+      for (int m = c + 1; m < i; ++m) {                 // (rows m < i of column c are the inverse's already)
+        mr += lr[i][m] * lr[m][c] - li[i][m] * li[m][c];
+        mi += lr[i][m] * li[m][c] + li[i][m] * lr[m][c];
+      }
+      lr[i][c] = -mr;
+      li[i][c] = -mi;
+    }
+  double* __restrict__ sCk = sC + k * (R * 16);
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    const int pi0 = gss_packed_row(i, D);
+#pragma unroll
+    for (int j = i; j < D; ++j) {
+      // entry (i, j) of the inverse: sum over p >= j of conj(M_pi) M_pj / d_p, M_jj = 1
+      double ar, ai = 0.0;
+      if (i == j) {
+        ar = rd[i];
+#pragma unroll
+        for (int p = i + 1; p < D; ++p) ar += (lr[p][i] * lr[p][i] + li[p][i] * li[p][i]) * rd[p];
+      } else {
+        ar = lr[j][i] * rd[j];
+        ai = -li[j][i] * rd[j];
+#pragma unroll
+        for (int p = j + 1; p < D; ++p) {
+          ar += (lr[p][i] * lr[p][j] + li[p][i] * li[p][j]) * rd[p];
+          ai += (lr[p][i] * li[p][j] - li[p][i] * lr[p][j]) * rd[p];
+        }
+      }
+      if (on) {
+        if (i == j) {
+          sCk[pi0] = ar;
+        } else {
+          sCk[pi0 + 1 + 2 * (j - i - 1)] = 2.0 * ar;
+          sCk[pi0 + 2 + 2 * (j - i - 1)] = 2.0 * ai;
+        }
+      }
+    }
+  }
+  const double pi_k = weight_mode == 1 ? Nk * rcp_f64(fmax(Ntot, GSS_EPS_N)) : 1.0 / (double)K;
+  if (on) sCC[k] = fmax(pi_k, GSS_EPS_PI) * rcp_f64(det);
+}
+
 // ----------------------------------------------------------------------------------------------
 // Factor kernel for D <= 8: one workgroup per (segment, frequency), one wavefront per class.
 // Sums the chunk partials in a fixed order (deterministic), forms B = D R / N, regularises (trace D,
@@ -743,26 +852,29 @@ __global__ __launch_bounds__(256) void em_order_segments(gss_yview yv, const int
 }
 
 // One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile (NW > 1,
-// resident_tiles), or tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are
+// resident_tiles; `pre` by value: by reference the compiler shared its loads with those of the walk below and kept the frames
+// in scratch memory, 2 us of 33 for 200 frames of 2 channels), or tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are
 // registers to spare, and the frames of the next tile are requested from memory before the current tile is worked on.
 template <int D, int K, int NW, bool FINAL, bool RESIDENT, class MaskPtr>
 __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
-    bool resident_tiles, int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY,
+    bool resident_tiles, int wave, int lane, unsigned my_mask, TileRegs<D> pre, double* __restrict__ sY,
     double* __restrict__ sW, typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
   if constexpr (NW > 1) {
     if (resident_tiles) {
-      if (wave < tile_end)
+      if (wave < tile_end) {
         pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
-                                               wave * kWave, lane, my_mask, sY, sW, acc, nacc, &pre);
+                                               wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, sW, acc,
+                                               nacc, &pre);
+      }
       return;
     }
   }
   if constexpr (PassAcc<D, K>::direct && D * D * K <= kPrefetchMaxAcc) {
     constexpr unsigned kmask = (1u << K) - 1u;
-    TileRegs<D> cur = pre;                               // (zeros; replaced below when the first tile is live)
+    TileRegs<D> cur{};                                   // (replaced below when the first tile is live)
     int tile = wave;
     unsigned m = 0u;
     if (tile < tile_end) {
@@ -816,7 +928,7 @@ __device__ __forceinline__ void whole_pass(
 // ----------------------------------------------------------------------------------------------
 template <int D, int K, int NW>
 __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
-    gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
+    gss_yview yv, const uint8_t* __restrict__ act, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
     const int32_t* __restrict__ T_len, const int32_t* __restrict__ seg_order, float* __restrict__ gamma,
     uint32_t* __restrict__ status, int F, int Tmax, int iters, int weight_mode) {
   constexpr int E = D * D;
@@ -881,8 +993,20 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   pre.abits = 0u;
   if constexpr (NW > 1) {
     if (resident_tiles) {
-      if (wave < tiles_total) my_mask = tmrow[wave] & ((1u << K) - 1u);
-      if (my_mask != 0u) load_tile_regs<D>(pre, Yrow, abrow, wave * kWave, lane, T);   // a frame below T exists
+      // (its activity straight from the input: packing it would be a launch of its own in front of this one)
+      const int t = wave * kWave + lane;
+      unsigned bits = 0u;
+      if (t < T) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) bits |= (act[((long)s * K + k) * Tmax + t] != 0 ? 1u : 0u) << k;
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) my_mask |= (__ballot((int)((bits >> k) & 1u)) != 0 ? 1u : 0u) << k;
+      if (my_mask != 0u) {                              // a frame below T exists
+#pragma unroll
+        for (int d = 0; d < D; ++d) pre.y[d] = Yrow[(long)(t < T ? t : 0) * D + d];
+      }
+      pre.abits = bits;
     }
   }
 
@@ -968,7 +1092,8 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
     }
 
     // ---- M-step: B_k from (R_k, N_k), regularised, inverted; coefficients and class constants ----
-    factor_classes_in_wave<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
+    if constexpr (D <= kLaneFactorMaxD) factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
+    else factor_classes_in_wave<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
     wave_lds_sync();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -1064,8 +1189,6 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
   if (p.wgs_acc > 0x7fffffffL || p.wgs_fin > 0x7fffffffL) return GSS_EUNSUPPORTED;
   const dim3 block(kWave * kPassWaves);
-  hipLaunchKernelGGL(em_pack_activity<false>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
-                     Tmax, tiles);
   // Many problems per resident wavefront: one wavefront runs the whole EM of a problem (no partial sums, no
   // factor launches).  Few problems: each one is cut into chunks over several workgroups, one pass and one
   // factor launch per iteration.
@@ -1097,7 +1220,12 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
       }
     }
   }
-  if (iters > 0 && whole && n_sf <= 0x7fffffffL) {
+  whole = iters > 0 && whole && n_sf <= 0x7fffffffL;
+  // (tiny problems with a resident tile per wavefront read the activity themselves: 4 to 5 us of launch and kernel less)
+  if (!(whole && tiny && tiles <= kWholeQuad))
+    hipLaunchKernelGGL(em_pack_activity<false>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
+                       Tmax, tiles);
+  if (whole) {
     // a ragged batch is taken longest segment first
     const int32_t* seg_order = nullptr;
     if (S > 1 && T_len) {
@@ -1108,10 +1236,10 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
     if constexpr (D <= kWholeQuadMaxD) {
       if (tiny)
         hipLaunchKernelGGL((em_whole_small<D, K, kWholeQuad>), dim3((unsigned)n_sf), dim3(kWave * kWholeQuad), 0, st, Y,
-                           abyte, tmask, T_len, seg_order, gamma, ctx->status, F, Tmax, iters, weight_mode);
+                           act, abyte, tmask, T_len, seg_order, gamma, ctx->status, F, Tmax, iters, weight_mode);
     }
     if (!tiny)
-      hipLaunchKernelGGL((em_whole_small<D, K, 1>), dim3((unsigned)n_sf), dim3(kWave), 0, st, Y, abyte, tmask, T_len,
+      hipLaunchKernelGGL((em_whole_small<D, K, 1>), dim3((unsigned)n_sf), dim3(kWave), 0, st, Y, act, abyte, tmask, T_len,
                          seg_order, gamma, ctx->status, F, Tmax, iters, weight_mode);
     gss_profile_end(ctx, 0, st);
     if (hipGetLastError() != hipSuccess) return GSS_EHIP;
