@@ -213,23 +213,36 @@ __global__ __launch_bounds__(kWave) void mvdr_solve_small(
     sGr[i][j] = hr; sGi[i][j] = hi;
   }
   __syncthreads();
-  // powers of candidate r: h_r^H Phi h_r, lanes l < D handle r = l
-  if (l < D) {
-    const int r = l;
-    double pk = 0.0, pb = 0.0;
-    for (int a = 0; a < D; ++a) {
-      double tkr = 0.0, tki = 0.0, tbr = 0.0, tbi = 0.0;       // (Phi h_r)[a]
-      for (int b = 0; b < D; ++b) {
-        const double hr = sGr[b][r], hi = sGi[b][r];
-        tkr += sKr[a][b] * hr - sKi[a][b] * hi;  tki += sKr[a][b] * hi + sKi[a][b] * hr;
-        tbr += sBr[a][b] * hr - sBi[a][b] * hi;  tbi += sBr[a][b] * hi + sBi[a][b] * hr;
-      }
-      const double hr = sGr[a][r], hi = sGi[a][r];
-      pk += hr * tkr + hi * tki;                               // Re(conj(h_a) * t_a)
-      pb += hr * tbr + hi * tbi;
+  // powers of candidate r: h_r^H Phi h_r; lane (a, r) = (i, j) forms its term Re(conj(h_ar) (Phi h_r)_a), then lane r adds
+  // them in the order of a (every candidate on one lane: D^2 dependent steps; 16 segments of 8 channels 347 -> 332 us, 40 of 4 channels 470 -> 359)
+  double tk = 0.0, tb = 0.0;
+  if (on) {
+    double tkr = 0.0, tki = 0.0, tbr = 0.0, tbi = 0.0;         // (Phi h_r)[a]
+#pragma unroll
+    for (int b = 0; b < D; ++b) {
+      const double hr = sGr[b][j], hi = sGi[b][j];
+      tkr += sKr[i][b] * hr - sKi[i][b] * hi;  tki += sKr[i][b] * hi + sKi[i][b] * hr;
+      tbr += sBr[i][b] * hr - sBi[i][b] * hi;  tbi += sBr[i][b] * hi + sBi[i][b] * hr;
     }
-    pw[(sf * D + r) * 2 + 0] = pk;
-    pw[(sf * D + r) * 2 + 1] = pb;
+    const double hr = sGr[i][j], hi = sGi[i][j];
+    tk = hr * tkr + hi * tki;
+    tb = hr * tbr + hi * tbi;
+  }
+  __syncthreads();
+  if (on) {
+    sMr[i][j] = tk;                                            // (the inverse has been used)
+    sMi[i][j] = tb;
+  }
+  __syncthreads();
+  if (l < D) {
+    double pk = 0.0, pb = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      pk += sMr[a][l];
+      pb += sMi[a][l];
+    }
+    pw[(sf * D + l) * 2 + 0] = pk;
+    pw[(sf * D + l) * 2 + 1] = pb;
   }
 }
 
@@ -303,8 +316,11 @@ __global__ __launch_bounds__(256) void mvdr_apply_small(
     gss_yview yv, const double2* __restrict__ H, const int32_t* __restrict__ ref,
     const int32_t* __restrict__ T_len, float2* __restrict__ X, int F, int Tmax, int C, int frames_per_chunk,
     int ref_per_f) {
-  const int chunk = blockIdx.x % C;
-  const long sf = blockIdx.x / C;
+  // last row first: the covariances were formed from the first to the last, so the observations read last are still in the 256
+  // MB cache (16 segments, 0.55 GB of observations: the whole call 332 -> 315 us; a call that fits the cache gains nothing)
+  const unsigned block = gridDim.x - 1 - blockIdx.x;
+  const int chunk = block % C;
+  const long sf = block / C;
   const int s = (int)(sf / F);
   int T;
   const float2* __restrict__ Yrow = y_row(yv, T_len, s, (int)(sf % F), D, Tmax, T);
