@@ -479,8 +479,18 @@ __device__ __forceinline__ void accumulate_tile_masked(const double* __restrict_
     double e[cnt][D], w[cnt][KW];
     static_for<0, cnt>([&](auto UI) {
       constexpr int u = UI.value;
+      const double* __restrict__ wr = pw + (rest ? last : (j + u) * L::next) * WS;
+      if constexpr (KW % 2 == 0 && WS % 2 == 0) {
 #pragma unroll
-      for (int k = 0; k < KW; ++k) w[u][k] = pw[(rest ? last : (j + u) * L::next) * WS + k];
+        for (int k = 0; k < KW; k += 2) {
+          const double2 w2 = *reinterpret_cast<const double2*>(wr + k);
+          w[u][k] = w2.x;
+          w[u][k + 1] = w2.y;
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < KW; ++k) w[u][k] = wr[k];
+      }
       tile_entries<D>(y[u], e[u]);
     });
     constexpr int j2 = j + cnt, left = L::steps - j2;

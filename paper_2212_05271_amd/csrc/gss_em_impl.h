@@ -81,8 +81,10 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // Grid: blockIdx.x = chunk + C * (f + F * s).  A chunk is `tiles_per_chunk` tiles of 64 frames.
 // ----------------------------------------------------------------------------------------------
 
-// Doubles per frame row of the weight tile in LDS (odd: spreads the rows over the banks).
-__host__ __device__ constexpr int weight_stride(int K) { return K | 1; }
+// Doubles per frame row of the weight tile in LDS: odd, which spreads the rows over the banks, or an even number of classes
+// without padding, whose weights phase 2 reads in pairs (5 to 7 channels: 1 to 2 % less time; 8 channels: 1 % more, and
+// 24 % with 8 classes, where the compiler runs out of registers; 4 channels 0.7 % more).
+__host__ __device__ constexpr int weight_stride(int D, int K) { return D >= 5 && D <= 7 && K % 2 == 0 ? K : K | 1; }
 // Doubles of a wavefront's LDS region: the tile of 64 frame rows and its weights, or the rows of the reduction over the frame
 // groups that use the same memory after the last tile.
 template <int D>
@@ -155,7 +157,7 @@ __device__ __forceinline__ void pass_tile(
     TileRegs<D>* cur = nullptr, int next_t0 = 0) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
-  constexpr int WS = weight_stride(K);
+  constexpr int WS = weight_stride(D, K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;
   const int tg = lane / D, eg = lane - tg * D;
   tmask &= (1u << K) - 1u;
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr bool RESIDENT = K * R <= kResidentRegs;
-  constexpr int WS = weight_stride(K);
+  constexpr int WS = weight_stride(D, K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;        // no tiles in LDS then
   constexpr int kTileDoubles = DIRECT ? 0 : tile_region_doubles<D>(WS);
   constexpr int kCoefDoubles = RESIDENT ? 0 : K * R * 16;
@@ -934,7 +936,7 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr bool RESIDENT = K * R <= kResidentRegs;
-  constexpr int WS = weight_stride(K);
+  constexpr int WS = weight_stride(D, K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;       // no tiles in LDS then
   constexpr int kCoefDoubles = K * R * 16;             // packed coefficients, padded to whole registers
   constexpr int kSumDoubles = K * E + K;               // packed weighted scatter sums, then the class counts
