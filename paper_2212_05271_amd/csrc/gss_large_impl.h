@@ -288,7 +288,7 @@ __device__ __forceinline__ void reduce_large(const double4v (&acc)[KW][LargeShar
 }
 
 // ----------------------------------------------------------------------------------------------
-// EM pass, 9 <= D <= 32.  Grid: blockIdx.x = chunk + C * (f + F * s).  The workgroup's four wavefronts share every tile of 64
+// EM pass, 9 <= D <= 32.  Grid: block0 + blockIdx.x = chunk + C * (f + F * s).  The workgroup's four wavefronts share every tile of 64
 // frames: wavefront w has frames 16 w .. 16 w + 15 in the E-step, straight from memory (requested before the sums of the tile
 // before), puts them into LDS as fp64 and, with their weights in place, takes its share of the tiles of the sums
 // (LargeShare).  Two buffers for frames and weights, so one barrier per tile.  The final pass has no sums: no tile in LDS, no
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
     const int32_t* __restrict__ T_len,
     const double* __restrict__ coef, const double* __restrict__ cmant, const int32_t* __restrict__ cexp,
     double* __restrict__ part, double* __restrict__ npart, float* __restrict__ gamma, uint32_t* __restrict__ status,
-    int F, int Tmax, int D, ChunkMap cmap) {
+    int F, int Tmax, int D, ChunkMap cmap, unsigned block0) {
   extern __shared__ __attribute__((aligned(16))) double lds_large[];
   constexpr int P = large_pitch(NB), NT = large_tiles(NB), C = LargeShare<NB>::count;
   constexpr int kBuf = FINAL ? 0 : kWave * P + K * kWave;   // one buffer: weights, then the tile
@@ -328,7 +328,8 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
   const int g = lane >> 4, n = lane & 15;
   long sf;
   int chunk, tiles_per_chunk;
-  chunk_decode(cmap, blockIdx.x, sf, chunk, tiles_per_chunk);
+  const unsigned block = block0 + blockIdx.x;
+  chunk_decode(cmap, block, sf, chunk, tiles_per_chunk);
   const int s = (int)((unsigned)sf / (unsigned)F);
   const int f = (int)((unsigned)sf % (unsigned)F);
   int T;
@@ -565,12 +566,12 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
     }
   }
   if constexpr (!FINAL) {
-    reduce_large<NB, K, large_red_classes(K, NB)>(acc, role, sBuf, part + (long)blockIdx.x * (2 * K) * num_items(D), D, lane);
+    reduce_large<NB, K, large_red_classes(K, NB)>(acc, role, sBuf, part + (long)block * (2 * K) * num_items(D), D, lane);
     // class counts: the 64 frame columns in their order (written before the barriers of the reduction)
     if (threadIdx.x < K) {
       double sum = 0.0;
       for (int x = 0; x < kWave; ++x) sum += sN[((x >> 4) * K + threadIdx.x) * 16 + (x & 15)];
-      npart[(long)blockIdx.x * K + threadIdx.x] = sum;
+      npart[(long)block * K + threadIdx.x] = sum;
     }
   }
 }
@@ -627,13 +628,13 @@ template <int BS>
 __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
     const double* __restrict__ part, const double* __restrict__ npart,
     double* __restrict__ coef, double* __restrict__ cmant, int32_t* __restrict__ cexp, uint32_t* __restrict__ status,
-    int D, int K, ChunkMap cmap, int weight_mode) {
+    int D, int K, ChunkMap cmap, int weight_mode, unsigned sf0) {
   constexpr int W = 8 * BS;                                // padded matrix size
   __shared__ double sPiv[GSS_MAX_K][4][W];                 // per wavefront: pivot row (re, im), pivot column (re, im)
   extern __shared__ __attribute__((aligned(16))) double sItems[];   // per wavefront: the class's packed sums, 2 M doubles
   const int lane = threadIdx.x & (kWave - 1);
   const int k = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const long sf = blockIdx.x;
+  const long sf = sf0 + blockIdx.x;
   const int a = lane >> 3, b = lane & 7;
   const int M = num_items(D);
   int C;
@@ -1132,42 +1133,83 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   const ChunkMap fin_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, true>, lds_fin), n_sf, tiles, 1, 0, true);
   const long wgs_acc = chunk_map_wgs(acc_map, n_sf), wgs_fin = chunk_map_wgs(fin_map, n_sf);
   if (wgs_acc > 0x7fffffffL || wgs_fin > 0x7fffffffL || n_sf * K > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  size_t o = 0;
-  const size_t off_coef = o;  o = gss_align_up(o + (size_t)n_sf * K * large_coef(NB) * sizeof(double), 256);
-  const size_t off_cm = o;    o = gss_align_up(o + (size_t)n_sf * K * sizeof(double), 256);
-  const size_t off_ce = o;    o = gss_align_up(o + (size_t)n_sf * K * sizeof(int32_t), 256);
-  const size_t off_part = o;  o = gss_align_up(o + (size_t)wgs_acc * M * K * 2 * sizeof(double), 256);
-  const size_t off_npart = o; o = gss_align_up(o + (size_t)wgs_acc * K * sizeof(double), 256);
-  const size_t off_abyte = o; o = gss_align_up(o + (size_t)S * Tmax, 256);
-  const size_t off_masks = o; o = gss_align_up(o + (size_t)S * tiles * sizeof(uint32_t), 256);
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  int rc = gss_ensure_scratch(ctx, o);
+  // Problems [p0, p1) in one go: working memory for `n` problems and `wgs` workgroups of the accumulating pass.
+  struct Offsets { size_t cm, ce, part, npart, abyte, masks, end; };
+  auto layout = [&](long n, long wgs) {
+    Offsets q;
+    q.cm = gss_align_up((size_t)n * K * large_coef(NB) * sizeof(double), 256);
+    q.ce = gss_align_up(q.cm + (size_t)n * K * sizeof(double), 256);
+    q.part = gss_align_up(q.ce + (size_t)n * K * sizeof(int32_t), 256);
+    q.npart = gss_align_up(q.part + (size_t)wgs * M * K * 2 * sizeof(double), 256);
+    q.abyte = gss_align_up(q.npart + (size_t)wgs * K * sizeof(double), 256);
+    q.masks = gss_align_up(q.abyte + (size_t)S * Tmax, 256);
+    q.end = gss_align_up(q.masks + (size_t)S * tiles * sizeof(uint32_t), 256);
+    return q;
+  };
+  auto first_block = [](const ChunkMap& m, long p) {
+    int count;
+    return chunk_base(m, p, count);
+  };
+  long group = n_sf;                                       // problems in one go
+  Offsets off = layout(n_sf, wgs_acc);
+  if (ctx->scratch_fixed && off.end > ctx->scratch_cap) {
+    // Scratch of a given size: what fits is what would fit with the packed Hermitian coefficients (16 bytes per item, the
+    // items of a row in groups of 8), a half to a fifth of W's tiles; groups of problems share the memory.  The chunks of a
+    // problem stay the same, and with them every bit of the result.
+    int packed = 0;
+    for (int r = 1; r <= D; ++r) packed += (r + 7) / 8 * 16;
+    const size_t need = (size_t)n_sf * K * (packed * sizeof(double) + 12) + (size_t)wgs_acc * K * (M * 16 + 8) +
+                        (size_t)S * (Tmax + tiles * sizeof(uint32_t));
+    if (need > ctx->scratch_cap) return GSS_ETOOBIG;
+    long groups = 1;
+    do {
+      if (group == 1) return GSS_ETOOBIG;
+      group = (n_sf + groups) / (groups + 1);
+      ++groups;
+      long most = 0;
+      for (long p0 = 0; p0 < n_sf; p0 += group) {
+        const long p1 = p0 + group < n_sf ? p0 + group : n_sf;
+        const long wgs = first_block(acc_map, p1) - first_block(acc_map, p0);
+        most = wgs > most ? wgs : most;
+      }
+      off = layout(group, most);
+    } while (off.end > ctx->scratch_cap);
+  }
+  int rc = gss_ensure_scratch(ctx, off.end);
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
-  uint8_t* abyte = (uint8_t*)(base + off_abyte);
-  uint32_t* masks = (uint32_t*)(base + off_masks);
-  double* coef = (double*)(base + off_coef);
-  double* cm = (double*)(base + off_cm);
-  int32_t* ce = (int32_t*)(base + off_ce);
-  double* part = (double*)(base + off_part);
-  double* npart = (double*)(base + off_npart);
+  uint8_t* abyte = (uint8_t*)(base + off.abyte);
+  uint32_t* masks = (uint32_t*)(base + off.masks);
   const dim3 block(kWave * kLargeWaves);
   hipLaunchKernelGGL(em_pack_activity<true>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, masks, K,
                      Tmax, tiles);
-  for (int it = 0; it < iters; ++it) {
-    gss_profile_begin(ctx, 0, st);
-    hipLaunchKernelGGL((em_pass_large<K, NB, false>), dim3((unsigned)wgs_acc), block, lds_acc, st, Y, abyte, masks, T_len,
-                       it == 0 ? (const double*)nullptr : coef, cm, ce, part, npart, (float*)nullptr, ctx->status, F, Tmax, D,
-                       acc_map);
-    gss_profile_end(ctx, 0, st);
-    gss_profile_begin(ctx, 1, st);
-    hipLaunchKernelGGL(em_factor_large<NB>, dim3((unsigned)n_sf), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
-                       ctx->status, D, K, acc_map, weight_mode);
-    gss_profile_end(ctx, 1, st);
+  for (long p0 = 0; p0 < n_sf; p0 += group) {
+    const long p1 = p0 + group < n_sf ? p0 + group : n_sf;
+    const unsigned np = (unsigned)(p1 - p0);
+    const long a0 = first_block(acc_map, p0), f0 = first_block(fin_map, p0);
+    const unsigned na = (unsigned)(first_block(acc_map, p1) - a0), nf = (unsigned)(first_block(fin_map, p1) - f0);
+    // (the kernels index by problem and workgroup of the whole call)
+    double* coef = (double*)base - p0 * K * large_coef(NB);
+    double* cm = (double*)(base + off.cm) - p0 * K;
+    int32_t* ce = (int32_t*)(base + off.ce) - p0 * K;
+    double* part = (double*)(base + off.part) - a0 * M * K * 2;
+    double* npart = (double*)(base + off.npart) - a0 * K;
+    for (int it = 0; it < iters; ++it) {
+      gss_profile_begin(ctx, 0, st);
+      hipLaunchKernelGGL((em_pass_large<K, NB, false>), dim3(na), block, lds_acc, st, Y, abyte, masks, T_len,
+                         it == 0 ? (const double*)nullptr : coef, cm, ce, part, npart, (float*)nullptr, ctx->status, F, Tmax, D,
+                         acc_map, (unsigned)a0);
+      gss_profile_end(ctx, 0, st);
+      gss_profile_begin(ctx, 1, st);
+      hipLaunchKernelGGL(em_factor_large<NB>, dim3(np), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
+                         ctx->status, D, K, acc_map, weight_mode, (unsigned)p0);
+      gss_profile_end(ctx, 1, st);
+    }
+    hipLaunchKernelGGL((em_pass_large<K, NB, true>), dim3(nf), block, lds_fin, st, Y, abyte, masks, T_len,
+                       iters == 0 ? (const double*)nullptr : coef, cm, ce, (double*)nullptr, (double*)nullptr, gamma, ctx->status,
+                       F, Tmax, D, fin_map, (unsigned)f0);
   }
-  hipLaunchKernelGGL((em_pass_large<K, NB, true>), dim3((unsigned)wgs_fin), block, lds_fin, st, Y, abyte, masks, T_len,
-                     iters == 0 ? (const double*)nullptr : coef, cm, ce, (double*)nullptr, (double*)nullptr, gamma, ctx->status,
-                     F, Tmax, D, fin_map);
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
 }

@@ -44,6 +44,31 @@ def test_noalloc_matches_allocating_entry_point_twice():
         assert ctx.get_status() == 0
 
 
+@pytest.mark.parametrize("S,D,K", [(5, 9, 5), (2, 24, 5), (1, 32, 5), (1, 32, 6)])
+def test_noalloc_large_arrays_up_to_the_size_limit(S, D, K):
+    """More than 8 channels, 513 bins: calls whose coefficients take more than the array in the kernels' own layout, but not
+    packed, run in groups of problems, with the bits of the ordinary entry point.  What does not fit packed is refused."""
+    import torch
+    from paper_2212_05271_amd import binding as gss
+
+    F, T = 513, 70
+    Y, act, T_len = _problem(np.random.default_rng(D + K), S, F, T, D, K)
+    Yd, ad, Td = (torch.from_numpy(a).cuda() for a in (Y, act, T_len))
+    with gss.Context(0) as ctx:
+        for iters in (0, 3):
+            out = torch.full((S, K, F, T), -7.0, dtype=torch.float32, device="cuda")
+            gss.gss_cacgmm_em_noalloc(ctx, Yd, ad, Td, iters, out=out)
+            assert torch.equal(out, gss.gss_cacgmm_em(ctx, Yd, ad, Td, iters))
+        n = 1 + (1 << 26) // (8 * F * K * D * (D + 1))             # packed: at least 8 D (D + 1) bytes per class and matrix, twice
+        out = torch.full((n, K, F, T), -7.0, dtype=torch.float32, device="cuda")
+        with pytest.raises(gss.GssError) as e:
+            gss.gss_cacgmm_em_noalloc(ctx, Yd[:1].expand(n, -1, -1, -1).contiguous(), ad[:1].expand(n, -1, -1).contiguous(), None, 1,
+                                      out=out)
+        assert e.value.code == gss.GSS_ETOOBIG
+        torch.cuda.synchronize()
+        assert bool((out == -7.0).all())
+
+
 def test_noalloc_rejects_what_does_not_fit():
     import torch
     from paper_2212_05271_amd import binding as gss
