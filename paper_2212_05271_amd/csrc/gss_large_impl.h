@@ -1036,22 +1036,34 @@ __global__ __launch_bounds__(1024) void mvdr_solve_large(
     sGr[i][j] = hr; sGi[i][j] = hi;
   }
   __syncthreads();
+  // powers of candidate r: h_r^H Phi h_r; thread (a, r) = (i, j) forms its term Re(conj(h_ar) (Phi h_r)_a), then thread r adds
+  // them in the order of a (every candidate on one thread, D^2 dependent steps: one segment of 24 channels 286 us, now 247)
+  double tk = 0.0, tb = 0.0;
+  if (on) {
+    double tkr = 0.0, tki = 0.0, tbr = 0.0, tbi = 0.0;         // (Phi h_r)[a]
+    for (int b = 0; b < D; ++b) {
+      const double hr = sGr[b][j], hi = sGi[b][j];
+      tkr += sKr[i][b] * hr - sKi[i][b] * hi;  tki += sKr[i][b] * hi + sKi[i][b] * hr;
+      tbr += sBr[i][b] * hr - sBi[i][b] * hi;  tbi += sBr[i][b] * hi + sBi[i][b] * hr;
+    }
+    const double hr = sGr[i][j], hi = sGi[i][j];
+    tk = hr * tkr + hi * tki;
+    tb = hr * tbr + hi * tbi;
+  }
+  __syncthreads();
+  if (on) {
+    sKr[i][j] = tk;                                            // (the covariances have been used)
+    sKi[i][j] = tb;
+  }
+  __syncthreads();
   if (tid < D) {
-    const int r = tid;
     double pk = 0.0, pb = 0.0;
     for (int a = 0; a < D; ++a) {
-      double tkr = 0.0, tki = 0.0, tbr = 0.0, tbi = 0.0;
-      for (int b = 0; b < D; ++b) {
-        const double hr = sGr[b][r], hi = sGi[b][r];
-        tkr += sKr[a][b] * hr - sKi[a][b] * hi;  tki += sKr[a][b] * hi + sKi[a][b] * hr;
-        tbr += sBr[a][b] * hr - sBi[a][b] * hi;  tbi += sBr[a][b] * hi + sBi[a][b] * hr;
-      }
-      const double hr = sGr[a][r], hi = sGi[a][r];
-      pk += hr * tkr + hi * tki;
-      pb += hr * tbr + hi * tbi;
+      pk += sKr[a][tid];
+      pb += sKi[a][tid];
     }
-    pw[(sf * D + r) * 2 + 0] = pk;
-    pw[(sf * D + r) * 2 + 1] = pb;
+    pw[(sf * D + tid) * 2 + 0] = pk;
+    pw[(sf * D + tid) * 2 + 1] = pb;
   }
 }
 
