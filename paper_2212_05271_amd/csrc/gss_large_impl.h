@@ -25,14 +25,6 @@ constexpr int kLargeWaves = 4;
 __host__ __device__ inline int item_index(int i, int j, int D) { return i * D - i * (i - 1) / 2 + (j - i); }   // i <= j
 __host__ __device__ inline int num_items(int D) { return D * (D + 1) / 2; }
 
-// (i, j) of item m, by walking the rows (run once per lane and item at kernel start).
-__device__ __forceinline__ void item_ij(int m, int D, int& i, int& j) {
-  int r = 0, left = m;
-  while (left >= D - r) { left -= D - r; ++r; }
-  i = r;
-  j = r + left;
-}
-
 __device__ __forceinline__ double ipow_rt(double x, int n) {   // x^n, n >= 1
   double r = 1.0, b = x;
   while (n) {
@@ -144,10 +136,13 @@ struct LargeFrames {
   unsigned abits, mask;                                     // (mask: the masks of a tile further on, the same in every lane)
   __device__ __forceinline__ void request(const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, int t, int T,
                                           int D, int g) {
+    abits = abrow[t < T ? t : 0];
+    request(Yrow, t, T, D, g);
+  }
+  __device__ __forceinline__ void request(const float2* __restrict__ Yrow, int t, int T, int D, int g) {
     struct __attribute__((packed, aligned(8))) pair { float x0, y0, x1, y1; };
     const bool valid = t < T;
     const float2* __restrict__ src = Yrow + (long)(valid ? t : 0) * D + 2 * g;     // (frame 0 exists where a tile is live)
-    abits = abrow[valid ? t : 0];
 #pragma unroll
     for (int b = 0; b + 1 < NB; ++b) {
       const pair q = *reinterpret_cast<const pair*>(src + 8 * b);
@@ -160,9 +155,8 @@ struct LargeFrames {
     v[NB - 1][0] = src[c + 2 * g < D ? c : c - 8];
     v[NB - 1][1] = src[c + 2 * g + 1 < D ? c + 1 : c - 7];
   }
-  __device__ __forceinline__ void convert(double (&u)[NB][4], unsigned& bits, int t, int T, int D, int g) const {
+  __device__ __forceinline__ void convert(double (&u)[NB][4], int t, int T, int D, int g) const {
     const bool valid = t < T;
-    bits = valid ? abits : 0u;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -416,8 +410,8 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
       const unsigned live = (mq >> (8 * wave)) & kmask;     // classes of this wavefront's 16 frames
       const int next = live_tile(tile + 1, mnext);
       double u[NB][4];
-      unsigned abits;
-      frames.convert(u, abits, t, T, D, g);
+      const unsigned abits = t < T ? frames.abits : 0u;
+      frames.convert(u, t, T, D, g);
       if constexpr (!FINAL) {
         // the next tile's frames and the masks of the one after (behind the last tile: the same again, so that the loads need
         // no branch)
@@ -816,116 +810,32 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
   }
 }
 
-// Cooperative, coalesced copy of one tile of frames [t0, t0 + 64) of a (segment, frequency) row into the
-// wavefront's LDS tile sY[frame][D] (float2, row stride RS float2); frames at or beyond T become zero.
-// The tile is one contiguous run of 64 D values in memory; lane l copies values l, l + 64, ... (D of them).  Their
-// frame and channel are stepped without divisions, and the loads go out six at a time before the first of them
-// is stored (one at a time, every value would wait out a full memory latency).
-__device__ __forceinline__ void load_tile(const float2* __restrict__ Yrow, int t0, int T, int D, int RS,
-                                          float2* __restrict__ sY, int lane) {
-  constexpr int kBatch = 12;
-  const int rstep = kWave / D, cstep = kWave % D;          // frame and channel advance per 64 values
-  int r = lane / D, c = lane - r * D;
-  const float2* __restrict__ src = Yrow + (long)t0 * D + lane;
-  const int rows = T - t0;                                   // frames of the tile that exist (may exceed 64)
-  for (int i0 = 0; i0 < D; i0 += kBatch) {
-    float2 v[kBatch];
-    int off[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      v[u] = make_float2(0.f, 0.f);
-      off[u] = r * RS + c;
-      if (i0 + u < D) {
-        if (r < rows) v[u] = src[(long)(i0 + u) * kWave];
-        c += cstep;
-        r += rstep;
-        if (c >= D) { c -= D; ++r; }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (i0 + u < D) sY[off[u]] = v[u];
-  }
-}
-
-// The weighted sums of the lane's NR items over the 64 frames of the tile, for the classes of `mask` (wave-uniform; the
-// weights of the other classes are zero in every frame of the tile).
-template <int KW, int NR>
-__device__ __forceinline__ void accumulate_items(const float2* __restrict__ sY, const double* __restrict__ sW, int RS,
-                                                 int WS, const int (&oi)[NR], const int (&oj)[NR], unsigned mask,
-                                                 double (&acc)[NR][2][KW]) {
-#pragma unroll 1
-  for (int r = 0; r < kWave; ++r) {
-    double w[KW];
-#pragma unroll
-    for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
-    double re[NR], im[NR];
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      const float2 a = sY[r * RS + oi[n]];
-      const float2 b = sY[r * RS + oj[n]];
-      const double ar = a.x, ai = a.y, br = b.x, bi = b.y;
-      re[n] = ar * br + ai * bi;          // Re(y_i conj(y_j)); |y_i|^2 on the diagonal
-      im[n] = ai * br - ar * bi;          // Im(y_i conj(y_j)); 0 on the diagonal
-    }
-    static_for<0, KW>([&](auto KI) {
-      constexpr int k = KI.value;
-      if (class_on(mask, k)) {
-#pragma unroll
-        for (int n = 0; n < NR; ++n) {
-          acc[n][0][k] = fma(w[k], re[n], acc[n][0][k]);
-          acc[n][1][k] = fma(w[k], im[n], acc[n][1][k]);
-        }
-      }
-    });
-  }
-}
-
-// Sums the accumulators of the workgroup's wavefronts through LDS and writes out[m][k][2].
-template <int KW, int NR>
-__device__ __forceinline__ void reduce_items(double (&acc)[NR][2][KW], double* __restrict__ red, double* __restrict__ out,
-                                             int M, int lane, int wave) {
-  __syncthreads();
-  for (int w = 0; w < kLargeWaves; ++w) {
-    if (wave == w) {
-#pragma unroll
-      for (int n = 0; n < NR; ++n) {
-        const int m = lane + kWave * n;
-        if (m < M) {
-#pragma unroll
-          for (int k = 0; k < KW; ++k)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-              double* dst = &red[((long)m * KW + k) * 2 + p];
-              *dst = (w == 0) ? acc[n][p][k] : *dst + acc[n][p][k];
-            }
-        }
-      }
-    }
-    __syncthreads();
-  }
-  const int total = M * KW * 2;
-  for (int x = threadIdx.x; x < total; x += kWave * kLargeWaves) out[x] = red[x];
-}
-
 // ----------------------------------------------------------------------------------------------
-// MVDR, 9 <= D <= 32
+// Masked covariances, 9 <= D <= 32: the sums of the EM pass with two weights per frame, gamma of the target and the sum of the
+// others.  Grid: blockIdx.x = chunk + C * (f + F * s).  Output: part[chunk][2][m][2] (0: target, 1: background).
+// Bound: the fp64 matrix rate (24 channels: 48 products of 64 cycles per 16 frames, 75 us for 513 x 1500); the next tile is
+// requested before the sums.  513 x 1500 frames of 24 channels 164 -> 109 us (a lane with a few items, formed on the vector units,
+// and a partial tile per wavefront at the end); whole call, 4 to 6 classes: 9 channels 175 -> 99 us, 16 208 -> 116, 24 247 -> 192,
+// 32 484 -> 297 (17 to 32 channels: some 40 us of it are the candidates' powers), 250 frames of 24 channels 139 -> 74.
 // ----------------------------------------------------------------------------------------------
-template <int NR>
-__global__ __launch_bounds__(kWave * kLargeWaves) void mvdr_cov_large(
+__host__ __device__ constexpr int cov_lds_doubles(int NB) { return 2 * (kWave * large_pitch(NB) + 2 * kWave); }
+
+template <int NB>
+__global__ __launch_bounds__(kWave * kLargeWaves, 2) void mvdr_cov_large(
     gss_yview yv, const float* __restrict__ gamma, const int32_t* __restrict__ T_len,
     const int32_t* __restrict__ target, double* __restrict__ part, uint32_t* __restrict__ status,
-    int F, int Tmax, int D, int K, ChunkMap cmap, int RS, int tile_bytes) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  constexpr int WS = 3;
-  const int M = num_items(D);
+    int F, int Tmax, int D, int K, ChunkMap cmap) {
+  extern __shared__ __attribute__((aligned(16))) double lds_large[];
+  constexpr int P = large_pitch(NB), C = LargeShare<NB>::count;
+  constexpr int kBuf = kWave * P + 2 * kWave;               // one buffer: weights, then the tile
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int g = lane >> 4, n = lane & 15;
   long sf;
   int chunk, tiles_per_chunk;
   chunk_decode(cmap, blockIdx.x, sf, chunk, tiles_per_chunk);
-  const int s = (int)(sf / F);
-  const int f = (int)(sf % F);
+  const int s = (int)((unsigned)sf / (unsigned)F);
+  const int f = (int)((unsigned)sf % (unsigned)F);
   int T;
   const float2* __restrict__ Yrow = y_row(yv, T_len, s, f, D, Tmax, T);
   int tgt = target[s];
@@ -933,42 +843,56 @@ __global__ __launch_bounds__(kWave * kLargeWaves) void mvdr_cov_large(
     if (threadIdx.x == 0 && chunk == 0 && f == 0) atomicOr(status, GSS_STATUS_BAD_TARGET);
     tgt = tgt < 0 ? 0 : K - 1;
   }
-  float2* __restrict__ sY = reinterpret_cast<float2*>(lds_raw + (size_t)wave * tile_bytes);
-  double* __restrict__ sW = reinterpret_cast<double*>(lds_raw + (size_t)wave * tile_bytes + (size_t)kWave * RS * sizeof(float2));
   const float* __restrict__ grow = gamma + ((long)s * K * F + f) * Tmax;
   const long gk = (long)F * Tmax;
 
-  int oi[NR], oj[NR];
-  double acc[NR][2][2];
+  const LargeRole<NB> role(wave);
+  double4v acc[2][C];
 #pragma unroll
-  for (int n = 0; n < NR; ++n) {
-    int m = lane + kWave * n;
-    if (m >= M) m = 0;
-    item_ij(m, D, oi[n], oj[n]);
-    acc[n][0][0] = acc[n][0][1] = acc[n][1][0] = acc[n][1][1] = 0.0;
-  }
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int r = 0; r < C; ++r) acc[k][r] = double4v{0.0, 0.0, 0.0, 0.0};
   const int tile_lo = chunk * tiles_per_chunk;
   int tile_hi = tile_lo + tiles_per_chunk;
   const int tile_end = (T + kWave - 1) / kWave;
   tile_hi = tile_hi < tile_end ? tile_hi : tile_end;
-  for (int tile = tile_lo + wave; tile < tile_hi; tile += kLargeWaves) {
-    const int t0 = tile * kWave;
-    const int t = t0 + lane;
-    const bool valid = t < T;
-    load_tile(Yrow, t0, T, D, RS, sY, lane);
+  LargeFrames<NB> frames;
+  float gv[GSS_MAX_K];
+  auto request = [&](int tile) {
+    const int t = tile * kWave + 16 * wave + n;
+    frames.request(Yrow, t, T, D, g);
+    const float* __restrict__ p = grow + (t < T ? t : 0);
+#pragma unroll
+    for (int k = 0; k < GSS_MAX_K; ++k) gv[k] = p[k < K ? k * gk : 0];
+  };
+  if (tile_lo < tile_hi) request(tile_lo);
+  int buf = 0;
+  for (int tile = tile_lo; tile < tile_hi; ++tile) {
+    double* sW = lds_large + buf * kBuf;                    // [2][64] weights
+    double* sT = sW + 2 * kWave;                            // [64][P]
+    const int t = tile * kWave + 16 * wave + n;
+    double u[NB][4];
+    frames.convert(u, t, T, D, g);
     double wt = 0.0, wb = 0.0;
-    for (int k = 0; k < K; ++k) {
-      const double g = (double)grow[k * gk + (valid ? t : 0)];
-      if (k == tgt) wt = g; else wb += g;
+#pragma unroll
+    for (int k = 0; k < GSS_MAX_K; ++k)
+      if (k < K) {
+        if (k == tgt) wt = (double)gv[k];
+        else wb += (double)gv[k];
+      }
+    if (tile + 1 < tile_hi) request(tile + 1);
+    double* dst = sT + (16 * wave + n) * P + 4 * g;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      *reinterpret_cast<double2*>(dst + 16 * b) = make_double2(u[b][0], u[b][1]);
+      *reinterpret_cast<double2*>(dst + 16 * b + 2) = make_double2(u[b][2], u[b][3]);
     }
-    sW[lane * WS + 0] = valid ? wt : 0.0;
-    sW[lane * WS + 1] = valid ? wb : 0.0;
-    wave_lds_sync();
-    accumulate_items<2, NR>(sY, sW, RS, WS, oi, oj, 3u, acc);
-    wave_lds_sync();
+    if (g < 2) sW[g * kWave + 16 * wave + n] = t < T ? (g == 0 ? wt : wb) : 0.0;
+    __syncthreads();                                        // (one barrier per tile: the buffers take turns)
+    accumulate_large<NB, 2>(sT, sW, role, 0x03030303u, lane, acc);
+    buf ^= 1;
   }
-  double* __restrict__ red = reinterpret_cast<double*>(lds_raw);
-  reduce_items<2, NR>(acc, red, part + (long)blockIdx.x * M * 4, M, lane, wave);
+  reduce_large<NB, 2, large_red_classes(2, NB)>(acc, role, lds_large, part + (long)blockIdx.x * 4 * num_items(D), D, lane);
 }
 
 // One workgroup per (segment, frequency), D*D active threads.  H[sf][r][d], pw[sf][r][2] as for D <= 8.
@@ -989,8 +913,8 @@ __global__ __launch_bounds__(1024) void mvdr_solve_large(
     const int m = item_index(i, j, D);
     double kr = 0.0, ki = 0.0, br = 0.0, bi = 0.0;
     for (int c = 0; c < C; ++c) {
-      const double* p = part + ((slot0 + c) * (long)M + m) * 4;     // [k = 0 target, 1 background][re, im]
-      kr += p[0]; ki += p[1]; br += p[2]; bi += p[3];
+      const double* p = part + ((slot0 + c) * 2 * (long)M + m) * 2;  // [k = 0 target, 1 background][m][re, im]
+      kr += p[0]; ki += p[1]; br += p[2 * M]; bi += p[2 * M + 1];
     }
     if (i == j) { ki = 0.0; bi = 0.0; }
     sKr[i][j] = kr; sKi[i][j] = ki; sBr[i][j] = br; sBi[i][j] = bi;
@@ -1097,22 +1021,6 @@ __global__ __launch_bounds__(256) void mvdr_apply_large(
     }
     Xrow[t] = make_float2((float)xr, (float)xi);
   }
-}
-
-struct LargePlan {
-  int RS, tile_bytes, lds_bytes;
-};
-
-// LDS geometry of the tile kernels: per wavefront a tile of 64 frame rows of RS float2 plus the weights.
-LargePlan plan_large(int D, int KW) {
-  LargePlan p;
-  p.RS = D + 1;                                            // float2 per frame row (odd: spreads the banks)
-  const int ws = KW | 1;
-  p.tile_bytes = (int)gss_align_up((size_t)kWave * p.RS * sizeof(float2) + (size_t)kWave * ws * sizeof(double), 16);
-  const int red = num_items(D) * KW * 2 * (int)sizeof(double) + kLargeWaves * KW * (int)sizeof(double);
-  const int tiles_b = kLargeWaves * p.tile_bytes;
-  p.lds_bytes = tiles_b > red ? tiles_b : red;
-  return p;
 }
 
 // Resident workgroup slots of a tile kernel with its dynamic LDS size.
@@ -1234,17 +1142,16 @@ int dispatch_nb(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int3
   return run_em_large<K, 4>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
 }
 
-template <int NR>
+template <int NB>
 int run_mvdr_large(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const int32_t* T_len, int S, int F, int Tmax,
                    int D, int K, const int32_t* target, int32_t* ref, int ref_per_f, float2* X, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int M = num_items(D);
-  const LargePlan p = plan_large(D, 2);
-  if (hipFuncSetAttribute((const void*)mvdr_cov_large<NR>, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes) !=
-      hipSuccess)
+  constexpr int lds = cov_lds_doubles(NB) * (int)sizeof(double);
+  if (hipFuncSetAttribute((const void*)mvdr_cov_large<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
     return GSS_EHIP;
   const int tiles = (Tmax + kWave - 1) / kWave;
-  const ChunkMap cmap = plan_chunk_map(large_slots(ctx, mvdr_cov_large<NR>, p.lds_bytes), n_sf, tiles, kLargeWaves, 0, true);
+  const ChunkMap cmap = plan_chunk_map(large_slots(ctx, mvdr_cov_large<NB>, lds), n_sf, tiles, 1, 0, true);
   const long wgs = chunk_map_wgs(cmap, n_sf);
   if (wgs > 0x7fffffffL) return GSS_EUNSUPPORTED;
   size_t o = 0;
@@ -1257,8 +1164,8 @@ int run_mvdr_large(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const i
   double* part = (double*)(base + off_part);
   double2* H = (double2*)(base + off_H);
   double* pw = (double*)(base + off_pw);
-  hipLaunchKernelGGL((mvdr_cov_large<NR>), dim3((unsigned)wgs), dim3(kWave * kLargeWaves), p.lds_bytes, st, Y, gamma, T_len,
-                     target, part, ctx->status, F, Tmax, D, K, cmap, p.RS, p.tile_bytes);
+  hipLaunchKernelGGL((mvdr_cov_large<NB>), dim3((unsigned)wgs), dim3(kWave * kLargeWaves), lds, st, Y, gamma, T_len,
+                     target, part, ctx->status, F, Tmax, D, K, cmap);
   const int sthreads = (D * D + 63) / 64 * 64;
   hipLaunchKernelGGL(mvdr_solve_large, dim3((unsigned)n_sf), dim3(sthreads), 0, st, part, H, pw, ctx->status, D, cmap);
   gss_launch_mvdr_ref(pw, ref, ctx->status, S, F, D, ref_per_f, st);

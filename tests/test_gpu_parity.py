@@ -367,6 +367,30 @@ def test_large_arrays(env, D, K, T):
     assert int(ra[0]) == int(ro[0])
 
 
+@pytest.mark.parametrize("D,K", [(9, 2), (16, 8), (17, 3), (24, 5), (25, 2), (32, 8)])
+def test_large_array_covariances(env, D, K):
+    """The masked covariances on the matrix cores: lengths around the groups of 16 frames and the tiles of 64, several chunks,
+    padded channels, junk behind the end of a segment.  Bound: condition of the loaded covariance (at most D / 1e-6 = 3.2e7)
+    times the rounding of sums of some hundred terms, 1e-6 or less; the output's own rounding is 6e-8."""
+    rng = np.random.default_rng(50 * D + K)
+    F, T = 3, 330
+    T_len = np.array([330, 1, 15, 16, 17, 63, 64, 65, 129], dtype=np.int32)
+    S = len(T_len)
+    Y = (_cn(rng, (S, F, T, D)) * np.exp(rng.standard_normal((S, F, T, 1)))).astype(np.complex64)
+    gamma = rng.dirichlet(np.ones(K), (S, F, T)).transpose(0, 3, 1, 2).astype(np.float32)
+    gamma[:, 0, :, 32:48] = 0                                          # a group without the target
+    for s, n in enumerate(T_len):
+        Y[s, :, n:] = np.inf
+        gamma[s, :, :, n:] = np.nan
+    target = (np.arange(S) % K).astype(np.int32)
+    for ref in (0, D - 1):
+        Xg, _ = _gpu_mvdr(env, Y, gamma, T_len, target, [ref] * S)
+        for s, n in enumerate(T_len):
+            Xo, _, _ = env["o"].mvdr(Y[s, :, :n], gamma[s, :, :, :n].astype(np.float64), int(target[s]), ref=ref)
+            assert np.linalg.norm(Xg[s, :, :n] - Xo) <= 1e-5 * np.linalg.norm(Xo), (int(n), ref)
+            assert np.all(Xg[s, :, n:] == 0)
+
+
 def test_config3_full_size_sampled_bins(env):
     """24-channel multi-array segment (F = 513, T = 1500, K = 5, 20 iterations); oracle on every 64th bin."""
     seg = env["synth"].config3()
