@@ -614,9 +614,11 @@ __device__ __forceinline__ void gauss_jordan_large(double (*sMr)[33], double (*s
 // beyond D are those of the identity and stay so).  Elimination without pivoting (B is Hermitian positive definite after
 // the loading; the product of the pivots is det B), in place: sweep p subtracts row p times a_ip / pivot from the rows i > p
 // and leaves -a_ip / pivot in column p, so that the strictly lower triangle ends as that of M = the inverse of the unit
-// lower factor, and the diagonal holds the pivots d.  W = d^-1/2 M.  The lanes that hold pivot row p and
-// pivot column p publish them in the wavefront's LDS, every lane reads back the entries of its own columns and
-// rows.  Nothing is shared between wavefronts, so there is no workgroup barrier.
+// lower factor, and the diagonal holds the pivots d.  W = d^-1/2 M.  The lanes that hold pivot row p
+// publish it in the wavefront's LDS, every lane reads back the entries of its own columns and, conjugated for the pivot column,
+// of its own rows.  Nothing is shared between wavefronts, so there is no workgroup barrier.
+// Bound: latency, a chain of LDS round trip, reciprocal and update per sweep.  513 problems of 24 channels, 5 classes: 43 us (47 us
+// with the pivot column published as well and reals in LDS; whole EM calls 0.3 % (16 channels) to 8 % (32 channels) slower).
 // ----------------------------------------------------------------------------------------------
 template <int BS>
 __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
     double* __restrict__ coef, double* __restrict__ cmant, int32_t* __restrict__ cexp, uint32_t* __restrict__ status,
     int D, int K, ChunkMap cmap, int weight_mode, unsigned sf0) {
   constexpr int W = 8 * BS;                                // padded matrix size
-  __shared__ double sPiv[GSS_MAX_K][4][W];                 // per wavefront: pivot row (re, im), pivot column (re, im)
+  __shared__ __attribute__((aligned(16))) double2 sPiv[GSS_MAX_K][W];   // per wavefront: pivot row
   extern __shared__ __attribute__((aligned(16))) double sItems[];   // per wavefront: the class's packed sums, 2 M doubles
   const int lane = threadIdx.x & (kWave - 1);
   const int k = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -633,10 +635,7 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
   const int M = num_items(D);
   int C;
   const long slot0 = chunk_base(cmap, sf, C);
-  double* __restrict__ rowR = sPiv[k][0];
-  double* __restrict__ rowI = sPiv[k][1];
-  double* __restrict__ colR = sPiv[k][2];
-  double* __restrict__ colI = sPiv[k][3];
+  double2* __restrict__ row = sPiv[k];
 
   // class counts: lane l < K adds the chunks' counts of class l (in chunk order)
   double nl = 0.0;
@@ -731,19 +730,17 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
       if (p < D) {                                         // the same in every lane
         if (a == pg) {
 #pragma unroll
-          for (int c = 0; c < BS; ++c) { rowR[b * BS + c] = mr[pp][c]; rowI[b * BS + c] = mi[pp][c]; }
-        }
-        if (b == pg) {
-#pragma unroll
-          for (int r = 0; r < BS; ++r) { colR[a * BS + r] = mr[r][pp]; colI[a * BS + r] = mi[r][pp]; }
+          for (int c = 0; c < BS; ++c) row[b * BS + c] = make_double2(mr[pp][c], mi[pp][c]);
         }
         wave_lds_sync();
-        double piv = rowR[p];
+        double piv = row[p].x;
         double pr[BS], pim[BS], cr[BS], cim[BS];
 #pragma unroll
-        for (int c = 0; c < BS; ++c) { pr[c] = rowR[b * BS + c]; pim[c] = rowI[b * BS + c]; }
-#pragma unroll
-        for (int r = 0; r < BS; ++r) { cr[r] = colR[a * BS + r]; cim[r] = colI[a * BS + r]; }
+        for (int c = 0; c < BS; ++c) {
+          const double2 v = row[b * BS + c], h = row[a * BS + c];
+          pr[c] = v.x; pim[c] = v.y;
+          cr[c] = h.x; cim[c] = -h.y;                      // the pivot column below the pivot: what is left there is Hermitian
+        }
         wave_lds_sync();                                   // read before the next sweep writes
         if (!(piv > 1e-300)) {
           piv = 1e-300;
@@ -780,14 +777,14 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
   // neighbours there.  Zero above the diagonal and beyond D.
   if (a == b) {
 #pragma unroll
-    for (int r = 0; r < BS; ++r) rowR[a * BS + r] = 1.0 / sqrt(fmax(mr[r][r], 1e-300));
+    for (int r = 0; r < BS; ++r) row[a * BS + r].x = 1.0 / sqrt(fmax(mr[r][r], 1e-300));
   }
   wave_lds_sync();
   double* __restrict__ cf = coef + (sf * K + k) * (long)large_coef(BS);
 #pragma unroll
   for (int r = 0; r < BS; ++r) {
     const int i = a * BS + r;
-    const double ds = rowR[i];
+    const double ds = row[i].x;
 #pragma unroll
     for (int c = 0; c < BS; ++c) {
       const int j = b * BS + c;
