@@ -61,7 +61,8 @@ typedef enum gss_status {
 #define GSS_STATUS_BAD_TARGET 4u     /* a target index was outside [0, K); it was clamped                       */
 #define GSS_STATUS_NONPD_WPE 8u      /* the loaded WPE correlation matrix had a non-positive pivot; floored     */
 #define GSS_STATUS_ZERO_FRAME 16u    /* gss_cacgmm_em met a frame t < T_len[s] with ||y||^2 < 1e-20 (Eq. (2) is
-                                        0/0 there): it was normalised to the zero vector, its q clamped        */
+                                        0/0 there): it was normalised to the zero vector, its q clamped.  Stretches
+                                        of 64 frames (64 i .. 64 i + 63) without any active class are not looked at */
 #define GSS_STATUS_BAD_REF 32u       /* a reference channel >= D was passed to gss_mvdr; it was chosen instead  */
 
 typedef struct gss_ctx gss_ctx;

@@ -360,10 +360,18 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
   if constexpr (FINAL) {
     // zeros of the classes that are not active in a group of 16 frames
     for (int tile = tile_lo; tile < tile_hi; ++tile) {
-      const unsigned live = (mrow[tile] >> (8 * wave)) & kmask;
+      const unsigned any = mrow[tile], live = (any >> (8 * wave)) & kmask;
       const int t = tile * kWave + 16 * wave + n;
       for (int k = g; k < K; k += 4)
         if (((live >> k) & 1u) == 0u && t < Tmax) grow[k * gk + t] = 0.f;
+      if (live == 0u && any != 0u) {
+        // frames without energy are flagged in every tile that has an active class; the walk below passes this group by
+        const float2* __restrict__ y = Yrow + (long)(t < T ? t : 0) * D;
+        double n2 = 0.0;
+        for (int d = g; d < D; d += 4) n2 += (double)y[d].x * (double)y[d].x + (double)y[d].y * (double)y[d].y;
+        n2 = sum_rows_f64(n2);
+        if (g == 0 && t < T && !(n2 >= GSS_EPS_NORM_SQ)) atomicOr(status, GSS_STATUS_ZERO_FRAME);
+      }
     }
   }
   __syncthreads();

@@ -454,6 +454,27 @@ def test_degenerate_frames(env):
     assert np.all(g[:, :, :, 100:] == 0) and env["ctx"].get_status() == 0
 
 
+@pytest.mark.parametrize("D", [4, 8, 9, 24, 32])
+def test_zero_frame_flag(env, D):
+    """A frame without energy is flagged wherever its stretch of 64 frames has an active class, whether or not one is active
+    in the frame's own group of 16; a stretch without any active class is not looked at.  Same rule for every channel count."""
+    rng = np.random.default_rng(70 + D)
+    F, T, K = 3, 200, 3
+    Y = _cn(rng, (F, T, D)).astype(np.complex64)
+    act = np.ones((K, T), np.uint8)
+    act[:, 16:32] = 0                                          # a group of a live stretch
+    act[:, 64:128] = 0                                         # a whole stretch
+    env["ctx"].get_status()
+    for t, flagged in ((5, True), (16, True), (31, True), (63, True), (64, False), (127, False), (128, True), (199, True)):
+        Yz = Y.copy()
+        Yz[F - 1, t] = 0
+        g = _gpu_em(env, Yz[None], act[None], None, 2)[0]
+        assert env["ctx"].get_status() == (16 if flagged else 0), t
+        assert np.all(np.isfinite(g)) and np.all(g[:, :, 16:32] == 0) and np.all(g[:, :, 64:128] == 0)
+        _gpu_em(env, Yz[None], act[None], [t], 2)              # the frame is padding now
+        assert env["ctx"].get_status() == 0, t
+
+
 def test_bitwise_determinism_and_frequency_independence(env):
     seg = env["synth"].config1(F=20, T=333)
     g1 = _gpu_em(env, seg.Y[None], seg.activity[None], None, 10)
