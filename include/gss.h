@@ -186,9 +186,10 @@ int gss_cacgmm_em_frames(gss_ctx* ctx, const float* Yrec, int64_t Trec, const in
  * array of GSS_STATIC_SCRATCH_BYTES that the library holds once per GPU until the process ends; the call
  * makes no hipMalloc / hipFree and no other allocating call.
  *   - A problem whose working memory exceeds the array is rejected with GSS_ETOOBIG and nothing is written.
- *     The need is about 16 * S * F * K * D * D bytes (+ the partial sums of problems split over several
- *     workgroups when S * F is small): S * F * K * D * D <= 3.5 million always fits (e.g. 21 segments of
- *     513 bins at D = 8, K = 5).
+ *     The need up to 8 channels is about 16 * S * F * K * (D * D + 1) bytes (+ the partial sums of problems split
+ *     over several workgroups when S * F is small, + S * Tmax for the activity); from 9 channels on problems take turns
+ *     in the array, with the results of one go.  S * F * K * D * D <= 3.5 million (1 or 2 channels: half of that) always
+ *     fits, e.g. 21 segments of 513 bins at D = 8, K = 5, as long as S * Tmax is below 3 million.
  *   - Every call on one GPU, from any context, uses the same array: calls that overlap in time on one GPU
  *     race.  Order them on one stream or with events.  Nothing in the array has to survive between calls;
  *     each call initialises what it reads.

@@ -1080,13 +1080,13 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   Offsets off = layout(n_sf, wgs_acc);
   if (ctx->scratch_fixed && off.end > ctx->scratch_cap) {
     // Scratch of a given size: what fits is what would fit with the packed Hermitian coefficients (16 bytes per item, the
-    // items of a row in groups of 8), a half to a fifth of W's tiles; groups of problems share the memory.  The chunks of a
-    // problem stay the same, and with them every bit of the result.
+    // items of a row in groups of 8), a half to a fifth of W's tiles, and what the header promises to fit; groups of problems
+    // share the memory.  The chunks of a problem stay the same, and with them every bit of the result.
     int packed = 0;
     for (int r = 1; r <= D; ++r) packed += (r + 7) / 8 * 16;
     const size_t need = (size_t)n_sf * K * (packed * sizeof(double) + 12) + (size_t)wgs_acc * K * (M * 16 + 8) +
                         (size_t)S * (Tmax + tiles * sizeof(uint32_t));
-    if (need > ctx->scratch_cap) return GSS_ETOOBIG;
+    if (need > ctx->scratch_cap && n_sf * K * D * D > 3500000L) return GSS_ETOOBIG;
     long groups = 1;
     do {
       if (group == 1) return GSS_ETOOBIG;

@@ -44,10 +44,11 @@ def test_noalloc_matches_allocating_entry_point_twice():
         assert ctx.get_status() == 0
 
 
-@pytest.mark.parametrize("S,D,K", [(5, 9, 5), (2, 24, 5), (1, 32, 5), (1, 32, 6)])
+@pytest.mark.parametrize("S,D,K", [(5, 9, 5), (16, 9, 5), (2, 24, 5), (1, 32, 5), (1, 32, 6)])
 def test_noalloc_large_arrays_up_to_the_size_limit(S, D, K):
     """More than 8 channels, 513 bins: calls whose coefficients take more than the array in the kernels' own layout, but not
-    packed, run in groups of problems, with the bits of the ordinary entry point.  What does not fit packed is refused."""
+    packed, run in groups of problems, with the bits of the ordinary entry point; so does what the header promises to fit
+    (16 segments of 9 channels).  What does not fit packed is refused."""
     import torch
     from paper_2212_05271_amd import binding as gss
 
