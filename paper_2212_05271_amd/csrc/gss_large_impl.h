@@ -1038,6 +1038,10 @@ long large_slots(const gss_ctx* ctx, Kern kern, int lds_bytes) {
   return (long)ctx->num_cu * per_cu;
 }
 
+// Scratch memory that a call may take before its problems share it in groups: some 20,000 problems of 9 to 16 channels and 8
+// classes, forty rounds of workgroups, so that the launches of a group do not show.
+constexpr size_t kLargeScratch = (size_t)1 << 30;
+
 template <int K, int NB>
 int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
                  int D, int iters, int weight_mode, float* gamma, hipStream_t st) {
@@ -1078,28 +1082,31 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   };
   long group = n_sf;                                       // problems in one go
   Offsets off = layout(n_sf, wgs_acc);
-  if (ctx->scratch_fixed && off.end > ctx->scratch_cap) {
-    // Scratch of a given size: what fits is what would fit with the packed Hermitian coefficients (16 bytes per item, the
-    // items of a row in groups of 8), a half to a fifth of W's tiles, and what the header promises to fit; groups of problems
-    // share the memory.  The chunks of a problem stay the same, and with them every bit of the result.
-    int packed = 0;
-    for (int r = 1; r <= D; ++r) packed += (r + 7) / 8 * 16;
-    const size_t need = (size_t)n_sf * K * (packed * sizeof(double) + 12) + (size_t)wgs_acc * K * (M * 16 + 8) +
-                        (size_t)S * (Tmax + tiles * sizeof(uint32_t));
-    if (need > ctx->scratch_cap && n_sf * K * D * D > 3500000L) return GSS_ETOOBIG;
-    long groups = 1;
-    do {
-      if (group == 1) return GSS_ETOOBIG;
-      group = (n_sf + groups) / (groups + 1);
-      ++groups;
-      long most = 0;
-      for (long p0 = 0; p0 < n_sf; p0 += group) {
-        const long p1 = p0 + group < n_sf ? p0 + group : n_sf;
-        const long wgs = first_block(acc_map, p1) - first_block(acc_map, p0);
-        most = wgs > most ? wgs : most;
-      }
-      off = layout(group, most);
-    } while (off.end > ctx->scratch_cap);
+  // W's tiles are two to five times as large as the packed Hermitian coefficients (16 bytes per item, the items of a row in
+  // groups of 8).  A call takes no more scratch than it would with these, or than kLargeScratch or the context's present scratch
+  // if that is more: groups of problems share the memory.  The chunks of a problem stay the same, and with them every bit of
+  // the result.  Scratch of a given size: what fits is what would fit with the packed coefficients, and what the header
+  // promises to fit.
+  int packed = 0;
+  for (int r = 1; r <= D; ++r) packed += (r + 7) / 8 * 16;
+  const size_t need = (size_t)n_sf * K * (packed * sizeof(double) + 12) + (size_t)wgs_acc * K * (M * 16 + 8) +
+                      (size_t)S * (Tmax + tiles * sizeof(uint32_t));
+  size_t most_scratch = ctx->scratch_cap;
+  if (!ctx->scratch_fixed) {
+    most_scratch = need > most_scratch ? need : most_scratch;
+    most_scratch = kLargeScratch > most_scratch ? kLargeScratch : most_scratch;
+  } else if (need > ctx->scratch_cap && n_sf * K * D * D > 3500000L) {
+    return GSS_ETOOBIG;
+  }
+  for (long groups = 2; off.end > most_scratch && group > 1; ++groups) {
+    group = (n_sf + groups - 1) / groups;
+    long most = 0;
+    for (long p0 = 0; p0 < n_sf; p0 += group) {
+      const long p1 = p0 + group < n_sf ? p0 + group : n_sf;
+      const long wgs = first_block(acc_map, p1) - first_block(acc_map, p0);
+      most = wgs > most ? wgs : most;
+    }
+    off = layout(group, most);
   }
   int rc = gss_ensure_scratch(ctx, off.end);
   if (rc != GSS_OK) return rc;

@@ -391,6 +391,27 @@ def test_large_array_covariances(env, D, K):
             assert np.all(Xg[s, :, n:] == 0)
 
 
+def test_large_array_working_memory():
+    """Large batches of 9 channels and more: a call whose class matrices would take more than 1 GiB (the context rounds a
+    growth up by an eighth and to a MiB) runs in groups of problems, with the bits of smaller calls (60 segments of 513 bins,
+    8 classes: 1.5 GB of matrices; one tile per problem, so its chunk is the same in every batch)."""
+    import torch
+    from paper_2212_05271_amd import binding as gss
+
+    S, F, T, D, K = 60, 513, 20, 9, 8
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Y = torch.randn((S, F, T, D), dtype=torch.complex64, device="cuda", generator=gen)
+    act = (torch.rand((S, K, T), device="cuda", generator=gen) < 0.6).to(torch.uint8)
+    act[:, K - 1] = 1
+    with gss.Context(0) as ctx:
+        g = gss.gss_cacgmm_em(ctx, Y, act, None, 2)
+        assert ctx.scratch_bytes() <= (1 << 30) // 8 * 9 + (1 << 20)
+    with gss.Context(0) as ctx:
+        for s in (0, 19, 20, 29, 30, 39, 40, 59):
+            assert torch.equal(g[s:s + 1], gss.gss_cacgmm_em(ctx, Y[s:s + 1].contiguous(), act[s:s + 1].contiguous(), None, 2)), s
+        assert ctx.get_status() == 0
+
+
 def test_config3_full_size_sampled_bins(env):
     """24-channel multi-array segment (F = 513, T = 1500, K = 5, 20 iterations); oracle on every 64th bin."""
     seg = env["synth"].config3()
