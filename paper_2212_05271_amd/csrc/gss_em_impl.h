@@ -1223,7 +1223,11 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
     }
   }
   whole = iters > 0 && whole && n_sf <= 0x7fffffffL;
-  // (tiny problems with a resident tile per wavefront read the activity themselves: 4 to 5 us of launch and kernel less)
+  // (tiny problems with a resident tile per wavefront read the activity themselves: 4 to 5 us of launch and kernel less.  Not
+  // where the masks are written over the activity: a workgroup may start when another one is done.)
+  const uintptr_t act0 = (uintptr_t)act, act1 = act0 + (size_t)S * K * Tmax, out0 = (uintptr_t)gamma,
+                  out1 = out0 + (size_t)n_sf * K * Tmax * sizeof(float);
+  if (tiles <= kWholeQuad && act0 < out1 && out0 < act1) tiny = false;
   if (!(whole && tiny && tiles <= kWholeQuad))
     hipLaunchKernelGGL(em_pack_activity<false>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
                        Tmax, tiles);

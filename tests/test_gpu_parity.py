@@ -222,6 +222,25 @@ def test_every_tiny_problem_instantiation(env, D):
     assert env["ctx"].get_status() == 16                                # the zero-energy frame, nothing else
 
 
+@pytest.mark.parametrize("D,T", [(2, 200), (4, 60), (3, 700), (8, 200), (9, 200)])
+def test_masks_over_the_activity(env, D, T):
+    """The activity may lie in the memory that the masks are written to (here where the first frequency's masks go): it has
+    been read before the first mask is written.  Tolerance: another order of the sums."""
+    t, gss = env["torch"], env["gss"]
+    rng = np.random.default_rng(D + T)
+    F, K = 513, 3
+    Y = t.from_numpy((_cn(rng, (1, F, T, D)) * np.exp(rng.standard_normal((1, F, T, 1)))).astype(np.complex64)).cuda()
+    act = (rng.random((1, K, T)) < 0.6).astype(np.uint8)
+    act[:, K - 1] = 1
+    act = t.from_numpy(act).cuda()
+    g = gss.gss_cacgmm_em(env["ctx"], Y, act, None, 3)
+    out = t.empty((1, K, F, T), dtype=t.float32, device="cuda")
+    over = out.view(t.uint8).flatten()[:K * T].view(1, K, T)
+    over.copy_(act)
+    gss.gss_cacgmm_em(env["ctx"], Y, over, None, 3, out=out)
+    assert float((out - g).abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("D", [1, 2, 3, 4])
 def test_few_channels_four_wavefronts_many_tiles(env, D):
     """Few problems of more than 4 tiles at up to 4 channels: where the per-lane accumulators fit in registers
