@@ -853,28 +853,22 @@ __global__ __launch_bounds__(256) void em_order_segments(gss_yview yv, const int
   order[rank] = s;
 }
 
-// One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile (NW > 1,
-// resident_tiles; `pre` by value: by reference the compiler shared its loads with those of the walk below and kept the frames
-// in scratch memory, 2 us of 33 for 200 frames of 2 channels), or tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are
-// registers to spare, and the frames of the next tile are requested from memory before the current tile is worked on.
-template <int D, int K, int NW, bool FINAL, bool RESIDENT, class MaskPtr>
+// One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile `pre` (ONE_TILE), or
+// tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are registers to spare, and the frames
+// of the next tile are requested from memory before the current tile is worked on.
+template <int D, int K, int NW, bool ONE_TILE, bool FINAL, bool RESIDENT, class MaskPtr>
 __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
-    bool resident_tiles, int wave, int lane, unsigned my_mask, TileRegs<D> pre, double* __restrict__ sY,
-    double* __restrict__ sW, typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
-  if constexpr (NW > 1) {
-    if (resident_tiles) {
-      if (wave < tile_end) {
-        pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
-                                               wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, sW, acc,
-                                               nacc, &pre);
-      }
-      return;
-    }
-  }
-  if constexpr (PassAcc<D, K>::direct && D * D * K <= kPrefetchMaxAcc) {
+    int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY, double* __restrict__ sW,
+    typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
+  if constexpr (ONE_TILE) {
+    if (wave < tile_end)
+      pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+                                             wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, sW, acc,
+                                             nacc, &pre);
+  } else if constexpr (PassAcc<D, K>::direct && D * D * K <= kPrefetchMaxAcc) {
     constexpr unsigned kmask = (1u << K) - 1u;
     TileRegs<D> cur{};                                   // (replaced below when the first tile is live)
     int tile = wave;
@@ -916,20 +910,32 @@ __device__ __forceinline__ void whole_pass(
 // iteration, and the same fixed summation order on every run.
 //   NW = 1: for batches with many problems (segments x frequencies >> resident wavefronts); the wavefront
 //           walks all tiles of its problem; nothing is shared between wavefronts.
-//   NW = 4: for few problems of few channels.  At most NW tiles (256 frames): wavefront w owns tile w and keeps
+//   NW = 4: for few problems of few channels.  ONE_TILE, at most NW tiles (256 frames): wavefront w owns tile w and keeps
 //           its frames in registers for all iterations, so an iteration reads nothing from memory.  More tiles:
 //           wavefront w walks tiles w, w + NW, ...  The wavefronts' sums meet in LDS (two buffers, used in turn,
 //           one barrier per iteration), and every wavefront adds them up in the same order and runs the same
 //           factorisation on its own copy.
 //
-// Factorisation in the wavefront: lane (k, i) = (lane / 8, lane % 8) holds row i of the matrix of class k
-// (8 complex numbers) in registers.  B_k = D R_k / N_k is Hermitised by construction (packed sums), scaled
-// to trace D and loaded with delta I (identity for a class without data); in-place Gauss-Jordan sweeps
-// without pivoting (the pivots of a Hermitian positive-definite matrix are positive; their product is
-// det B): the owner of pivot row p publishes it in LDS, the 8 lanes of the class read it back.
+// Factorisation: up to 4 channels a lane per class (factor_class_in_lane), otherwise a lane per row of a class
+// (factor_classes_in_wave).
+//
+// Walk and resident tile are kernels of their own: in one kernel they need up to 57 registers more (4 channels and 2 classes 204,
+// now 151 and 139), and with them a wavefront per SIMD less (one segment of 1860 frames, 3 iterations, 2 channels and 7 classes 66.0
+// -> 52.3 us).
 // ----------------------------------------------------------------------------------------------
-template <int D, int K, int NW>
-__global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
+constexpr int kWholeQuad = 4;                 // wavefronts per problem of the variant for few problems
+constexpr int kWholeQuadMaxD = 4;             // ... which is built for up to this many channels
+// Wavefronts per SIMD that the kernel is compiled for.  Up to 2 channels the tile loop lives in two registers for every
+// accumulator, coefficient, partial sum and count, and some 40 more; the compiler takes one or two more than a step of the
+// register file allows (2 channels: 74 with 2 classes, 169 with 8) unless it is told: 24 segments of up to 700 frames, 2
+// classes, 3 iterations 88 -> 80 us, 48 segments of up to 300 frames, 8 classes 244 -> 209.
+__host__ __device__ constexpr int whole_waves_per_simd(int D, int K) {
+  if (D > 2) return 2;
+  const int regs = 2 * K * (D * D + 4) + 40, waves = 512 / ((regs + 7) / 8 * 8);
+  return waves < 8 ? waves : 8;
+}
+template <int D, int K, int NW, bool ONE_TILE>
+__global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, K)) void em_whole_small(
     gss_yview yv, const uint8_t* __restrict__ act, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
     const int32_t* __restrict__ T_len, const int32_t* __restrict__ seg_order, float* __restrict__ gamma,
     uint32_t* __restrict__ status, int F, int Tmax, int iters, int weight_mode) {
@@ -985,31 +991,28 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
   const long gamma_kstride = (long)F * Tmax;
   const int tiles = (T + kWave - 1) / kWave;
 
-  // NW > 1 and at most NW tiles: this wavefront's one tile: its mask, and the lane's frame in registers.
-  // (NW > 1 and more tiles: wavefront w walks tiles w, w + NW, ... like the single wavefront of NW = 1.)
-  const bool resident_tiles = NW > 1 && tiles_total <= NW;
+  // ONE_TILE: this wavefront's one tile: its mask, and the lane's frame in registers.
+  // (Otherwise wavefront w walks tiles w, w + NW, ...)
   TileRegs<D> pre;
   unsigned my_mask = 0u;
 #pragma unroll
   for (int d = 0; d < D; ++d) pre.y[d] = make_float2(0.f, 0.f);
   pre.abits = 0u;
-  if constexpr (NW > 1) {
-    if (resident_tiles) {
-      // (its activity straight from the input: packing it would be a launch of its own in front of this one)
-      const int t = wave * kWave + lane;
-      unsigned bits = 0u;
-      if (t < T) {
+  if constexpr (ONE_TILE) {
+    // (its activity straight from the input: packing it would be a launch of its own in front of this one)
+    const int t = wave * kWave + lane;
+    unsigned bits = 0u;
+    if (t < T) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) bits |= (act[((long)s * K + k) * Tmax + t] != 0 ? 1u : 0u) << k;
-      }
-#pragma unroll
-      for (int k = 0; k < K; ++k) my_mask |= (__ballot((int)((bits >> k) & 1u)) != 0 ? 1u : 0u) << k;
-      if (my_mask != 0u) {                              // a frame below T exists
-#pragma unroll
-        for (int d = 0; d < D; ++d) pre.y[d] = Yrow[(long)(t < T ? t : 0) * D + d];
-      }
-      pre.abits = bits;
+      for (int k = 0; k < K; ++k) bits |= (act[((long)s * K + k) * Tmax + t] != 0 ? 1u : 0u) << k;
     }
+#pragma unroll
+    for (int k = 0; k < K; ++k) my_mask |= (__ballot((int)((bits >> k) & 1u)) != 0 ? 1u : 0u) << k;
+    if (my_mask != 0u) {                                // a frame below T exists
+#pragma unroll
+      for (int d = 0; d < D; ++d) pre.y[d] = Yrow[(long)(t < T ? t : 0) * D + d];
+    }
+    pre.abits = bits;
   }
 
   // pass 0: B = I, uniform weights
@@ -1051,8 +1054,8 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, false, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax, tiles,
-                                          resident_tiles, wave, lane, my_mask, pre, sY, sW, acc, nacc);
+    whole_pass<D, K, NW, ONE_TILE, false, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
+                                                    tiles, wave, lane, my_mask, pre, sY, sW, acc, nacc);
 
     int le = lane;                                      // the lane number again, opaque
     asm volatile("" : "+v"(le));
@@ -1123,21 +1126,37 @@ __global__ __launch_bounds__(kWave * NW, 2) void em_whole_small(
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, true, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
-                                         tiles_total, resident_tiles, wave, lane, my_mask, pre, sY, sW, acc, nacc);
+    whole_pass<D, K, NW, ONE_TILE, true, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
+                                                   Tmax, tiles_total, wave, lane, my_mask, pre, sY, sW, acc, nacc);
   }
 }
 
 // ----------------------------------------------------------------------------------------------
 // Host-side plan and dispatch
 // ----------------------------------------------------------------------------------------------
-// The whole-EM kernel is used when the batch holds at least this many problems per resident wavefront (so that
-// the last, partly filled round of wavefronts is a small part of the run).
-constexpr int kWholeMinRounds = 3;
+// Problems per compute unit from which on the whole-EM kernel is used.  Measured on ragged batches of 300 to 1860 frames, every
+// channel and class count: from 16 per compute unit on (8 segments of 513 bins) 5 to 8 channels take 0.4 to 0.95 times as long as
+// in chunks (1 class, 7 channels, 1860 frames 1.03), the direct layout 0.5 to 0.95 times from 8 per compute unit on.  (The line
+// was three rounds of the wavefronts that fit the chip: with fewer registers the kernel got more wavefronts and the call went back
+// to chunks, 16 segments of 640 frames, 3 iterations, 7 channels and 2 classes 262 -> 317 us, 2 channels and 8 classes 132 -> 285.)
+template <int D, int K>
+constexpr int kWholeMinPerCu = direct_layout(D, K) ? 8 : 16;
 constexpr int kWholeMaxTilesAlways = 5;
-constexpr int kWholeQuad = 4;                 // wavefronts per problem of the variant for tiny problems
-constexpr int kWholeQuadMaxD = 4;             // ... which is built for up to this many channels
 constexpr int kWholeDirectMaxTiles = 25;      // direct layout: tiles in a row up to which a pass costs less than its launches
+// Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but each of them adds up and factorises for
+// itself, which costs the more the more of them share a SIMD (`load` problems per compute unit = wavefronts per SIMD), the more
+// channels there are, and where registers let two of them at most onto a SIMD, which then wait for each other's latencies.
+// Over 1 to 8 classes, 1 to 24 segments of 40 to 1860 frames, 3 to 10 iterations, the four are the faster ones where they save
+// three quarters of D (load^2 / 10 + 1) tiles: one segment of 513 bins from 3 tiles with 1 channel to 8 with 4, four segments from
+// 10 (1 channel) or 30 (3 channels).  With a tile per wavefront they also save a launch, which a call of few and short
+// iterations gains by.  Over these the choice is 0.13 % off the better of both on average, 28 % at most.  (By the rounds of
+// workgroups that the registers allow: 3 segments of 130 frames, 10 iterations, 2 channels and 1 class 34 us with four, 23
+// with one; one segment of 64 frames, 4 channels and 2 classes 44 and 27.)
+inline bool use_quad(int D, int K, double load, int wgs_per_cu, int tiles, int iters) {
+  const double line = D * (load * load / 10 + 1) * (wgs_per_cu > 2 ? 1.0 : 1.4);
+  const double saved = (tiles - (tiles + kWholeQuad - 1) / kWholeQuad) * (4.0 / 3.0);
+  return saved >= line || (tiles <= kWholeQuad && iters * (line - saved) * (D + 1) * (K + 2) < 200);
+}
 
 struct EmPlan {
   ChunkMap acc;          // chunking of the accumulating passes
@@ -1191,35 +1210,22 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
   if (p.wgs_acc > 0x7fffffffL || p.wgs_fin > 0x7fffffffL) return GSS_EUNSUPPORTED;
   const dim3 block(kWave * kPassWaves);
-  // Many problems per resident wavefront: one wavefront runs the whole EM of a problem (no partial sums, no
-  // factor launches).  Few problems: each one is cut into chunks over several workgroups, one pass and one
-  // factor launch per iteration.
-  static const int waves_per_cu = resident_wgs(em_whole_small<D, K, 1>, kWave, 8);
-  const long whole_min = ctx->em_whole_min_problems >= 0 ? (long)ctx->em_whole_min_problems
-                                                         : (long)kWholeMinRounds * ctx->num_cu * waves_per_cu;
-  // (Problems of a few tiles also go there whatever their number: two launches per iteration cost more than
-  // the whole EM of such a problem in one wavefront.)
-  bool whole = n_sf >= whole_min || (ctx->em_whole_min_problems < 0 && tiles <= kWholeMaxTilesAlways);
-  // Up to 4 channels there is the variant with four wavefronts per problem.  Tiny problems (at most 4 tiles) that
-  // fit the GPU in one round of such workgroups: one tile per wavefront, its frames resident in registers.  With
-  // the direct layout (cheap tiles, a launch costs as much as a few dozen of them) also longer problems, the
-  // wavefronts taking every fourth tile, when that means fewer tiles in a row than one wavefront per problem
-  // (rounds of resident wavefronts x tiles each; the meeting of the four sums counts as one tile); such batches
-  // go to the whole-EM kernel unless a pass is so long that the launches per iteration no longer matter.
+  // Many problems: one wavefront runs the whole EM of a problem (no partial sums, no factor launches).  Few problems: each one
+  // is cut into chunks over several workgroups, one pass and one factor launch per iteration, unless it has few tiles: two
+  // launches per iteration cost more than the whole EM of such a problem in one wavefront.
+  const bool choose = ctx->em_whole_min_problems < 0;
+  bool whole = n_sf >= (choose ? (long)kWholeMinPerCu<D, K> * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
+               (choose && tiles <= kWholeMaxTilesAlways);
+  // Up to 4 channels there is the variant with four wavefronts per problem (use_quad), and with the direct layout (cheap tiles,
+  // a launch costs as much as a few dozen of them) few problems go to the whole-EM kernel as well unless a pass is so long that
+  // the launches per iteration no longer matter.
   bool tiny = false;
   if constexpr (D <= kWholeQuadMaxD) {
-    if (ctx->em_whole_min_problems < 0 && n_sf > 0) {
-      static const int quads_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad>, kWave * kWholeQuad, 2);
-      const long slots1 = (long)ctx->num_cu * waves_per_cu, slots4 = (long)ctx->num_cu * quads_per_cu;
-      const long cost1 = (n_sf + slots1 - 1) / slots1 * tiles;
-      const long cost4 = (n_sf + slots4 - 1) / slots4 * ((tiles + kWholeQuad - 1) / kWholeQuad + 1);
-      if (tiles <= kWholeQuad && n_sf <= slots4) {
-        tiny = whole;
-      } else if (direct_layout(D, K) && tiles > 1) {
-        const long best = cost4 < cost1 ? cost4 : cost1;
-        if (!whole && best <= kWholeDirectMaxTiles) whole = true;
-        tiny = whole && cost4 < cost1;
-      }
+    if (choose && (direct_layout(D, K) || tiles <= kWholeQuad)) {
+      static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
+      static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
+      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, tiles <= kWholeQuad ? ones_per_cu : walks_per_cu, tiles, iters);
+      if (direct_layout(D, K) && (tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles) <= kWholeDirectMaxTiles) whole = true;
     }
   }
   whole = iters > 0 && whole && n_sf <= 0x7fffffffL;
@@ -1227,8 +1233,8 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   // where the masks are written over the activity: a workgroup may start when another one is done.)
   const uintptr_t act0 = (uintptr_t)act, act1 = act0 + (size_t)S * K * Tmax, out0 = (uintptr_t)gamma,
                   out1 = out0 + (size_t)n_sf * K * Tmax * sizeof(float);
-  if (tiles <= kWholeQuad && act0 < out1 && out0 < act1) tiny = false;
-  if (!(whole && tiny && tiles <= kWholeQuad))
+  if (!whole || (tiles <= kWholeQuad && act0 < out1 && out0 < act1)) tiny = false;
+  if (!(tiny && tiles <= kWholeQuad))
     hipLaunchKernelGGL(em_pack_activity<false>, dim3((unsigned)(S * tiles)), dim3(kWave), 0, st, Y, act, T_len, abyte, tmask, K,
                        Tmax, tiles);
   if (whole) {
@@ -1241,11 +1247,12 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
     gss_profile_begin(ctx, 0, st);
     if constexpr (D <= kWholeQuadMaxD) {
       if (tiny)
-        hipLaunchKernelGGL((em_whole_small<D, K, kWholeQuad>), dim3((unsigned)n_sf), dim3(kWave * kWholeQuad), 0, st, Y,
-                           act, abyte, tmask, T_len, seg_order, gamma, ctx->status, F, Tmax, iters, weight_mode);
+        hipLaunchKernelGGL((tiles <= kWholeQuad ? em_whole_small<D, K, kWholeQuad, true> : em_whole_small<D, K, kWholeQuad, false>),
+                           dim3((unsigned)n_sf), dim3(kWave * kWholeQuad), 0, st, Y, act, abyte, tmask, T_len, seg_order, gamma,
+                           ctx->status, F, Tmax, iters, weight_mode);
     }
     if (!tiny)
-      hipLaunchKernelGGL((em_whole_small<D, K, 1>), dim3((unsigned)n_sf), dim3(kWave), 0, st, Y, act, abyte, tmask, T_len,
+      hipLaunchKernelGGL((em_whole_small<D, K, 1, false>), dim3((unsigned)n_sf), dim3(kWave), 0, st, Y, act, abyte, tmask, T_len,
                          seg_order, gamma, ctx->status, F, Tmax, iters, weight_mode);
     gss_profile_end(ctx, 0, st);
     if (hipGetLastError() != hipSuccess) return GSS_EHIP;

@@ -222,6 +222,19 @@ def test_every_tiny_problem_instantiation(env, D):
     assert env["ctx"].get_status() == 16                                # the zero-energy frame, nothing else
 
 
+@pytest.mark.parametrize("D,K,S,T", [(2, 2, 24, 700), (2, 8, 16, 640), (2, 8, 5, 1100), (5, 4, 16, 640), (7, 2, 16, 640)])
+def test_batches_run_in_one_launch(env, D, K, S, T):
+    """Batches go to the whole-EM kernel (one launch instead of two per iteration) from a number of problems on that does not
+    depend on how many wavefronts the registers of the kernel let onto a SIMD."""
+    t, gss = env["torch"], env["gss"]
+    Y = t.randn((S, 513, T, D), dtype=t.complex64, device="cuda")
+    act = t.ones((S, K, T), dtype=t.uint8, device="cuda")
+    with gss.Context(0) as ctx:
+        ctx.profile_enable()
+        gss.gss_cacgmm_em(ctx, Y, act, None, 3)
+        assert ctx.profile_get(0)[1] == 1
+
+
 @pytest.mark.parametrize("D,T", [(2, 200), (4, 60), (3, 700), (8, 200), (9, 200)])
 def test_masks_over_the_activity(env, D, T):
     """The activity may lie in the memory that the masks are written to (here where the first frequency's masks go): it has
