@@ -853,6 +853,12 @@ __global__ __launch_bounds__(256) void em_order_segments(gss_yview yv, const int
   order[rank] = s;
 }
 
+// Whether the whole-EM kernel requests the next tile's frames before phase 2 (tile layout): not where the 2 D + 1 registers are
+// missed.  8 channels: with 2 classes they cost the third wavefront of a SIMD (172 registers instead of 156; 48 segments of up to
+// 300 frames, 3 iterations 551 -> 522 us), with 8 classes, whose accumulators leave no room, the spills lie in the tile (1373 ->
+// 1286).
+__host__ __device__ constexpr bool request_ahead(int D, int K) { return D < 8 || (K != 2 && K < 8); }
+
 // One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile `pre` (ONE_TILE), or
 // tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are registers to spare, and the frames
 // of the next tile are requested from memory before the current tile is worked on.
@@ -893,7 +899,7 @@ __device__ __forceinline__ void whole_pass(
       m = mn;
       tile = next;
     }
-  } else if constexpr (PassAcc<D, K>::direct || FINAL || NW > 1) {
+  } else if constexpr (PassAcc<D, K>::direct || FINAL || NW > 1 || !request_ahead(D, K)) {
     for (int tile = wave; tile < tile_end; tile += NW)
       pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, sW, acc, nacc);
