@@ -357,8 +357,8 @@ def test_tile_frame_groups(env, D, K):
 
 @pytest.mark.parametrize("D", [10, 20, 26, 32])
 def test_every_large_instantiation(env, D):
-    """Every (class count, items-per-lane) instantiation of the large-array kernels: K = 1..8 at one channel
-    count out of each items-per-lane range, problems cut into chunks."""
+    """Every (class count, NB = ceil(D / 8)) instantiation of the large-array kernels: K = 1..8 with a partly filled last block
+    of channels (D = 10, 20, 26) and a full one (32), one tile per workgroup."""
     env["ctx"].get_status()                                            # clear what earlier tests raised
     for K in range(1, 9):
         rng = np.random.default_rng(10 * D + K)
@@ -377,8 +377,8 @@ def test_every_large_instantiation(env, D):
 @pytest.mark.parametrize("D,K,T", [(9, 3, 100), (11, 2, 70), (12, 5, 150), (14, 2, 60), (16, 2, 70), (21, 3, 90),
                                    (23, 3, 90), (24, 5, 200), (29, 2, 80), (32, 4, 130)])
 def test_large_arrays(env, D, K, T):
-    """9 <= D <= 32 channels (run-time D kernels; the rows of the packed triangle end in coefficient groups of
-    every length 1..8, and the channel counts cover every remainder of D modulo 8 between them and the tests above)."""
+    """9 <= D <= 32 channels (the channel counts cover every remainder of D modulo 8, i.e. every padding of the last block of
+    channels, between them and the tests around this one)."""
     rng = np.random.default_rng(1000 + D)
     F = 5
     v = _cn(rng, (K, F, D))
@@ -401,8 +401,8 @@ def test_large_arrays(env, D, K, T):
 
 @pytest.mark.parametrize("D,K", [(9, 2), (16, 8), (17, 3), (24, 5), (25, 2), (32, 8)])
 def test_large_array_covariances(env, D, K):
-    """The masked covariances on the matrix cores: lengths around the groups of 16 frames and the tiles of 64, several chunks,
-    padded channels, junk behind the end of a segment.  Bound: condition of the loaded covariance (at most D / 1e-6 = 3.2e7)
+    """The masked covariances on the matrix cores: lengths around the groups of 16 frames and the tiles of 64, a tile per
+    workgroup, padded channels, junk behind the end of a segment.  Bound: condition of the loaded covariance (at most D / 1e-6 = 3.2e7)
     times the rounding of sums of some hundred terms, 1e-6 or less; the output's own rounding is 6e-8."""
     rng = np.random.default_rng(50 * D + K)
     F, T = 3, 330
@@ -421,6 +421,53 @@ def test_large_array_covariances(env, D, K):
             Xo, _, _ = env["o"].mvdr(Y[s, :, :n], gamma[s, :, :, :n].astype(np.float64), int(target[s]), ref=ref)
             assert np.linalg.norm(Xg[s, :, :n] - Xo) <= 1e-5 * np.linalg.norm(Xo), (int(n), ref)
             assert np.all(Xg[s, :, n:] == 0)
+
+
+@pytest.mark.parametrize("D,K", [(9, 3), (16, 8), (17, 8), (24, 4), (25, 5), (32, 7)])
+@pytest.mark.parametrize("F", [3, 300])
+def test_large_array_dead_stretches(env, D, K, F):
+    """EM and beamformer of 9 and more channels where groups of 16 frames and whole tiles of 64 have no active class, at the start,
+    in the middle and at the end of a segment, and a class is never active; junk behind the segments.  F = 300 (1500
+    problems): a workgroup walks all tiles of its problem (buffers in turn, masks and class matrices requested ahead);
+    F = 3: one tile each, some workgroups without a live one.  Every class that is active has more frames than channels; masks
+    to 1e-5, as for short segments elsewhere; beamformer as in test_large_array_covariances."""
+    t, gss, o = env["torch"], env["gss"], env["o"]
+    T, iters = 400, 3
+    T_len = np.array([400, 337, 321, 190, 60], dtype=np.int32)
+    S = len(T_len)
+    rng = np.random.default_rng(100 * D + F)
+    gen = t.Generator(device="cuda").manual_seed(D)
+    Y = t.randn((S, F, T, D), dtype=t.complex64, device="cuda", generator=gen)
+    Y *= t.randn((S, F, T, 1), device="cuda", generator=gen).exp()
+    act = (rng.random((S, K, T)) < 0.8).astype(np.uint8)
+    act[:, 0, 336:] = 1
+    act[:, 1] = 0                                                      # never active
+    act[:, :, :64] = 0                                                 # a tile at the start,
+    act[:, :, 80:96] = 0                                               # a group,
+    act[:, :, 192:320] = 0                                             # two tiles (the end of the fourth segment)
+    act[:, :, 352:368] = 0
+    for s, n in enumerate(T_len):
+        Y[s, :, n:] = float("nan")
+    ctx = env["ctx"]
+    ctx.get_status()
+    g = gss.gss_cacgmm_em(ctx, Y, t.from_numpy(act).cuda(), t.from_numpy(T_len).cuda(), iters)
+    fs = np.unique(np.linspace(0, F - 1, 5).astype(int))
+    Ys, gs = Y[:, fs].cpu().numpy(), g[:, :, fs].cpu().numpy()
+    for s, n in enumerate(T_len):
+        go = o.cacgmm_em(Ys[s, :, :n], act[s, :, :n], iters)
+        assert np.max(np.abs(gs[s, :, :, :n] - go)) <= 1e-5, int(n)
+        live = (act[s] != 0) & (np.arange(T) < n)
+        assert bool((g[s][~t.from_numpy(live).cuda()[:, None].expand(K, F, T)] == 0).all())
+    for s, n in enumerate(T_len):
+        g[s, :, :, n:] = float("nan")
+    target = np.zeros(S, np.int32)
+    ref = t.full((S,), D - 1, dtype=t.int32, device="cuda")
+    X = gss.gss_mvdr(ctx, Y, g, t.from_numpy(target).cuda(), ref, t.from_numpy(T_len).cuda()).cpu().numpy()
+    for s, n in enumerate(T_len):
+        Xo, _, _ = o.mvdr(Ys[s, :, :n], gs[s, :, :, :n].astype(np.float64), 0, ref=D - 1)
+        assert np.linalg.norm(X[s, fs, :n] - Xo) <= 1e-5 * np.linalg.norm(Xo), int(n)
+        assert np.all(X[s, :, n:] == 0)
+    assert ctx.get_status() == 0
 
 
 def test_large_array_working_memory():
