@@ -23,9 +23,15 @@ int gss_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* activity, cons
 
 int gss_mvdr_large(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const int32_t* T_len, int S, int F, int Tmax,
                    int D, int K, const int32_t* target, int32_t* ref, int ref_per_f, float* X, hipStream_t st) {
-  const gss_yview& Yc = Y;
   float2* Xc = (float2*)X;
-  if (D <= 16) return run_mvdr_large<2>(ctx, Yc, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st);
-  if (D <= 24) return run_mvdr_large<3>(ctx, Yc, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st);
-  return run_mvdr_large<4>(ctx, Yc, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st);
+  const int rest = large_rest(D, 2);
+  auto blocks = [&](auto NB) {
+    constexpr int nb = decltype(NB)::value;
+    return rest == 1   ? run_mvdr_large<nb, 1>(ctx, Y, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st)
+           : rest == 2 ? run_mvdr_large<nb, 2>(ctx, Y, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st)
+                       : run_mvdr_large<nb, 0>(ctx, Y, gamma, T_len, S, F, Tmax, D, K, target, ref, ref_per_f, Xc, st);
+  };
+  if (D <= 16) return blocks(std::integral_constant<int, 2>{});
+  if (D <= 24) return blocks(std::integral_constant<int, 3>{});
+  return blocks(std::integral_constant<int, 4>{});
 }

@@ -11,6 +11,8 @@
 //     B^-1: better conditioned than the quadratic form itself.
 //   * M-step sums: sum_t w_t u_t u_t^T by 16 x 16 tiles on and above the diagonal; the Hermitian sums are
 //     Re = (re re) + (im im), Im = (im re) - (re im) of them, formed once at the end.
+//   * A last block of up to 4 channels (H = 1: up to 2, H = 2: 3 or 4; H = 0: more) is 4 H rows of W and columns of the sums
+//     instead of 16, by the 4 x 4 x 4 products.
 //   * A class that is inactive in a group of 16 frames is skipped for the group in both steps.
 #pragma once
 
@@ -46,6 +48,11 @@ typedef double double2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double4v mfma_f64(double a, double b, double4v c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+// Four products of 4 x 4 and 4 x 4 doubles, a fifth of the time of the above.  Lane 16 k + 4 b + i holds A[i][k] and B[k][i] of
+// product b, and D[k][i].  So a lane's A above is A of the rows 4 b .. 4 b + 3, and its B above is B of the columns 4 b .. 4 b + 3.
+__device__ __forceinline__ double mfma4_f64(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
 // Sum over the four rows of 16 lanes, in every lane.
 __device__ __forceinline__ double sum_rows_f64(double v) {
   auto add = [](auto lo, auto hi) { return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]); };
@@ -71,6 +78,18 @@ __host__ __device__ constexpr int large_pitch(int NB) { return 16 * NB + 4; }
 __host__ __device__ constexpr int large_tiles(int NB) { return NB * (NB + 1) / 2; }
 __host__ __device__ constexpr int large_coef(int NB) { return 256 * large_tiles(NB); }
 
+// The last block of channels: H = 0: 16 reals, 1 or 2: 4 H (see above); the blocks that are taken in full.  With the block in full
+// calls whose classes are all active most of the time lost to the vector units: 513 x 1500 frames, 3 iterations, all classes
+// active in 9 of 10 frames, items on the vector units / block in full / now: 9 channels and 8 classes 0.85 / 1.16 / 0.85 ms, 12 and 5
+// 0.74 / 0.80 / 0.68, 17 and 5 1.02 / 1.33 / 1.13, 17 and 8 1.36 / 1.98 / 1.78, 25 and 8 4.54 / 3.60 / 2.90; speaker turns: 9 and 5
+// 0.55 / 0.45 / 0.43, 17 and 5 0.90 / 0.78 / 0.71, 25 and 5 1.79 / 1.27 / 1.09.  19 and 20 channels with 7 or 8 classes keep the
+// block in full: the 8 accumulators and 2 for the rest of every class do not fit in registers (8 classes 1.04 against 1.24).
+inline int large_rest(int D, int K) {
+  const int c = (D - 1) % 8 + 1;
+  return c <= 2 ? 1 : c <= 4 && !(D > 16 && D <= 24 && K > 6) ? 2 : 0;
+}
+__host__ __device__ constexpr int full_blocks(int NB, int H) { return H > 0 ? NB - 1 : NB; }
+
 // Tiles of the weighted sums: which of the NB (NB + 1) / 2 tiles on and above the diagonal a wavefront of the workgroup adds
 // up, over which of the four groups of 16 frames of a tile of frames.  A wavefront has one left operand (row of tiles `left`)
 // and `count` right ones; left > right is the transposed tile.  Every wavefront gets the same number of products (3, 6 and
@@ -79,6 +98,15 @@ __host__ __device__ constexpr int large_coef(int NB) { return 256 * large_tiles(
 // (0: they are the first).
 template <int NB>
 struct LargeShare;
+template <>
+struct LargeShare<1> {
+  static constexpr int count = 1;
+  static constexpr int left[4] = {0, 0, 0, 0};
+  static constexpr int right[4][1] = {{0}, {0}, {0}, {0}};
+  static constexpr int groups[4][1] = {{1}, {2}, {4}, {8}};
+  static constexpr int full = 0, phases = 4;
+  static constexpr int phase[4][1] = {{0}, {1}, {2}, {3}};
+};
 template <>
 struct LargeShare<2> {
   static constexpr int count = 2;
@@ -106,12 +134,28 @@ struct LargeShare<4> {
   static constexpr int full = 2, phases = 2;
   static constexpr int phase[4][3] = {{0, 0, 0}, {0, 0, 1}, {0, 0, 0}, {0, 0, 1}};
 };
-// A wavefront's share in registers (wave-uniform).
+// The 4 H columns of a last block of few channels: which 16 rows of them a wavefront adds up, over which groups of frames; the
+// rows of its other tiles where there is a choice.
 template <int NB>
+struct RestShare;
+template <>
+struct RestShare<2> {
+  static constexpr int row[4] = {0, 1, 0, 1}, groups[4] = {3, 3, 12, 12}, phase[4] = {0, 0, 1, 1};
+};
+template <>
+struct RestShare<3> {
+  static constexpr int row[4] = {0, 2, 1, 2}, groups[4] = {15, 3, 15, 12}, phase[4] = {0, 0, 0, 1};
+};
+template <>
+struct RestShare<4> {
+  static constexpr int row[4] = {0, 3, 1, 2}, groups[4] = {15, 15, 15, 15}, phase[4] = {0, 0, 0, 0};
+};
+// A wavefront's share in registers (wave-uniform).
+template <int NB, int H>
 struct LargeRole {
-  int left, right[LargeShare<NB>::count], groups[LargeShare<NB>::count], phase[LargeShare<NB>::count];
+  using S = LargeShare<full_blocks(NB, H)>;
+  int left, right[S::count], groups[S::count], phase[S::count], rest_row = 0, rest_groups = 0, rest_phase = -1;
   __device__ __forceinline__ explicit LargeRole(int wave) {
-    using S = LargeShare<NB>;
     left = 0;
 #pragma unroll
     for (int w = 0; w < kLargeWaves; ++w)
@@ -123,7 +167,29 @@ struct LargeRole {
           groups[r] = S::groups[w][r];
           phase[r] = S::phase[w][r];
         }
+        if constexpr (H > 0) {
+          rest_row = RestShare<NB>::row[w];
+          rest_groups = RestShare<NB>::groups[w];
+          rest_phase = RestShare<NB>::phase[w];
+        }
       }
+  }
+};
+// A wavefront's sums of KW classes: its 16 x 16 tiles, and 16 x 4 H of the last block of channels (lane l: row 4 (l / 4 % 4) + l / 16,
+// column 4 h + l % 4).
+template <int NB, int H, int KW>
+struct LargeAcc {
+  static constexpr int C = LargeShare<full_blocks(NB, H)>::count;
+  double4v full[KW][C];
+  double rest[KW][H > 0 ? H : 1];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+#pragma unroll
+      for (int r = 0; r < C; ++r) full[k][r] = double4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int h = 0; h < (H > 0 ? H : 1); ++h) rest[k][h] = 0.0;
+    }
   }
 };
 
@@ -178,17 +244,20 @@ struct LargeFrames {
 // `masks`).  sW: [KW][64] weights.  Step s of a group takes frames 4 g + s (lane row g): a lane's four weights are contiguous,
 // and the four products of a tile follow each other on the same accumulators (a product on other accumulators starts about
 // ten of its 64 cycles later).
-template <int NB, int KW>
+template <int NB, int H, int KW>
 __device__ __forceinline__ void accumulate_large(const double* __restrict__ sY, const double* __restrict__ sW,
-                                                 const LargeRole<NB>& role, unsigned masks, int lane,
-                                                 double4v (&acc)[KW][LargeShare<NB>::count]) {
-  constexpr int P = large_pitch(NB), C = LargeShare<NB>::count;
+                                                 const LargeRole<NB, H>& role, unsigned masks, int lane,
+                                                 LargeAcc<NB, H, KW>& acc) {
+  using S = LargeShare<full_blocks(NB, H)>;
+  constexpr int P = large_pitch(NB), C = S::count;
   const double* __restrict__ p = sY + 4 * (lane >> 4) * P + (lane & 15);
+  const double* __restrict__ pr = sY + 4 * (lane >> 4) * P + 16 * (NB - 1) + (lane & 3);
   const double* __restrict__ pw = sW + 4 * (lane >> 4);
   // Requested ahead of their use: the operands of the next group of frames and the weights of the next class, whatever the
-  // masks say (an unused read costs less than a wait; 4 x 4 tiles: the registers allow the weights only).
-  constexpr bool kAheadOps = NB < 4;
+  // masks say (an unused read costs less than a wait; 4 x 4 tiles, and 3 x 3 with a rest: the registers allow the weights only).
+  constexpr bool kAheadOps = NB < 4 && (NB < 3 || H == 0);
   double l[2][4], b[2][C][4];
+  double x[H > 0 ? 4 : 1], y[H > 0 ? H : 1][4];           // the last block's: rows, columns
   auto operands = [&](int slot, int g) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -204,6 +273,14 @@ __device__ __forceinline__ void accumulate_large(const double* __restrict__ sY, 
     double2 w[2][2];
     w[0][0] = *reinterpret_cast<const double2*>(pw + 16 * g);
     w[0][1] = *reinterpret_cast<const double2*>(pw + 16 * g + 2);
+    if constexpr (H > 0) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        x[s] = p[(16 * g + s) * P + 16 * role.rest_row];
+#pragma unroll
+        for (int h = 0; h < H; ++h) y[h][s] = pr[(16 * g + s) * P + 4 * h];
+      }
+    }
     if constexpr (kAheadOps && g < 3) operands(cur ^ 1, g + 1);
     unsigned mask = (masks >> (8 * g)) & 0xffu;
     static_for<0, KW>([&](auto KI) {
@@ -217,9 +294,18 @@ __device__ __forceinline__ void accumulate_large(const double* __restrict__ sY, 
         const double a[4] = {w0.x * l[cur][0], w0.y * l[cur][1], w1.x * l[cur][2], w1.y * l[cur][3]};
 #pragma unroll
         for (int r = 0; r < C; ++r) {
-          if (r < LargeShare<NB>::full || class_on((unsigned)role.groups[r], g)) {
+          if (r < S::full || class_on((unsigned)role.groups[r], g)) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) acc[k][r] = mfma_f64(a[s], b[cur][r][s], acc[k][r]);
+            for (int s = 0; s < 4; ++s) acc.full[k][r] = mfma_f64(a[s], b[cur][r][s], acc.full[k][r]);
+          }
+        }
+        if constexpr (H > 0) {
+          if (class_on((unsigned)role.rest_groups, g)) {
+            const double v[4] = {w0.x * x[0], w0.y * x[1], w1.x * x[2], w1.y * x[3]};
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+              for (int s = 0; s < 4; ++s) acc.rest[k][h] = mfma4_f64(v[s], y[h][s], acc.rest[k][h]);
           }
         }
       }
@@ -236,16 +322,32 @@ __host__ __device__ constexpr int large_red_classes(int K, int NB) {
   return room < K ? room : K;
 }
 __host__ __device__ constexpr int upper_tile(int i, int j, int NB) { return i * NB - i * (i - 1) / 2 + (j - i); }   // i <= j
-template <int NB, int KW, int BATCH>
-__device__ __forceinline__ void reduce_large(const double4v (&acc)[KW][LargeShare<NB>::count], const LargeRole<NB>& role,
+template <int NB, int H, int KW, int BATCH>
+__device__ __forceinline__ void reduce_large(const LargeAcc<NB, H, KW>& acc, const LargeRole<NB, H>& role,
                                              double* __restrict__ red, double* __restrict__ out, int D, int lane) {
-  constexpr int C = LargeShare<NB>::count, kClass = kRedTile * large_tiles(NB);
+  using S = LargeShare<full_blocks(NB, H)>;
+  constexpr int C = S::count, kClass = kRedTile * large_tiles(NB);
+  static_assert(S::phases >= 2, "the last block's sums join in the first two");
   const int row = lane >> 4, col = lane & 15, M = num_items(D);
 #pragma unroll
   for (int k0 = 0; k0 < KW; k0 += BATCH) {
     __syncthreads();
 #pragma unroll
-    for (int ph = 0; ph < LargeShare<NB>::phases; ++ph) {
+    for (int ph = 0; ph < S::phases; ++ph) {
+      if constexpr (H > 0) {
+        if (role.rest_phase == ph) {
+          double* __restrict__ dst = red + kRedTile * upper_tile(role.rest_row, NB - 1, NB) + 17 * (4 * ((lane >> 2) & 3) + row) + (lane & 3);
+#pragma unroll
+          for (int c = 0; c < BATCH; ++c)
+            if (k0 + c < KW) {
+#pragma unroll
+              for (int h = 0; h < H; ++h) {
+                const double x = acc.rest[k0 + c < KW ? k0 + c : 0][h];
+                dst[c * kClass + 4 * h] = ph == 0 ? x : dst[c * kClass + 4 * h] + x;
+              }
+            }
+        }
+      }
 #pragma unroll
       for (int r = 0; r < C; ++r) {
         if (role.phase[r] == ph) {
@@ -258,7 +360,7 @@ __device__ __forceinline__ void reduce_large(const double4v (&acc)[KW][LargeShar
             if (k0 + c < KW) {
 #pragma unroll
               for (int v = 0; v < 4; ++v) {
-                const double x = acc[k0 + c < KW ? k0 + c : 0][r][v];
+                const double x = acc.full[k0 + c < KW ? k0 + c : 0][r][v];
                 dst[c * kClass + v * step] = ph == 0 ? x : dst[c * kClass + v * step] + x;
               }
             }
@@ -299,13 +401,15 @@ __device__ __forceinline__ void reduce_large(const double4v (&acc)[KW][LargeShar
 // pass 122 us (181).  Ways there: frames through LDS with two barriers per tile 274 us, every lane all classes; loads under a
 // branch (waited for at its end) 258; masks through the scalar path, W two tiles ahead, no priorities 249.
 // ----------------------------------------------------------------------------------------------
+// Wavefronts per SIMD: one where the accumulators of two would not fit (25 to 32 channels, 7 or 8 classes: 128 to 192 registers and
+// as many again for operands; 25 channels, 8 classes 2.09 ms with one, 2.46 with two and 120 spilled registers).
 constexpr int pass_waves_per_simd(int K, int NB) { return NB == 4 && K > 6 ? 1 : 2; }
 __host__ __device__ constexpr int large_lds_doubles(int K, int NB, bool final_pass) {
   const int fixed = 2 * K + kWave * K;                      // constants and counts
   return fixed + (final_pass ? 4 * (K + 1) * kWave : 2 * (kWave * large_pitch(NB) + K * kWave));
 }
 
-template <int K, int NB, bool FINAL>
+template <int K, int NB, int H, bool FINAL>
 __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) void em_pass_large(
     gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ masks,
     const int32_t* __restrict__ T_len,
@@ -313,7 +417,7 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
     double* __restrict__ part, double* __restrict__ npart, float* __restrict__ gamma, uint32_t* __restrict__ status,
     int F, int Tmax, int D, ChunkMap cmap, unsigned block0) {
   extern __shared__ __attribute__((aligned(16))) double lds_large[];
-  constexpr int P = large_pitch(NB), NT = large_tiles(NB), C = LargeShare<NB>::count;
+  constexpr int P = large_pitch(NB), NF = full_blocks(NB, H);
   constexpr int kBuf = FINAL ? 0 : kWave * P + K * kWave;   // one buffer: weights, then the tile
   constexpr int kRows = (K + 3) / 4;                        // classes of a lane row in the posterior
   constexpr unsigned kmask = (1u << K) - 1u;
@@ -342,12 +446,9 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
   float* __restrict__ grow = FINAL ? gamma + ((long)s * K * F + f) * Tmax : nullptr;
   const long gk = (long)F * Tmax;
 
-  const LargeRole<NB> role(wave);
-  double4v acc[FINAL ? 1 : K][C];
-#pragma unroll
-  for (int k = 0; k < (FINAL ? 1 : K); ++k)
-#pragma unroll
-    for (int r = 0; r < C; ++r) acc[k][r] = double4v{0.0, 0.0, 0.0, 0.0};
+  const LargeRole<NB, H> role(wave);
+  LargeAcc<NB, H, FINAL ? 1 : K> acc;
+  acc.clear();
   for (int x = threadIdx.x; x < kWave * K; x += kWave * kLargeWaves) sN[x] = 0.0;
   if (threadIdx.x < K)
     sC[threadIdx.x] = cf ? make_double2(cmant[sf * K + threadIdx.x], (double)cexp[sf * K + threadIdx.x])
@@ -391,19 +492,29 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
   if (tile < tile_hi) {
     LargeFrames<NB> frames;
     frames.request(Yrow, abrow, tile * kWave + 16 * wave + n, T, D, g);
-    // W comes from memory tile by tile, kRing tiles ahead of its use, across the classes (behind the last class: the same
+    // W comes from memory piece by piece (its tiles in their order, of those of a last block of few channels 4 rows at a time,
+    // which every group of 4 lanes has), kRing pieces ahead of their use, across the classes (behind the last class: the same
     // again) and from one tile of frames to the next: a register set is refilled when its products have been issued
-    constexpr int kRing = NB == 4 ? 5 : NB == 3 && K <= 6 && !FINAL ? 6 : 3;
+    constexpr int NM = large_tiles(NF), NT = NM + (H > 0 ? NB * H : 0);
+    // (as far as registers allow: 24 channels, 3 iterations, 6 segments, 2 classes, 900 frames 1589 us with 3 ahead, 1544 with 6, 6
+    // classes, 100 frames 932 and 905, one segment of 5 classes the same; 28 channels, 6 classes: 7 ahead spill in the loop,
+    // 1.52 ms, 2 ahead 1.27)
+    constexpr bool kAhead6 = NT == 6 && H == 0 && K <= 6 && !FINAL, kAhead2 = NB == 4 && H > 0 && K >= 4 && K <= 6;
+    constexpr int kRing = kAhead2 ? 2 : kAhead6 ? 6 : NT % 5 == 0 ? 5 : NT % 7 == 0 ? 7 : 3;
     static_assert(NT % kRing == 0, "a class starts with the first register set");
+    const int rest_lane = 2 * ((lane & 3) - n);             // from the lane's place in a tile to the first 4 rows'
     double2v w[kRing][2];
-    auto fetch = [&](double2v (&dst)[2], const double* __restrict__ c, int tl) {
-      dst[0] = *reinterpret_cast<const double2v*>(c + 256 * tl);
-      dst[1] = *reinterpret_cast<const double2v*>(c + 256 * tl + 128);
+    auto fetch = [&](double2v (&dst)[2], const double* __restrict__ c, auto TI) {
+      constexpr int t = decltype(TI)::value, rest = t < NM ? 0 : t - NM, rh = H > 0 ? H : 1;
+      constexpr int at = t < NM ? 256 * t : 256 * (NM + rest / rh) + 8 * (rest % rh);
+      const double* __restrict__ src = t < NM ? c + at : c + rest_lane + at;
+      dst[0] = *reinterpret_cast<const double2v*>(src);
+      dst[1] = *reinterpret_cast<const double2v*>(src + 128);
     };
     auto fetch_first = [&](unsigned m) {                    // the first tiles of the first class of this wavefront's frames
       const unsigned own = (m >> (8 * wave)) & kmask;
       const double* __restrict__ c = cf + (long)(own != 0u ? __builtin_ctz(own) : 0) * large_coef(NB);
-      static_for<0, kRing>([&](auto TI) { fetch(w[TI.value], c, TI.value); });
+      static_for<0, kRing>([&](auto TI) { fetch(w[TI.value], c, TI); });
     };
     if (cf) fetch_first(mq);
     int buf = 0;
@@ -445,26 +556,49 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
             const double* __restrict__ cn = cf + (long)kn * large_coef(NB);
             double qs = 0.0;
             double4v z[2];
-            static_for<0, NB>([&](auto II) {
+            auto refill = [&](auto TI) {
+              constexpr int t = decltype(TI)::value, ta = t + kRing;
+              __builtin_amdgcn_sched_barrier(0);            // (the scheduler would put all of a class's loads in one place)
+              fetch(w[t % kRing], ta < NT ? ck : cn, std::integral_constant<int, (ta < NT ? ta : ta - NT)>{});
+            };
+            static_for<0, NF>([&](auto II) {
               constexpr int i = II.value;
               z[i & 1] = double4v{0.0, 0.0, 0.0, 0.0};
               static_for<0, i + 1>([&](auto JI) {
-                constexpr int j = JI.value, tl = i * (i + 1) / 2 + j, ta = tl + kRing;
+                constexpr int j = JI.value, tl = i * (i + 1) / 2 + j;
                 const double2v w0 = w[tl % kRing][0], w1 = w[tl % kRing][1];
                 z[i & 1] = mfma_f64(w0.x, u[j][0], z[i & 1]);
                 z[i & 1] = mfma_f64(w0.y, u[j][1], z[i & 1]);
                 z[i & 1] = mfma_f64(w1.x, u[j][2], z[i & 1]);
                 z[i & 1] = mfma_f64(w1.y, u[j][3], z[i & 1]);
-                __builtin_amdgcn_sched_barrier(0);          // (the scheduler would put all of a class's loads in one place)
-                fetch(w[tl % kRing], ta < NT ? ck : cn, ta < NT ? ta : ta - NT);
+                refill(std::integral_constant<int, tl>{});
                 if constexpr (i > 0 && j == 0) {            // the row before: its products are done by now
 #pragma unroll
                   for (int v = 0; v < 4; ++v) qs = fma(z[(i - 1) & 1][v], z[(i - 1) & 1][v], qs);
                 }
               });
             });
+            if constexpr (H > 0) {                          // lane row g: rows 4 h + g of the last block
+              double zr[H];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) qs = fma(z[(NB - 1) & 1][v], z[(NB - 1) & 1][v], qs);
+              for (int h = 0; h < H; ++h) zr[h] = 0.0;
+              static_for<0, NB * H>([&](auto RI) {
+                constexpr int j = RI.value / H, h = RI.value % H, tl = NM + RI.value;
+                const double2v w0 = w[tl % kRing][0], w1 = w[tl % kRing][1];
+                zr[h] = mfma4_f64(w0.x, u[j][0], zr[h]);
+                zr[h] = mfma4_f64(w0.y, u[j][1], zr[h]);
+                zr[h] = mfma4_f64(w1.x, u[j][2], zr[h]);
+                zr[h] = mfma4_f64(w1.y, u[j][3], zr[h]);
+                refill(std::integral_constant<int, tl>{});
+              });
+#pragma unroll
+              for (int v = 0; v < 4; ++v) qs = fma(z[(NF - 1) & 1][v], z[(NF - 1) & 1][v], qs);
+#pragma unroll
+              for (int h = 0; h < H; ++h) qs = fma(zr[h], zr[h], qs);
+            } else {
+#pragma unroll
+              for (int v = 0; v < 4; ++v) qs = fma(z[(NF - 1) & 1][v], z[(NF - 1) & 1][v], qs);
+            }
             sQ[k * kWave + 4 * n + g] = qs;                 // (added up by the reader: no chain of lane permutes per class)
             k = kn;
             ck = cn;
@@ -556,7 +690,7 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
         __syncthreads();                                 // every frame and its weights are in place
         if (cf) fetch_first(next < tile_hi ? mnext : mq);
         __builtin_amdgcn_s_setprio(0);
-        accumulate_large<NB, K>(sT, sW, role, mq, lane, acc);
+        accumulate_large<NB, H, K>(sT, sW, role, mq, lane, acc);
         __builtin_amdgcn_s_setprio(2);
         buf ^= 1;
       }
@@ -568,7 +702,7 @@ __global__ __launch_bounds__(kWave * kLargeWaves, pass_waves_per_simd(K, NB)) vo
     }
   }
   if constexpr (!FINAL) {
-    reduce_large<NB, K, large_red_classes(K, NB)>(acc, role, sBuf, part + (long)block * (2 * K) * num_items(D), D, lane);
+    reduce_large<NB, H, K, large_red_classes(K, NB)>(acc, role, sBuf, part + (long)block * (2 * K) * num_items(D), D, lane);
     // class counts: the 64 frame columns in their order (written before the barriers of the reduction)
     if (threadIdx.x < K) {
       double sum = 0.0;
@@ -818,20 +952,22 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
 // ----------------------------------------------------------------------------------------------
 // Masked covariances, 9 <= D <= 32: the sums of the EM pass with two weights per frame, gamma of the target and the sum of the
 // others.  Grid: blockIdx.x = chunk + C * (f + F * s).  Output: part[chunk][2][m][2] (0: target, 1: background).
-// Bound: the fp64 matrix rate (24 channels: 48 products of 64 cycles per 16 frames, 75 us for 513 x 1500); the next tile is
-// requested before the sums.  513 x 1500 frames of 24 channels 164 -> 109 us (a lane with a few items, formed on the vector units,
-// and a partial tile per wavefront at the end); whole call, 4 to 6 classes: 9 channels 175 -> 99 us, 16 208 -> 116, 24 247 -> 192,
-// 32 484 -> 297 (17 to 32 channels: some 40 us of it are the candidates' powers), 250 frames of 24 channels 139 -> 74.
+// Bound: the fp64 matrix rate (24 channels: 48 products of 64 cycles per 16 frames, 63 us for 513 x 1500 by the counters); the
+// next tile is requested before the sums.  513 x 1500 frames of 24 channels 164 -> 109 us (a lane with a few items, formed on
+// the vector units, and a partial tile per wavefront at the end); whole call, 4 to 6 classes: 9 channels 175 -> 99 us, 16
+// 208 -> 116, 24 247 -> 192, 32 484 -> 297 (both sides with a candidate's powers on all threads), 250 frames of 24 channels
+// 139 -> 74.  4 H columns of the last block instead of 16: 9 channels 102 -> 87 us, 12 119 -> 111, 17 177 -> 166, 25 276 -> 253
+// (513 x 1560).
 // ----------------------------------------------------------------------------------------------
 __host__ __device__ constexpr int cov_lds_doubles(int NB) { return 2 * (kWave * large_pitch(NB) + 2 * kWave); }
 
-template <int NB>
+template <int NB, int H>
 __global__ __launch_bounds__(kWave * kLargeWaves, 2) void mvdr_cov_large(
     gss_yview yv, const float* __restrict__ gamma, const int32_t* __restrict__ T_len,
     const int32_t* __restrict__ target, double* __restrict__ part, uint32_t* __restrict__ status,
     int F, int Tmax, int D, int K, ChunkMap cmap) {
   extern __shared__ __attribute__((aligned(16))) double lds_large[];
-  constexpr int P = large_pitch(NB), C = LargeShare<NB>::count;
+  constexpr int P = large_pitch(NB);
   constexpr int kBuf = kWave * P + 2 * kWave;               // one buffer: weights, then the tile
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -851,12 +987,9 @@ __global__ __launch_bounds__(kWave * kLargeWaves, 2) void mvdr_cov_large(
   const float* __restrict__ grow = gamma + ((long)s * K * F + f) * Tmax;
   const long gk = (long)F * Tmax;
 
-  const LargeRole<NB> role(wave);
-  double4v acc[2][C];
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-#pragma unroll
-    for (int r = 0; r < C; ++r) acc[k][r] = double4v{0.0, 0.0, 0.0, 0.0};
+  const LargeRole<NB, H> role(wave);
+  LargeAcc<NB, H, 2> acc;
+  acc.clear();
   const int tile_lo = chunk * tiles_per_chunk;
   int tile_hi = tile_lo + tiles_per_chunk;
   const int tile_end = (T + kWave - 1) / kWave;
@@ -894,10 +1027,10 @@ __global__ __launch_bounds__(kWave * kLargeWaves, 2) void mvdr_cov_large(
     }
     if (g < 2) sW[g * kWave + 16 * wave + n] = t < T ? (g == 0 ? wt : wb) : 0.0;
     __syncthreads();                                        // (one barrier per tile: the buffers take turns)
-    accumulate_large<NB, 2>(sT, sW, role, 0x03030303u, lane, acc);
+    accumulate_large<NB, H, 2>(sT, sW, role, 0x03030303u, lane, acc);
     buf ^= 1;
   }
-  reduce_large<NB, 2, large_red_classes(2, NB)>(acc, role, lds_large, part + (long)blockIdx.x * 4 * num_items(D), D, lane);
+  reduce_large<NB, H, 2, large_red_classes(2, NB)>(acc, role, lds_large, part + (long)blockIdx.x * 4 * num_items(D), D, lane);
 }
 
 // One workgroup per (segment, frequency), D*D active threads.  H[sf][r][d], pw[sf][r][2] as for D <= 8.
@@ -1042,14 +1175,14 @@ long large_slots(const gss_ctx* ctx, Kern kern, int lds_bytes) {
 // classes, forty rounds of workgroups, so that the launches of a group do not show.
 constexpr size_t kLargeScratch = (size_t)1 << 30;
 
-template <int K, int NB>
+template <int K, int NB, int H>
 int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
                  int D, int iters, int weight_mode, float* gamma, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int M = num_items(D);
   constexpr int lds_acc = large_lds_doubles(K, NB, false) * (int)sizeof(double);
   constexpr int lds_fin = large_lds_doubles(K, NB, true) * (int)sizeof(double);
-  if (hipFuncSetAttribute((const void*)em_pass_large<K, NB, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  if (hipFuncSetAttribute((const void*)em_pass_large<K, NB, H, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                           lds_acc) != hipSuccess)
     return GSS_EHIP;
   // the factor kernel adds the chunks of every class in LDS (up to 68 KB: 8 classes of 32 channels); one limit for every call
@@ -1058,8 +1191,8 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   if (hipFuncSetAttribute((const void*)em_factor_large<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, factor_max) != hipSuccess)
     return GSS_EHIP;
   const int tiles = (Tmax + kWave - 1) / kWave;
-  const ChunkMap acc_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, false>, lds_acc), n_sf, tiles, 1, 0, true);
-  const ChunkMap fin_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, true>, lds_fin), n_sf, tiles, 1, 0, true);
+  const ChunkMap acc_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, H, false>, lds_acc), n_sf, tiles, 1, 0, true);
+  const ChunkMap fin_map = plan_chunk_map(large_slots(ctx, em_pass_large<K, NB, H, true>, lds_fin), n_sf, tiles, 1, 0, true);
   const long wgs_acc = chunk_map_wgs(acc_map, n_sf), wgs_fin = chunk_map_wgs(fin_map, n_sf);
   if (wgs_acc > 0x7fffffffL || wgs_fin > 0x7fffffffL || n_sf * K > 0x7fffffffL) return GSS_EUNSUPPORTED;
   if ((long)S * tiles > 0x7fffffffL) return GSS_EUNSUPPORTED;
@@ -1129,7 +1262,7 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
     double* npart = (double*)(base + off.npart) - a0 * K;
     for (int it = 0; it < iters; ++it) {
       gss_profile_begin(ctx, 0, st);
-      hipLaunchKernelGGL((em_pass_large<K, NB, false>), dim3(na), block, lds_acc, st, Y, abyte, masks, T_len,
+      hipLaunchKernelGGL((em_pass_large<K, NB, H, false>), dim3(na), block, lds_acc, st, Y, abyte, masks, T_len,
                          it == 0 ? (const double*)nullptr : coef, cm, ce, part, npart, (float*)nullptr, ctx->status, F, Tmax, D,
                          acc_map, (unsigned)a0);
       gss_profile_end(ctx, 0, st);
@@ -1138,7 +1271,7 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
                          ctx->status, D, K, acc_map, weight_mode, (unsigned)p0);
       gss_profile_end(ctx, 1, st);
     }
-    hipLaunchKernelGGL((em_pass_large<K, NB, true>), dim3(nf), block, lds_fin, st, Y, abyte, masks, T_len,
+    hipLaunchKernelGGL((em_pass_large<K, NB, H, true>), dim3(nf), block, lds_fin, st, Y, abyte, masks, T_len,
                        iters == 0 ? (const double*)nullptr : coef, cm, ce, (double*)nullptr, (double*)nullptr, gamma, ctx->status,
                        F, Tmax, D, fin_map, (unsigned)f0);
   }
@@ -1149,21 +1282,28 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
 template <int K>
 int dispatch_nb(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_t* T_len, int S, int F, int Tmax,
                 int D, int iters, int weight_mode, float* gamma, hipStream_t st) {
-  if (D <= 16) return run_em_large<K, 2>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
-  if (D <= 24) return run_em_large<K, 3>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
-  return run_em_large<K, 4>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
+  const int rest = large_rest(D, K);
+  auto blocks = [&](auto NB) {
+    constexpr int nb = decltype(NB)::value;
+    return rest == 1   ? run_em_large<K, nb, 1>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st)
+           : rest == 2 ? run_em_large<K, nb, 2>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st)
+                       : run_em_large<K, nb, 0>(ctx, Y, act, T_len, S, F, Tmax, D, iters, weight_mode, gamma, st);
+  };
+  if (D <= 16) return blocks(std::integral_constant<int, 2>{});
+  if (D <= 24) return blocks(std::integral_constant<int, 3>{});
+  return blocks(std::integral_constant<int, 4>{});
 }
 
-template <int NB>
+template <int NB, int H>
 int run_mvdr_large(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const int32_t* T_len, int S, int F, int Tmax,
                    int D, int K, const int32_t* target, int32_t* ref, int ref_per_f, float2* X, hipStream_t st) {
   const long n_sf = (long)S * F;
   const int M = num_items(D);
   constexpr int lds = cov_lds_doubles(NB) * (int)sizeof(double);
-  if (hipFuncSetAttribute((const void*)mvdr_cov_large<NB>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+  if (hipFuncSetAttribute((const void*)mvdr_cov_large<NB, H>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
     return GSS_EHIP;
   const int tiles = (Tmax + kWave - 1) / kWave;
-  const ChunkMap cmap = plan_chunk_map(large_slots(ctx, mvdr_cov_large<NB>, lds), n_sf, tiles, 1, 0, true);
+  const ChunkMap cmap = plan_chunk_map(large_slots(ctx, mvdr_cov_large<NB, H>, lds), n_sf, tiles, 1, 0, true);
   const long wgs = chunk_map_wgs(cmap, n_sf);
   if (wgs > 0x7fffffffL) return GSS_EUNSUPPORTED;
   size_t o = 0;
@@ -1174,17 +1314,17 @@ int run_mvdr_large(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const i
   if (rc != GSS_OK) return rc;
   char* base = (char*)ctx->scratch;
   double* part = (double*)(base + off_part);
-  double2* H = (double2*)(base + off_H);
+  double2* filters = (double2*)(base + off_H);
   double* pw = (double*)(base + off_pw);
-  hipLaunchKernelGGL((mvdr_cov_large<NB>), dim3((unsigned)wgs), dim3(kWave * kLargeWaves), lds, st, Y, gamma, T_len,
+  hipLaunchKernelGGL((mvdr_cov_large<NB, H>), dim3((unsigned)wgs), dim3(kWave * kLargeWaves), lds, st, Y, gamma, T_len,
                      target, part, ctx->status, F, Tmax, D, K, cmap);
   const int sthreads = (D * D + 63) / 64 * 64;
-  hipLaunchKernelGGL(mvdr_solve_large, dim3((unsigned)n_sf), dim3(sthreads), 0, st, part, H, pw, ctx->status, D, cmap);
+  hipLaunchKernelGGL(mvdr_solve_large, dim3((unsigned)n_sf), dim3(sthreads), 0, st, part, filters, pw, ctx->status, D, cmap);
   gss_launch_mvdr_ref(pw, ref, ctx->status, S, F, D, ref_per_f, st);
   const int fpc = 1024;
   const int CA = (Tmax + fpc - 1) / fpc;
   if (n_sf * CA > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  hipLaunchKernelGGL(mvdr_apply_large, dim3((unsigned)(n_sf * CA)), dim3(256), 0, st, Y, H, ref, T_len, X, F, Tmax, D,
+  hipLaunchKernelGGL(mvdr_apply_large, dim3((unsigned)(n_sf * CA)), dim3(256), 0, st, Y, filters, ref, T_len, X, F, Tmax, D,
                      CA, fpc, ref_per_f);
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
