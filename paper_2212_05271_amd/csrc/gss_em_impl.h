@@ -1140,15 +1140,19 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 // ----------------------------------------------------------------------------------------------
 // Host-side plan and dispatch
 // ----------------------------------------------------------------------------------------------
-// Problems per compute unit from which on the whole-EM kernel is used.  Measured on ragged batches of 300 to 1860 frames, every
-// channel and class count: from 16 per compute unit on (8 segments of 513 bins) 5 to 8 channels take 0.4 to 0.95 times as long as
-// in chunks (1 class, 7 channels, 1860 frames 1.03), the direct layout 0.5 to 0.95 times from 8 per compute unit on.  (The line
-// was three rounds of the wavefronts that fit the chip: with fewer registers the kernel got more wavefronts and the call went back
-// to chunks, 16 segments of 640 frames, 3 iterations, 7 channels and 2 classes 262 -> 317 us, 2 channels and 8 classes 132 -> 285.)
-template <int D, int K>
-constexpr int kWholeMinPerCu = direct_layout(D, K) ? 8 : 16;
+// Problems per compute unit from which on the whole-EM kernel is used.  Against chunks, all channel and class counts, 3
+// iterations: tile layout, 8 segments of 513 bins (16 per compute unit) and more, up to 32 tiles 0.4 to 0.95 times the time
+// in ragged batches, 0.7 to 1.0 in uniform ones (8 segments of 1860 frames, 8 channels and 8 classes 1.06); longer problems of one
+// length end in a partly filled round (8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14) and wait for 12.  Direct
+// layout: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones wait
+// for 8 segments).  (The line was three rounds of the wavefronts that fit the chip: with
+// fewer registers the kernel got more wavefronts and the call went back to chunks, 16 segments of 640 frames, 3 iterations,
+// 7 channels and 2 classes 262 -> 317 us, 2 channels and 8 classes 132 -> 285.)
+constexpr int whole_min_per_cu(bool direct, int tiles) { return (direct ? 8 : 16) + (tiles <= 32 ? 0 : 8); }
 constexpr int kWholeMaxTilesAlways = 5;
-constexpr int kWholeDirectMaxTiles = 25;      // direct layout: tiles in a row up to which a pass costs less than its launches
+// Direct layout: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
+// compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
+constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
 // Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but each of them adds up and factorises for
 // itself, which costs the more the more of them share a SIMD (`load` problems per compute unit = wavefronts per SIMD), the more
 // channels there are, and where registers let two of them at most onto a SIMD, which then wait for each other's latencies.
@@ -1225,7 +1229,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   // is cut into chunks over several workgroups, one pass and one factor launch per iteration, unless it has few tiles: two
   // launches per iteration cost more than the whole EM of such a problem in one wavefront.
   const bool choose = ctx->em_whole_min_problems < 0;
-  bool whole = n_sf >= (choose ? (long)kWholeMinPerCu<D, K> * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
+  bool whole = n_sf >= (choose ? (long)whole_min_per_cu(direct_layout(D, K), tiles) * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
                (choose && tiles <= kWholeMaxTilesAlways);
   // Up to 4 channels there is the variant with four wavefronts per problem (use_quad), and with the direct layout (cheap tiles,
   // a launch costs as much as a few dozen of them) few problems go to the whole-EM kernel as well unless a pass is so long that
@@ -1235,8 +1239,10 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
     if (choose && (direct_layout(D, K) || tiles <= kWholeQuad)) {
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
-      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, tiles <= kWholeQuad ? ones_per_cu : walks_per_cu, tiles, iters);
-      if (direct_layout(D, K) && (tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles) <= kWholeDirectMaxTiles) whole = true;
+      const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
+      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, quads_per_cu, tiles, iters);
+      const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
+      if (direct_layout(D, K) && row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }
   }
   whole = iters > 0 && whole && n_sf <= 0x7fffffffL;
