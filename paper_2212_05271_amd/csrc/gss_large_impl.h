@@ -92,8 +92,8 @@ __host__ __device__ constexpr int full_blocks(int NB, int H) { return H > 0 ? NB
 
 // Tiles of the weighted sums: which of the NB (NB + 1) / 2 tiles on and above the diagonal a wavefront of the workgroup adds
 // up, over which of the four groups of 16 frames of a tile of frames.  A wavefront has one left operand (row of tiles `left`)
-// and `count` right ones; left > right is the transposed tile.  Every wavefront gets the same number of products (3, 6 and
-// 10 of them in four: three, six and ten groups x tiles), with few accumulators: 8 count K registers.  The first `full` right
+// and `count` right ones; left > right is the transposed tile.  Every wavefront gets the same number of products (1, 3, 6 and
+// 10 tiles in four: one, three, six and ten groups x tiles), with few accumulators: 8 count K registers.  The first `full` right
 // operands of every wavefront take all groups.  `phase`: when the wavefront's sums of the tile join the others' at the end
 // (0: they are the first).
 template <int NB>
