@@ -1231,6 +1231,12 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   } else if (need > ctx->scratch_cap && n_sf * K * D * D > 3500000L) {
     return GSS_ETOOBIG;
   }
+  const Offsets one = layout(1, acc_map.c_main > acc_map.c_tail ? acc_map.c_main : acc_map.c_tail);
+  if (off.end > most_scratch && one.end > most_scratch) {  // (the activity alone fills it)
+    group = 1;
+    off = one;
+    most_scratch = one.end;
+  }
   for (long groups = 2; off.end > most_scratch && group > 1; ++groups) {
     group = (n_sf + groups - 1) / groups;
     long most = 0;
