@@ -290,8 +290,8 @@ __device__ __forceinline__ bool class_on(unsigned mask, int k) {
 // wavefront's 8 rows takes 4 cycles (frames tg, tg + 8, ...: 9 cycles; calls of one segment 1 to 9 % slower).  D < 8: frames
 // tg, tg + 64 / D, ..., no padding: the rows read together are one run of memory (odd D) or start at an odd multiple of 16
 // bytes (D = 2 and 6).  Measured against 8 lane types whatever D (zero channels up to 8), 10 iterations: 48 segments of up to
-// 1000 frames and 4 classes 5 channels 3.41 -> 2.33 ms, 6 channels 3.75 -> 3.37, 7 channels 4.23 -> 4.00; 8 classes: 4
-// channels, 24 segments 3.05 -> 1.54, 32 segments of 5 channels 4.85 -> 2.70 ms (the accumulators no longer spill).
+// 1000 frames and 4 classes 5 channels 3.64 -> 2.32 ms, 6 channels 3.86 -> 3.23, 7 channels 4.51 -> 3.99; 8 classes: 4 channels,
+// 24 segments of up to 700 frames 2.35 -> 1.31, 32 segments of 5 channels 5.41 -> 2.70 ms (the accumulators no longer spill).
 constexpr int kPassWaves = 4;
 template <int D>
 struct TileLayout {

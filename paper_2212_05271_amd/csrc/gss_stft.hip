@@ -169,9 +169,9 @@ __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (
 // window had a table).  Two workgroups per compute unit are resident, held there by 128 registers and, for two units, by LDS;
 // each has one unit of samples in flight.  At 128 registers 14 (two units) or 10 (one) are spilled to scratch memory.  Ten
 // minutes of 8 channels: 504 us = 3.0 TB/s (window from the cosine table, a fifth round of the split loop for bin 256 alone:
-// 530 us; before that an even share of consecutive frames per workgroup instead of turns 583 us, one workgroup per frame,
-// 64-byte runs 722 us).  6000 frames of 8 channels 73 -> 63 us, 3000 frames of 12 channels 64 -> 59.  Three workgroups per
-// compute unit at 80 registers: 55 to 70 spilled, twice as slow.
+// 530 us, on a second card 518 and 546; before that an even share of consecutive frames per workgroup instead of turns 583 us,
+// one workgroup per frame, 64-byte runs 722 us).  6000 frames of 8 channels 73 -> 63 us, 3000 frames of 12 channels 64 -> 59.
+// Three workgroups per compute unit at 80 registers: 55 to 70 spilled, twice as slow.
 //
 // One unit per step for short calls (gss_stft): 8 channels 7.7, 10.7, 17.2 us at 130, 510, 1020 frames (two units 11.0, 12.5,
 // 17.0; one workgroup per frame 8.1, 11.2, 20.6).
