@@ -266,6 +266,78 @@ __device__ __forceinline__ void fma_bcast_chain(double (&q)[3], double c, const 
 #undef GSS_BCAST_FMA
 }
 
+// acc[b] += sum over n of w[lane n of the row] * x[b][n], n = 0 .. 15, b = 0 .. NB - 1 (1 to 4): the FMAs of fma_bcast with the
+// accumulators in turn, so that an FMA does not wait for the one before it (one accumulator: three partial sums).  Statements of
+// 16 FMAs or fewer, each with the two idle states in front (a statement may be moved up to the write of w).
+template <int NB, int n0>
+__device__ __forceinline__ void fma_bcast_rows_4(double (&acc)[NB], double w, const double (&x)[NB][16]) {
+#define GSS_ROW_FMA(a, p, n) "v_fmac_f64_dpp %[a" #a "], %[w], %[x" #a #p "] row_newbcast:%[n" #n "] row_mask:0xf bank_mask:0xf\n\t"
+#define GSS_ROW_IN(b) [x##b##0] "v"(x[b][n0]), [x##b##1] "v"(x[b][n0 + 1]), [x##b##2] "v"(x[b][n0 + 2]), [x##b##3] "v"(x[b][n0 + 3])
+#define GSS_ROW_LANES [n0] "n"(n0), [n1] "n"(n0 + 1), [n2] "n"(n0 + 2), [n3] "n"(n0 + 3)
+  if constexpr (NB == 4)
+    asm("s_nop 1\n\t"
+        GSS_ROW_FMA(0, 0, 0) GSS_ROW_FMA(1, 0, 0) GSS_ROW_FMA(2, 0, 0) GSS_ROW_FMA(3, 0, 0)
+        GSS_ROW_FMA(0, 1, 1) GSS_ROW_FMA(1, 1, 1) GSS_ROW_FMA(2, 1, 1) GSS_ROW_FMA(3, 1, 1)
+        GSS_ROW_FMA(0, 2, 2) GSS_ROW_FMA(1, 2, 2) GSS_ROW_FMA(2, 2, 2) GSS_ROW_FMA(3, 2, 2)
+        GSS_ROW_FMA(0, 3, 3) GSS_ROW_FMA(1, 3, 3) GSS_ROW_FMA(2, 3, 3) GSS_ROW_FMA(3, 3, 3)
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3])
+        : [w] "v"(w), GSS_ROW_IN(0), GSS_ROW_IN(1), GSS_ROW_IN(2), GSS_ROW_IN(3), GSS_ROW_LANES);
+  else if constexpr (NB == 3)
+    asm("s_nop 1\n\t"
+        GSS_ROW_FMA(0, 0, 0) GSS_ROW_FMA(1, 0, 0) GSS_ROW_FMA(2, 0, 0) GSS_ROW_FMA(0, 1, 1) GSS_ROW_FMA(1, 1, 1) GSS_ROW_FMA(2, 1, 1)
+        GSS_ROW_FMA(0, 2, 2) GSS_ROW_FMA(1, 2, 2) GSS_ROW_FMA(2, 2, 2) GSS_ROW_FMA(0, 3, 3) GSS_ROW_FMA(1, 3, 3) GSS_ROW_FMA(2, 3, 3)
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2])
+        : [w] "v"(w), GSS_ROW_IN(0), GSS_ROW_IN(1), GSS_ROW_IN(2), GSS_ROW_LANES);
+  else
+    asm("s_nop 1\n\t"
+        GSS_ROW_FMA(0, 0, 0) GSS_ROW_FMA(1, 0, 0) GSS_ROW_FMA(0, 1, 1) GSS_ROW_FMA(1, 1, 1)
+        GSS_ROW_FMA(0, 2, 2) GSS_ROW_FMA(1, 2, 2) GSS_ROW_FMA(0, 3, 3) GSS_ROW_FMA(1, 3, 3)
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1])
+        : [w] "v"(w), GSS_ROW_IN(0), GSS_ROW_IN(1), GSS_ROW_LANES);
+#undef GSS_ROW_FMA
+#undef GSS_ROW_IN
+#undef GSS_ROW_LANES
+}
+template <int NB>
+__device__ __forceinline__ void fma_bcast_rows(double (&acc)[NB], double w, const double (&x)[NB][16]) {
+  static_assert(NB >= 1 && NB <= 4, "blocks of 16 entries");
+  if constexpr (NB == 1) {
+    double t[3] = {acc[0], 0.0, 0.0};
+    fma_bcast_chain<16>(t, w, x[0]);
+    acc[0] = t[0] + (t[1] + t[2]);
+  } else {
+    fma_bcast_rows_4<NB, 0>(acc, w, x);
+    fma_bcast_rows_4<NB, 4>(acc, w, x);
+    fma_bcast_rows_4<NB, 8>(acc, w, x);
+    fma_bcast_rows_4<NB, 12>(acc, w, x);
+  }
+}
+
+// Sums of N per-lane doubles over the four rows of 16 lanes (lane l of every row belongs together), in a fixed order: two
+// exchange steps, at each of which a lane keeps one value of every pair, by the instructions that swap halves (rows) of two
+// registers.  Afterwards lane l of row q holds in v[j] the total of value row_sum_index(q, j) (where that is below N).
+__device__ __forceinline__ int row_sum_index(int q, int j) { return 4 * j + ((q & 1) << 1 | q >> 1); }
+template <int N>
+__device__ __forceinline__ void row_sums(double (&v)[N]) {
+  auto step = [&](auto CNT, auto HALVES) {
+    constexpr int n = decltype(CNT)::value;
+    static_for<0, (n + 1) / 2>([&](auto MI) {
+      constexpr int m = MI.value;
+      const double a = v[2 * m], b = 2 * m + 1 < n ? v[2 * m + 1 < n ? 2 * m + 1 : 0] : 0.0;
+      unsigned al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+      if constexpr (decltype(HALVES)::value) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+        v[m] = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+      } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false), hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+        v[m] = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+      }
+    });
+  };
+  step(std::integral_constant<int, N>{}, std::true_type{});
+  step(std::integral_constant<int, (N + 1) / 2>{}, std::false_type{});
+}
+
 // Wave-uniform test of bit k of `mask`, re-evaluated from the one scalar register that holds the mask at every
 // use (the empty asm statement keeps the compiler from caching the K booleans in scalar register pairs).
 __device__ __forceinline__ bool class_on(unsigned mask, int k) {
@@ -398,81 +470,6 @@ __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, c
   if constexpr (L::rest > 0) {
     if (tg < L::rest) frame(tg + L::steps * L::next);
   }
-}
-
-// The same for the classes of `mask` only (wave-uniform): the weights of the other classes are zero in every
-// frame of the tile (their columns of sW hold stale values that are read and never used).  A step takes the entries of NF
-// frames, requests the rows of the next step from LDS, and then each class of the mask adds its products under one uniform
-// branch, so the LDS latency is covered by the current step's arithmetic.  Two frames per step where their entries fit into
-// registers beside up to 40 accumulators: a test is three scalar instructions and a branch, and a wavefront issues one
-// instruction in five cycles whatever its kind.  Ten minutes of 8 channels, 200 segments: 62.7 -> 61.4 ms.
-template <int D, int KW, int WS>
-__device__ __forceinline__ void accumulate_tile_masked(const double* __restrict__ sY, const double* __restrict__ sW,
-                                                       int tg, int i, unsigned mask, double (&acc)[D][KW]) {
-  using L = TileLayout<D>;
-  constexpr int NF = D * KW <= 40 ? 2 : 1;
-  // a row pointer per operand and one weight pointer; every access of a full step is one of them plus a constant
-  // (the constant goes into the offset field of the LDS instruction)
-  const double* __restrict__ py[L::reads];
-#pragma unroll
-  for (int n = 0; n < L::reads; ++n) py[n] = sY + L::first(tg) * L::row + tile_operand<D>(i, n);
-  const double* __restrict__ pw = sW + L::first(tg) * WS;
-  double2 y[NF][L::reads];
-  auto fetch = [&](auto JF, auto CNT) {                      // the rows of frames j .. j + cnt - 1 of the group
-    static_for<0, decltype(CNT)::value>([&](auto UI) {
-      constexpr int u = UI.value, o = (decltype(JF)::value + u) * L::next * L::row;
-#pragma unroll
-      for (int n = 0; n < L::reads; ++n) y[u][n] = *reinterpret_cast<const double2*>(py[n] + o);
-    });
-  };
-  // a group without a frame in the last step reads its first row there, and adds nothing
-  const int last = tg < L::rest ? L::steps * L::next : 0;
-  auto step = [&](auto JI, auto CNT, auto REST) {
-    constexpr int j = decltype(JI)::value, cnt = decltype(CNT)::value;
-    constexpr bool rest = decltype(REST)::value;
-    double e[cnt][D], w[cnt][KW];
-    static_for<0, cnt>([&](auto UI) {
-      constexpr int u = UI.value;
-      const double* __restrict__ wr = pw + (rest ? last : (j + u) * L::next) * WS;
-      if constexpr (KW % 2 == 0 && WS % 2 == 0) {
-#pragma unroll
-        for (int k = 0; k < KW; k += 2) {
-          const double2 w2 = *reinterpret_cast<const double2*>(wr + k);
-          w[u][k] = w2.x;
-          w[u][k + 1] = w2.y;
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < KW; ++k) w[u][k] = wr[k];
-      }
-      tile_entries<D>(y[u], e[u]);
-    });
-    constexpr int j2 = j + cnt, left = L::steps - j2;
-    if constexpr (!rest && left > 0) {
-      fetch(std::integral_constant<int, j2>{}, std::integral_constant<int, (left < NF ? left : NF)>{});
-    } else if constexpr (!rest && L::rest > 0) {
-#pragma unroll
-      for (int n = 0; n < L::reads; ++n) y[0][n] = *reinterpret_cast<const double2*>(py[n] + last * L::row);
-    }
-    if (!rest || tg < L::rest) {
-      static_for<0, KW>([&](auto KI) {
-        constexpr int k = KI.value;
-        if (class_on(mask, k)) {
-#pragma unroll
-          for (int u = 0; u < cnt; ++u)
-#pragma unroll
-            for (int n = 0; n < D; ++n) acc[n][k] = fma(w[u][k], e[u][n], acc[n][k]);
-        }
-      });
-    }
-  };
-  constexpr int nfull = L::steps / NF, odd = L::steps % NF;
-  fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, (L::steps < NF ? L::steps : NF)>{});
-  static_for<0, nfull>([&](auto SI) {
-    step(std::integral_constant<int, NF * SI.value>{}, std::integral_constant<int, NF>{}, std::false_type{});
-  });
-  if constexpr (odd > 0) step(std::integral_constant<int, NF * nfull>{}, std::integral_constant<int, odd>{}, std::false_type{});
-  if constexpr (L::rest > 0) step(std::integral_constant<int, L::steps>{}, std::integral_constant<int, 1>{}, std::true_type{});
 }
 
 // Reduction of the per-lane accumulators of a workgroup of kPassWaves wavefronts into packed partial

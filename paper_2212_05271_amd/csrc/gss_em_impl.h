@@ -59,56 +59,69 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // workgroup barrier inside the tile loop.
 //
 // Class coefficients.  The packed coefficients of B_k^-1 (D * D reals per class) are the same for every
-// frame.  They live in vector registers for the whole kernel, 16 per register: lane l of every row of 16
-// lanes holds entry 16 r + (l mod 16) of register r, and the FMAs of phase 1 read them with the
+// frame.  Lane l of every row of 16 lanes holds entry 16 r + (l mod 16) of register r, and the FMAs of phase 1 read them with the
 // row-broadcast lane selector of the double-precision vector FMA (v_fmac_f64 ... row_newbcast:n takes its
-// first factor from lane n of the executing lane's row).  No scalar loads and no LDS traffic in the inner
-// loop; D = 8, K = 5 needs 20 register pairs.  When K * ceil(D*D/16) exceeds kResidentRegs the registers
-// of one 16-entry block are fetched from an LDS copy of the coefficients at the start of the block instead.
+// first factor from lane n of the executing lane's row).  No scalar loads in the inner loop.  They are resident for the whole
+// kernel where registers have room beside the outer product (resident_coefs); otherwise a class's registers are fetched from an
+// LDS copy in front of its FMAs (8 channels, 5 classes: 64 segments 14.5 ms; resident, 10 registers spilled, 14.7; fetched a class
+// ahead 14.5).
 //
 // Classes that are not active anywhere in a tile (activity mask, Eq. (5)) have posterior 0 in all of its
 // frames and add nothing to any sum: the tile's arithmetic for them is skipped under wave-uniform branches.
 //
-// Phase 1 (lane = frame): the Hermitian outer product is generated 16 entries at a time in fp64, and
-//   q_k = <coef_k, y y^H> takes 16 row-broadcast FMAs per live class and block; posterior over the active
-//   classes; weights w_k = gamma_k / q_k.  y (as fp64) and w go to the wavefront's LDS tile.
-// Phase 2 (lane = (frame group, lane type), TileLayout): a lane reads the channels of its type and the weights for the frames
-//   of its group, forms its D entries exactly and accumulates R_k[e] += w_k * P[e] in fp64.  The accumulators stay in
-//   registers across the tiles of the chunk.  The frames of the next live tile are requested from memory before phase 2
-//   (stream_tiles): a wavefront used to wait 1300 of the 9700 cycles of a tile for them (8 channels, 5 classes, two
-//   wavefronts per SIMD); 200 segments of 8 channels 64.2 -> 62.7 ms.
+// Phase 1 (lane = frame): the Hermitian outer product P in fp64, all D * D reals in registers; q_k = <coef_k, P> takes D * D
+//   row-broadcast FMAs per live class; posterior over the active classes; weights w_k = gamma_k / q_k.
+// Phase 2 (lane = (row of 16 frames, entry of a block of 16)): the blocks of P are transposed within their rows of 16 lanes through
+//   8 KB of LDS, and lane (row, e) adds w_k[n] * P[e][n] over the 16 frames n of its row: the weights are where they were computed,
+//   in lane n of the row, and the FMAs take them through the same row selector.  An accumulator per class and block, which stays
+//   in its register across the tiles; nothing is formed twice, and no weight goes through LDS.
+//   The frames of the next live tile are requested from memory before phase 2 (stream_tiles): a wavefront used to wait 1300 of
+//   the 9700 cycles of a tile for them (8 channels, 5 classes, two wavefronts per SIMD).
+//
+// Bound: the vector ALUs, with the clock held at 2.1 GHz by their power (2.4 GHz under a fill kernel), so what counts is the number
+// of vector instructions, not the waits.  With y and the weights in LDS and the products formed again from y by 8 lane types in
+// phase 2 a tile of 8 channels took about 830 of them, now 700 (of which the end of an iteration, shared by 17 tiles, is 90).
+// Times, us: 64 segments of up to 1875 frames, 8 channels, 5 classes, 15 iterations 15931 -> 14517; 3 segments of up to 701, 6
+// channels, 4 classes, 10 iterations 430 -> 350; 24 segments of up to 700, 5 iterations, 8 channels and 2 / 5 / 8 classes 730 -> 725
+// / 1079 -> 978 / 1971 -> 1281 (the accumulators no longer spill), 5 channels and 5 classes 653 -> 520.  Fewer tests of the class
+// mask (20 instead of 55 per tile, over 32 FMAs each) left the times as they were.
 //
 // Grid: blockIdx.x = chunk + C * (f + F * s).  A chunk is `tiles_per_chunk` tiles of 64 frames.
 // ----------------------------------------------------------------------------------------------
 
-// Doubles per frame row of the weight tile in LDS: odd, which spreads the rows over the banks, or an even number of classes
-// without padding, whose weights phase 2 reads in pairs (5 to 7 channels: 1 to 2 % less time; 8 channels: 1 % more, and
-// 24 % with 8 classes, where the compiler runs out of registers; 4 channels 0.7 % more).
-__host__ __device__ constexpr int weight_stride(int D, int K) { return D >= 5 && D <= 7 && K % 2 == 0 ? K : K | 1; }
-// Doubles of a wavefront's LDS region: the tile of 64 frame rows and its weights, or the rows of the reduction over the frame
-// groups that use the same memory after the last tile.
-template <int D>
-__host__ __device__ constexpr int tile_region_doubles(int WS) {
-  const int tile = kWave * TileLayout<D>::row + kWave * WS, red = reduce_wave_doubles(D);
-  return ((tile > red ? tile : red) + 1) / 2 * 2;
-}
-
-// Registers (pairs) of 16 coefficients per class, and how many of them a wavefront keeps resident.
-__host__ __device__ constexpr int coef_regs(int D) { return (D * D + 15) / 16; }
-constexpr int kResidentRegs = 20;
-
 // Few channels: the lane that owns a frame in phase 1 has all D * D entries of its outer product in registers
 // anyway (one block of at most 16), so it adds w_k * P[e] to K * D * D accumulators of its own, and there is no
-// LDS tile and no phase 2.  Used
-// when the accumulators fit in registers beside phase 1.  The accumulators are acc[k][e] then (packed order)
-// instead of acc[slot n][k], and the sums over the lanes are taken at the end of the pass (transpose_reduce).
+// phase 2.  Used when the accumulators fit in registers beside phase 1.  The accumulators are acc[k][e] then (packed order),
+// and the sums over the lanes are taken at the end of the pass (transpose_reduce).
 constexpr int kDirectMaxAcc = 80;
 constexpr int kPrefetchMaxAcc = 64;            // the whole-EM kernel requests the next tile ahead up to this many
 __host__ __device__ constexpr bool direct_layout(int D, int K) { return D <= 4 && D * D * K <= kDirectMaxAcc; }
+
+// Tile layout: the D * D packed entries of the outer product in blocks of 16, which phase 2 takes transposed (lane = entry of a
+// block), and up to 4 entries left over (6 and 7 channels), which a lane adds up for its own frame as in the direct layout.
+template <int D>
+struct TileSums {
+  static constexpr int E = D * D;
+  static constexpr int rest = E % 16 <= 4 ? E % 16 : 0;
+  static constexpr int blocks = (E - rest + 15) / 16;
+};
+// Doubles between the rows (entries) of a block of 16 x 64 in LDS: a lane writes its frame's entries, 512 bytes in a row for the
+// wavefront, and reads two frames of its entry at a time; 16 rows 528 bytes apart are 16 bytes apart modulo 256, which is what
+// LDS delivers per cycle.
+constexpr int kBlockRow = kWave + 2;
+constexpr int kBlockDoubles = 16 * kBlockRow;
+
+// Registers (pairs) of 16 coefficients per class, and whether a wavefront keeps them all resident: they have to fit beside the outer
+// product, the accumulators, counts, posterior terms and partial sums, with some 40 registers left of 256 for everything else.
+__host__ __device__ constexpr int coef_regs(int D) { return (D * D + 15) / 16; }
+__host__ __device__ constexpr bool resident_coefs(int D, int K) {
+  return direct_layout(D, K) || 2 * (D * D + K * coef_regs(D) + 3 * K + 3 + K * coef_regs(D)) <= 215;
+}
+
 template <int D, int K>
 struct PassAcc {
   static constexpr bool direct = direct_layout(D, K);
-  static constexpr int rows = direct ? K : D, cols = direct ? D * D : K;
+  static constexpr int rows = direct ? K : TileSums<D>::blocks + TileSums<D>::rest, cols = direct ? D * D : K;
   using type = double[rows][cols];
 };
 template <int A, int B>
@@ -143,6 +156,7 @@ __device__ __forceinline__ void load_tile_regs(TileRegs<D>& r, const float2* __r
 // One tile of 64 frames starting at frame t0.  `tmask` (wave-uniform) is the tile's activity mask.
 //   creg : the resident coefficient registers [K * coef_regs(D)] (used when RESIDENT)
 //   sC   : LDS copy of the coefficients, [K * coef_regs(D)][16] doubles (used otherwise)
+//   sY   : the wavefront's LDS for a block of 16 entries of its 64 frames (tile layout)
 //   cc   : class constants pi_k / det B_k (wave-uniform)
 //   cur  : the lane's frame, loaded by the caller (nothing is read from Yrow / abrow): TILE_KEEP leaves it as it is;
 //          TILE_STREAM replaces it by the lane's frame of the tile at next_t0, requested before phase 2, when the
@@ -153,26 +167,23 @@ __device__ __forceinline__ void pass_tile(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, const double (&creg)[RESIDENT ? K * coef_regs(D) : 1],
     const double* __restrict__ sC, const double (&cc)[K], float* __restrict__ gamma_row /* + k*F*Tmax */,
     uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int t0, int lane, unsigned tmask,
-    double* __restrict__ sY, double* __restrict__ sW, typename PassAcc<D, K>::type& acc, double (&nacc)[K],
+    double* __restrict__ sY, typename PassAcc<D, K>::type& acc, double (&nacc)[K],
     TileRegs<D>* cur = nullptr, int next_t0 = 0) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
-  constexpr int WS = weight_stride(D, K);
   constexpr bool DIRECT = PassAcc<D, K>::direct;
-  const int tg = lane / D, eg = lane - tg * D;
   tmask &= (1u << K) - 1u;
   const int t = t0 + lane;
-  if constexpr (FINAL) {
-    // the classes that are not live anywhere in the tile: their zeros
-    static_for<0, K>([&](auto KI) {
-      constexpr int k = KI.value;
-      if (!class_on(tmask, k)) {
-        if (t < Tmax) gamma_row[k * gamma_kstride + t] = 0.f;
-      }
-    });
-  }
   if constexpr (SRC != TILE_STREAM) {
-    if (tmask == 0u) return;                  // no frame of the tile has an active class
+    if (tmask == 0u) {                        // no frame of the tile has an active class
+      if constexpr (FINAL) {
+        if (t < Tmax) {
+#pragma unroll
+          for (int k = 0; k < K; ++k) gamma_row[k * gamma_kstride + t] = 0.f;
+        }
+      }
+      return;
+    }
   }
 
   // ---- phase 1: load y ----
@@ -201,51 +212,18 @@ __device__ __forceinline__ void pass_tile(
     abits = valid ? abits : 0u;
   }
 
-  // ---- q_k = <coef_k, y y^H>, 16 entries of the outer product at a time; three partial sums per class (an FMA
-  // does not wait for the one before it) ----
-  constexpr int NQ = DIRECT ? 2 : 3;          // (fewer registers where the accumulators need them)
-  double q[K][3];
-  double n2 = 0.0;
-  double Pd[DIRECT && !FINAL ? E : 1];        // DIRECT: the frame's packed outer product (one block)
-#pragma unroll
-  for (int k = 0; k < K; ++k) { q[k][0] = 0.0; q[k][1] = 0.0; q[k][2] = 0.0; }
-  static_for<0, R>([&](auto RI) {
-    constexpr int r = RI.value;
-    constexpr int ng = (E - 16 * r) < 16 ? (E - 16 * r) : 16;
-    double c[K];
-    if constexpr (!RESIDENT) {
-      // this block's coefficient registers, from the LDS copy (requested before the products are formed)
-#pragma unroll
-      for (int k = 0; k < K; ++k) c[k] = sC[(k * R + r) * 16 + (lane & 15)];
-    }
-    double P[ng];
-    static_for<0, ng>([&](auto EI) {
-      constexpr int e = EI.value;
-      P[e] = packed_entry<D, 16 * r + e>(yr, yi);
-      if constexpr (packed_part(16 * r + e, D) == 0) n2 += P[e];
-      if constexpr (DIRECT && !FINAL) Pd[16 * r + e] = P[e];
-    });
-    static_for<0, K>([&](auto KI) {
-      constexpr int k = KI.value;
-      if (class_on(tmask, k)) {
-        double ck;
-        if constexpr (RESIDENT) ck = creg[k * R + r]; else ck = c[k];
-        if constexpr (NQ == 3) {
-          fma_bcast_chain<ng>(q[k], ck, P);
-        } else {
-          static_for<0, ng>([&](auto EI) {
-            constexpr int e = EI.value;
-            fma_bcast<e, e == 0>(q[k][e % NQ], ck, P[e]);
-          });
-        }
-      }
-    });
+  // ---- the outer product, and q_k = <coef_k, y y^H>: 16 FMAs per block on three partial sums (an FMA does not wait for the one
+  // before it).  v_k = pi_k / det B_k * q_k^-D with q_k = max(qraw_k / n2c, eps_q), normalised over k below.  For D <= 8 this
+  // needs no scaling: B has trace D and eigenvalues >= 1e-6, so 1e-6 <= q <= 1e6 on unit vectors (floored at 1e-10), q^-D lies
+  // in [1e-48, 1e80], 1 / det B in [1, 1e42] and pi in [1e-30, 1]: every v_k is a normal double. ----
+  double P[R * 16], n2 = 0.0;
+  static_for<0, E>([&](auto EI) {
+    constexpr int e = EI.value;
+    P[e] = packed_entry<D, e>(yr, yi);
+    if constexpr (packed_part(e, D) == 0) n2 += P[e];
   });
-
-  // ---- posterior over the active classes: v_k = pi_k / det B_k * q_k^-D with q_k = max(qraw_k / n2c, eps_q),
-  // normalised over k.  For D <= 8 this needs no scaling: B has trace D and eigenvalues >= 1e-6, so
-  // 1e-6 <= q <= 1e6 on unit vectors (floored at 1e-10), q^-D lies in [1e-48, 1e80], 1 / det B in
-  // [1, 1e42] and pi in [1e-30, 1]: every v_k is a normal double.
+#pragma unroll
+  for (int e = E; e < R * 16; ++e) P[e] = 0.0;
   const double n2c = fmax(n2, GSS_EPS_NORM_SQ);
   const double qfloor = GSS_EPS_Q * n2c;
   double rq[K], v[K], Z = 0.0;
@@ -254,9 +232,20 @@ __device__ __forceinline__ void pass_tile(
     rq[k] = 0.0;
     v[k] = 0.0;
     if (class_on(tmask, k)) {
-      rq[k] = rcp_f64_fast(fmax(NQ == 3 ? q[k][0] + q[k][1] + q[k][2] : q[k][0] + q[k][1], qfloor));   // 1 / (q * n2c): the M-step weight is gamma * rq
-      const double u = rq[k] * n2c;                             // 1 / q
-      const double p = cc[k] * ipow<D>(u);
+      double c[R], q[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if constexpr (RESIDENT) c[r] = creg[k * R + r]; else c[r] = sC[(k * R + r) * 16 + (lane & 15)];
+      }
+      static_for<0, R>([&](auto RI) {
+        constexpr int r = RI.value, ng = E - 16 * r < 16 ? E - 16 * r : 16;
+        double Pb[ng];
+#pragma unroll
+        for (int e = 0; e < ng; ++e) Pb[e] = P[16 * r + e];
+        fma_bcast_chain<ng>(q, c[r], Pb);
+      });
+      rq[k] = rcp_f64_fast(fmax(q[0] + q[1] + q[2], qfloor));   // 1 / (q * n2c): the M-step weight is gamma * rq
+      const double p = cc[k] * ipow<D>(rq[k] * n2c);            // (1 / q)^D
       v[k] = ((abits >> k) & 1u) ? p : 0.0;
       Z += v[k];
     }
@@ -264,12 +253,10 @@ __device__ __forceinline__ void pass_tile(
   const double rz = Z > 0.0 ? rcp_f64_fast(Z) : 0.0;
   if constexpr (FINAL) {
     if (valid && !(n2 >= GSS_EPS_NORM_SQ)) atomicOr(status, GSS_STATUS_ZERO_FRAME);
-    static_for<0, K>([&](auto KI) {
-      constexpr int k = KI.value;
-      if (class_on(tmask, k)) {
-        if (t < Tmax) gamma_row[k * gamma_kstride + t] = (float)(v[k] * rz);
-      }
-    });
+    if (t < Tmax) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) gamma_row[k * gamma_kstride + t] = (float)(v[k] * rz);
+    }
   } else if constexpr (DIRECT) {
     static_for<0, K>([&](auto KI) {
       constexpr int k = KI.value;
@@ -278,36 +265,61 @@ __device__ __forceinline__ void pass_tile(
         nacc[k] += g;
         const double w = g * rq[k];
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[k][e] = fma(w, Pd[e], acc[k][e]);
+        for (int e = 0; e < E; ++e) acc[k][e] = fma(w, P[e], acc[k][e]);
       }
     });
   } else {
-    // this tile's y and weights go to LDS, then phase 2 runs over it
-    store_tile_row<D>(sY + lane * TileLayout<D>::row, yr, yi);
+    // ---- phase 2: lane = (row of 16 frames, entry e of a block).  The blocks change places through LDS one after the other (the
+    // LDS executes a wavefront's instructions in order); the weights of the row's 16 frames lie in the row's own lanes. ----
+    constexpr int NB = TileSums<D>::blocks;
+    double w[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double g = v[k] * rz;
+      nacc[k] += g;
+      w[k] = g * rq[k];
+    }
+    if constexpr (SRC == TILE_STREAM) load_tile_regs<D>(*cur, Yrow, abrow, next_t0, lane, T);
+    double x[NB][16];
+    double* __restrict__ sw = sY + lane;
+    const double* __restrict__ sr = sY + (lane & 15) * kBlockRow + (lane & 48);
+    static_for<0, NB>([&](auto BI) {
+      constexpr int b = BI.value;
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (16 * b + e < E) sw[e * kBlockRow] = P[16 * b + e];
+      wave_lds_sync();
+#pragma unroll
+      for (int n = 0; n < 16; n += 2) {
+        const double2 p2 = *reinterpret_cast<const double2*>(sr + n);
+        x[b][n] = p2.x;
+        x[b][n + 1] = p2.y;
+      }
+      wave_lds_sync();
+    });
     static_for<0, K>([&](auto KI) {
       constexpr int k = KI.value;
       if (class_on(tmask, k)) {
-        const double g = v[k] * rz;
-        nacc[k] += g;
-        sW[lane * WS + k] = g * rq[k];
+        double a[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) a[b] = acc[b][k];
+        fma_bcast_rows<NB>(a, w[k], x);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][k] = a[b];
+#pragma unroll
+        for (int j = 0; j < TileSums<D>::rest; ++j) acc[NB + j][k] = fma(w[k], P[16 * NB + j], acc[NB + j][k]);
       }
     });
-    if constexpr (SRC == TILE_STREAM) load_tile_regs<D>(*cur, Yrow, abrow, next_t0, lane, T);
-    wave_lds_sync();
-
-    // ---- phase 2 ----
-    accumulate_tile_masked<D, K, WS>(sY, sW, tg, eg, tmask, acc);
-    wave_lds_sync();
   }
 }
 
-// The accumulating pass over tiles lo .. hi - 1 with the LDS tile: every live tile's frames are requested while the live
+// The accumulating pass over tiles lo .. hi - 1 in the tile layout: every live tile's frames are requested while the live
 // tile before it is in phase 2.
 template <int D, int K, bool RESIDENT, class MaskPtr>
 __device__ __forceinline__ void stream_tiles(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K], int T,
-    int Tmax, int lo, int hi, int lane, double* __restrict__ sY, double* __restrict__ sW,
+    int Tmax, int lo, int hi, int lane, double* __restrict__ sY,
     typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
   constexpr unsigned kmask = (1u << K) - 1u;
   int tile = lo;
@@ -323,7 +335,7 @@ __device__ __forceinline__ void stream_tiles(
     const bool last = next >= hi;
     // (after the last live tile its own frames are requested again, so that the load needs no branch)
     pass_tile<D, K, false, RESIDENT, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
-                                           sW, acc, nacc, &cur, (last ? tile : next) * kWave);
+                                           acc, nacc, &cur, (last ? tile : next) * kWave);
     if (last) break;
     tile = next;
     m = mn;
@@ -360,6 +372,36 @@ __device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K>::
   }
 }
 
+// Tile layout: the same, out[k * E + e] and out[K * E + k].
+template <int D, int K>
+__device__ __forceinline__ void store_tile_sums(const typename PassAcc<D, K>::type& acc, const double (&nacc)[K],
+                                                double* __restrict__ out, int lane) {
+  constexpr int E = D * D, NB = TileSums<D>::blocks, NR = TileSums<D>::rest, N = K * NB;
+  double v[N], u[K * (NR + 1)];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) v[k * NB + b] = acc[b][k];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) u[k * NR + j] = acc[NB + j][k];
+    u[K * NR + k] = nacc[k];
+  }
+  row_sums<N>(v);
+#pragma unroll
+  for (int j = 0; j < (N + 3) / 4; ++j) {
+    const int i = row_sum_index(lane >> 4, j), k = i / NB, e = 16 * (i - k * NB) + (lane & 15);
+    if (i < N && e < E) out[k * E + e] = v[j];
+  }
+  transpose_reduce<K * (NR + 1)>(u, lane);
+  const int i = transposed_index(lane);                  // (at most 64 values)
+  if (i < K * NR) {
+    const int k = i / (NR > 0 ? NR : 1);
+    out[k * E + 16 * NB + (i - k * NR)] = u[0];
+  } else if (i < K * (NR + 1)) {
+    out[K * E + (i - K * NR)] = u[0];
+  }
+}
+
 template <int D, int K, bool FINAL>
 __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
     gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
@@ -369,15 +411,13 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
     int F, int Tmax, ChunkMap cmap) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
-  constexpr bool RESIDENT = K * R <= kResidentRegs;
-  constexpr int WS = weight_stride(D, K);
-  constexpr bool DIRECT = PassAcc<D, K>::direct;        // no tiles in LDS then
-  constexpr int kTileDoubles = DIRECT ? 0 : tile_region_doubles<D>(WS);
+  constexpr bool RESIDENT = resident_coefs(D, K);
+  constexpr bool DIRECT = PassAcc<D, K>::direct;        // no blocks in LDS then
+  // per wavefront: a block on its way through LDS; then the wavefront's sums
+  constexpr int kSumDoubles = (K * E + K + 1) / 2 * 2;
+  constexpr int kTileDoubles = DIRECT || kSumDoubles > kBlockDoubles ? kSumDoubles : kBlockDoubles;
   constexpr int kCoefDoubles = RESIDENT ? 0 : K * R * 16;
-  // per-wavefront tiles (+ the coefficient copy); the tiles are reused at the end for the cross-wavefront
-  // reduction (needs kPassWaves * (64 * K + K); DIRECT: kPassWaves * (K * E + K))
-  constexpr int kRedDoubles = DIRECT ? kPassWaves * (K * E + K) : kPassWaves * (64 * K + K);
-  constexpr int kTilesDoubles = FINAL ? 2 : (kPassWaves * kTileDoubles > kRedDoubles ? kPassWaves * kTileDoubles : kRedDoubles);
+  constexpr int kTilesDoubles = FINAL ? 2 : kPassWaves * kTileDoubles;
   __shared__ __attribute__((aligned(16))) double lds[kTilesDoubles + kCoefDoubles];
 
   const int lane = threadIdx.x & (kWave - 1);
@@ -393,7 +433,6 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
 
   const double* __restrict__ cf = coef + sf * (long)(K * E);
   double* __restrict__ sY = lds + (FINAL ? 0 : wave * kTileDoubles);
-  double* __restrict__ sW = sY + (FINAL ? 0 : kWave * TileLayout<D>::row);
   double* __restrict__ sC = lds + kTilesDoubles;
 
   // The class coefficients: register r of class k holds entries 16 r .. 16 r + 15 of its packed coefficients,
@@ -450,28 +489,23 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   if constexpr (DIRECT || FINAL) {
     for (int tile = my_lo; tile < my_hi; ++tile)
       pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
-                                       lane, tmrow[tile], sY, sW, acc, nacc);
+                                       lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, lane, sY, sW, acc, nacc);
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, lane, sY, acc, nacc);
   }
   if (FINAL) return;
 
-  if constexpr (DIRECT) {
-    // every wavefront's totals meet in LDS and are added in the order of the wavefronts
-    constexpr int N = K * E + K;
-    store_direct_sums<D, K>(acc, nacc, lds + wave * N, lane);
-    __syncthreads();
-    for (int x = threadIdx.x; x < N; x += kWave * kPassWaves) {
-      double sum = lds[x];
+  // every wavefront's totals meet in LDS and are added in the order of the wavefronts
+  constexpr int N = K * E + K;
+  if constexpr (DIRECT) store_direct_sums<D, K>(acc, nacc, sY, lane);
+  else store_tile_sums<D, K>(acc, nacc, sY, lane);
+  __syncthreads();
+  for (int x = threadIdx.x; x < N; x += kWave * kPassWaves) {
+    double sum = lds[x];
 #pragma unroll
-      for (int w = 1; w < kPassWaves; ++w) sum += lds[w * N + x];
-      if (x < K * E) part[(long)blockIdx.x * (K * E) + x] = sum;
-      else npart[(long)blockIdx.x * K + (x - K * E)] = sum;
-    }
-  } else {
-    // Reduce over the frame groups and over the wavefronts; write the chunk's packed partial sums and counts.
-    reduce_and_store_partials<D, K, true>(acc, nacc, sY, lds, part + (long)blockIdx.x * (K * E),
-                                          npart + (long)blockIdx.x * K, lane, wave);
+    for (int w = 1; w < kPassWaves; ++w) sum += lds[w * kTileDoubles + x];
+    if (x < K * E) part[(long)blockIdx.x * (K * E) + x] = sum;
+    else npart[(long)blockIdx.x * K + (x - K * E)] = sum;
   }
 }
 
@@ -867,12 +901,12 @@ __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
-    int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY, double* __restrict__ sW,
+    int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY,
     typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
   if constexpr (ONE_TILE) {
     if (wave < tile_end)
       pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
-                                             wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, sW, acc,
+                                             wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, acc,
                                              nacc, &pre);
   } else if constexpr (PassAcc<D, K>::direct && D * D * K <= kPrefetchMaxAcc) {
     constexpr unsigned kmask = (1u << K) - 1u;
@@ -893,7 +927,7 @@ __device__ __forceinline__ void whole_pass(
       }
       // (the mask is the same in every lane; the compiler has to be told after the loop-carried copy)
       pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
-                                             tile * kWave, lane, __builtin_amdgcn_readfirstlane(m), sY, sW, acc, nacc,
+                                             tile * kWave, lane, __builtin_amdgcn_readfirstlane(m), sY, acc, nacc,
                                              &cur);
       cur = nxt;
       m = mn;
@@ -902,15 +936,15 @@ __device__ __forceinline__ void whole_pass(
   } else if constexpr (PassAcc<D, K>::direct || FINAL || NW > 1 || !request_ahead(D, K)) {
     for (int tile = wave; tile < tile_end; tile += NW)
       pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
-                                       lane, tmrow[tile], sY, sW, acc, nacc);
+                                       lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, 0, tile_end, lane, sY, sW, acc, nacc);
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, 0, tile_end, lane, sY, acc, nacc);
   }
 }
 
 // ----------------------------------------------------------------------------------------------
 // Whole-EM kernel: a workgroup of NW wavefronts owns one (segment, frequency) for all iterations.  Per
-// iteration every wavefront walks its tiles (pass_tile above), sums its accumulators over the frame groups
+// iteration every wavefront walks its tiles (pass_tile above), sums its accumulators over the rows of lanes
 // through LDS, and factorises the K class matrices itself, so that the coefficients of the next iteration go
 // from LDS straight back into its registers: no partial sums in memory, no second kernel, no launch per
 // iteration, and the same fixed summation order on every run.
@@ -947,38 +981,27 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
     uint32_t* __restrict__ status, int F, int Tmax, int iters, int weight_mode) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
-  constexpr bool RESIDENT = K * R <= kResidentRegs;
-  constexpr int WS = weight_stride(D, K);
-  constexpr bool DIRECT = PassAcc<D, K>::direct;       // no tiles in LDS then
+  constexpr bool RESIDENT = resident_coefs(D, K);
+  constexpr bool DIRECT = PassAcc<D, K>::direct;       // no blocks in LDS then
   constexpr int kCoefDoubles = K * R * 16;             // packed coefficients, padded to whole registers
   constexpr int kSumDoubles = K * E + K;               // packed weighted scatter sums, then the class counts
   // The sums, counts and class constants of the M-step live only between the last tile of a pass and the first
-  // tile of the next one: they share the tile's region, behind the rows that the reduction of the accumulators
-  // uses for staging.  So do the coefficients when they are resident in registers during a pass (otherwise the
-  // pass reads them from LDS and they keep a place of their own behind the tile).
-  constexpr bool SHARED_MSTEP = !DIRECT;
-  constexpr int kSharedDoubles = kSumDoubles + K + (RESIDENT ? kCoefDoubles : 0);
-  constexpr int kTileOnly = DIRECT ? 0 : tile_region_doubles<D>(WS);
-  constexpr int kMstepDoubles = SHARED_MSTEP ? (reduce_wave_doubles(D) + kSharedDoubles + 1) / 2 * 2 : 0;
-  constexpr int kTileDoubles = kTileOnly > kMstepDoubles ? kTileOnly : kMstepDoubles;
-  constexpr int kWaveDoubles = !SHARED_MSTEP ? (kTileDoubles + kCoefDoubles + kSumDoubles + K + 1) / 2 * 2
-                               : RESIDENT    ? kTileDoubles
-                                             : (kTileDoubles + kCoefDoubles + 1) / 2 * 2;
+  // tile of the next one: they share the memory of the blocks.  So do the coefficients when they are resident in registers
+  // during a pass (otherwise the pass reads them from LDS and they keep a place of their own).
+  constexpr int kMstepDoubles = kSumDoubles + K + (RESIDENT ? kCoefDoubles : 0);
+  constexpr int kTileDoubles = ((DIRECT || kMstepDoubles > kBlockDoubles ? kMstepDoubles : kBlockDoubles) + 1) / 2 * 2;
+  constexpr int kWaveDoubles = kTileDoubles + (RESIDENT ? 0 : kCoefDoubles);
   constexpr int kShareRows = DIRECT ? 4 : 1;           // sets of sums per wavefront in the shared buffer (NW > 1)
   constexpr int kShareDoubles = NW > 1 ? 2 * NW * kShareRows * kSumDoubles : 0;
   __shared__ __attribute__((aligned(16))) double lds[NW * kWaveDoubles + kShareDoubles];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0;
   double* __restrict__ sY = lds + wave * kWaveDoubles;
-  double* __restrict__ sW = sY + kWave * TileLayout<D>::row;
-  double* __restrict__ sC = sY + (SHARED_MSTEP && RESIDENT ? reduce_wave_doubles(D) : kTileDoubles);   // [K][R * 16] coefficients of B^-1 for the next pass
-  double* __restrict__ sR = SHARED_MSTEP && !RESIDENT ? sY + reduce_wave_doubles(D) : sC + kCoefDoubles;   // [K][E] packed weighted scatter sums
+  double* __restrict__ sR = sY;                        // [K][E] packed weighted scatter sums
   double* __restrict__ sN = sR + K * E;                // [K] class counts
   double* __restrict__ sCC = sN + K;                   // [K] class constants pi / det B
+  double* __restrict__ sC = RESIDENT ? sCC + K : sY + kTileDoubles;   // [K][R * 16] coefficients of B^-1 for the next pass
   double* __restrict__ sShare = lds + NW * kWaveDoubles;   // [2][NW][kShareRows][kSumDoubles] sums of the wavefronts (NW > 1)
-  __shared__ int sSlotAll[NW * kWave];
-  int* __restrict__ sSlot = sSlotAll + wave * kWave;       // [64] packed index and sign of the lane's reduction slot
-
   // workgroup -> (segment, frequency): the segments in the order of seg_order (longest first), if given
   const long sf = blockIdx.x;
   int s = (int)((unsigned)sf / (unsigned)F);
@@ -1043,16 +1066,10 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
     wave_lds_sync();
   }
 
-  // Where the lane's share of the frame-group sums goes: looked up once (the table sits in memory) and parked in
-  // LDS.  Everything the end of an iteration derives from the lane number is derived there anew, from a copy of
+  // Everything the end of an iteration derives from the lane number is derived there anew, from a copy of
   // the lane number that the compiler cannot see through: values computed ahead of the iteration loop would be
   // live across the tile loop, where there is no register for them, and come back from scratch memory one
   // dependent load at a time.
-  if constexpr (!DIRECT) {
-    static constexpr SlotTable<D> kSlots = make_slot_table<D>();
-    const int pi0 = kSlots.index[lane];                // lane o = D n + i reads back slot (i, n)
-    sSlot[lane] = (pi0 < 0 ? 0x4000 : pi0) | (kSlots.sign[lane] < 0 ? 0x8000 : 0);
-  }
   wave_lds_sync();
   for (int it = 0; it < iters; ++it) {
     typename PassAcc<D, K>::type acc;
@@ -1061,35 +1078,16 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
     whole_pass<D, K, NW, ONE_TILE, false, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
-                                                    tiles, wave, lane, my_mask, pre, sY, sW, acc, nacc);
+                                                    tiles, wave, lane, my_mask, pre, sY, acc, nacc);
 
     int le = lane;                                      // the lane number again, opaque
     asm volatile("" : "+v"(le));
-    // ---- sums over the frame groups -> packed sR[k][e]; class counts over the lanes -> sN[k] ----
+    // ---- sums over the rows of lanes -> packed sR[k][e]; class counts over the lanes -> sN[k] ----
     // (NW > 1: into this wavefront's slot of the shared buffer of this iteration)
     double* __restrict__ sOut = NW > 1 ? sShare + ((it & 1) * NW + wave) * (kShareRows * kSumDoubles) : sR;
-    if constexpr (DIRECT) {
-      store_direct_sums<D, K, (NW > 1)>(acc, nacc, sOut, le);
-      wave_lds_sync();
-    } else {
-    const int code = sSlot[le];
-    const int pidx = (code & 0x4000) ? -1 : (code & 0x3fff);
-    const double sgn = (code & 0x8000) ? -1.0 : 1.0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      double nv = wave_sum_f64(nacc[k]);
-      if (le == 0) sOut[K * E + k] = nv;
-    }
-#pragma unroll
-    for (int k0 = 0; k0 < K; k0 += 2) {
-      double S[2];
-      sum_frame_groups<D, K>(acc, k0, sY, le, S);
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        if (k0 + c < K && pidx >= 0) sOut[(k0 + c) * E + pidx] = sgn * S[c];
-    }
+    if constexpr (DIRECT) store_direct_sums<D, K, (NW > 1)>(acc, nacc, sOut, le);
+    else store_tile_sums<D, K>(acc, nacc, sOut, le);
     wave_lds_sync();
-    }
     if constexpr (NW > 1) {
       __syncthreads();                                  // every wavefront's sums of this iteration are in place
       const double* __restrict__ all = sShare + (it & 1) * (NW * kShareRows * kSumDoubles);
@@ -1133,7 +1131,7 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
     whole_pass<D, K, NW, ONE_TILE, true, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
-                                                   Tmax, tiles_total, wave, lane, my_mask, pre, sY, sW, acc, nacc);
+                                                   Tmax, tiles_total, wave, lane, my_mask, pre, sY, acc, nacc);
   }
 }
 

@@ -355,6 +355,31 @@ def test_tile_frame_groups(env, D, K):
             assert np.max(np.abs(g - go)) <= 1e-5, (T, forced)
 
 
+@pytest.mark.parametrize("D,K", [(4, 7), (5, 5), (6, 3), (7, 4), (8, 2), (8, 5), (8, 8)])
+def test_tile_rows_of_frames(env, D, K):
+    """The transposed blocks of the accumulating passes: 16 frames per row of lanes, whose weights the row's lanes hand round.
+    Every class but the last is active in a few frames of one row only (its first, its last, a row of its own), lengths around
+    the rows and the tile edge, the one-wavefront kernel and the chunked kernels.  Tolerance of test_rank_deficient_classes."""
+    gss, ctx = env["gss"], env["ctx"]
+    for T in (1, 15, 16, 17, 49, 64, 80, 129):
+        rng = np.random.default_rng(2000 * D + T)
+        Y = (_cn(rng, (2, T, D)) * np.exp(rng.standard_normal((2, T, 1)))).astype(np.complex64)
+        act = np.zeros((K, T), np.uint8)
+        act[K - 1] = 1
+        for k in range(K - 1):
+            row = slice(16 * (k % 4), 16 * (k % 4) + 16)
+            act[k, row] = [1, 0] * 8 if k % 3 == 0 and T >= row.stop else 1
+            act[k, 15 + 16 * k:T:64] = 1
+        go = env["o"].cacgmm_em(Y, act, 2)
+        for forced in (0, 1 << 40):
+            ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, forced)
+            try:
+                g = _gpu_em(env, Y[None], act[None], None, 2)[0]
+            finally:
+                ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, -1)
+            assert np.max(np.abs(g - go)) <= 1e-5, (T, forced)
+
+
 @pytest.mark.parametrize("D", [10, 20, 26, 32])
 def test_every_large_instantiation(env, D):
     """Every (class count, NB = ceil(D / 8)) instantiation of the large-array kernels: K = 1..8 with a partly filled last block
