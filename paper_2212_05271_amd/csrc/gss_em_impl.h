@@ -90,12 +90,19 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // ----------------------------------------------------------------------------------------------
 
 // Few channels: the lane that owns a frame in phase 1 has all D * D entries of its outer product in registers
-// anyway (one block of at most 16), so it adds w_k * P[e] to K * D * D accumulators of its own, and there is no
-// phase 2.  Used when the accumulators fit in registers beside phase 1.  The accumulators are acc[k][e] then (packed order),
-// and the sums over the lanes are taken at the end of the pass (transpose_reduce).
-constexpr int kDirectMaxAcc = 80;
+// anyway (one block of at most 16), and in the direct layout adds w_k * P[e] to K * D * D accumulators of its own: no
+// phase 2.  The accumulators are acc[k][e] then (packed order), and the sums over the lanes are taken at the end of the pass
+// (transpose_reduce).  `one`: the kernel whose wavefronts have one tile each.
+// The line lies where the layouts were measured against each other: the direct one costs no LDS round trip, but its accumulators
+// keep wavefronts from the SIMDs and take longer to add up.  Direct / tile layout, us, 32 segments of up to 700 frames, 5
+// iterations: 3 channels and 3 / 4 / 5 / 8 classes 266 / 276, 312 / 313, 404 / 364, 582 / 496, 4 channels and 2 / 3 / 5 classes
+// 304 / 302, 411 / 350, 571 / 445.  One segment of 200 frames, a tile per wavefront, 10 iterations: 3 channels and 2 / 5 classes
+// 32.7 / 28.5, 54.6 / 39.3, 4 channels and 2 / 5 classes 43.4 / 45.6, 68.7 / 61.2.  (4 segments of 3 channels and 5 to 7 classes,
+// two wavefronts per SIMD, are 4 to 7 % faster with the direct one.)
 constexpr int kPrefetchMaxAcc = 64;            // the whole-EM kernel requests the next tile ahead up to this many
-__host__ __device__ constexpr bool direct_layout(int D, int K) { return D <= 4 && D * D * K <= kDirectMaxAcc; }
+__host__ __device__ constexpr bool direct_layout(int D, int K, bool one) {
+  return D <= 2 || (D == 3 && !one && K <= 4) || (D == 4 && K <= 2);
+}
 
 // Tile layout: the D * D packed entries of the outer product in blocks of 16, which phase 2 takes transposed (lane = entry of a
 // block), and up to 4 entries left over (6 and 7 channels), which a lane adds up for its own frame as in the direct layout.
@@ -115,13 +122,12 @@ constexpr int kBlockDoubles = 16 * kBlockRow;
 // product, the accumulators, counts, posterior terms and partial sums, with some 40 registers left of 256 for everything else.
 __host__ __device__ constexpr int coef_regs(int D) { return (D * D + 15) / 16; }
 __host__ __device__ constexpr bool resident_coefs(int D, int K) {
-  return direct_layout(D, K) || 2 * (D * D + K * coef_regs(D) + 3 * K + 3 + K * coef_regs(D)) <= 215;
+  return D <= 4 || 2 * (D * D + K * coef_regs(D) + 3 * K + 3 + K * coef_regs(D)) <= 215;
 }
 
-template <int D, int K>
+template <int D, int K, bool DIRECT>
 struct PassAcc {
-  static constexpr bool direct = direct_layout(D, K);
-  static constexpr int rows = direct ? K : TileSums<D>::blocks + TileSums<D>::rest, cols = direct ? D * D : K;
+  static constexpr int rows = DIRECT ? K : TileSums<D>::blocks + TileSums<D>::rest, cols = DIRECT ? D * D : K;
   using type = double[rows][cols];
 };
 template <int A, int B>
@@ -162,16 +168,15 @@ __device__ __forceinline__ void load_tile_regs(TileRegs<D>& r, const float2* __r
 //          TILE_STREAM replaces it by the lane's frame of the tile at next_t0, requested before phase 2, when the
 //          posterior's registers are free, and wants a mask that is not empty.
 enum TileSource { TILE_LOAD, TILE_KEEP, TILE_STREAM };
-template <int D, int K, bool FINAL, bool RESIDENT, TileSource SRC = TILE_LOAD>
+template <int D, int K, bool FINAL, bool RESIDENT, bool DIRECT, TileSource SRC = TILE_LOAD>
 __device__ __forceinline__ void pass_tile(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, const double (&creg)[RESIDENT ? K * coef_regs(D) : 1],
     const double* __restrict__ sC, const double (&cc)[K], float* __restrict__ gamma_row /* + k*F*Tmax */,
     uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int t0, int lane, unsigned tmask,
-    double* __restrict__ sY, typename PassAcc<D, K>::type& acc, double (&nacc)[K],
+    double* __restrict__ sY, typename PassAcc<D, K, DIRECT>::type& acc, double (&nacc)[K],
     TileRegs<D>* cur = nullptr, int next_t0 = 0) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
-  constexpr bool DIRECT = PassAcc<D, K>::direct;
   tmask &= (1u << K) - 1u;
   const int t = t0 + lane;
   if constexpr (SRC != TILE_STREAM) {
@@ -319,22 +324,22 @@ template <int D, int K, bool RESIDENT, class MaskPtr>
 __device__ __forceinline__ void stream_tiles(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K], int T,
-    int Tmax, int lo, int hi, int lane, double* __restrict__ sY,
-    typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
+    int Tmax, int lo, int hi, int by, int lane, double* __restrict__ sY,
+    typename PassAcc<D, K, false>::type& acc, double (&nacc)[K]) {
   constexpr unsigned kmask = (1u << K) - 1u;
   int tile = lo;
   unsigned m = 0u;
-  while (tile < hi && (m = tmrow[tile] & kmask) == 0u) ++tile;
+  while (tile < hi && (m = tmrow[tile] & kmask) == 0u) tile += by;
   if (tile >= hi) return;
   TileRegs<D> cur;
   load_tile_regs<D>(cur, Yrow, abrow, tile * kWave, lane, T);
   for (;;) {
-    int next = tile + 1;
+    int next = tile + by;
     unsigned mn = 0u;
-    while (next < hi && (mn = tmrow[next] & kmask) == 0u) ++next;
+    while (next < hi && (mn = tmrow[next] & kmask) == 0u) next += by;
     const bool last = next >= hi;
     // (after the last live tile its own frames are requested again, so that the load needs no branch)
-    pass_tile<D, K, false, RESIDENT, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
+    pass_tile<D, K, false, RESIDENT, false, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
                                            acc, nacc, &cur, (last ? tile : next) * kWave);
     if (last) break;
     tile = next;
@@ -347,7 +352,7 @@ __device__ __forceinline__ void stream_tiles(
 // lanes separately, row r at out[r * (K * E + K) + ...], for a caller that adds several such sets anyway (two
 // exchange steps less).
 template <int D, int K, bool ROWS = false>
-__device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K>::type& acc, const double (&nacc)[K],
+__device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K, true>::type& acc, const double (&nacc)[K],
                                                   double* __restrict__ out, int lane) {
   constexpr int E = D * D, N = K * E + K;
   double v[N];
@@ -374,7 +379,7 @@ __device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K>::
 
 // Tile layout: the same, out[k * E + e] and out[K * E + k].
 template <int D, int K>
-__device__ __forceinline__ void store_tile_sums(const typename PassAcc<D, K>::type& acc, const double (&nacc)[K],
+__device__ __forceinline__ void store_tile_sums(const typename PassAcc<D, K, false>::type& acc, const double (&nacc)[K],
                                                 double* __restrict__ out, int lane) {
   constexpr int E = D * D, NB = TileSums<D>::blocks, NR = TileSums<D>::rest, N = K * NB;
   double v[N], u[K * (NR + 1)];
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr bool RESIDENT = resident_coefs(D, K);
-  constexpr bool DIRECT = PassAcc<D, K>::direct;        // no blocks in LDS then
+  constexpr bool DIRECT = direct_layout(D, K, false);   // no blocks in LDS then
   // per wavefront: a block on its way through LDS; then the wavefront's sums
   constexpr int kSumDoubles = (K * E + K + 1) / 2 * 2;
   constexpr int kTileDoubles = DIRECT || kSumDoubles > kBlockDoubles ? kSumDoubles : kBlockDoubles;
@@ -464,7 +469,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
     for (int k = 0; k < K; ++k) cc[k] = ccp[k];
   }
 
-  typename PassAcc<D, K>::type acc;
+  typename PassAcc<D, K, DIRECT>::type acc;
   double nacc[K];
   zero_acc(acc);
 #pragma unroll
@@ -488,10 +493,10 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   const int my_hi = tile_lo + (n_tiles * (wave + 1)) / kPassWaves;
   if constexpr (DIRECT || FINAL) {
     for (int tile = my_lo; tile < my_hi; ++tile)
-      pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
+      pass_tile<D, K, FINAL, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, lane, sY, acc, nacc);
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, 1, lane, sY, acc, nacc);
   }
   if (FINAL) return;
 
@@ -887,28 +892,26 @@ __global__ __launch_bounds__(256) void em_order_segments(gss_yview yv, const int
   order[rank] = s;
 }
 
-// Whether the whole-EM kernel requests the next tile's frames before phase 2 (tile layout): not where the 2 D + 1 registers are
-// missed.  8 channels: with 2 classes they cost the third wavefront of a SIMD (172 registers instead of 156; 48 segments of up to
-// 300 frames, 3 iterations 551 -> 522 us), with 8 classes, whose accumulators leave no room, the spills lie in the tile (1373 ->
-// 1286).
-__host__ __device__ constexpr bool request_ahead(int D, int K) { return D < 8 || (K != 2 && K < 8); }
+// Whether the whole-EM kernel requests the next tile's frames before phase 2 (tile layout): not with 8 channels and 8 classes, where
+// the 17 registers are missed (12 segments of up to 300 frames, 5 iterations 517 us, requested ahead 541).
+__host__ __device__ constexpr bool request_ahead(int D, int K) { return D * K < 64; }
 
 // One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile `pre` (ONE_TILE), or
 // tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are registers to spare, and the frames
 // of the next tile are requested from memory before the current tile is worked on.
-template <int D, int K, int NW, bool ONE_TILE, bool FINAL, bool RESIDENT, class MaskPtr>
+template <int D, int K, int NW, bool ONE_TILE, bool FINAL, bool RESIDENT, bool DIRECT, class MaskPtr>
 __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
     int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY,
-    typename PassAcc<D, K>::type& acc, double (&nacc)[K]) {
+    typename PassAcc<D, K, DIRECT>::type& acc, double (&nacc)[K]) {
   if constexpr (ONE_TILE) {
     if (wave < tile_end)
-      pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+      pass_tile<D, K, FINAL, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, acc,
                                              nacc, &pre);
-  } else if constexpr (PassAcc<D, K>::direct && D * D * K <= kPrefetchMaxAcc) {
+  } else if constexpr (DIRECT && D * D * K <= kPrefetchMaxAcc) {
     constexpr unsigned kmask = (1u << K) - 1u;
     TileRegs<D> cur{};                                   // (replaced below when the first tile is live)
     int tile = wave;
@@ -926,19 +929,19 @@ __device__ __forceinline__ void whole_pass(
         if (mn != 0u) load_tile_regs<D>(nxt, Yrow, abrow, next * kWave, lane, T);
       }
       // (the mask is the same in every lane; the compiler has to be told after the loop-carried copy)
-      pass_tile<D, K, FINAL, RESIDENT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+      pass_tile<D, K, FINAL, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              tile * kWave, lane, __builtin_amdgcn_readfirstlane(m), sY, acc, nacc,
                                              &cur);
       cur = nxt;
       m = mn;
       tile = next;
     }
-  } else if constexpr (PassAcc<D, K>::direct || FINAL || NW > 1 || !request_ahead(D, K)) {
+  } else if constexpr (DIRECT || FINAL || !request_ahead(D, K)) {
     for (int tile = wave; tile < tile_end; tile += NW)
-      pass_tile<D, K, FINAL, RESIDENT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
+      pass_tile<D, K, FINAL, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, 0, tile_end, lane, sY, acc, nacc);
+    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, wave, tile_end, NW, lane, sY, acc, nacc);
   }
 }
 
@@ -982,7 +985,7 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr bool RESIDENT = resident_coefs(D, K);
-  constexpr bool DIRECT = PassAcc<D, K>::direct;       // no blocks in LDS then
+  constexpr bool DIRECT = direct_layout(D, K, ONE_TILE);   // no blocks in LDS then
   constexpr int kCoefDoubles = K * R * 16;             // packed coefficients, padded to whole registers
   constexpr int kSumDoubles = K * E + K;               // packed weighted scatter sums, then the class counts
   // The sums, counts and class constants of the M-step live only between the last tile of a pass and the first
@@ -1072,12 +1075,12 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
   // dependent load at a time.
   wave_lds_sync();
   for (int it = 0; it < iters; ++it) {
-    typename PassAcc<D, K>::type acc;
+    typename PassAcc<D, K, DIRECT>::type acc;
     double nacc[K];
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, ONE_TILE, false, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
+    whole_pass<D, K, NW, ONE_TILE, false, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
                                                     tiles, wave, lane, my_mask, pre, sY, acc, nacc);
 
     int le = lane;                                      // the lane number again, opaque
@@ -1125,12 +1128,12 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 
   // final pass: the posteriors = the masks, zero padding included
   {
-    typename PassAcc<D, K>::type acc;
+    typename PassAcc<D, K, DIRECT>::type acc;
     double nacc[K];
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, ONE_TILE, true, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
+    whole_pass<D, K, NW, ONE_TILE, true, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
                                                    Tmax, tiles_total, wave, lane, my_mask, pre, sY, acc, nacc);
   }
 }
@@ -1139,16 +1142,16 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 // Host-side plan and dispatch
 // ----------------------------------------------------------------------------------------------
 // Problems per compute unit from which on the whole-EM kernel is used.  Against chunks, all channel and class counts, 3
-// iterations: tile layout, 8 segments of 513 bins (16 per compute unit) and more, up to 32 tiles 0.4 to 0.95 times the time
+// iterations: 5 channels and more, 8 segments of 513 bins (16 per compute unit) and more, up to 32 tiles 0.4 to 0.95 times the time
 // in ragged batches, 0.7 to 1.0 in uniform ones (8 segments of 1860 frames, 8 channels and 8 classes 1.06); longer problems of one
-// length end in a partly filled round (8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14) and wait for 12.  Direct
-// layout: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones wait
-// for 8 segments).  (The line was three rounds of the wavefronts that fit the chip: with
+// length end in a partly filled round (8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14) and wait for 12.  Up to
+// 4 channels: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones wait
+// for 8 segments; 4 segments of up to 700 frames, 4 channels and 8 classes 190 us in chunks, 120 in one launch).  (The line was three rounds of the wavefronts that fit the chip: with
 // fewer registers the kernel got more wavefronts and the call went back to chunks, 16 segments of 640 frames, 3 iterations,
 // 7 channels and 2 classes 262 -> 317 us, 2 channels and 8 classes 132 -> 285.)
-constexpr int whole_min_per_cu(bool direct, int tiles) { return (direct ? 8 : 16) + (tiles <= 32 ? 0 : 8); }
+constexpr int whole_min_per_cu(bool few, int tiles) { return (few ? 8 : 16) + (tiles <= 32 ? 0 : 8); }
 constexpr int kWholeMaxTilesAlways = 5;
-// Direct layout: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
+// Up to 4 channels: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
 // compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
 constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
 // Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but each of them adds up and factorises for
@@ -1202,11 +1205,11 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   // resident workgroups per compute unit of the two pass kernels: asked once per instantiation
   static const int wgs_per_cu = resident_wgs(em_pass_small<D, K, false>, kWave * kPassWaves, 2);
   static const int wgs_per_cu_fin = resident_wgs(em_pass_small<D, K, true>, kWave * kPassWaves, 2);
-  // Tile layout: chunks for two workgroups per compute unit also where registers and LDS have room for more.  The 513 problems of
+  // From 5 channels on chunks for two workgroups per compute unit also where registers and LDS have room for more.  The 513 problems of
   // a segment are a chunk each then, and the 513th goes to the free places in pieces; planned for three, all of them are
   // cut in two, and the launch is a round and a third (1560 frames, 5 iterations, 5 channels and 3 classes 156 -> 127 us, 7
   // channels and 2 classes 175 -> 144).
-  const int plan_wgs = direct_layout(D, K) || wgs_per_cu < 2 ? wgs_per_cu : 2;
+  const int plan_wgs = D <= kWholeQuadMaxD || wgs_per_cu < 2 ? wgs_per_cu : 2;
   const EmPlan p = make_plan(ctx, n_sf, S, Tmax, D, K, plan_wgs, wgs_per_cu_fin);
   int rc = gss_ensure_scratch(ctx, p.total);
   if (rc != GSS_OK) return rc;
@@ -1227,20 +1230,20 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   // is cut into chunks over several workgroups, one pass and one factor launch per iteration, unless it has few tiles: two
   // launches per iteration cost more than the whole EM of such a problem in one wavefront.
   const bool choose = ctx->em_whole_min_problems < 0;
-  bool whole = n_sf >= (choose ? (long)whole_min_per_cu(direct_layout(D, K), tiles) * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
+  bool whole = n_sf >= (choose ? (long)whole_min_per_cu(D <= kWholeQuadMaxD, tiles) * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
                (choose && tiles <= kWholeMaxTilesAlways);
-  // Up to 4 channels there is the variant with four wavefronts per problem (use_quad), and with the direct layout (cheap tiles,
-  // a launch costs as much as a few dozen of them) few problems go to the whole-EM kernel as well unless a pass is so long that
+  // Up to 4 channels there is the variant with four wavefronts per problem (use_quad), and as tiles are cheap (a launch costs as
+  // much as a few dozen of them) few problems go to the whole-EM kernel as well unless a pass is so long that
   // the launches per iteration no longer matter.
   bool tiny = false;
   if constexpr (D <= kWholeQuadMaxD) {
-    if (choose && (direct_layout(D, K) || tiles <= kWholeQuad)) {
+    if (choose) {
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
       const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
       tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, quads_per_cu, tiles, iters);
       const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
-      if (direct_layout(D, K) && row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
+      if (row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }
   }
   whole = iters > 0 && whole && n_sf <= 0x7fffffffL;
