@@ -58,17 +58,24 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return (r[0] + r[1]) + (r[2] + r[3]);
 }
 
-// The value that lane 8 * (lane / 8) + N holds, in every lane of that group of 8: a row of 16 lanes is served by
+// The values that lane 8 * (lane / 8) + N holds, in every lane of that group of 8: a row of 16 lanes is served by
 // two lane-permute moves, each confined to one half of the row by its bank mask.  Every lane of the wavefront
-// must be active.  (s_nop: a vector write of the source needs two wait states before the permute reads it.)
-template <int N>
-__device__ __forceinline__ double class_row_bcast(double src) {
-  double r;
-  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0x3\n\t"
-      "v_mov_b64_dpp %0, %1 row_newbcast:%3 row_mask:0xf bank_mask:0xc"
-      : "=&v"(r)
-      : "v"(src), "n"(N), "n"(N + 8));
-  return r;
+// must be active.  (s_nop: a vector write of a source needs two wait states before the permute reads it.)
+template <int N, int M>
+__device__ __forceinline__ void class_row_bcast(const double (&src)[M], double (&dst)[M]) {
+#define GSS_CLASS_BCAST(d, s)                                                       \
+  "v_mov_b64_dpp %" #d ", %" #s " row_newbcast:%[lo] row_mask:0xf bank_mask:0x3\n\t" \
+  "v_mov_b64_dpp %" #d ", %" #s " row_newbcast:%[hi] row_mask:0xf bank_mask:0xc\n\t"
+  constexpr int m4 = M / 4 * 4;
+#pragma unroll
+  for (int m = 0; m < m4; m += 4)
+    asm("s_nop 1\n\t" GSS_CLASS_BCAST(0, 4) GSS_CLASS_BCAST(1, 5) GSS_CLASS_BCAST(2, 6) GSS_CLASS_BCAST(3, 7)
+        : "=&v"(dst[m]), "=&v"(dst[m + 1]), "=&v"(dst[m + 2]), "=&v"(dst[m + 3])
+        : "v"(src[m]), "v"(src[m + 1]), "v"(src[m + 2]), "v"(src[m + 3]), [lo] "n"(N), [hi] "n"(N + 8));
+#pragma unroll
+  for (int m = m4; m < M; ++m)
+    asm("s_nop 1\n\t" GSS_CLASS_BCAST(0, 1) : "=&v"(dst[m]) : "v"(src[m]), [lo] "n"(N), [hi] "n"(N + 8));
+#undef GSS_CLASS_BCAST
 }
 
 template <int N>
@@ -316,7 +323,7 @@ __device__ __forceinline__ void fma_bcast_rows(double (&acc)[NB], double w, cons
 // Sums of N per-lane doubles over the four rows of 16 lanes (lane l of every row belongs together), in a fixed order: two
 // exchange steps, at each of which a lane keeps one value of every pair, by the instructions that swap halves (rows) of two
 // registers.  Afterwards lane l of row q holds in v[j] the total of value row_sum_index(q, j) (where that is below N).
-__device__ __forceinline__ int row_sum_index(int q, int j) { return 4 * j + ((q & 1) << 1 | q >> 1); }
+__device__ __forceinline__ int row_sum_index(int q, int j) { return 4 * j + ((q & 1) << 1 | (q >> 1 & 1)); }
 template <int N>
 __device__ __forceinline__ void row_sums(double (&v)[N]) {
   auto step = [&](auto CNT, auto HALVES) {

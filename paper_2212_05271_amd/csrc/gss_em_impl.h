@@ -515,76 +515,139 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
 }
 
 // ----------------------------------------------------------------------------------------------
-// M-step in one wavefront: the K class matrices B_k = D R_k / N_k from the packed sums sR[K][E] and the class
-// counts sN[K] (both in LDS), Hermitised by construction, scaled to trace D, loaded with delta I (identity for a
-// class without data), inverted in place; the packed coefficients of B_k^-1 go to sC[K][coef_regs(D) * 16] and
-// the class constants pi_k / det B_k to sCC[K] (LDS).  Lane (k, i) = (le / 8, le % 8) holds row i of the matrix
-// of class k (8 complex numbers) in registers.  Every lane of the wavefront must be active.  The caller orders
-// the LDS traffic before and after (wave_lds_sync).
+// End of an iteration in one wavefront (5 channels and more): the accumulators are added up, the K class matrices B_k =
+// D R_k / N_k scaled to trace D, loaded with delta I (identity for a class without data) and inverted in place; the packed
+// coefficients of B_k^-1 go to sC[K][coef_regs(D) * 16] (LDS) and the class constants pi_k / det B_k to cc (wave-uniform).
+// Lane (k, i) = (le / 8, le % 8) holds row i of the matrix of class k in registers.  Every lane of the wavefront must be active.
+//
+// Between the lanes that add up and the lanes that eliminate, the matrices pass through LDS as full rows (row pitch of 9
+// complex numbers: the rows of two classes are read without bank conflicts): an entry of the upper triangle is written to both
+// of its places, and a row is read with D loads and no choices.  The coefficients are collected from the inverse in the same
+// way.  A wavefront of a batch runs this once per iteration for 17 tiles on average (64 segments of up to 1875 frames), where it
+// was 1500 vector instructions of 700 per tile; now 900.
 // ----------------------------------------------------------------------------------------------
+constexpr int kMatRow = 18;                              // doubles per row of a class matrix in LDS
+__host__ __device__ constexpr int mat_doubles(int D) { return D * kMatRow; }
+// The two places of packed entry e within a class matrix, and the factor of the second: conj for an imaginary part, and the (zero)
+// imaginary part for a diagonal entry.  place | second << 8 | factor << 16.
+template <int D>
+struct MatPlaces { int code[kWave]; };
+template <int D>
+constexpr MatPlaces<D> make_mat_places() {
+  MatPlaces<D> t{};
+  for (int e = 0; e < D * D; ++e) {
+    const int i = packed_i(e, D), j = packed_j(e, D), part = packed_part(e, D);
+    const int at = i * kMatRow + 2 * j + (part == 2 ? 1 : 0);
+    const int second = part == 0 ? at + 1 : j * kMatRow + 2 * i + (part == 2 ? 1 : 0);
+    t.code[e] = at | second << 8 | (part == 0 ? 0 : part == 1 ? 1 : -1) * (1 << 16);
+  }
+  return t;
+}
+// Sums of N per-lane doubles over the wavefront, the same in the 8 lanes of group g for value 8 r + g: out[r].  buf: 8 rows of
+// kBlockRow doubles.
+template <int N>
+__device__ __forceinline__ void lane_sums(const double (&v)[N], double* __restrict__ buf, int le, double (&out)[(N + 7) / 8]) {
+#pragma unroll
+  for (int r = 0; r < (N + 7) / 8; ++r) {
+#pragma unroll
+    for (int n = 8 * r; n < (8 * r + 8 < N ? 8 * r + 8 : N); ++n) buf[(n - 8 * r) * kBlockRow + le] = v[n];
+    wave_lds_sync();
+    double2 p[4];
+    const double* __restrict__ src = buf + (le >> 3) * kBlockRow + 8 * (le & 7);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = *reinterpret_cast<const double2*>(src + 2 * j);
+    wave_lds_sync();
+    double sum = ((p[0].x + p[0].y) + (p[1].x + p[1].y)) + ((p[2].x + p[2].y) + (p[3].x + p[3].y));
+    sum += dpp_permute_f64<0xB1>(sum);                   // quad_perm [1, 0, 3, 2]
+    sum += dpp_permute_f64<0x4E>(sum);                   // quad_perm [2, 3, 0, 1]
+    sum += dpp_permute_f64<0x141>(sum);                  // row_half_mirror
+    out[r] = sum;
+  }
+}
 template <int D, int K>
-__device__ __forceinline__ void factor_classes_in_wave(const double* __restrict__ sR, const double* __restrict__ sN,
-                                                       double* __restrict__ sC, double* __restrict__ sCC, int le,
-                                                       int weight_mode, uint32_t* __restrict__ status) {
-  constexpr int E = D * D;
-  constexpr int R = coef_regs(D);
+__device__ __forceinline__ void m_step_in_wave(const typename PassAcc<D, K, false>::type& acc, const double (&nacc)[K],
+                                               double* __restrict__ sM, const int* __restrict__ sPlaces, double* __restrict__ sC,
+                                               double (&cc)[K], int le, int weight_mode, uint32_t* __restrict__ status) {
+  constexpr int E = D * D, R = coef_regs(D), NB = TileSums<D>::blocks, NR = TileSums<D>::rest, N = K * NB;
   const int fk = le >> 3, fi = le & 7;                  // class and row of this lane
-  // (Written without branches: every lane reads from valid addresses and the unused values are deselected,
-  // so that the LDS reads go out together instead of one wait per row entry.)
   const bool on = fk < K && fi < D;
-  const int fkc = fk < K ? fk : K - 1, fic = fi < D ? fi : D - 1;
-  const double* __restrict__ sRk = sR + fkc * E;
-  double ar[8], ai[8];                                  // row fi of class fk
-  double tr = 0.0;
+  auto put = [&](int k, int e, double v) {
+    const int code = sPlaces[e];
+    sM[k * mat_doubles(D) + (code & 0xff)] = v;
+    sM[k * mat_doubles(D) + (code >> 8 & 0xff)] = v * (double)(code >> 16);
+  };
+  // ---- sums: the class counts and the entries of the last block, then the blocks ----
+  double u[K * (NR + 1)], us[(K * (NR + 1) + 7) / 8];
 #pragma unroll
-  for (int d = 0; d < D; ++d) tr += sRk[gss_packed_row(d, D)];
-  const double Nk = sN[fkc];
-  double Ntot = 0.0;
+  for (int k = 0; k < K; ++k) {
+    u[k] = nacc[k];
 #pragma unroll
-  for (int k = 0; k < K; ++k) Ntot += sN[k];
+    for (int j = 0; j < NR; ++j) u[K + k * NR + j] = acc[NB + j][k];
+  }
+  lane_sums<K * (NR + 1)>(u, sM, le, us);
+  const double Nk = us[0];
+  if constexpr (NR > 0) {
+#pragma unroll
+    for (int r = 0; r < (K * (NR + 1) + 7) / 8; ++r) {
+      const int n = 8 * r + fk - K;
+      if (fi == 0 && n >= 0 && n < K * NR) put(n / NR, 16 * NB + n % NR, us[r]);
+    }
+  }
+  double v[N];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) v[k * NB + b] = acc[b][k];
+  row_sums<N>(v);
+#pragma unroll
+  for (int j = 0; j < (N + 3) / 4; ++j) {
+    const unsigned i0 = row_sum_index(le >> 4, 0);       // value 4 j + i0 = entry e of class k
+    const unsigned k = 4 % NB == 0 ? j * (4 / NB) + i0 / NB : (4 * j + i0) / NB;
+    const unsigned b = 4 % NB == 0 ? i0 % NB : 4 * j + i0 - k * NB, e = 16 * b + (le & 15);
+    if ((4 * j + 3 < N && 16 * NB <= E) || (k < (unsigned)K && e < (unsigned)E)) put(k, e, v[j]);
+  }
+  wave_lds_sync();
+
+  // ---- row fi of class fk (lanes without one read along) ----
+  double* __restrict__ row = sM + (fk < K ? fk : K - 1) * mat_doubles(D) + (fi < D ? fi : D - 1) * kMatRow;
+  double ar[D], ai[D];
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const double2 m = *reinterpret_cast<const double2*>(row + 2 * j);
+    ar[j] = m.x;
+    ai[j] = m.y;
+  }
+  double tr = fi < D ? row[2 * (fi < D ? fi : 0)] : 0.0;
+  tr += dpp_permute_f64<0xB1>(tr);
+  tr += dpp_permute_f64<0x4E>(tr);
+  tr += dpp_permute_f64<0x141>(tr);
   // B = D R / max(N, eps); dead if its trace <= eps; else rescaled to trace D (= R * D / tr R)
   // (the test without its division, the scale with a reciprocal: both sit in front of the sweeps)
   const bool dead = !((double)D * tr > GSS_EPS_N * fmax(Nk, GSS_EPS_N));
-  const double sc = dead ? 0.0 : (double)D * rcp_f64(tr);
-  {
-    double v0[8], v1[8];
+  const double sc = dead ? 0.0 : (double)D * rcp_f64(tr), load = dead ? 1.0 + GSS_DELTA : GSS_DELTA;
+  if (__ballot(dead) != 0) {                             // (entries may be infinite)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      // packed position of entry (min, max) of the row's pair (fi, j): the diagonal entry for j = fi (its
-      // neighbour is read along and dropped), Re and Im of the off-diagonal entry otherwise
-      const int jc = j < D ? j : D - 1;
-      const int lo = fic < jc ? fic : jc, hi = fic < jc ? jc : fic;
-      int p = gss_packed_row(lo, D) + (hi > lo ? 1 + 2 * (hi - lo - 1) : 0);
-      p = p > E - 2 ? E - 2 : p;                          // the last diagonal entry has no neighbour (D = 1: none at all)
-      v0[j] = sRk[hi > lo ? p : gss_packed_row(lo, D)];
-      v1[j] = sRk[E > 1 ? p + 1 : 0];
+    for (int j = 0; j < D; ++j) {
+      ar[j] = dead ? 0.0 : ar[j];
+      ai[j] = dead ? 0.0 : ai[j];
     }
+  }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const bool diag = j == fi;
-      const bool use = on && j < D && (diag || !dead);
-      double re = v0[j] * sc;
-      double im = v1[j] * sc;
-      re = diag ? (dead ? 1.0 : re) + GSS_DELTA : re;
-      im = diag ? 0.0 : (fi > j ? -im : im);              // lower triangle = conjugate
-      ar[j] = use ? re : 0.0;
-      ai[j] = use ? im : 0.0;
-    }
+  for (int j = 0; j < D; ++j) {
+    ar[j] = fma(ar[j], sc, j == fi ? load : 0.0);
+    ai[j] *= sc;
   }
   // Gauss-Jordan sweeps.  The 8 lanes of a class sit in one half of a row of 16 lanes, so the pivot row
   // reaches them through the lane-permute move (class_row_bcast): nothing goes through LDS, nothing waits.
   // Executed by all lanes (the permute reads lanes, so none may be switched off); lanes without a row carry
-  // zeros or garbage that is never stored.  Pivot lane: row scaled by 1 / pivot; the others: row minus
-  // (a_ip / pivot) x pivot row -- one expression with the factors selected per lane.
+  // values that are never stored.  Row minus (a_ip / pivot) x pivot row; the pivot row itself minus (1 - 1 / pivot) x itself
+  // (pivots are at most D, so the difference cancels to an eighth of its terms at worst).
   double det = 1.0;
   static_for<0, D>([&](auto PI) {
     constexpr int p = PI.value;
     double pr[D], pi[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      pr[j] = class_row_bcast<p>(ar[j]);
-      pi[j] = class_row_bcast<p>(ai[j]);
-    }
+    class_row_bcast<p>(ar, pr);
+    class_row_bcast<p>(ai, pi);
     double piv = pr[p];
     if (!(piv > 1e-300)) {
       piv = 1e-300;
@@ -594,54 +657,50 @@ __device__ __forceinline__ void factor_classes_in_wave(const double* __restrict_
     const double rp = rcp_f64(piv);
     const bool is_piv = fi == p;
     const double fr = ar[p] * rp, fim = ai[p] * rp;      // M_ip / pivot
-    const double cr = is_piv ? -rp : fr, ci = is_piv ? 0.0 : fim;
+    const double cr = is_piv ? 1.0 - rp : fr, ci = is_piv ? 0.0 : fim;
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       if (j != p) {
-        const double br = is_piv ? 0.0 : ar[j], bi = is_piv ? 0.0 : ai[j];
-        ar[j] = br - (cr * pr[j] - ci * pi[j]);
-        ai[j] = bi - (cr * pi[j] + ci * pr[j]);
+        ar[j] = fma(ci, pi[j], fma(-cr, pr[j], ar[j]));
+        ai[j] = fma(-ci, pr[j], fma(-cr, pi[j], ai[j]));
       }
     }
     ar[p] = is_piv ? rp : -fr;
-    ai[p] = is_piv ? 0.0 : -fim;
+    ai[p] = -ci;
   });
   // packed coefficients of q = sum_i A_ii P_ii + 2 sum_{i<j} (Re A_ij Re P_ij + Im A_ij Im P_ij), A = the
   // Hermitian part of the computed inverse: the coefficient of the pair i < j is A_ij + conj(A_ji), not 2 A_ij.
   // (Rounding leaves the computed inverse slightly non-Hermitian.  For an ill-conditioned B, e.g. a class with
   // fewer frames than channels, whose inverse has entries of 1e6, the quadratic form of the Hermitian part is
   // still good to 1e-10 for the class's own frames, while that of one triangle mirrored is off by up to 1e-4.)
-  // The row owners write their upper-triangle entries, then add the conjugates of their lower-triangle entries.
-  // (One predicate per entry, the divisions as reciprocals: every lane computes the class constant, one stores.)
-  {
-    double* __restrict__ sCk = sC + fkc * (R * 16);
-    const int prow = gss_packed_row(fic, D);
+  if (on) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const bool diag = j == fi;
-      const int pj = diag ? prow : prow + 1 + 2 * (j - fic - 1);
-      if (on && j >= fi) {
-        sCk[pj] = ar[j];
-        if (!diag) sCk[pj + 1] = ai[j];
-      }
-    }
-    wave_lds_sync();
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      // entry (fi, j) with j < fi belongs to the pair (j, fi)
-      const int pj = gss_packed_row(j, D) + 1 + 2 * (fic - j - 1);
-      if (on && j < fi) {
-        sCk[pj] += ar[j];
-        sCk[pj + 1] -= ai[j];
-      }
-    }
-    const double pi_k = weight_mode == 1 ? Nk * rcp_f64(fmax(Ntot, GSS_EPS_N)) : 1.0 / (double)K;
-    const double cck = fmax(pi_k, GSS_EPS_PI) * rcp_f64(det);
-    if (on && fi == 0) sCC[fk] = cck;
+    for (int j = 0; j < D; ++j) *reinterpret_cast<double2*>(row + 2 * j) = make_double2(ar[j], j == fi ? 0.0 : ai[j]);
   }
+  wave_lds_sync();
+  if (le < E) {
+    const int code = sPlaces[le];
+    const double f = (double)(code >> 16);
+    const double* __restrict__ m0 = sM + (code & 0xff);
+    const double* __restrict__ m1 = sM + (code >> 8 & 0xff);
+#pragma unroll
+    for (int k = 0; k < K; ++k) sC[k * (R * 16) + le] = fma(f, m1[k * mat_doubles(D)], m0[k * mat_doubles(D)]);
+  }
+  // (every lane of a class computes the class constant; it is kept in scalar registers across the tile loop)
+  auto of_class = [](double x, int k) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 8 * k), __builtin_amdgcn_readlane(__double2loint(x), 8 * k));
+  };
+  double Ntot = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) Ntot += of_class(Nk, k);
+  const double pi_k = weight_mode == 1 ? Nk * rcp_f64(fmax(Ntot, GSS_EPS_N)) : 1.0 / (double)K;
+  const double cck = fmax(pi_k, GSS_EPS_PI) * rcp_f64(det);
+#pragma unroll
+  for (int k = 0; k < K; ++k) cc[k] = of_class(cck, k);
 }
 
-// The same for few channels, every class in one lane: lane k mod 8 has the packed matrix of class k in registers and eliminates
+// The M-step for few channels from the packed sums sR[K][E] and the class counts sN[K] (LDS), the class constants to sCC[K] (LDS),
+// every class in one lane: lane k mod 8 has the packed matrix of class k in registers and eliminates
 // it alone, B = L diag(d) L^H, M = L^-1, B^-1 = M^H diag(1 / d) M (Hermitian by construction).  Nothing crosses lanes between
 // the reads of the sums and the writes of the coefficients.  Up to 4 channels its chain of dependent instructions is shorter
 // than that of the sweeps with a row per lane: one segment of 200 frames, 10 iterations, 2 channels and 3 classes 36.8 -> 32.6
@@ -847,7 +906,7 @@ __global__ __launch_bounds__(kWave * K) void em_factor_small(
   // packed coefficients of q = sum_i A_ii P_ii + 2 sum_{i<j} (Re A_ij Re P_ij + Im A_ij Im P_ij), A = B^-1
   if (on && i <= j) {
     double* __restrict__ cf = coef + (sf * K + k) * (long)E;
-    // (the Hermitian part of the computed inverse: A_ij + conj(A_ji), see factor_classes_in_wave)
+    // (the Hermitian part of the computed inverse: A_ij + conj(A_ji), see m_step_in_wave)
     if (i == j) {
       cf[gss_packed_row(i, D)] = sMr[k][i][i];
     } else {
@@ -959,8 +1018,8 @@ __device__ __forceinline__ void whole_pass(
 //           one barrier per iteration), and every wavefront adds them up in the same order and runs the same
 //           factorisation on its own copy.
 //
-// Factorisation: up to 4 channels a lane per class (factor_class_in_lane), otherwise a lane per row of a class
-// (factor_classes_in_wave).
+// End of an iteration: up to 4 channels a lane per class (factor_class_in_lane), otherwise a lane per row of a class
+// (m_step_in_wave).
 //
 // Walk and resident tile are kernels of their own: in one kernel they need up to 57 registers more (4 channels and 2 classes 204,
 // now 151 and 139), and with them a wavefront per SIMD less (one segment of 1860 frames, 3 iterations, 2 channels and 7 classes 66.0
@@ -991,7 +1050,9 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
   // The sums, counts and class constants of the M-step live only between the last tile of a pass and the first
   // tile of the next one: they share the memory of the blocks.  So do the coefficients when they are resident in registers
   // during a pass (otherwise the pass reads them from LDS and they keep a place of their own).
-  constexpr int kMstepDoubles = kSumDoubles + K + (RESIDENT ? kCoefDoubles : 0);
+  constexpr bool IN_WAVE = D > kLaneFactorMaxD;        // m_step_in_wave: the class matrices instead of sums, counts and constants
+  constexpr int kMstepKept = IN_WAVE ? K * mat_doubles(D) : kSumDoubles + K;
+  constexpr int kMstepDoubles = kMstepKept + (RESIDENT ? kCoefDoubles : 0);
   constexpr int kTileDoubles = ((DIRECT || kMstepDoubles > kBlockDoubles ? kMstepDoubles : kBlockDoubles) + 1) / 2 * 2;
   constexpr int kWaveDoubles = kTileDoubles + (RESIDENT ? 0 : kCoefDoubles);
   constexpr int kShareRows = DIRECT ? 4 : 1;           // sets of sums per wavefront in the shared buffer (NW > 1)
@@ -1003,8 +1064,15 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
   double* __restrict__ sR = sY;                        // [K][E] packed weighted scatter sums
   double* __restrict__ sN = sR + K * E;                // [K] class counts
   double* __restrict__ sCC = sN + K;                   // [K] class constants pi / det B
-  double* __restrict__ sC = RESIDENT ? sCC + K : sY + kTileDoubles;   // [K][R * 16] coefficients of B^-1 for the next pass
+  double* __restrict__ sC = sY + (RESIDENT ? kMstepKept : kTileDoubles);   // [K][R * 16] coefficients of B^-1 for the next pass
   double* __restrict__ sShare = lds + NW * kWaveDoubles;   // [2][NW][kShareRows][kSumDoubles] sums of the wavefronts (NW > 1)
+  __shared__ int sPlaces[IN_WAVE ? kWave : 1];
+  static_assert(!IN_WAVE || NW == 1, "one table of places");
+  if constexpr (IN_WAVE) {
+    static constexpr MatPlaces<D> kPlaces = make_mat_places<D>();
+    sPlaces[lane] = kPlaces.code[lane];
+  }
+
   // workgroup -> (segment, frequency): the segments in the order of seg_order (longest first), if given
   const long sf = blockIdx.x;
   int s = (int)((unsigned)sf / (unsigned)F);
@@ -1081,47 +1149,50 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
     whole_pass<D, K, NW, ONE_TILE, false, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
-                                                    tiles, wave, lane, my_mask, pre, sY, acc, nacc);
+                                                            tiles, wave, lane, my_mask, pre, sY, acc, nacc);
 
     int le = lane;                                      // the lane number again, opaque
     asm volatile("" : "+v"(le));
-    // ---- sums over the rows of lanes -> packed sR[k][e]; class counts over the lanes -> sN[k] ----
-    // (NW > 1: into this wavefront's slot of the shared buffer of this iteration)
-    double* __restrict__ sOut = NW > 1 ? sShare + ((it & 1) * NW + wave) * (kShareRows * kSumDoubles) : sR;
-    if constexpr (DIRECT) store_direct_sums<D, K, (NW > 1)>(acc, nacc, sOut, le);
-    else store_tile_sums<D, K>(acc, nacc, sOut, le);
-    wave_lds_sync();
-    if constexpr (NW > 1) {
-      __syncthreads();                                  // every wavefront's sums of this iteration are in place
-      const double* __restrict__ all = sShare + (it & 1) * (NW * kShareRows * kSumDoubles);
-      for (int e = le; e < kSumDoubles; e += kWave) {
-        double sum = all[e];
-#pragma unroll
-        for (int w = 1; w < NW * kShareRows; ++w) sum += all[w * kSumDoubles + e];
-        sR[e] = sum;                                    // sN follows sR
-      }
+    if constexpr (IN_WAVE) {
+      m_step_in_wave<D, K>(acc, nacc, sY, sPlaces, sC, cc, le, weight_mode, status);
       wave_lds_sync();
-    }
-
-    // ---- M-step: B_k from (R_k, N_k), regularised, inverted; coefficients and class constants ----
-    if constexpr (D <= kLaneFactorMaxD) factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
-    else factor_classes_in_wave<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
-    wave_lds_sync();
+    } else {
+      // ---- sums over the lanes -> packed sR[k][e]; class counts -> sN[k] ----
+      // (NW > 1: into this wavefront's slot of the shared buffer of this iteration)
+      double* __restrict__ sOut = NW > 1 ? sShare + ((it & 1) * NW + wave) * (kShareRows * kSumDoubles) : sR;
+      if constexpr (DIRECT) store_direct_sums<D, K, (NW > 1)>(acc, nacc, sOut, le);
+      else store_tile_sums<D, K>(acc, nacc, sOut, le);
+      wave_lds_sync();
+      if constexpr (NW > 1) {
+        __syncthreads();                                // every wavefront's sums of this iteration are in place
+        const double* __restrict__ all = sShare + (it & 1) * (NW * kShareRows * kSumDoubles);
+        for (int e = le; e < kSumDoubles; e += kWave) {
+          double sum = all[e];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      {
+          for (int w = 1; w < NW * kShareRows; ++w) sum += all[w * kSumDoubles + e];
+          sR[e] = sum;                                  // sN follows sR
+        }
+        wave_lds_sync();
+      }
+      // ---- M-step: B_k from (R_k, N_k), regularised, inverted; coefficients and class constants ----
+      factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
+      wave_lds_sync();
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
         // the class constant is the same in every lane: kept in scalar registers across the tile loop
         const double c = sCC[k];
         cc[k] = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(c)),
                                  __builtin_amdgcn_readfirstlane(__double2loint(c)));
       }
-      if constexpr (RESIDENT) {
+    }
+    if constexpr (RESIDENT) {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const int e = 16 * r + (le & 15);
           creg[k * R + r] = sC[k * (R * 16) + (e < E ? e : E - 1)];
         }
-      }
     }
     wave_lds_sync();
   }
