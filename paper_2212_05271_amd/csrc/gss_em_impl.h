@@ -10,8 +10,8 @@
 //                              i = iters: write gamma
 //   factor i (i = 1 .. iters): B_k from (R_k, N_k), regularise, invert, log-det -> coefficients for pass i
 //
-// Pass 0 runs with B = I and uniform weights, which reproduces the initial posteriors
-// gamma^0 = activity / (number of active classes) and q^0 = 1.
+// Pass 0 has B = I and uniform weights, which are the initial posteriors
+// gamma^0 = activity / (number of active classes) and q^0 = 1 (PASS_FIRST).
 //
 // Arithmetic.  The quadratic form is evaluated as the real inner product <B^-1, y y^H> over the D*D real
 // degrees of freedom of the Hermitian outer product.  That form cancels heavily when B is
@@ -168,7 +168,11 @@ __device__ __forceinline__ void load_tile_regs(TileRegs<D>& r, const float2* __r
 //          TILE_STREAM replaces it by the lane's frame of the tile at next_t0, requested before phase 2, when the
 //          posterior's registers are free, and wants a mask that is not empty.
 enum TileSource { TILE_LOAD, TILE_KEEP, TILE_STREAM };
-template <int D, int K, bool FINAL, bool RESIDENT, bool DIRECT, TileSource SRC = TILE_LOAD>
+// PASS_FIRST: B = I and uniform weights, so q = |y|^2 and the active classes share the posterior: no coefficients and none of phase
+// 1's D * D FMAs per class (6 iterations, 8 channels and 5 classes: 12 segments of up to 300 frames 409 -> 392 us, 5 channels 225 ->
+// 202; 15 iterations of 64 segments 1 %).
+enum PassKind { PASS_FIRST, PASS_NEXT, PASS_FINAL };
+template <int D, int K, PassKind KIND, bool RESIDENT, bool DIRECT, TileSource SRC = TILE_LOAD>
 __device__ __forceinline__ void pass_tile(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, const double (&creg)[RESIDENT ? K * coef_regs(D) : 1],
     const double* __restrict__ sC, const double (&cc)[K], float* __restrict__ gamma_row /* + k*F*Tmax */,
@@ -177,6 +181,7 @@ __device__ __forceinline__ void pass_tile(
     TileRegs<D>* cur = nullptr, int next_t0 = 0) {
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
+  constexpr bool FINAL = KIND == PASS_FINAL;
   tmask &= (1u << K) - 1u;
   const int t = t0 + lane;
   if constexpr (SRC != TILE_STREAM) {
@@ -231,12 +236,17 @@ __device__ __forceinline__ void pass_tile(
   for (int e = E; e < R * 16; ++e) P[e] = 0.0;
   const double n2c = fmax(n2, GSS_EPS_NORM_SQ);
   const double qfloor = GSS_EPS_Q * n2c;
+  const double rq_first = KIND == PASS_FIRST ? rcp_f64_fast(fmax(n2, qfloor)) : 0.0;
   double rq[K], v[K], Z = 0.0;
   static_for<0, K>([&](auto KI) {
     constexpr int k = KI.value;
     rq[k] = 0.0;
     v[k] = 0.0;
-    if (class_on(tmask, k)) {
+    if constexpr (KIND == PASS_FIRST) {
+      rq[k] = rq_first;
+      v[k] = ((abits >> k) & 1u) ? 1.0 : 0.0;
+      Z += v[k];
+    } else if (class_on(tmask, k)) {
       double c[R], q[3] = {0.0, 0.0, 0.0};
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -320,7 +330,7 @@ __device__ __forceinline__ void pass_tile(
 
 // The accumulating pass over tiles lo .. hi - 1 in the tile layout: every live tile's frames are requested while the live
 // tile before it is in phase 2.
-template <int D, int K, bool RESIDENT, class MaskPtr>
+template <int D, int K, PassKind KIND, bool RESIDENT, class MaskPtr>
 __device__ __forceinline__ void stream_tiles(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K], int T,
@@ -339,7 +349,7 @@ __device__ __forceinline__ void stream_tiles(
     while (next < hi && (mn = tmrow[next] & kmask) == 0u) next += by;
     const bool last = next >= hi;
     // (after the last live tile its own frames are requested again, so that the load needs no branch)
-    pass_tile<D, K, false, RESIDENT, false, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
+    pass_tile<D, K, KIND, RESIDENT, false, TILE_STREAM>(Yrow, abrow, creg, sC, cc, nullptr, nullptr, 0, T, Tmax, tile * kWave, lane, m, sY,
                                            acc, nacc, &cur, (last ? tile : next) * kWave);
     if (last) break;
     tile = next;
@@ -407,13 +417,14 @@ __device__ __forceinline__ void store_tile_sums(const typename PassAcc<D, K, fal
   }
 }
 
-template <int D, int K, bool FINAL>
+template <int D, int K, PassKind KIND>
 __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
     gss_yview yv, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
     const int32_t* __restrict__ T_len,
     const double* __restrict__ coef, const double* __restrict__ cconst,
     double* __restrict__ part, double* __restrict__ npart, float* __restrict__ gamma, uint32_t* __restrict__ status,
     int F, int Tmax, ChunkMap cmap) {
+  constexpr bool FINAL = KIND == PASS_FINAL, FIRST = KIND == PASS_FIRST;
   constexpr int E = D * D;
   constexpr int R = coef_regs(D);
   constexpr bool RESIDENT = resident_coefs(D, K);
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   // per wavefront: a block on its way through LDS; then the wavefront's sums
   constexpr int kSumDoubles = (K * E + K + 1) / 2 * 2;
   constexpr int kTileDoubles = DIRECT || kSumDoubles > kBlockDoubles ? kSumDoubles : kBlockDoubles;
-  constexpr int kCoefDoubles = RESIDENT ? 0 : K * R * 16;
+  constexpr int kCoefDoubles = RESIDENT || FIRST ? 0 : K * R * 16;
   constexpr int kTilesDoubles = FINAL ? 2 : kPassWaves * kTileDoubles;
   __shared__ __attribute__((aligned(16))) double lds[kTilesDoubles + kCoefDoubles];
 
@@ -444,7 +455,9 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   // entry 16 r + (lane mod 16) in every lane (a lane past the end of the class reads the last entry of the
   // array instead: its value is never used).
   double creg[RESIDENT ? K * R : 1];
-  if constexpr (RESIDENT) {
+  if constexpr (FIRST) {
+    creg[0] = 0.0;
+  } else if constexpr (RESIDENT) {
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -462,7 +475,10 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   }
   // class constants pi_k / det B_k (wave-uniform, read through the scalar path)
   double cc[K];
-  {
+  if constexpr (FIRST) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) cc[k] = 1.0;
+  } else {
     typedef const __attribute__((address_space(4))) double* cc_ptr_t;
     const cc_ptr_t ccp = (cc_ptr_t)(uintptr_t)(cconst + sf * K);
 #pragma unroll
@@ -493,10 +509,10 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
   const int my_hi = tile_lo + (n_tiles * (wave + 1)) / kPassWaves;
   if constexpr (DIRECT || FINAL) {
     for (int tile = my_lo; tile < my_hi; ++tile)
-      pass_tile<D, K, FINAL, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
+      pass_tile<D, K, KIND, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, 1, lane, sY, acc, nacc);
+    stream_tiles<D, K, KIND, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, my_lo, my_hi, 1, lane, sY, acc, nacc);
   }
   if (FINAL) return;
 
@@ -958,16 +974,17 @@ __host__ __device__ constexpr bool request_ahead(int D, int K) { return D * K < 
 // One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile `pre` (ONE_TILE), or
 // tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are registers to spare, and the frames
 // of the next tile are requested from memory before the current tile is worked on.
-template <int D, int K, int NW, bool ONE_TILE, bool FINAL, bool RESIDENT, bool DIRECT, class MaskPtr>
+template <int D, int K, int NW, bool ONE_TILE, PassKind KIND, bool RESIDENT, bool DIRECT, class MaskPtr>
 __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
     const double (&creg)[RESIDENT ? K * coef_regs(D) : 1], const double* __restrict__ sC, const double (&cc)[K],
     float* __restrict__ gamma_row, uint32_t* __restrict__ status, long gamma_kstride, int T, int Tmax, int tile_end,
     int wave, int lane, unsigned my_mask, TileRegs<D>& pre, double* __restrict__ sY,
     typename PassAcc<D, K, DIRECT>::type& acc, double (&nacc)[K]) {
+  constexpr bool FINAL = KIND == PASS_FINAL;
   if constexpr (ONE_TILE) {
     if (wave < tile_end)
-      pass_tile<D, K, FINAL, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+      pass_tile<D, K, KIND, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, acc,
                                              nacc, &pre);
   } else if constexpr (DIRECT && D * D * K <= kPrefetchMaxAcc) {
@@ -988,7 +1005,7 @@ __device__ __forceinline__ void whole_pass(
         if (mn != 0u) load_tile_regs<D>(nxt, Yrow, abrow, next * kWave, lane, T);
       }
       // (the mask is the same in every lane; the compiler has to be told after the loop-carried copy)
-      pass_tile<D, K, FINAL, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
+      pass_tile<D, K, KIND, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              tile * kWave, lane, __builtin_amdgcn_readfirstlane(m), sY, acc, nacc,
                                              &cur);
       cur = nxt;
@@ -997,10 +1014,10 @@ __device__ __forceinline__ void whole_pass(
     }
   } else if constexpr (DIRECT || FINAL || !request_ahead(D, K)) {
     for (int tile = wave; tile < tile_end; tile += NW)
-      pass_tile<D, K, FINAL, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
+      pass_tile<D, K, KIND, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, acc, nacc);
   } else {
-    stream_tiles<D, K, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, wave, tile_end, NW, lane, sY, acc, nacc);
+    stream_tiles<D, K, KIND, RESIDENT>(Yrow, abrow, tmrow, creg, sC, cc, T, Tmax, wave, tile_end, NW, lane, sY, acc, nacc);
   }
 }
 
@@ -1115,27 +1132,13 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
     pre.abits = bits;
   }
 
-  // pass 0: B = I, uniform weights
+  // (written by the end of the first iteration)
   double creg[RESIDENT ? K * R : 1];
   double cc[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    cc[k] = 1.0;
+  for (int k = 0; k < K; ++k) cc[k] = 1.0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int e = 16 * r + (lane & 15);
-      double v = 0.0;
-#pragma unroll
-      for (int d = 0; d < D; ++d)
-        if (e == gss_packed_row(d, D)) v = 1.0;
-      if constexpr (RESIDENT) creg[k * R + r] = v;
-      else if (lane < 16) sC[(k * R + r) * 16 + lane] = v;
-    }
-  }
-  if constexpr (!RESIDENT) {
-    creg[0] = 0.0;
-    wave_lds_sync();
-  }
+  for (int r = 0; r < (RESIDENT ? K * R : 1); ++r) creg[r] = 0.0;
 
   // Everything the end of an iteration derives from the lane number is derived there anew, from a copy of
   // the lane number that the compiler cannot see through: values computed ahead of the iteration loop would be
@@ -1148,8 +1151,12 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, ONE_TILE, false, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride, T, Tmax,
-                                                            tiles, wave, lane, my_mask, pre, sY, acc, nacc);
+    if (it == 0)
+      whole_pass<D, K, NW, ONE_TILE, PASS_FIRST, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride,
+                                                                   T, Tmax, tiles, wave, lane, my_mask, pre, sY, acc, nacc);
+    else
+      whole_pass<D, K, NW, ONE_TILE, PASS_NEXT, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, nullptr, status, gamma_kstride,
+                                                                  T, Tmax, tiles, wave, lane, my_mask, pre, sY, acc, nacc);
 
     int le = lane;                                      // the lane number again, opaque
     asm volatile("" : "+v"(le));
@@ -1204,7 +1211,7 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
     zero_acc(acc);
 #pragma unroll
     for (int k = 0; k < K; ++k) nacc[k] = 0.0;
-    whole_pass<D, K, NW, ONE_TILE, true, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
+    whole_pass<D, K, NW, ONE_TILE, PASS_FINAL, RESIDENT, DIRECT>(Yrow, abrow, tmrow, creg, sC, cc, gamma_row, status, gamma_kstride, T,
                                                    Tmax, tiles_total, wave, lane, my_mask, pre, sY, acc, nacc);
   }
 }
@@ -1274,8 +1281,8 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
               int iters, int weight_mode, float* gamma, hipStream_t st) {
   const long n_sf = (long)S * F;
   // resident workgroups per compute unit of the two pass kernels: asked once per instantiation
-  static const int wgs_per_cu = resident_wgs(em_pass_small<D, K, false>, kWave * kPassWaves, 2);
-  static const int wgs_per_cu_fin = resident_wgs(em_pass_small<D, K, true>, kWave * kPassWaves, 2);
+  static const int wgs_per_cu = resident_wgs(em_pass_small<D, K, PASS_NEXT>, kWave * kPassWaves, 2);
+  static const int wgs_per_cu_fin = resident_wgs(em_pass_small<D, K, PASS_FINAL>, kWave * kPassWaves, 2);
   // From 5 channels on chunks for two workgroups per compute unit also where registers and LDS have room for more.  The 513 problems of
   // a segment are a chunk each then, and the 513th goes to the free places in pieces; planned for three, all of them are
   // cut in two, and the launch is a round and a third (1560 frames, 5 iterations, 5 channels and 3 classes 156 -> 127 us, 7
@@ -1347,10 +1354,10 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
     if (hipGetLastError() != hipSuccess) return GSS_EHIP;
     return GSS_OK;
   }
-  hipLaunchKernelGGL(em_init_coef, dim3(1024), dim3(256), 0, st, coef, cc, D, K, n_sf);
+  if (iters == 0) hipLaunchKernelGGL(em_init_coef, dim3(1024), dim3(256), 0, st, coef, cc, D, K, n_sf);
   for (int it = 0; it < iters; ++it) {
     gss_profile_begin(ctx, 0, st);
-    hipLaunchKernelGGL((em_pass_small<D, K, false>), dim3((unsigned)p.wgs_acc), block, 0, st, Y, abyte, tmask, T_len, coef,
+    hipLaunchKernelGGL((it == 0 ? em_pass_small<D, K, PASS_FIRST> : em_pass_small<D, K, PASS_NEXT>), dim3((unsigned)p.wgs_acc), block, 0, st, Y, abyte, tmask, T_len, coef,
                        cc, part, npart, (float*)nullptr, ctx->status, F, Tmax, p.acc);
     gss_profile_end(ctx, 0, st);
     gss_profile_begin(ctx, 1, st);
@@ -1358,7 +1365,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
                        ctx->status, p.acc, weight_mode);
     gss_profile_end(ctx, 1, st);
   }
-  hipLaunchKernelGGL((em_pass_small<D, K, true>), dim3((unsigned)p.wgs_fin), block, 0, st, Y, abyte, tmask, T_len, coef, cc,
+  hipLaunchKernelGGL((em_pass_small<D, K, PASS_FINAL>), dim3((unsigned)p.wgs_fin), block, 0, st, Y, abyte, tmask, T_len, coef, cc,
                      (double*)nullptr, (double*)nullptr, gamma, ctx->status, F, Tmax, p.fin);
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
