@@ -101,7 +101,7 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // two wavefronts per SIMD, are 4 to 7 % faster with the direct one.)
 constexpr int kPrefetchMaxAcc = 64;            // the whole-EM kernel requests the next tile ahead up to this many
 __host__ __device__ constexpr bool direct_layout(int D, int K, bool one) {
-  return D <= 2 || (D == 3 && !one && K <= 4) || (D == 4 && K <= 2);
+  return D <= 2 || (!one && ((D == 3 && K <= 4) || (D == 4 && K <= 2)));
 }
 
 // Tile layout: the D * D packed entries of the outer product in blocks of 16, which phase 2 takes transposed (lane = entry of a
@@ -358,32 +358,57 @@ __device__ __forceinline__ void stream_tiles(
 }
 
 // Direct layout: the wavefront's totals of the accumulators acc[k][e] and the class counts nacc[k], written as
-// out[k * E + e] and out[K * E + k] (LDS; the caller orders the traffic).  ROWS: the sums of the four rows of 16
-// lanes separately, row r at out[r * (K * E + K) + ...], for a caller that adds several such sets anyway (two
-// exchange steps less).
-template <int D, int K, bool ROWS = false>
-__device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K, true>::type& acc, const double (&nacc)[K],
-                                                  double* __restrict__ out, int lane) {
-  constexpr int E = D * D, N = K * E + K;
-  double v[N];
+// out[k * E + e] and out[K * E + k] (LDS; the caller orders the traffic).
+template <int D, int K>
+__device__ __forceinline__ void direct_values(const typename PassAcc<D, K, true>::type& acc, const double (&nacc)[K],
+                                              double (&v)[K * D * D + K]) {
+  constexpr int E = D * D;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
 #pragma unroll
     for (int e = 0; e < E; ++e) v[k * E + e] = acc[k][e];
     v[K * E + k] = nacc[k];
   }
-  transpose_reduce<N, ROWS>(v, lane);
-  if constexpr (ROWS) {
-    const int n0 = transposed_index(lane & 15);
-    double* __restrict__ orow = out + (lane >> 4) * N;
+}
+template <int D, int K>
+__device__ __forceinline__ void store_direct_sums(const typename PassAcc<D, K, true>::type& acc, const double (&nacc)[K],
+                                                  double* __restrict__ out, int lane) {
+  constexpr int N = K * D * D + K;
+  double v[N];
+  direct_values<D, K>(acc, nacc, v);
+  transpose_reduce<N>(v, lane);
+  const int n0 = transposed_index(lane);
 #pragma unroll
-    for (int j = 0; j < (N + 15) / 16; ++j)
-      if (n0 + 16 * j < N) orow[n0 + 16 * j] = v[j];
-  } else {
-    const int n0 = transposed_index(lane);
+  for (int j = 0; j < (N + kWave - 1) / kWave; ++j)
+    if (n0 + kWave * j < N) out[n0 + kWave * j] = v[j];
+}
+// The same by way of LDS, 16 values at a time, four lanes adding up 16 frames each of a value: a third of the instructions, where
+// 9 KB per wavefront are there (buf: 16 rows of kReduceRow doubles; rows 64 bytes apart modulo 256, so that the four lanes of
+// four rows read without bank conflicts).
+template <int D, int K>
+__device__ __forceinline__ void store_direct_sums_lds(const typename PassAcc<D, K, true>::type& acc, const double (&nacc)[K],
+                                                      double* __restrict__ buf, double* __restrict__ out, int lane) {
+  constexpr int N = K * D * D + K;
+  double v[N];
+  direct_values<D, K>(acc, nacc, v);
+  const double* __restrict__ src = buf + (lane >> 2) * kReduceRow + 2 * (lane & 3);
 #pragma unroll
-    for (int j = 0; j < (N + kWave - 1) / kWave; ++j)
-      if (n0 + kWave * j < N) out[n0 + kWave * j] = v[j];
+  for (int n0 = 0; n0 < N; n0 += 16) {
+#pragma unroll
+    for (int n = n0; n < (n0 + 16 < N ? n0 + 16 : N); ++n) buf[(n - n0) * kReduceRow + lane] = v[n];
+    wave_lds_sync();
+    double2 p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = *reinterpret_cast<const double2*>(src + 8 * i);
+    wave_lds_sync();
+    double h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h[i] = (p[i].x + p[i].y) + (p[i + 4].x + p[i + 4].y);
+    double sum = (h[0] + h[1]) + (h[2] + h[3]);
+    sum += dpp_permute_f64<0xB1>(sum);                   // quad_perm [1, 0, 3, 2]
+    sum += dpp_permute_f64<0x4E>(sum);                   // quad_perm [2, 3, 0, 1]
+    const int n = n0 + (lane >> 2);
+    if ((lane & 3) == 0 && n < N) out[n] = sum;
   }
 }
 
@@ -742,6 +767,29 @@ __device__ __forceinline__ void factor_class_in_lane(const double* __restrict__ 
 #pragma unroll
   for (int c = 0; c < K; ++c) Ntot += n[c];
   const bool dead = !((double)D * tr > GSS_EPS_N * fmax(Nk, GSS_EPS_N));
+  if constexpr (D == 2) {
+    // B = (2 / tr) R', R' = R + delta tr / 2 I: B^-1 = (tr / 2) adj R' / det R' and det B = det R' (2 / tr)^2, one reciprocal
+    // behind the sums instead of four in a row (the M-step 900 -> 600 cycles)
+    const double half = dead ? 1.0 : 0.5 * tr;
+    const double a = fma(GSS_DELTA, half, dead ? 1.0 : h[0]), d = fma(GSS_DELTA, half, dead ? 1.0 : h[3]);
+    const double br = dead ? 0.0 : h[1], bi = dead ? 0.0 : h[2];
+    double det = fma(a, d, -fma(br, br, bi * bi));
+    if (!(det > 0.0)) {
+      det = 1e-300;
+      if (on) atomicOr(status, GSS_STATUS_NONPD_B);
+    }
+    const double s = half * rcp_f64(det);
+    const double pi_k = weight_mode == 1 ? Nk * rcp_f64(fmax(Ntot, GSS_EPS_N)) : 1.0 / (double)K;
+    if (on) {
+      double* __restrict__ sCk = sC + k * (R * 16);
+      sCk[0] = d * s;
+      sCk[1] = -2.0 * br * s;
+      sCk[2] = -2.0 * bi * s;
+      sCk[3] = a * s;
+      sCC[k] = fmax(pi_k, GSS_EPS_PI) * (half * s);
+    }
+    return;
+  }
   const double sc = dead ? 0.0 : (double)D * rcp_f64(tr);
   // upper triangle: hr/hi[i][j] = entry (i, j), i <= j
   double hr[D][D], hi[D][D];
@@ -1031,9 +1079,10 @@ __device__ __forceinline__ void whole_pass(
 //           walks all tiles of its problem; nothing is shared between wavefronts.
 //   NW = 4: for few problems of few channels.  ONE_TILE, at most NW tiles (256 frames): wavefront w owns tile w and keeps
 //           its frames in registers for all iterations, so an iteration reads nothing from memory.  More tiles:
-//           wavefront w walks tiles w, w + NW, ...  The wavefronts' sums meet in LDS (two buffers, used in turn,
-//           one barrier per iteration), and every wavefront adds them up in the same order and runs the same
-//           factorisation on its own copy.
+//           wavefront w walks tiles w, w + NW, ...  The wavefronts' sums meet in LDS, and the first wavefront adds them up and
+//           factorises for all of them (by each for itself on two sets of buffers, one barrier instead of two per iteration:
+//           one segment of 200 frames, 10 iterations, 2 channels and 3 classes 26.6 -> 20.7 us (19.8 with the closed form at 2 channels), with
+//           store_direct_sums_lds, 1500 frames, 8 iterations 54.0 -> 48.9; 4 channels and 5 classes 119 -> 112).
 //
 // End of an iteration: up to 4 channels a lane per class (factor_class_in_lane), otherwise a lane per row of a class
 // (m_step_in_wave).
@@ -1044,17 +1093,19 @@ __device__ __forceinline__ void whole_pass(
 // ----------------------------------------------------------------------------------------------
 constexpr int kWholeQuad = 4;                 // wavefronts per problem of the variant for few problems
 constexpr int kWholeQuadMaxD = 4;             // ... which is built for up to this many channels
-// Wavefronts per SIMD that the kernel is compiled for.  Up to 2 channels the tile loop lives in two registers for every
+// Wavefronts per SIMD that the kernel is compiled for.  With a tile per wavefront three, also where that spills up to 42 registers
+// (2 and 4 channels, 8 classes): the 513 problems of a segment do not fit the chip at two (60 frames, 3 / 4 channels and 8 classes 1.68 /
+// 1.64 times as long).  Up to 2 channels the tile loop lives in two registers for every
 // accumulator, coefficient, partial sum and count, and some 40 more; the compiler takes one or two more than a step of the
 // register file allows (2 channels: 74 with 2 classes, 169 with 8) unless it is told: 24 segments of up to 700 frames, 2
 // classes, 3 iterations 88 -> 80 us, 48 segments of up to 300 frames, 8 classes 244 -> 209.
-__host__ __device__ constexpr int whole_waves_per_simd(int D, int K) {
+__host__ __device__ constexpr int whole_waves_per_simd(int D, int K, int NW) {
   if (D > 2) return 2;
-  const int regs = 2 * K * (D * D + 4) + 40, waves = 512 / ((regs + 7) / 8 * 8);
-  return waves < 8 ? waves : 8;
+  const int regs = 2 * K * (D * D + 4) + 40, waves = 512 / ((regs + 7) / 8 * 8), most = NW > 1 ? 4 : 8;   // (four wavefronts: LDS)
+  return waves < most ? waves : most;
 }
 template <int D, int K, int NW, bool ONE_TILE>
-__global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, K)) void em_whole_small(
+__global__ __launch_bounds__(kWave * NW, ONE_TILE ? 3 : whole_waves_per_simd(D, K, NW)) void em_whole_small(
     gss_yview yv, const uint8_t* __restrict__ act, const uint8_t* __restrict__ abyte, const uint32_t* __restrict__ tmask,
     const int32_t* __restrict__ T_len, const int32_t* __restrict__ seg_order, float* __restrict__ gamma,
     uint32_t* __restrict__ status, int F, int Tmax, int iters, int weight_mode) {
@@ -1070,19 +1121,22 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
   constexpr bool IN_WAVE = D > kLaneFactorMaxD;        // m_step_in_wave: the class matrices instead of sums, counts and constants
   constexpr int kMstepKept = IN_WAVE ? K * mat_doubles(D) : kSumDoubles + K;
   constexpr int kMstepDoubles = kMstepKept + (RESIDENT ? kCoefDoubles : 0);
-  constexpr int kTileDoubles = ((DIRECT || kMstepDoubles > kBlockDoubles ? kMstepDoubles : kBlockDoubles) + 1) / 2 * 2;
+  // (NW > 1: the sums of every wavefront, and the buffers of the M-step, are in a part of their own; the wavefront's part is a
+  // block's or store_direct_sums_lds's)
+  constexpr int kBlocks = DIRECT ? (NW > 1 ? 16 * kReduceRow : 0) : kBlockDoubles;
+  constexpr int kTileDoubles = NW > 1 ? kBlocks : ((kMstepDoubles > kBlocks ? kMstepDoubles : kBlocks) + 1) / 2 * 2;
   constexpr int kWaveDoubles = kTileDoubles + (RESIDENT ? 0 : kCoefDoubles);
-  constexpr int kShareRows = DIRECT ? 4 : 1;           // sets of sums per wavefront in the shared buffer (NW > 1)
-  constexpr int kShareDoubles = NW > 1 ? 2 * NW * kShareRows * kSumDoubles : 0;
+  constexpr int kShareDoubles = NW > 1 ? NW * kSumDoubles + kMstepDoubles : 0;
+  static_assert(NW == 1 || RESIDENT, "coefficients from the shared part go to registers");
   __shared__ __attribute__((aligned(16))) double lds[NW * kWaveDoubles + kShareDoubles];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0;
   double* __restrict__ sY = lds + wave * kWaveDoubles;
-  double* __restrict__ sR = sY;                        // [K][E] packed weighted scatter sums
+  double* __restrict__ sR = NW > 1 ? lds + NW * kWaveDoubles : sY;   // [K][E] packed weighted scatter sums
   double* __restrict__ sN = sR + K * E;                // [K] class counts
   double* __restrict__ sCC = sN + K;                   // [K] class constants pi / det B
-  double* __restrict__ sC = sY + (RESIDENT ? kMstepKept : kTileDoubles);   // [K][R * 16] coefficients of B^-1 for the next pass
-  double* __restrict__ sShare = lds + NW * kWaveDoubles;   // [2][NW][kShareRows][kSumDoubles] sums of the wavefronts (NW > 1)
+  double* __restrict__ sC = RESIDENT ? sR + kMstepKept : sY + kTileDoubles;   // [K][R * 16] coefficients of B^-1 for the next pass
+  double* __restrict__ sShare = lds + NW * kWaveDoubles + kMstepDoubles;      // [NW][kSumDoubles] sums of the wavefronts (NW > 1)
   __shared__ int sPlaces[IN_WAVE ? kWave : 1];
   static_assert(!IN_WAVE || NW == 1, "one table of places");
   if constexpr (IN_WAVE) {
@@ -1165,25 +1219,32 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 2 : whole_waves_per_simd(D, 
       wave_lds_sync();
     } else {
       // ---- sums over the lanes -> packed sR[k][e]; class counts -> sN[k] ----
-      // (NW > 1: into this wavefront's slot of the shared buffer of this iteration)
-      double* __restrict__ sOut = NW > 1 ? sShare + ((it & 1) * NW + wave) * (kShareRows * kSumDoubles) : sR;
-      if constexpr (DIRECT) store_direct_sums<D, K, (NW > 1)>(acc, nacc, sOut, le);
-      else store_tile_sums<D, K>(acc, nacc, sOut, le);
-      wave_lds_sync();
+      // (NW > 1: the wavefronts' sums meet in LDS; the first one adds them up and runs the M-step for all of
+      // them: run by each of them it took issue slots that the others of the SIMD miss)
       if constexpr (NW > 1) {
+        double* __restrict__ sOut = sShare + wave * kSumDoubles;
+        if constexpr (DIRECT) store_direct_sums_lds<D, K>(acc, nacc, sY, sOut, le);
+        else store_tile_sums<D, K>(acc, nacc, sOut, le);
         __syncthreads();                                // every wavefront's sums of this iteration are in place
-        const double* __restrict__ all = sShare + (it & 1) * (NW * kShareRows * kSumDoubles);
-        for (int e = le; e < kSumDoubles; e += kWave) {
-          double sum = all[e];
+        if (wave == 0) {
+          for (int e = le; e < kSumDoubles; e += kWave) {
+            double sum = sShare[e];
 #pragma unroll
-          for (int w = 1; w < NW * kShareRows; ++w) sum += all[w * kSumDoubles + e];
-          sR[e] = sum;                                  // sN follows sR
+            for (int w = 1; w < NW; ++w) sum += sShare[w * kSumDoubles + e];
+            sR[e] = sum;                                // sN follows sR
+          }
+          wave_lds_sync();
+          factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
         }
+        __syncthreads();
+      } else {
+        if constexpr (DIRECT) store_direct_sums<D, K>(acc, nacc, sR, le);
+        else store_tile_sums<D, K>(acc, nacc, sR, le);
+        wave_lds_sync();
+        // ---- M-step: B_k from (R_k, N_k), regularised, inverted; coefficients and class constants ----
+        factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
         wave_lds_sync();
       }
-      // ---- M-step: B_k from (R_k, N_k), regularised, inverted; coefficients and class constants ----
-      factor_class_in_lane<D, K>(sR, sN, sC, sCC, le, weight_mode, status);
-      wave_lds_sync();
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         // the class constant is the same in every lane: kept in scalar registers across the tile loop
@@ -1232,19 +1293,14 @@ constexpr int kWholeMaxTilesAlways = 5;
 // Up to 4 channels: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
 // compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
 constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
-// Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but each of them adds up and factorises for
-// itself, which costs the more the more of them share a SIMD (`load` problems per compute unit = wavefronts per SIMD), the more
-// channels there are, and where registers let two of them at most onto a SIMD, which then wait for each other's latencies.
-// Over 1 to 8 classes, 1 to 24 segments of 40 to 1860 frames, 3 to 10 iterations, the four are the faster ones where they save
-// three quarters of D (load^2 / 10 + 1) tiles: one segment of 513 bins from 3 tiles with 1 channel to 8 with 4, four segments from
-// 10 (1 channel) or 30 (3 channels).  With a tile per wavefront they also save a launch, which a call of few and short
-// iterations gains by.  Over these the choice is 0.13 % off the better of both on average, 28 % at most.  (By the rounds of
-// workgroups that the registers allow: 3 segments of 130 frames, 10 iterations, 2 channels and 1 class 34 us with four, 23
-// with one; one segment of 64 frames, 4 channels and 2 classes 44 and 27.)
-inline bool use_quad(int D, int K, double load, int wgs_per_cu, int tiles, int iters) {
-  const double line = D * (load * load / 10 + 1) * (wgs_per_cu > 2 ? 1.0 : 1.4);
-  const double saved = (tiles - (tiles + kWholeQuad - 1) / kWholeQuad) * (4.0 / 3.0);
-  return saved >= line || (tiles <= kWholeQuad && iters * (line - saved) * (D + 1) * (K + 2) < 200);
+// Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but barriers, and one of the four adds up and
+// factorises while the others wait, which costs the more the more problems share a compute unit (`load`).  Four / one, us, 8
+// iterations, 2 channels and 3 classes: one segment of 60 / 250 / 1000 frames 0.88 / 0.64 / 0.55 times as long, two 1.21 / 0.79 /
+// 0.67, four 1.45 / 0.99 / 0.79, eight 1.70 / 1.17 / 0.94; 4 channels and 5 classes 0.97 / 0.65 / 0.58, 1.31 / 0.82 / 0.67, 1.58 /
+// 1.03 / 0.80, 1.96 / 1.21 / 0.93.  Over 496 calls of 1 to 4 channels, 2 to 8 classes, 1 to 8 segments of 60 to 1800 frames the
+// choice takes 0.5 % longer than the better of both on average, 34 % at most (one tile, 2 channels and 8 classes).
+inline bool use_quad(double load, int tiles) {
+  return tiles - (tiles + kWholeQuad - 1) / kWholeQuad >= 0.04 * load * load - 0.3;
 }
 
 struct EmPlan {
@@ -1319,7 +1375,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
       const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
-      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, quads_per_cu, tiles, iters);
+      tiny = use_quad((double)n_sf / ctx->num_cu, tiles);
       const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
       if (row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }
