@@ -1280,16 +1280,26 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 3 : whole_waves_per_simd(D, 
 // ----------------------------------------------------------------------------------------------
 // Host-side plan and dispatch
 // ----------------------------------------------------------------------------------------------
-// Problems per compute unit from which on the whole-EM kernel is used.  Against chunks, all channel and class counts, 3
-// iterations: 5 channels and more, 8 segments of 513 bins (16 per compute unit) and more, up to 32 tiles 0.4 to 0.95 times the time
-// in ragged batches, 0.7 to 1.0 in uniform ones (8 segments of 1860 frames, 8 channels and 8 classes 1.06); longer problems of one
-// length end in a partly filled round (8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14) and wait for 12.  Up to
-// 4 channels: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones wait
-// for 8 segments; 4 segments of up to 700 frames, 4 channels and 8 classes 190 us in chunks, 120 in one launch).  (The line was three rounds of the wavefronts that fit the chip: with
-// fewer registers the kernel got more wavefronts and the call went back to chunks, 16 segments of 640 frames, 3 iterations,
-// 7 channels and 2 classes 262 -> 317 us, 2 channels and 8 classes 132 -> 285.)
-constexpr int whole_min_per_cu(bool few, int tiles) { return (few ? 8 : 16) + (tiles <= 32 ? 0 : 8); }
-constexpr int kWholeMaxTilesAlways = 5;
+// Where the whole-EM kernel with a wavefront per problem is used: tiles per problem, by the problems per compute unit (`load`; 2 for
+// the 513 bins of a segment) and whether the segments have lengths of their own, so that the wavefronts end at different times.
+// The line lies where the routes were measured against each other, 8 iterations, time in one launch over time in chunks:
+//   segments of   330 frames   400         701         1200        1875 frames (8 channels and 5 classes, uniform / ragged)
+//   1             0.92         0.97        1.22        1.44        1.70
+//   2             0.82 / 0.71  0.90 / 0.72 1.06 / 0.87 1.18 / 1.05 1.33 / 1.23
+//   3             0.66 / 0.64  0.69 / 0.70 0.84 / 0.83 0.97 / 0.98 1.06 / 1.15
+//   4             0.73 / 0.63  0.79 / 0.61 0.95 / 0.68 1.03 / 0.79 1.12 / 0.86
+//   5             0.65 / 0.62  0.70 / 0.64 0.80 / 0.77 0.89 / 0.88 0.92 / 0.96
+//   8             0.67 / 0.60  0.70 / 0.62 0.80 / 0.68 0.84 / 0.75 0.95 / 0.78
+// and within 0.1 of that at 5 to 8 channels and 3 to 8 classes.  Problems of more than 32 tiles of one length end in a partly filled
+// round and wait for 12 segments (3 iterations, 8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14).
+// Up to 4 channels: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones
+// wait for 8 segments; 4 segments of up to 700 frames, 4 channels and 8 classes 190 us in chunks, 120 in one launch).
+inline bool use_whole(int D, double load, int tiles, bool ragged) {
+  if (D <= 4) return load >= (tiles <= 32 ? 8 : 16) || tiles <= 5;
+  if (tiles > 32) return load >= 24;
+  const int most = load >= 10 ? 32 : load >= 8 ? (ragged ? 32 : 16) : load >= 6 ? (ragged ? 19 : 16) : load >= 4 ? (ragged ? 10 : 9) : D >= 7 ? 6 : 7;
+  return tiles <= most;
+}
 // Up to 4 channels: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
 // compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
 constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
@@ -1364,8 +1374,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
   // is cut into chunks over several workgroups, one pass and one factor launch per iteration, unless it has few tiles: two
   // launches per iteration cost more than the whole EM of such a problem in one wavefront.
   const bool choose = ctx->em_whole_min_problems < 0;
-  bool whole = n_sf >= (choose ? (long)whole_min_per_cu(D <= kWholeQuadMaxD, tiles) * ctx->num_cu : (long)ctx->em_whole_min_problems) ||
-               (choose && tiles <= kWholeMaxTilesAlways);
+  bool whole = choose ? use_whole(D, (double)n_sf / ctx->num_cu, tiles, T_len != nullptr) : n_sf >= (long)ctx->em_whole_min_problems;
   // Up to 4 channels there is the variant with four wavefronts per problem (use_quad), and as tiles are cheap (a launch costs as
   // much as a few dozen of them) few problems go to the whole-EM kernel as well unless a pass is so long that
   // the launches per iteration no longer matter.
