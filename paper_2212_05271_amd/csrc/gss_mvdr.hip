@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
   const int tile_end = (T + kWave - 1) / kWave;
   tile_hi = tile_hi < tile_end ? tile_hi : tile_end;
   // One tile of 64 frames per step; the loads of the wavefront's next tile are issued before the arithmetic
-  // of the current one.  A lane beyond T reads frame 0 (its weights are forced to zero).
+  // of the current one.  The masks are read past the caches, which keep the observations for the beamformer.  A lane beyond T reads frame 0 (its weights are forced to zero).
   float2 yraw[D];
   float gv[GSS_MAX_K];
   auto load_tile = [&](int tile) {
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
 #pragma unroll
     for (int d = 0; d < D; ++d) yraw[d] = Yrow[tc * D + d];
 #pragma unroll
-    for (int k = 0; k < GSS_MAX_K; ++k) gv[k] = k < K ? grow[k * gk + tc] : 0.f;
+    for (int k = 0; k < GSS_MAX_K; ++k) gv[k] = k < K ? __builtin_nontemporal_load(grow + k * gk + tc) : 0.f;
   };
   int tile = tile_lo + wave;
   if (tile < tile_hi) load_tile(tile);
@@ -260,9 +260,16 @@ __global__ __launch_bounds__(1024) void mvdr_ref(const double* __restrict__ pw, 
   const int r = threadIdx.x & 31, j = threadIdx.x >> 5;
   double num = 0.0, den = 0.0;
   if (r < D) {
-    for (int f = j; f < F; f += 32) {
-      num += pw[(((long)s * F + f) * D + r) * 2 + 0];
-      den += pw[(((long)s * F + f) * D + r) * 2 + 1];
+    const double2* __restrict__ p = reinterpret_cast<const double2*>(pw) + (long)s * F * D + r;
+    for (int f0 = j; f0 < F; f0 += 8 * 32) {
+      double2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = f0 + 32 * u < F ? p[(long)(f0 + 32 * u) * D] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        num += v[u].x;
+        den += v[u].y;
+      }
     }
   }
   snum[r][j] = num;
@@ -311,13 +318,14 @@ __global__ __launch_bounds__(256) void mvdr_ref_freq(const double* __restrict__ 
 // Apply: X[s][f][t] = sum_d conj(h[d]) y[t][d], lane = frame; the filter is wave-uniform.
 // Grid: blockIdx.x = chunk + C * (f + F * s), 256 frames per workgroup step.
 // ----------------------------------------------------------------------------------------------
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(256) void mvdr_apply_small(
     gss_yview yv, const double2* __restrict__ H, const int32_t* __restrict__ ref,
     const int32_t* __restrict__ T_len, float2* __restrict__ X, int F, int Tmax, int C, int frames_per_chunk,
     int ref_per_f) {
   // last row first: the covariances were formed from the first to the last, so the observations read last are still in the 256
-  // MB cache (16 segments, 0.55 GB of observations: the whole call 332 -> 315 us; a call that fits the cache gains nothing)
+  // MB cache (16 segments, 0.55 GB of observations: the whole call 332 -> 315 us; a call that fits the cache gains nothing), and
+  // where they do not all fit it the output and the masks go past it (STREAM; 315 -> 302, 2048 frames per workgroup 292)
   const unsigned block = gridDim.x - 1 - blockIdx.x;
   const int chunk = block % C;
   const long sf = block / C;
@@ -347,7 +355,9 @@ __global__ __launch_bounds__(256) void mvdr_apply_small(
         xi += hr[d] * (double)v.y - hi[d] * (double)v.x;
       }
     }
-    Xrow[t] = make_float2((float)xr, (float)xi);
+    const float2 v = make_float2((float)xr, (float)xi);
+    if constexpr (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(double, v), reinterpret_cast<double*>(Xrow + t));
+    else Xrow[t] = v;
   }
 }
 
@@ -382,11 +392,12 @@ int run_mvdr_small(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const i
                      target, part, ctx->status, F, Tmax, K, C, tpc);
   hipLaunchKernelGGL((mvdr_solve_small<D>), dim3((unsigned)n_sf), dim3(kWave), 0, st, part, H, pw, ctx->status, C);
   gss_launch_mvdr_ref(pw, ref, ctx->status, S, F, D, ref_per_f, st);
-  const int fpc = 1024;
+  const int fpc = 2048;
   const int CA = (Tmax + fpc - 1) / fpc;
   if (n_sf * CA > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  hipLaunchKernelGGL((mvdr_apply_small<D>), dim3((unsigned)(n_sf * CA)), dim3(256), 0, st, Y, H, ref, T_len, X, F, Tmax,
-                     CA, fpc, ref_per_f);
+  const bool past = (double)n_sf * Tmax * D * sizeof(float2) > 200e6;
+  hipLaunchKernelGGL((past ? mvdr_apply_small<D, true> : mvdr_apply_small<D, false>), dim3((unsigned)(n_sf * CA)), dim3(256), 0, st, Y, H,
+                     ref, T_len, X, F, Tmax, CA, fpc, ref_per_f);
   if (hipGetLastError() != hipSuccess) return GSS_EHIP;
   return GSS_OK;
 }
