@@ -159,19 +159,18 @@ __device__ __forceinline__ int fft_bin(int lane) { return (lane >> 3) + 8 * (lan
 __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (long)((unsigned long)w * (unsigned long)n / (unsigned long)wgs); }
 
 // ----------------------------------------------------------------------------------------------
-// STFT.  A workgroup takes steps of (segment, frame) items; a step is UNITS units of 8 transforms, one per wavefront: a unit
-// is all channels of a frame (of 8 / D consecutive frames with fewer than 5 channels), or 8 channels of a frame with more
-// than 8.  The samples of the next unit are requested before the current transforms.  The spectrum replaces the transform in
+// STFT.  A workgroup of W wavefronts takes steps of (segment, frame) items; a step is UNITS units of W transforms, one per wavefront: a
+// unit is all channels of W / D consecutive frames, or 8 channels of a frame with more than 8 (W = 8).  The samples of the next unit are requested before the current transforms.  The spectrum replaces the transform in
 // the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and X[512 - k]), and the workgroup
 // writes a bin's values of the step as one run of memory (128 bytes for two units of 8 channels).
 //
-// Bound: latency, with the LDS busy for some 40 % of the time (484 cycles per transform, 209 of them bank conflicts, before the
-// window had a table).  Two workgroups per compute unit are resident, held there by 128 registers and, for two units, by LDS;
-// each has one unit of samples in flight.  At 128 registers 14 (two units) or 10 (one) are spilled to scratch memory.  Ten
-// minutes of 8 channels: 504 us = 3.0 TB/s (window from the cosine table, a fifth round of the split loop for bin 256 alone:
-// 530 us, on a second card 518 and 546; before that an even share of consecutive frames per workgroup instead of turns 583 us,
-// one workgroup per frame, 64-byte runs 722 us).  6000 frames of 8 channels 73 -> 63 us, 3000 frames of 12 channels 64 -> 59.
-// Three workgroups per compute unit at 80 registers: 55 to 70 spilled, twice as slow.
+// Bound: memory and latency.  W = 8: two workgroups per compute unit are resident, held there by 128 registers and, for two
+// units, by LDS; each has one unit of samples in flight.  W = 16 (long calls): one workgroup per compute unit with 256-byte runs per
+// bin.  At 128 registers 14 to 24 (two units) or 10 (one) are spilled to scratch memory.  Ten minutes of 8 channels: 504 us -> 434
+// with the spectrum written past the caches (STREAM) -> 370 us = 4.2 TB/s with W = 16 as well (a large copy: 4.7).  On the way: an
+// even share of consecutive frames per workgroup instead of turns 583 us, one workgroup per frame, 64-byte runs 722 us; turns of
+// 4 or 8 steps, whose frames share samples in the compute unit's own cache, 497 to 533 us: neighbouring workgroups then write
+// further apart.  Three workgroups per compute unit at 80 registers: 55 to 70 spilled, twice as slow.
 //
 // One unit per step for short calls (gss_stft): 8 channels 7.7, 10.7, 17.2 us at 130, 510, 1020 frames (two units 11.0, 12.5,
 // 17.0; one workgroup per frame 8.1, 11.2, 20.6).
@@ -181,8 +180,14 @@ constexpr int kStftWgsPerCu = 2;                           // resident workgroup
 constexpr int kStftRow = 577;
 static_assert(kStftRow >= 8 * kExStride && kStftRow >= kBins, "row pitch of the transforms in LDS");
 struct __attribute__((packed, aligned(4))) PairUnaligned { float a, b; };
-template <int UNITS>
-__global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
+// A store that does not stay in the caches (STREAM).
+template <bool STREAM>
+__device__ __forceinline__ void put(float2* p, float2 v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(double, v), reinterpret_cast<double*>(p));
+  else *p = v;
+}
+template <int W, int UNITS, bool STREAM>
+__global__ __launch_bounds__(64 * W, 4) void stft_kernel(const float* __restrict__ x, float2* __restrict__ Y,
                                                                 const float2* __restrict__ table, int D, long N, int T,
                                                                 long n_items) {
   // (two units: the split's half of the table only, so that two workgroups fit into a compute unit; the lanes' constants come
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
   constexpr int kTw = UNITS == 1 ? kH + 1 : kH / 2;
   __shared__ float2 tw[kTw];
   __shared__ float2 win[kH];
-  __shared__ float2 rows[UNITS * kFftWaves][kStftRow];
+  __shared__ float2 rows[UNITS * W][kStftRow];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -199,14 +204,14 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
   const int xcd = (int)(blockIdx.x % kXcds);
   const long j = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
   const bool by_frame = D <= 8;                            // the units of a step: frames, or groups of eight channels
-  const int per_unit = D <= 4 ? 8 / D : 1;                 // frames per unit
+  const int per_unit = D <= 8 ? W / D : 1;                 // frames per unit
   const int per_step = by_frame ? UNITS * per_unit : 1;    // frames per step
   constexpr int kChans = 8 * UNITS;                        // more than 8 channels: channels per step
   const long item1 = share_begin(xcd + 1, kXcds, n_items);
   long i = share_begin(xcd, kXcds, n_items) + j * per_step, block_end = i + per_step;
   if (i >= item1) return;
 
-  const int my_frame = D <= 4 ? wave / D : 0, my_chan = D <= 4 ? wave % D : wave;
+  const int my_frame = D <= 8 ? wave / D : 0, my_chan = D <= 8 ? wave % D : wave;
   // this wavefront's samples of unit u of the step at item i, channels from d0 on
   float2 raw[8];
   auto request = [&](long i, int d0, int u) {
@@ -264,7 +269,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
       else if (in < item1) request(in, dn, 0);
       const int fr = by_frame ? u * per_unit + my_frame : 0, dd = my_chan + (by_frame ? 0 : 8 * u);
       if (my_frame < per_unit && fr < nf && dd < nd) {
-        float2* __restrict__ Z = rows[u * kFftWaves + wave];
+        float2* __restrict__ Z = rows[u * W + wave];
         fft512(v, Z, fc, lane);
         const int kb = fft_bin(lane);
 #pragma unroll
@@ -288,17 +293,17 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
     }
     __syncthreads();
     // bin k: the step's nf frames x nd channels, one run of memory (several frames: all their channels)
-    const int nr = nf * nd, q = by_frame ? per_unit * D : kFftWaves;     // values per bin, of the first unit
+    const int nr = nf * nd, q = by_frame ? per_unit * D : W;     // values per bin, of the first unit
     float2* __restrict__ out = Y + ((long)s * kBins * T + t) * D + d0;
     const long pitch = (long)T * D;
-    constexpr int kFull = 8 * UNITS, kShift = UNITS == 1 ? 3 : 4;        // (a full step: the first unit has 8 values)
+    constexpr int kFull = W * UNITS, kShift = kFull == 8 ? 3 : kFull == 16 ? 4 : 5;        // (a full step: the first unit has 8 values)
     if (nr == kFull) {
-      for (int e = threadIdx.x; e < kBins * kFull; e += 64 * kFftWaves)
-        out[(e >> kShift) * pitch + (e & (kFull - 1))] = rows[e & (kFull - 1)][e >> kShift];
+      for (int e = threadIdx.x; e < kBins * kFull; e += 64 * W)
+        put<STREAM>(out + (e >> kShift) * pitch + (e & (kFull - 1)), rows[e & (kFull - 1)][e >> kShift]);
     } else {
-      for (int e = threadIdx.x; e < kBins * nr; e += 64 * kFftWaves) {
+      for (int e = threadIdx.x; e < kBins * nr; e += 64 * W) {
         const int k = (int)((unsigned)e / (unsigned)nr), r = e - k * nr;
-        out[k * pitch + r] = rows[r < q ? r : kFftWaves + r - q][k];
+        put<STREAM>(out + k * pitch + r, rows[r < q ? r : W + r - q][k]);
       }
     }
     __syncthreads();
@@ -308,63 +313,65 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void stft_kernel(const float* __
 }
 
 // ----------------------------------------------------------------------------------------------
-// Inverse STFT, overlap-add included.  A workgroup forms `8 steps - 3` consecutive blocks of 256 samples of one segment from
-// 8 steps frames (the three in front of its first block once more); a step is eight frames, one per wavefront, read as
-// 64-byte runs of X[bin][frame] and requested a step ahead.  The windowed frames stay in LDS; block th is the sum of
+// Inverse STFT, overlap-add included.  A workgroup of W wavefronts forms `W steps - 3` consecutive blocks of 256 samples of one segment
+// from W steps frames (the three in front of its first block once more); a step is W frames, one per wavefront, read as
+// runs of 8 W bytes of X[bin][frame] and requested a step ahead.  The windowed frames stay in LDS; block th is the sum of
 // its four frames, oldest first, and the three blocks that the next step completes are carried over as partial sums.
 //
-// Bound: latency, with the LDS busy for half of the time.  Two workgroups per compute unit, held there by 124 registers (its 48
-// KB of LDS would let a third in), each with one step requested ahead: 128 segments of 18 s 270 us = 2.7 TB/s, X read once and x
-// written once (window from the cosine table in a pass of its own through LDS: 291 us; through frames in memory, 1.9 GB
-// instead of 0.74 GB: 618 us).  The spectrum, the transform and the windowed frame share one LDS row per wavefront; the last
-// pass's values are windowed in registers.
+// Bound: latency, with the LDS busy for half of the time.  One workgroup of 16 wavefronts per compute unit (registers), with one
+// step requested ahead: 128 segments of 18 s 216 us = 3.4 TB/s, X read once and x written once (two workgroups of 8 wavefronts,
+// 64-byte runs 270 us; the same steps per workgroup as those 248: the number of steps is chosen so that the rounds of workgroups
+// are full; window from the cosine table in a pass of its own through LDS 291; through frames in memory, 1.9 GB instead of 0.74
+// GB: 618 us).  10 segments of 25 s 46 -> 32 us, 30 of 9 s 50 -> 33.  The spectrum, the transform and the windowed frame share one
+// LDS row per wavefront; the last pass's values are windowed in registers.
 // ----------------------------------------------------------------------------------------------
-constexpr int kIstftMaxSteps = 8;
-__global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* __restrict__ X, float* __restrict__ x,
+constexpr int kIstftFrames = 16, kIstftMaxSteps = 32;
+template <int W>
+__global__ __launch_bounds__(64 * W, 4) void istft_kernel(const float2* __restrict__ X, float* __restrict__ x,
                                                               const float2* __restrict__ table, long N, int T, int steps,
                                                               long wgs) {
   __shared__ float2 tw[kH + 1];
   __shared__ float2 win[kH];                               // window / 1.5, irfft's 1 / N
-  __shared__ float2 rows[kFftWaves][kRow];
+  __shared__ float2 rows[W][kRow];
   __shared__ float carry[3][kHop];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long wg = xcd_contiguous(blockIdx.x, wgs);
   if (wg < 0) return;
-  const int nb = 8 * steps - 3;                            // blocks per workgroup
+  const int nb = W * steps - 3;                            // blocks per workgroup
   const int per_seg = (T - 3 + nb - 1) / nb;               // blocks 3 .. T - 1 hold samples
   const int s = (int)((unsigned long)wg / (unsigned)per_seg);
   const int b0 = 3 + (int)(wg - (long)s * per_seg) * nb;   // first block; its frames are b0 - 3 .. b0
   const int b1 = b0 + nb < T ? b0 + nb : T;
-  constexpr int kLoads = (kBins * 8 + 64 * kFftWaves - 1) / (64 * kFftWaves);
+  constexpr int kLoads = (kBins * W + 64 * W - 1) / (64 * W);
   const float2* __restrict__ Xs = X + (long)s * kBins * T;
   float2 raw[kLoads];
   auto request = [&](int f0) {
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int e = threadIdx.x + u * 64 * kFftWaves;
-      const int k = e >> 3, t = f0 + (e & 7);
+      const int e = threadIdx.x + u * 64 * W;
+      const int k = e / W, t = f0 + (e & (W - 1));
       raw[u] = make_float2(0.f, 0.f);
-      if (e < kBins * 8 && t < T) raw[u] = Xs[(long)k * T + t];
+      if (e < kBins * W && t < T) raw[u] = Xs[(long)k * T + t];
     }
   };
   request(b0 - 3);
   fill_tables(tw, kH + 1, win, 1.0f / (1.5f * (float)kN), table);
-  for (int c = threadIdx.x; c < 3 * kHop; c += 64 * kFftWaves) carry[c / kHop][c % kHop] = 0.f;
+  for (int c = threadIdx.x; c < 3 * kHop; c += 64 * W) carry[c / kHop][c % kHop] = 0.f;
   __syncthreads();
   FftLane fc;
   fft_lane_init(fc, tw, lane);
   float2* __restrict__ z = rows[wave];
-  const int half = threadIdx.x >> 8, c = threadIdx.x & (kHop - 1);
-  for (int f0 = b0 - 3; f0 < b1; f0 += 8) {
+  const int part = threadIdx.x >> 8, c = threadIdx.x & (kHop - 1);
+  for (int f0 = b0 - 3; f0 < b1; f0 += W) {
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int e = threadIdx.x + u * 64 * kFftWaves;
-      if (e < kBins * 8) rows[e & 7][e >> 3] = raw[u];
+      const int e = threadIdx.x + u * 64 * W;
+      if (e < kBins * W) rows[e & (W - 1)][e / W] = raw[u];
     }
     __syncthreads();
-    if (f0 + 8 < b1) request(f0 + 8);
+    if (f0 + W < b1) request(f0 + W);
     // pack the half spectrum of a real signal into a 512-point complex one, conjugated so that a forward
     // transform inverts it:  Zc[k] = conj( (X[k] + conj X[512-k]) + i conj(w^k) (X[k] - conj X[512-k]) )
     // (a frame beyond the last one is zero and stays zero)
@@ -396,7 +403,7 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* 
     float sum[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
-      const int j = 2 * jj + half;
+      const int j = (W / 4) * jj + part;
       float acc = j < 3 ? carry[j < 3 ? j : 0][c] : 0.f;
 #pragma unroll
       for (int q = 3; q >= 0; --q)
@@ -404,19 +411,19 @@ __global__ __launch_bounds__(64 * kFftWaves, 4) void istft_kernel(const float2* 
       sum[jj] = acc;
     }
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {                          // block f0 + 8 + j so far
-      const int j = 2 * jj + half;
+    for (int jj = 0; jj < (W == 8 ? 2 : 1); ++jj) {           // block f0 + W + j so far
+      const int j = (W / 4) * jj + part;
       if (j < 3) {
         float acc = 0.f;
 #pragma unroll
         for (int q = 3; q >= 1; --q)
-          if (q > j) acc += sample(8 + j - q, q);
+          if (q > j) acc += sample(W + j - q, q);
         carry[j][c] = acc;
       }
     }
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
-      const int th = f0 + 2 * jj + half;
+      const int th = f0 + (W / 4) * jj + part;
       const long n = (long)th * kHop - kPad + c;
       if (th >= b0 && th < b1 && n < N) x[(long)s * N + n] = sum[jj];
     }
@@ -458,16 +465,28 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   const int rc = get_twiddles(ctx, (hipStream_t)stream, &table);
   if (rc != GSS_OK) return rc;
   const long n_items = (long)S * T, most = (long)ctx->num_cu * kStftWgsPerCu;
-  const int per_unit = D <= 4 ? 8 / D : 1;
+  const int per_unit = D <= 8 ? 8 / D : 1;
+  // Long calls: 16 wavefronts per workgroup, runs of 256 bytes per bin (8 channels), one workgroup per compute unit.  8 / 16 wavefronts,
+  // us: 8 channels, 512 MB 164 / 170, 640 MB 189 / 194, 768 MB 237 / 233, 1.23 GB 428 / 370, 3.8 GB 1673 / 1390; 6 channels 288 MB 138 /
+  // 136, 577 MB 315 / 251; 4 channels 616 MB 291 / 246; 5 channels 962 MB 608 / 426.
+  const double out_bytes = (double)S * kBins * T * D * sizeof(float2);
+  const bool wide = D <= 8 && out_bytes > (D == 8 ? 700e6 : 300e6);
   const long steps1 = (n_items + per_unit - 1) / per_unit;
   // Short calls take steps of one unit: the chip is not full otherwise, and each workgroup would do two units in a row.  The line
   // lies at four rounds of the resident workgroups (8 channels, one / two units: 510 frames, one round, 10.7 / 12.5 us; 2040, four
   // rounds, 29.9 / 31.1; 3000 37.9 / 38.1; 6000 79.8 / 68.7).  24 channels are three units per frame, of which pairs leave one
   // alone (510 frames 24.2 / 27.1, 6000 frames 275 / 288); other counts beyond 8 gain nothing from single units.
   const int units = (D <= 8 ? steps1 <= 4 * most : D % 16 == 8) ? 1 : 2;
-  const long per_step = D <= 8 ? units * per_unit : 1, steps = (n_items + per_step - 1) / per_step;
-  const long grid = ((steps < most ? steps : most) + kXcds - 1) / kXcds * kXcds;
-  hipLaunchKernelGGL(units == 1 ? stft_kernel<1> : stft_kernel<2>, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, (hipStream_t)stream,
+  const long per_step = wide ? 2 * (16 / D) : D <= 8 ? units * per_unit : 1, steps = (n_items + per_step - 1) / per_step;
+  const long res = wide ? most / 2 : most;
+  const long grid = ((steps < res ? steps : res) + kXcds - 1) / kXcds * kXcds;
+  // A spectrum that no cache holds until it is read anyway is written past them, so that the samples, which four neighbouring frames
+  // share, stay there: where the runs are whole 64-byte pieces.  With / without, us: 1.23 GB (8 channels) 434 / 504, 231 MB (24) 87 /
+  // 112, 197 MB (16) 110 / 130; but 128 MB (8) 48 / 46, and runs of other lengths: 6 channels, 577 MB 535 / 315.
+  const bool past = D % 8 == 0 && out_bytes > 190e6;
+  const auto kern = wide ? (past ? stft_kernel<16, 2, true> : stft_kernel<16, 2, false>)
+                    : units == 1 ? (past ? stft_kernel<8, 1, true> : stft_kernel<8, 1, false>) : (past ? stft_kernel<8, 2, true> : stft_kernel<8, 2, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * (wide ? 16 : kFftWaves)), 0, (hipStream_t)stream,
                      x, (float2*)Y, table, D, (long)N, T, n_items);
   return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
 }
@@ -493,16 +512,23 @@ extern "C" int gss_istft(gss_ctx* ctx, const float* X, int S, int T, int n_fft, 
     hipLaunchKernelGGL(copy_spectrum_kernel, dim3(ctx->num_cu * 8), dim3(256), 0, st, (const float2*)X, (float2*)ctx->scratch, n_spec);
     X = (const float*)ctx->scratch;
   }
-  // Steps of eight frames per workgroup: long runs (three of the frames are done twice) as long as the workgroups fill the
-  // compute units a few times over, single steps for small calls.
-  const long blocks = (long)S * (T - 3), want = (long)ctx->num_cu * 6;
-  int steps = kIstftMaxSteps;
-  while (steps > 1 && blocks / (8 * steps - 3) < want) --steps;
-  const int per_seg = (T - 3 + 8 * steps - 4) / (8 * steps - 3);
+  // Steps per workgroup: the fewest steps in a row over the rounds of workgroups (one per compute unit), with one more per workgroup for
+  // its start and the three frames that are done twice.
+  int steps = 1, per_seg = 0;
+  long best = 0;
+  for (int c = 1; c <= kIstftMaxSteps; ++c) {
+    const int n = (T - 3 + kIstftFrames * c - 4) / (kIstftFrames * c - 3);
+    const long cost = ((long)S * n + ctx->num_cu - 1) / ctx->num_cu * (c + 1);
+    if (c == 1 || cost < best) {
+      best = cost;
+      steps = c;
+      per_seg = n;
+    }
+  }
   const long wgs = (long)S * per_seg;
   const long grid = (wgs + kXcds - 1) / kXcds * kXcds;
   if (grid > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  hipLaunchKernelGGL(istft_kernel, dim3((unsigned)grid), dim3(64 * kFftWaves), 0, st, (const float2*)X, x, table, (long)N, T, steps,
+  hipLaunchKernelGGL(istft_kernel<kIstftFrames>, dim3((unsigned)grid), dim3(64 * kIstftFrames), 0, st, (const float2*)X, x, table, (long)N, T, steps,
                      wgs);
   return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
 }

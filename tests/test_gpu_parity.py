@@ -720,6 +720,43 @@ def _check_stft_istft(env, S, D, N):
     assert np.linalg.norm(back - x[:, 0]) <= TOL_STFT * np.linalg.norm(x[:, 0])
 
 
+@pytest.mark.parametrize("S,D,N", [(1, 8, 256 * 21400 + 1), (2, 5, 256 * 8000 + 100), (1, 3, 256 * 24500), (1, 24, 256 * 2100 + 7), (3, 8, 256 * 2100)])
+def test_stft_very_long_calls(env, S, D, N):
+    """Spectra of 200 to 700 MB: 16 wavefronts per workgroup, and stores past the caches.  Frames at the ends of the segments and of
+    the XCDs' shares and others drawn at random, against the transform in 64 bits."""
+    t, gss = env["torch"], env["gss"]
+    x = 0.1 * t.randn((S, D, N), device="cuda", generator=t.Generator(device="cuda").manual_seed(N))
+    Y = gss.gss_stft(env["ctx"], x)
+    T = Y.shape[2]
+    rng = np.random.default_rng(N)
+    frames = sorted(set(rng.integers(0, T, 60).tolist() + list(range(6)) + list(range(T - 6, T)) +
+                        [min(T - 1, T * q // 8 + o) for q in range(1, 8) for o in (-1, 0, 1)]))
+    w = 0.5 - 0.5 * np.cos(2.0 * np.pi * np.arange(1024) / 1024)
+    for s in range(S):
+        xs = np.pad(x[s].cpu().numpy().astype(np.float64), ((0, 0), (768, 1024 + 256)))
+        ref = np.stack([np.fft.rfft(xs[:, 256 * f:256 * f + 1024] * w) for f in frames])          # [frame, D, bin]
+        got = Y[s][:, frames].cpu().numpy().transpose(1, 2, 0)
+        err = np.linalg.norm(got - ref, axis=(1, 2)) / np.maximum(np.linalg.norm(ref, axis=(1, 2)), 1e-6)
+        assert np.max(err) <= TOL_STFT, (s, int(np.argmax(err)))
+
+
+@pytest.mark.parametrize("S,blocks", [(1, 1), (2, 12), (1, 13), (3, 14), (2, 29), (300, 30), (5, 509), (520, 77)])
+def test_istft_steps(env, S, blocks):
+    """Inverse transforms whose last step of 16 frames is full, one frame over or short, of one and of several steps per workgroup."""
+    t, gss = env["torch"], env["gss"]
+    N = 256 * blocks - (0 if blocks % 2 else 5)
+    T = -(-N // 256) + 3
+    X = t.randn((S, 513, T), dtype=t.complex64, device="cuda", generator=t.Generator(device="cuda").manual_seed(blocks))
+    x = gss.gss_istft(env["ctx"], X, N)
+    w = 0.5 - 0.5 * t.cos(2.0 * np.pi * t.arange(1024, dtype=t.float64, device="cuda") / 1024)
+    fr = t.fft.irfft(X.to(t.complex128).transpose(1, 2), n=1024) * w / 1.5                      # [S, T, 1024]
+    line = t.zeros((S, T + 3, 256), dtype=t.float64, device="cuda")
+    for q in range(4):
+        line[:, q:q + T] += fr[:, :, 256 * q:256 * q + 256]
+    ref = line.reshape(S, -1)[:, 768:768 + N]
+    assert float(t.linalg.norm(x - ref) / t.linalg.norm(ref)) <= TOL_STFT
+
+
 @pytest.mark.parametrize("S,N,shift", [(40, 256 * 600, 0), (3, 256 * 90 + 7, 4096), (70, 5000, 1)])
 def test_istft_output_over_its_input(env, S, N, shift):
     t, gss = env["torch"], env["gss"]
