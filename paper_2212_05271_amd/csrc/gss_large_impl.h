@@ -759,25 +759,32 @@ __device__ __forceinline__ void gauss_jordan_large(double (*sMr)[33], double (*s
 // lower factor, and the diagonal holds the pivots d.  W = d^-1/2 M.  The lanes that hold pivot row p
 // publish it in the wavefront's LDS, every lane reads back the entries of its own columns and, conjugated for the pivot column,
 // of its own rows.  Nothing is shared between wavefronts, so there is no workgroup barrier.
+// A problem of the tail comes in many chunks (513 problems: the last one in 24, which one compute unit took 16 us to read while all
+// others were done): its classes have a workgroup each, whose wavefronts take every K-th chunk; the first one goes on.
 // Bound: latency, a chain of LDS round trip, reciprocal and update per sweep.  513 problems of 24 channels, 5 classes: 43 us (47 us
-// with the pivot column published as well and reals in LDS; whole EM calls 0.3 % (16 channels) to 8 % (32 channels) slower).
+// with the pivot column published as well and reals in LDS; whole EM calls 0.3 % (16 channels) to 8 % (32 channels) slower), and
+// 38 with the tail's chunks shared.
 // ----------------------------------------------------------------------------------------------
 template <int BS>
 __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
     const double* __restrict__ part, const double* __restrict__ npart,
     double* __restrict__ coef, double* __restrict__ cmant, int32_t* __restrict__ cexp, uint32_t* __restrict__ status,
-    int D, int K, ChunkMap cmap, int weight_mode, unsigned sf0) {
+    int D, int K, ChunkMap cmap, int weight_mode, unsigned sf0, unsigned n_whole) {
   constexpr int W = 8 * BS;                                // padded matrix size
   __shared__ __attribute__((aligned(16))) double2 sPiv[GSS_MAX_K][W];   // per wavefront: pivot row
   extern __shared__ __attribute__((aligned(16))) double sItems[];   // per wavefront: the class's packed sums, 2 M doubles
   const int lane = threadIdx.x & (kWave - 1);
-  const int k = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const long sf = sf0 + blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  // (from workgroup n_whole on: a class of a problem each, whose wavefronts share the sums)
+  const bool shared = blockIdx.x >= n_whole;
+  const unsigned extra = shared ? blockIdx.x - n_whole : 0u;
+  const long sf = sf0 + (shared ? n_whole + extra / (unsigned)K : blockIdx.x);
+  const int k = shared ? (int)(extra % (unsigned)K) : wave;
   const int a = lane >> 3, b = lane & 7;
   const int M = num_items(D);
   int C;
   const long slot0 = chunk_base(cmap, sf, C);
-  double2* __restrict__ row = sPiv[k];
+  double2* __restrict__ row = sPiv[wave];
 
   // class counts: lane l < K adds the chunks' counts of class l (in chunk order)
   double nl = 0.0;
@@ -791,19 +798,20 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
   double mr[BS][BS], mi[BS][BS];
   {
     constexpr int kRun = (W * (W + 1) / 2 + kWave - 1) / kWave, kFly = BS == 4 ? 2 : 4;
-    double2* __restrict__ sP = reinterpret_cast<double2*>(sItems) + k * M;
+    double2* __restrict__ sP = reinterpret_cast<double2*>(sItems) + wave * M;
     const double2* __restrict__ pc = reinterpret_cast<const double2*>(part) + (slot0 * K + k) * (long)M;
     double2 sum[kRun];
 #pragma unroll
     for (int x = 0; x < kRun; ++x) sum[x] = make_double2(0.0, 0.0);
-    for (int c0 = 0; c0 < C; c0 += kFly) {
+    const int first = shared ? wave : 0, step = shared ? K : 1;   // the chunks first, first + step, ...
+    for (int c0 = first; c0 < C; c0 += kFly * step) {
       double2 v[kFly][kRun];
 #pragma unroll
       for (int c = 0; c < kFly; ++c)
 #pragma unroll
         for (int x = 0; x < kRun; ++x) {
           v[c][x] = make_double2(0.0, 0.0);
-          if (c0 + c < C && lane + kWave * x < M) v[c][x] = pc[(long)(c0 + c) * K * M + lane + kWave * x];
+          if (c0 + c * step < C && lane + kWave * x < M) v[c][x] = pc[(long)(c0 + c * step) * K * M + lane + kWave * x];
         }
 #pragma unroll
       for (int c = 0; c < kFly; ++c)
@@ -816,6 +824,16 @@ __global__ __launch_bounds__(kWave * GSS_MAX_K) void em_factor_large(
 #pragma unroll
     for (int x = 0; x < kRun; ++x)
       if (lane + kWave * x < M) sP[lane + kWave * x] = sum[x];
+    if (shared) {                                          // the wavefronts' sums, in their order
+      __syncthreads();
+      if (wave != 0) return;
+      for (int w = 1; w < K; ++w)
+        for (int x = lane; x < M; x += kWave) {
+          const double2 v = sP[w * M + x];
+          sP[x].x += v.x;
+          sP[x].y += v.y;
+        }
+    }
     wave_lds_sync();
 #pragma unroll
     for (int r = 0; r < BS; ++r)
@@ -1258,6 +1276,9 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
   for (long p0 = 0; p0 < n_sf; p0 += group) {
     const long p1 = p0 + group < n_sf ? p0 + group : n_sf;
     const unsigned np = (unsigned)(p1 - p0);
+    // problems of the tail, in many chunks, have a workgroup per class in the factor kernel
+    const long whole = acc_map.c_tail > 4 && acc_map.n_main < p1 ? (acc_map.n_main > p0 ? acc_map.n_main - p0 : 0) : np;
+    const unsigned n_whole = (unsigned)whole;
     const long a0 = first_block(acc_map, p0), f0 = first_block(fin_map, p0);
     const unsigned na = (unsigned)(first_block(acc_map, p1) - a0), nf = (unsigned)(first_block(fin_map, p1) - f0);
     // (the kernels index by problem and workgroup of the whole call)
@@ -1273,8 +1294,8 @@ int run_em_large(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int
                          acc_map, (unsigned)a0);
       gss_profile_end(ctx, 0, st);
       gss_profile_begin(ctx, 1, st);
-      hipLaunchKernelGGL(em_factor_large<NB>, dim3(np), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
-                         ctx->status, D, K, acc_map, weight_mode, (unsigned)p0);
+      hipLaunchKernelGGL(em_factor_large<NB>, dim3(n_whole + (np - n_whole) * K), dim3(kWave * K), factor_lds, st, part, npart, coef, cm, ce,
+                         ctx->status, D, K, acc_map, weight_mode, (unsigned)p0, n_whole);
       gss_profile_end(ctx, 1, st);
     }
     hipLaunchKernelGGL((em_pass_large<K, NB, H, true>), dim3(nf), block, lds_fin, st, Y, abyte, masks, T_len,

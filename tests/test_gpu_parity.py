@@ -495,6 +495,20 @@ def test_large_array_dead_stretches(env, D, K, F):
     assert ctx.get_status() == 0
 
 
+@pytest.mark.parametrize("D,K,T", [(9, 1, 400), (12, 5, 1000), (18, 8, 330), (24, 2, 1000), (30, 3, 400)])
+def test_large_array_tail_in_chunks(env, D, K, T):
+    """513 problems: the last one is cut into chunks of a tile, which the wavefronts of a workgroup per class add up."""
+    rng = np.random.default_rng(D * T)
+    F = 513
+    Y = (_cn(rng, (F, T, D)) * np.exp(rng.standard_normal((F, T, 1)))).astype(np.complex64)
+    act = (rng.random((K, T)) < 0.5).astype(np.uint8)
+    act[K - 1] = 1
+    fs = [0, 200, 510, 511, 512]
+    go = env["o"].cacgmm_em(Y[fs], act, 3)
+    g = _gpu_em(env, Y[None], act[None], None, 3)[0]
+    assert np.max(np.abs(g[:, fs] - go)) <= 1e-5
+
+
 def test_large_array_working_memory():
     """Large batches of 9 channels and more: a call whose class matrices would take more than 1 GiB (the context rounds a
     growth up by an eighth and to a MiB) runs in groups of problems, with the bits of smaller calls (60 segments of 513 bins,
