@@ -10,12 +10,6 @@ namespace {
 
 constexpr int kWave = 64;
 
-__host__ __device__ constexpr int next_pow2(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 // ----------------------------------------------------------------------------------------------
 // fp64 helpers (no transcendental functions anywhere in the EM loop)
 // ----------------------------------------------------------------------------------------------
@@ -117,9 +111,7 @@ __device__ __forceinline__ double dpp_permute_f64(double x) {
 __device__ __forceinline__ int transposed_index(int lane) {
   return (int)(__brev((unsigned)(lane & 15)) >> 28) | (lane & 48);
 }
-// ROWS_ONLY: only the four steps inside the rows of 16 lanes: lane l then holds in v[j] the sum over its row of
-// value 16 j + transposed_index(l & 15), and the caller adds the four rows itself.
-template <int N, bool ROWS_ONLY = false>
+template <int N>
 __device__ __forceinline__ void transpose_reduce(double (&v)[N], int lane) {
   auto step = [&](auto CNT, bool second, auto perm) {
     constexpr int n = decltype(CNT)::value;
@@ -139,10 +131,8 @@ __device__ __forceinline__ void transpose_reduce(double (&v)[N], int lane) {
   step(std::integral_constant<int, n1>{}, (lane & 4) != 0, [](double x) { return dpp_permute_f64<0x141>(x); });  // row_half_mirror
   step(std::integral_constant<int, n2>{}, (lane & 2) != 0, [](double x) { return dpp_permute_f64<0x4E>(x); });   // quad_perm [2, 3, 0, 1]
   step(std::integral_constant<int, n3>{}, (lane & 1) != 0, [](double x) { return dpp_permute_f64<0xB1>(x); });   // quad_perm [1, 0, 3, 2]
-  if constexpr (!ROWS_ONLY) {
-    step(std::integral_constant<int, n4>{}, (lane & 16) != 0, [](double x) { return __shfl_xor(x, 16, kWave); });
-    step(std::integral_constant<int, n5>{}, (lane & 32) != 0, [](double x) { return __shfl_xor(x, 32, kWave); });
-  }
+  step(std::integral_constant<int, n4>{}, (lane & 16) != 0, [](double x) { return __shfl_xor(x, 16, kWave); });
+  step(std::integral_constant<int, n5>{}, (lane & 32) != 0, [](double x) { return __shfl_xor(x, 32, kWave); });
 }
 
 // Position (row i, column j >= i, part: 0 diagonal, 1 real, 2 imaginary) of packed index idx.
@@ -223,23 +213,13 @@ __global__ __launch_bounds__(kWave) void em_pack_activity(
   if (lane == 0) tmask[(long)s * tiles + tile] = b;
 }
 
-// acc += c[lane N of the row] * p: the double-precision FMA with the row-broadcast selector on its first
-// factor.  Every lane of the wavefront must be active (the selector reads other lanes).  The instruction is
-// written as an asm statement, which hides it from the compiler's hazard handling: a lane-selecting
-// instruction must not issue within two wait states of a vector instruction that writes one of its
-// registers, so the first FMA of a run (SETTLE) is preceded by the two idle states itself.
-template <int N, bool SETTLE>
-__device__ __forceinline__ void fma_bcast(double& acc, double c, double p) {
-  static_assert(N >= 0 && N < 16, "row_newbcast selects one of the 16 lanes of a row");
-  if constexpr (SETTLE)
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc) : "v"(c), "v"(p), "n"(N));
-  else
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(c), "v"(p), "n"(N));
-}
-
-// q[e mod 3] += c[lane e of the row] * P[e] for e = 0 .. NG - 1 (16, or what is left of D * D entries: 9, 4, 1), the FMAs of
-// fma_bcast in one statement: between separate statements the compiler puts an idle state in front of every third FMA, which
+// The double-precision FMA with the row-broadcast selector on its first factor: acc += c[lane n of the row] * p.  Every lane of the
+// wavefront must be active (the selector reads other lanes).  The instruction is written as an asm statement, which hides it
+// from the compiler's hazard handling: a lane-selecting instruction must not issue within two wait states of a vector
+// instruction that writes one of its registers, so a statement starts with two idle states.
+//
+// q[e mod 3] += c[lane e of the row] * P[e] for e = 0 .. NG - 1 (16, or what is left of D * D entries: 9, 4, 1) in
+// one statement: between separate statements the compiler puts an idle state in front of every third FMA, which
 // costs a wavefront an issue slot like any other instruction.  With three accumulators in turn each is read two issue slots
 // after it was written, and the two idle states in front separate the first FMA from the last write of its registers.
 template <int NG>
@@ -273,7 +253,7 @@ __device__ __forceinline__ void fma_bcast_chain(double (&q)[3], double c, const 
 #undef GSS_BCAST_FMA
 }
 
-// acc[b] += sum over n of w[lane n of the row] * x[b][n], n = 0 .. 15, b = 0 .. NB - 1 (1 to 4): the FMAs of fma_bcast with the
+// acc[b] += sum over n of w[lane n of the row] * x[b][n], n = 0 .. 15, b = 0 .. NB - 1 (1 to 4), with the
 // accumulators in turn, so that an FMA does not wait for the one before it (one accumulator: three partial sums).  Statements of
 // 16 FMAs or fewer, each with the two idle states in front (a statement may be moved up to the write of w).
 template <int NB, int n0>
@@ -352,10 +332,10 @@ __device__ __forceinline__ bool class_on(unsigned mask, int k) {
   return (mask >> k) & 1u;
 }
 
-// Tile geometry shared by the kernels that accumulate weighted outer products: a workgroup is
-// kPassWaves wavefronts, each wavefront owns whole tiles of 64 frames and a private LDS region.
+// A workgroup of the EM's pass kernel and of the MVDR covariances is kPassWaves wavefronts; each wavefront owns whole tiles of 64
+// frames and a private LDS region.
 //
-// Phase 2 of a tile: lane = (frame group tg, lane type i), D lane types and 64 / D frame groups (lanes left over idle along).
+// The covariances of a tile: lane = (frame group tg, lane type i), D lane types and 64 / D frame groups (lanes left over idle along).
 // Lane type i owns D of the D * D reals of the packed Hermitian matrix: Re and Im of y_i conj(y_b), b = (i + d) mod D, for the
 // circular distances d = 1 .. (D - 1) / 2, the real diagonal entry |y_i|^2, and for even D one half of the pair at distance
 // D / 2: Re of y_i conj(y_(i + D/2)) for i < D / 2 and Im of y_(i - D/2) conj(y_i) otherwise.  Both halves are
@@ -368,9 +348,7 @@ __device__ __forceinline__ bool class_on(unsigned mask, int k) {
 // consecutive frames: LDS delivers 256 bytes per cycle, rows 8 * 208 bytes apart are 128 modulo 256, and a 16-byte read of the
 // wavefront's 8 rows takes 4 cycles (frames tg, tg + 8, ...: 9 cycles; calls of one segment 1 to 9 % slower).  D < 8: frames
 // tg, tg + 64 / D, ..., no padding: the rows read together are one run of memory (odd D) or start at an odd multiple of 16
-// bytes (D = 2 and 6).  Measured against 8 lane types whatever D (zero channels up to 8), 10 iterations: 48 segments of up to
-// 1000 frames and 4 classes 5 channels 3.64 -> 2.32 ms, 6 channels 3.86 -> 3.23, 7 channels 4.51 -> 3.99; 8 classes: 4 channels,
-// 24 segments of up to 700 frames 2.35 -> 1.31, 32 segments of 5 channels 5.41 -> 2.70 ms (the accumulators no longer spill).
+// bytes (D = 2 and 6).
 constexpr int kPassWaves = 4;
 template <int D>
 struct TileLayout {
@@ -450,7 +428,7 @@ constexpr SlotTable<D> make_slot_table() {
   return t;
 }
 
-// Phase 2 of a tile: lane (tg, i) accumulates acc[n][k] += w_k[r] * (slot n of lane type i)[r] over the frames r of its group.
+// The covariances of a tile: lane (tg, i) accumulates acc[n][k] += w_k[r] * (slot n of lane type i)[r] over the frames r of its group.
 // sY: [64][TileLayout<D>::row] doubles, sW: [64][WS] doubles (KW weights per frame).
 template <int D, int KW, int WS, int UNROLL = 2>
 __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, const double* __restrict__ sW,
@@ -483,9 +461,7 @@ __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, c
 // sums: out[k * E + packed index] for k < KW, matrix size D.  Sums are taken in a fixed order (frame
 // groups ascending, then wavefronts ascending).
 //   wbuf: LDS private to the calling wavefront, reduce_wave_doubles(D) doubles (its tile region);
-//   red:  LDS scratch of the workgroup, kPassWaves * (64 * KW + KW) doubles, may overlap the wbuf regions.
-// WITH_N: nvals[k] is one more per-lane partial sum per class (lane = frame layout), summed over all lanes and
-// wavefronts into nout[k].
+//   red:  LDS scratch of the workgroup, kPassWaves * 64 * KW doubles, may overlap the wbuf regions.
 // The function starts with a barrier (every wavefront is done with its tiles).  First every wavefront
 // sums over its frame groups through its own LDS region, two classes at a time: entry n of all lanes
 // goes out as one contiguous row (lane = D tg + i), and lane o = D n + i reads the values of slot
@@ -520,19 +496,11 @@ __device__ __forceinline__ void sum_frame_groups(const double (&acc)[D][KW], int
   wave_lds_sync();
 }
 
-template <int D, int KW, bool WITH_N>
-__device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], double (&nvals)[KW], double* wbuf,
-                                                          double* red, double* __restrict__ out,
-                                                          double* __restrict__ nout, int lane, int wave) {
+template <int D, int KW>
+__device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], double* wbuf, double* red, double* __restrict__ out,
+                                                          int lane, int wave) {
   constexpr int E = D * D;
   double S[KW + 1];
-  if constexpr (WITH_N) {                    // per-lane scalars (one per class): summed over the wavefront
-#pragma unroll
-    for (int k = 0; k < KW; ++k) {
-      double nv = wave_sum_f64(nvals[k]);
-      nvals[k] = nv;
-    }
-  }
   __syncthreads();
 #pragma unroll
   for (int k0 = 0; k0 < KW; k0 += 2) {
@@ -542,15 +510,8 @@ __device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], 
     S[k0 + 1] = S2[1];
   }
   __syncthreads();                           // the private regions are free: `red` may overlap them
-  double* redn = red + kPassWaves * 64 * KW;
 #pragma unroll
   for (int k = 0; k < KW; ++k) red[(wave * KW + k) * 64 + lane] = S[k];
-  if constexpr (WITH_N) {
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < KW; ++k) redn[wave * KW + k] = nvals[k];
-    }
-  }
   __syncthreads();
   for (int x = threadIdx.x; x < 64 * KW; x += kWave * kPassWaves) {
     const int k = x / 64, slot = x % 64;
@@ -559,14 +520,6 @@ __device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], 
     for (int w = 0; w < kPassWaves; ++w) sum += red[(w * KW + k) * 64 + slot];
     static constexpr SlotTable<D> kSlots = make_slot_table<D>();
     if (slot < E) out[k * E + kSlots.index[slot]] = kSlots.sign[slot] < 0 ? -sum : sum;
-  }
-  if constexpr (WITH_N) {
-    if (threadIdx.x < KW) {
-      double sum = 0.0;
-#pragma unroll
-      for (int w = 0; w < kPassWaves; ++w) sum += redn[w * KW + threadIdx.x];
-      nout[threadIdx.x] = sum;
-    }
   }
 }
 
