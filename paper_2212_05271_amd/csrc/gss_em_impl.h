@@ -1304,10 +1304,13 @@ constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_pe
 // factorises while the others wait, which costs the more the more problems share a compute unit (`load`).  Four / one, us, 8
 // iterations, 2 channels and 3 classes: one segment of 60 / 250 / 1000 frames 0.88 / 0.64 / 0.55 times as long, two 1.21 / 0.79 /
 // 0.67, four 1.45 / 0.99 / 0.79, eight 1.70 / 1.17 / 0.94; 4 channels and 5 classes 0.97 / 0.65 / 0.58, 1.31 / 0.82 / 0.67, 1.58 /
-// 1.03 / 0.80, 1.96 / 1.21 / 0.93.  Over 496 calls of 1 to 4 channels, 2 to 8 classes, 1 to 8 segments of 60 to 1800 frames the
-// choice takes 0.5 % longer than the better of both on average, 34 % at most (one tile, 2 channels and 8 classes).
-inline bool use_quad(double load, int tiles) {
-  return tiles - (tiles + kWholeQuad - 1) / kWholeQuad >= 0.04 * load * load - 0.3;
+// 1.03 / 0.80, 1.96 / 1.21 / 0.93.  Segments of their own lengths save fewer tiles than the longest one says (4 segments of up to 578
+// frames, 3 channels and 3 classes 118 / 103 us; 4 of up to 300 83 / 61; 6 of up to 900, 4 channels and 2 classes 170 / 130).  Over
+// 496 calls of one length (1 to 4 channels, 2 to 8 classes, 1 to 8 segments of 60 to 1800 frames) the choice takes 1.0 % longer than
+// the better of both on average, 28 % at most.
+inline bool use_quad(double load, int tiles, bool ragged) {
+  const double saved = tiles - (tiles + kWholeQuad - 1) / kWholeQuad;
+  return (ragged ? 0.6 : 1.0) * saved >= 0.08 * load * load - 0.3;
 }
 
 struct EmPlan {
@@ -1381,7 +1384,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
       const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
-      tiny = use_quad((double)n_sf / ctx->num_cu, tiles);
+      tiny = use_quad((double)n_sf / ctx->num_cu, tiles, T_len != nullptr);
       const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
       if (row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }
