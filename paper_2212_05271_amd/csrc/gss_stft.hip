@@ -17,6 +17,7 @@
 // remapped such that every XCD walks a contiguous range of frames: neighbouring frames share three quarters
 // of their samples, and their 64-byte output runs are neighbours in memory.
 #include "gss_internal.h"
+#include "gss_rules.h"
 
 namespace {
 
@@ -318,14 +319,13 @@ __global__ __launch_bounds__(64 * W, 4) void stft_kernel(const float* __restrict
 // runs of 8 W bytes of X[bin][frame] and requested a step ahead.  The windowed frames stay in LDS; block th is the sum of
 // its four frames, oldest first, and the three blocks that the next step completes are carried over as partial sums.
 //
-// Bound: latency, with the LDS busy for half of the time.  One workgroup of 16 wavefronts per compute unit (registers), with one
-// step requested ahead: 128 segments of 18 s 216 us = 3.4 TB/s, X read once and x written once (two workgroups of 8 wavefronts,
-// 64-byte runs 270 us; the same steps per workgroup as those 248: the number of steps is chosen so that the rounds of workgroups
-// are full; window from the cosine table in a pass of its own through LDS 291; through frames in memory, 1.9 GB instead of 0.74
-// GB: 618 us).  10 segments of 25 s 46 -> 32 us, 30 of 9 s 50 -> 33.  The spectrum, the transform and the windowed frame share one
-// LDS row per wavefront; the last pass's values are windowed in registers.
+// Bound: latency, with the LDS busy for half of the time.  Which W and how many steps: plan_istft.  Long calls: one workgroup of
+// 16 wavefronts per compute unit (registers), with one step requested ahead: 128 segments of 18 s 216 us = 3.4 TB/s, X read once
+// and x written once (two workgroups of 8 wavefronts, 64-byte runs 270 us; the same steps per workgroup as those 248: the number
+// of steps is chosen so that the rounds of workgroups are full; window from the cosine table in a pass of its own through LDS
+// 291; through frames in memory, 1.9 GB instead of 0.74 GB: 618 us).  10 segments of 25 s 46 -> 32 us, 30 of 9 s 50 -> 33.  The
+// spectrum, the transform and the windowed frame share one LDS row per wavefront; the last pass's values are windowed in registers.
 // ----------------------------------------------------------------------------------------------
-constexpr int kIstftFrames = 16, kIstftMaxSteps = 32;
 template <int W>
 __global__ __launch_bounds__(64 * W, 4) void istft_kernel(const float2* __restrict__ X, float* __restrict__ x,
                                                               const float2* __restrict__ table, long N, int T, int steps,
@@ -512,23 +512,11 @@ extern "C" int gss_istft(gss_ctx* ctx, const float* X, int S, int T, int n_fft, 
     hipLaunchKernelGGL(copy_spectrum_kernel, dim3(ctx->num_cu * 8), dim3(256), 0, st, (const float2*)X, (float2*)ctx->scratch, n_spec);
     X = (const float*)ctx->scratch;
   }
-  // Steps per workgroup: the fewest steps in a row over the rounds of workgroups (one per compute unit), with one more per workgroup for
-  // its start and the three frames that are done twice.
-  int steps = 1, per_seg = 0;
-  long best = 0;
-  for (int c = 1; c <= kIstftMaxSteps; ++c) {
-    const int n = (T - 3 + kIstftFrames * c - 4) / (kIstftFrames * c - 3);
-    const long cost = ((long)S * n + ctx->num_cu - 1) / ctx->num_cu * (c + 1);
-    if (c == 1 || cost < best) {
-      best = cost;
-      steps = c;
-      per_seg = n;
-    }
-  }
-  const long wgs = (long)S * per_seg;
+  const IstftPlan p = plan_istft(S, T, ctx->num_cu);
+  const long wgs = S * p.per_seg;
   const long grid = (wgs + kXcds - 1) / kXcds * kXcds;
   if (grid > 0x7fffffffL) return GSS_EUNSUPPORTED;
-  hipLaunchKernelGGL(istft_kernel<kIstftFrames>, dim3((unsigned)grid), dim3(64 * kIstftFrames), 0, st, (const float2*)X, x, table, (long)N, T, steps,
-                     wgs);
+  hipLaunchKernelGGL((p.waves == 8 ? istft_kernel<8> : istft_kernel<16>), dim3((unsigned)grid), dim3(64 * p.waves), 0, st, (const float2*)X, x,
+                     table, (long)N, T, p.steps, wgs);
   return hipGetLastError() == hipSuccess ? GSS_OK : GSS_EHIP;
 }

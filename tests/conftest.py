@@ -1,4 +1,6 @@
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -27,3 +29,32 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+RULES_SOURCE = r"""
+#include "gss_rules.h"
+extern "C" void istft_plan(long S, long T, int num_cu, long* out) {
+  const IstftPlan p = plan_istft(S, T, num_cu);
+  out[0] = p.waves; out[1] = p.steps; out[2] = p.per_seg;
+}
+"""
+
+
+@pytest.fixture(scope="session")
+def rules(tmp_path_factory):
+    """The library's rules for choosing between kernels (csrc/gss_rules.h), built by the host compiler alone."""
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(RULES_SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2212_05271_amd", "csrc"),
+                    str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
+    lib = ctypes.CDLL(str(d / "rules.so"))
+
+    class Rules:
+        @staticmethod
+        def istft(S, T, num_cu=256):
+            """(wavefronts per workgroup, steps per workgroup, workgroups per segment) of gss_istft."""
+            out = (ctypes.c_long * 3)()
+            lib.istft_plan(ctypes.c_long(S), ctypes.c_long(T), ctypes.c_int(num_cu), out)
+            return tuple(out)
+
+    return Rules

@@ -754,10 +754,17 @@ def test_stft_very_long_calls(env, S, D, N):
         assert np.max(err) <= TOL_STFT, (s, int(np.argmax(err)))
 
 
-@pytest.mark.parametrize("S,blocks", [(1, 1), (2, 12), (1, 13), (3, 14), (2, 29), (300, 30), (5, 509), (520, 77)])
-def test_istft_steps(env, S, blocks):
-    """Inverse transforms whose last step of 16 frames is full, one frame over or short, of one and of several steps per workgroup."""
+@pytest.mark.parametrize("S,blocks,waves,several", [
+    (1, 1, 8, False), (2, 12, 8, False), (1, 13, 8, False), (3, 14, 8, False), (2, 29, 8, False), (8, 5, 8, False), (7, 4, 8, False),
+    (300, 30, 8, True), (257, 13, 8, True), (257, 12, 8, True), (29, 106, 8, True), (130, 111, 8, True),
+    (5, 509, 16, False), (7, 182, 16, False), (3, 430, 16, False),
+    (520, 77, 16, True), (130, 29, 16, True), (130, 28, 16, True), (52, 88, 16, True), (86, 154, 16, True), (172, 509, 16, True)])
+def test_istft_steps(env, rules, S, blocks, waves, several):
+    """Inverse transforms whose last step of 8 or 16 frames is full, one frame over or short, of one and of several steps per
+    workgroup (up to the most there are, 32)."""
     t, gss = env["torch"], env["gss"]
+    plan = rules.istft(S, blocks + 3, t.cuda.get_device_properties(0).multi_processor_count)
+    assert (plan[0], plan[1] > 1) == (waves, several), plan
     N = 256 * blocks - (0 if blocks % 2 else 5)
     T = -(-N // 256) + 3
     X = t.randn((S, 513, T), dtype=t.complex64, device="cuda", generator=t.Generator(device="cuda").manual_seed(blocks))
