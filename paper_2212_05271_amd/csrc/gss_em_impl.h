@@ -27,6 +27,7 @@
 #include "gss_internal.h"
 
 #include "gss_device.h"
+#include "gss_rules.h"
 
 
 namespace {
@@ -89,21 +90,7 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // Grid: blockIdx.x = chunk + C * (f + F * s).  A chunk is `tiles_per_chunk` tiles of 64 frames.
 // ----------------------------------------------------------------------------------------------
 
-// Few channels: the lane that owns a frame in phase 1 has all D * D entries of its outer product in registers
-// anyway (one block of at most 16), and in the direct layout adds w_k * P[e] to K * D * D accumulators of its own: no
-// phase 2.  The accumulators are acc[k][e] then (packed order), and the sums over the lanes are taken at the end of the pass
-// (transpose_reduce).  `one`: the kernel whose wavefronts have one tile each.
-// The line lies where the layouts were measured against each other: the direct one costs no LDS round trip, but its accumulators
-// keep wavefronts from the SIMDs and take longer to add up.  Direct / tile layout, us, 32 segments of up to 700 frames, 5
-// iterations: 3 channels and 3 / 4 / 5 / 8 classes 266 / 276, 312 / 313, 404 / 364, 582 / 496, 4 channels and 2 / 3 / 5 classes
-// 304 / 302, 411 / 350, 571 / 445.  One segment of 200 frames, a tile per wavefront, 10 iterations: 3 channels and 2 / 5 classes
-// 32.7 / 28.5, 54.6 / 39.3, 4 channels and 2 / 5 classes 43.4 / 45.6, 68.7 / 61.2.  (4 segments of 3 channels and 5 to 7 classes,
-// two wavefronts per SIMD, are 4 to 7 % faster with the direct one.)
 constexpr int kPrefetchMaxAcc = 64;            // the whole-EM kernel requests the next tile ahead up to this many
-__host__ __device__ constexpr bool direct_layout(int D, int K, bool one) {
-  return D <= 2 || (!one && ((D == 3 && K <= 4) || (D == 4 && K <= 2)));
-}
-
 // Tile layout: the D * D packed entries of the outer product in blocks of 16, which phase 2 takes transposed (lane = entry of a
 // block), and up to 4 entries left over (6 and 7 channels), which a lane adds up for its own frame as in the direct layout.
 template <int D>
@@ -1088,8 +1075,6 @@ __device__ __forceinline__ void whole_pass(
 // now 151 and 139), and with them a wavefront per SIMD less (one segment of 1860 frames, 3 iterations, 2 channels and 7 classes 66.0
 // -> 52.3 us).
 // ----------------------------------------------------------------------------------------------
-constexpr int kWholeQuad = 4;                 // wavefronts per problem of the variant for few problems
-constexpr int kWholeQuadMaxD = 4;             // ... which is built for up to this many channels
 // Wavefronts per SIMD that the kernel is compiled for.  With a tile per wavefront three, also where that spills up to 42 registers
 // (2 and 4 channels, 8 classes): the 513 problems of a segment do not fit the chip at two (60 frames, 3 / 4 channels and 8 classes 1.68 /
 // 1.64 times as long).  Up to 2 channels the tile loop lives in two registers for every
@@ -1277,42 +1262,6 @@ __global__ __launch_bounds__(kWave * NW, ONE_TILE ? 3 : whole_waves_per_simd(D, 
 // ----------------------------------------------------------------------------------------------
 // Host-side plan and dispatch
 // ----------------------------------------------------------------------------------------------
-// Where the whole-EM kernel with a wavefront per problem is used: tiles per problem, by the problems per compute unit (`load`; 2 for
-// the 513 bins of a segment) and whether the segments have lengths of their own, so that the wavefronts end at different times.
-// The line lies where the routes were measured against each other, 8 iterations, time in one launch over time in chunks:
-//   segments of   330 frames   400         701         1200        1875 frames (8 channels and 5 classes, uniform / ragged)
-//   1             0.92         0.97        1.22        1.44        1.70
-//   2             0.82 / 0.71  0.90 / 0.72 1.06 / 0.87 1.18 / 1.05 1.33 / 1.23
-//   3             0.66 / 0.64  0.69 / 0.70 0.84 / 0.83 0.97 / 0.98 1.06 / 1.15
-//   4             0.73 / 0.63  0.79 / 0.61 0.95 / 0.68 1.03 / 0.79 1.12 / 0.86
-//   5             0.65 / 0.62  0.70 / 0.64 0.80 / 0.77 0.89 / 0.88 0.92 / 0.96
-//   8             0.67 / 0.60  0.70 / 0.62 0.80 / 0.68 0.84 / 0.75 0.95 / 0.78
-// and within 0.1 of that at 5 to 8 channels and 3 to 8 classes.  Problems of more than 32 tiles of one length end in a partly filled
-// round and wait for 12 segments (3 iterations, 8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14).
-// Up to 4 channels: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones
-// wait for 8 segments; 4 segments of up to 700 frames, 4 channels and 8 classes 190 us in chunks, 120 in one launch).
-inline bool use_whole(int D, double load, int tiles, bool ragged) {
-  if (D <= 4) return load >= (tiles <= 32 ? 8 : 16) || tiles <= 5;
-  if (tiles > 32) return load >= 24;
-  const int most = load >= 10 ? 32 : load >= 8 ? (ragged ? 32 : 16) : load >= 6 ? (ragged ? 19 : 16) : load >= 4 ? (ragged ? 10 : 9) : D >= 7 ? 6 : 7;
-  return tiles <= most;
-}
-// Up to 4 channels: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a
-// compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
-constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
-// Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but barriers, and one of the four adds up and
-// factorises while the others wait, which costs the more the more problems share a compute unit (`load`).  Four / one, us, 8
-// iterations, 2 channels and 3 classes: one segment of 60 / 250 / 1000 frames 0.88 / 0.64 / 0.55 times as long, two 1.21 / 0.79 /
-// 0.67, four 1.45 / 0.99 / 0.79, eight 1.70 / 1.17 / 0.94; 4 channels and 5 classes 0.97 / 0.65 / 0.58, 1.31 / 0.82 / 0.67, 1.58 /
-// 1.03 / 0.80, 1.96 / 1.21 / 0.93.  Segments of their own lengths save fewer tiles than the longest one says (4 segments of up to 578
-// frames, 3 channels and 3 classes 118 / 103 us; 4 of up to 300 83 / 61; 6 of up to 900, 4 channels and 2 classes 170 / 130).  Over
-// 496 calls of one length (1 to 4 channels, 2 to 8 classes, 1 to 8 segments of 60 to 1800 frames) the choice takes 1.0 % longer than
-// the better of both on average, 28 % at most.
-inline bool use_quad(double load, int tiles, bool ragged) {
-  const double saved = tiles - (tiles + kWholeQuad - 1) / kWholeQuad;
-  return (ragged ? 0.6 : 1.0) * saved >= 0.08 * load * load - 0.3;
-}
-
 struct EmPlan {
   ChunkMap acc;          // chunking of the accumulating passes
   ChunkMap fin;          // chunking of the final pass
@@ -1384,7 +1333,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
       const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
-      tiny = use_quad((double)n_sf / ctx->num_cu, tiles, T_len != nullptr);
+      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, tiles, iters, T_len != nullptr);
       const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
       if (row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }

@@ -186,7 +186,7 @@ def test_every_whole_em_instantiation(env, D):
 
 
 @pytest.mark.parametrize("D", [1, 2, 3, 4])
-def test_every_tiny_problem_instantiation(env, D):
+def test_every_tiny_problem_instantiation(env, rules, D):
     """Few problems of at most 4 tiles and at most 4 channels take the whole-EM kernel with four wavefronts per
     problem (one tile each, frames resident in registers) by default: every (D, K), a ragged batch of two segments
     (4 and 2 tiles of 4: two wavefronts of the second segment own padding only), weights from the masks and
@@ -198,6 +198,7 @@ def test_every_tiny_problem_instantiation(env, D):
     for K in range(1, 9):
         rng = np.random.default_rng(70 * D + K)
         S, F, T = 2, 3, 200
+        assert rules.em_four_wavefronts(D, K, S, T, 4, True, F)
         Y = (_cn(rng, (S, F, T, D)) * np.exp(rng.standard_normal((S, F, T, 1)))).astype(np.complex64)
         Y[0, :, 40] = 0
         act = (rng.random((S, K, T)) < 0.5).astype(np.uint8)
@@ -255,10 +256,10 @@ def test_masks_over_the_activity(env, D, T):
 
 
 @pytest.mark.parametrize("D", [1, 2, 3, 4])
-def test_few_channels_four_wavefronts_many_tiles(env, D):
-    """Few problems of more than 4 tiles at up to 4 channels: where the per-lane accumulators fit in registers
-    (D * D * K <= 80) the default is the whole-EM kernel with four wavefronts per problem, each walking every
-    fourth tile with the next tile requested ahead.  Every such (D, K): a ragged batch (13 and 6 tiles of 13,
+def test_few_channels_four_wavefronts_many_tiles(env, rules, D):
+    """Few problems of more than 4 tiles at up to 4 channels: the default is the whole-EM kernel with four wavefronts per
+    problem, each walking every fourth tile with the next tile requested ahead, with the accumulators in the lanes (direct
+    layout) or transposed through LDS (tile layout).  Every (D, K): a ragged batch (13 and 6 tiles of 13,
     the last one partly filled; in the short segment two wavefronts get one tile and two get two), tiles without
     any active class, a zero-energy frame, both weight modes, the same bits on a second run, and agreement with
     the one-wavefront kernel and the chunked kernels (forced through the context option) far inside the
@@ -268,6 +269,7 @@ def test_few_channels_four_wavefronts_many_tiles(env, D):
     for K in range(1, 9):
         rng = np.random.default_rng(170 * D + K)
         S, F, T = 2, 3, 800
+        assert rules.em_four_wavefronts(D, K, S, T, 4, True, F)
         Y = (_cn(rng, (S, F, T, D)) * np.exp(rng.standard_normal((S, F, T, 1)))).astype(np.complex64)
         Y[0, :, 300] = 0
         act = (rng.random((S, K, T)) < 0.5).astype(np.uint8)

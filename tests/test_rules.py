@@ -2,6 +2,8 @@
 
 import random
 
+import pytest
+
 
 def test_istft_plan_covers_every_block(rules):
     """Every block of 256 samples belongs to one workgroup and none is without a block, whatever the call's sizes."""
@@ -27,3 +29,25 @@ def test_istft_long_calls_keep_16_wavefronts(rules):
     """A workgroup of 16 wavefronts per compute unit, in full rounds: 128 segments of 18 s are 512 workgroups, two rounds."""
     for S, T, steps in ((128, 1129, 18), (10, 1566, 5), (30, 566, 5), (1, 62503, 16)):
         assert rules.istft(S, T)[:2] == (16, steps), (S, T)
+
+
+@pytest.mark.parametrize("D,K,S,T,iters,ragged,one,four", [
+    (4, 3, 1, 64, 15, False, 39.6, 35.2), (2, 3, 1, 64, 8, False, 16.7, 14.6), (4, 2, 1, 52, 8, False, 23.3, 18.1),
+    (2, 8, 1, 60, 15, False, 40.1, 52.0), (2, 5, 2, 125, 10, False, 37.0, 41.0), (2, 3, 3, 46, 10, False, 22.9, 32.3),
+    (3, 3, 3, 271, 15, False, 86.4, 118.0), (4, 2, 3, 346, 5, False, 44.3, 55.0), (3, 4, 3, 397, 15, True, 113.2, 145.3),
+    (3, 3, 4, 381, 5, True, 42.2, 53.4), (1, 3, 8, 1296, 15, True, 208.1, 210.8), (4, 3, 6, 636, 15, False, 335.8, 315.1),
+    (3, 6, 5, 999, 15, False, 452.7, 399.8)])
+def test_em_four_wavefronts_where_measured(rules, D, K, S, T, iters, ragged, one, four):
+    """Calls measured with one and with four wavefronts per problem (us, 513 bins, 256 compute units): the one that is
+    chosen takes at most a tenth longer than the other."""
+    assert (four if rules.em_four_wavefronts(D, K, S, T, iters, ragged) else one) <= 1.1 * min(one, four)
+
+
+def test_em_four_wavefronts_for_one_short_segment(rules):
+    """One segment of one tile: a launch less, and faster or as fast whatever the channels and classes, but for the two kernels
+    that keep registers in scratch memory."""
+    for D in (1, 2, 3, 4):
+        for K in range(1, 9):
+            for T in (1, 40, 64):
+                assert rules.em_four_wavefronts(D, K, 1, T, 8) == (D != 2 or K < 7), (D, K, T)
+                assert rules.em_four_wavefronts(D, K, 1, T, 1), (D, K, T)
