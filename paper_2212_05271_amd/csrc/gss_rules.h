@@ -31,14 +31,17 @@ constexpr bool direct_layout(int D, int K, bool one) {
 //   4             0.73 / 0.63  0.79 / 0.61 0.95 / 0.68 1.03 / 0.79 1.12 / 0.86
 //   5             0.65 / 0.62  0.70 / 0.64 0.80 / 0.77 0.89 / 0.88 0.92 / 0.96
 //   8             0.67 / 0.60  0.70 / 0.62 0.80 / 0.68 0.84 / 0.75 0.95 / 0.78
-// and within 0.1 of that at 5 to 8 channels and 3 to 8 classes.  Problems of more than 32 tiles of one length end in a partly filled
-// round and wait for 12 segments (3 iterations, 8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14).
+// and within 0.1 of that at 5 to 8 channels and 3 to 8 classes.  With fewer problems than compute units the chunks of a problem have a
+// compute unit each: below load 0.7 5 tiles 0.91 to 1.14 (5 and 6 / 7 and 8 channels), 6 tiles 0.98 to 1.37, 8 and 9 1.33 to 2.0.  For
+// the loads between those of whole segments of 513 bins the line is on the safe side: 1.1 to 1.8 and 2.1 to 3.9 8 and 9 tiles 0.76
+// to 0.88, 10 to 12 0.82 to 1.01.  Problems of more than 32 tiles of one length end in a partly filled round and wait for 12
+// segments (3 iterations, 8 segments of 4000 frames 1.05 to 1.2, 12 segments 0.98 to 1.14).
 // Up to 4 channels: 0.5 to 0.95 times from 8 per compute unit on (4 channels, 5 classes, 2500 frames of one length 1.15: longer ones
 // wait for 8 segments; 4 segments of up to 700 frames, 4 channels and 8 classes 190 us in chunks, 120 in one launch).
 inline bool use_whole(int D, double load, int tiles, bool ragged) {
   if (D <= 4) return load >= (tiles <= 32 ? 8 : 16) || tiles <= 5;
   if (tiles > 32) return load >= 24;
-  const int most = load >= 10 ? 32 : load >= 8 ? (ragged ? 32 : 16) : load >= 6 ? (ragged ? 19 : 16) : load >= 4 ? (ragged ? 10 : 9) : D >= 7 ? 6 : 7;
+  const int most = load >= 10 ? 32 : load >= 8 ? (ragged ? 32 : 16) : load >= 6 ? (ragged ? 19 : 16) : load >= 4 ? (ragged ? 10 : 9) : load < 1 ? 5 : D >= 7 ? 6 : 7;
   return tiles <= most;
 }
 // Up to 4 channels: tiles in a row up to which a pass costs less than its launches; where two workgroups of four wavefronts fit a

@@ -37,6 +37,7 @@ extern "C" void istft_plan(long S, long T, int num_cu, long* out) {
   const IstftPlan p = plan_istft(S, T, num_cu);
   out[0] = p.waves; out[1] = p.steps; out[2] = p.per_seg;
 }
+extern "C" int em_whole(int D, double load, int tiles, int ragged) { return use_whole(D, load, tiles, ragged != 0); }
 extern "C" int em_quad(int D, int K, double load, int tiles, int iters, int ragged) { return use_quad(D, K, load, tiles, iters, ragged != 0); }
 """
 
@@ -57,6 +58,11 @@ def rules(tmp_path_factory):
             out = (ctypes.c_long * 3)()
             lib.istft_plan(ctypes.c_long(S), ctypes.c_long(T), ctypes.c_int(num_cu), out)
             return tuple(out)
+
+        @staticmethod
+        def em_one_launch(D, S, T, ragged=False, F=513, num_cu=256):
+            """Whether gss_cacgmm_em takes the whole-EM kernel with one wavefront per problem (5 to 8 channels)."""
+            return bool(lib.em_whole(D, ctypes.c_double(S * F / num_cu), (T + 63) // 64, int(ragged)))
 
         @staticmethod
         def em_four_wavefronts(D, K, S, T, iters, ragged=False, F=513, num_cu=256):

@@ -51,3 +51,12 @@ def test_em_four_wavefronts_for_one_short_segment(rules):
             for T in (1, 40, 64):
                 assert rules.em_four_wavefronts(D, K, 1, T, 8) == (D != 2 or K < 7), (D, K, T)
                 assert rules.em_four_wavefronts(D, K, 1, T, 1), (D, K, T)
+
+
+@pytest.mark.parametrize("D,K,S,T,F,one,chunks", [
+    (8, 5, 1, 348, 65, 132.8, 97.6), (8, 3, 1, 383, 65, 127.0, 104.5), (8, 2, 1, 346, 65, 115.5, 97.5), (8, 6, 3, 333, 65, 286.9, 228.4),
+    (7, 1, 1, 673, 65, 201.1, 131.0), (6, 4, 1, 300, 513, 0.92, 1.0), (8, 5, 1, 330, 513, 0.92, 1.0), (8, 5, 4, 701, 513, 0.95, 1.0),
+    (8, 5, 2, 1875, 513, 1.33, 1.0)])
+def test_em_one_launch_where_measured(rules, D, K, S, T, F, one, chunks):
+    """Calls of 5 to 8 channels measured in one launch and in chunks (us, or relative; 256 compute units): the faster one is chosen."""
+    assert rules.em_one_launch(D, S, T, False, F) == (one < chunks)
