@@ -260,15 +260,20 @@ __global__ __launch_bounds__(1024) void mvdr_ref(const double* __restrict__ pw, 
   double num = 0.0, den = 0.0;
   if (r < D) {
     const double2* __restrict__ p = reinterpret_cast<const double2*>(pw) + (long)s * F * D + r;
-    for (int f0 = j; f0 < F; f0 += 8 * 32) {
+    int f = j;
+    for (; f + 7 * 32 < F; f += 8 * 32) {
       double2 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = f0 + 32 * u < F ? p[(long)(f0 + 32 * u) * D] : make_double2(0.0, 0.0);
+      for (int u = 0; u < 8; ++u) v[u] = p[(long)(f + 32 * u) * D];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         num += v[u].x;
         den += v[u].y;
       }
+    }
+    for (; f < F; f += 32) {
+      num += p[(long)f * D].x;
+      den += p[(long)f * D].y;
     }
   }
   snum[r][j] = num;

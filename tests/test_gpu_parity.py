@@ -682,6 +682,30 @@ def test_reference_channel_choice(env):
         assert int(rf[0]) == 2 and np.linalg.norm(Xf[0] - Xo2) <= TOL_X * np.linalg.norm(Xo2)
 
 
+@pytest.mark.parametrize("F", [1, 31, 33, 224, 225, 256, 257, 480, 513])
+def test_reference_channel_sums_every_bin(env, F):
+    """The powers of a candidate are added up over the bins 256 at a time and the rest one by one: one loud bin (the first, one
+    behind the whole blocks, the last) decides the choice, as in the oracle (near ties apart)."""
+    o = env["o"]
+    D, T, checked = 4, 12, 0
+    for loud in sorted({0, min(F - 1, F // 256 * 256), F - 1}):
+        for seed in range(4):
+            rng = np.random.default_rng(1000 * F + 10 * loud + seed)
+            Y = _cn(rng, (F, T, D))
+            Y[loud] *= 100.0
+            Y = Y.astype(np.complex64)
+            g = rng.random((1, F, T)).astype(np.float32)
+            g = np.concatenate([g, 1.0 - g])
+            phi_k, phi_bg = o.masked_covariances(Y, g, 0)
+            pbl = o.load_background(phi_bg)
+            sc = np.sort(o.reference_channel_scores(o.souden_filters(phi_k, pbl), phi_k, pbl))[::-1]
+            _, rg = _gpu_mvdr(env, Y[None], g[None], None, [0], [-1])
+            if sc[0] - sc[1] > 1e-4 * sc[0]:
+                checked += 1
+                assert int(rg[0]) == o.mvdr(Y, g, 0)[1], (loud, seed)
+    assert checked >= 4
+
+
 def test_mvdr_target_class_and_literal_normalised_input(env):
     """Target other than 0, and the paper's literal reading (beamformer fed the unit-normalised Y)."""
     o = env["o"]
