@@ -682,6 +682,24 @@ def test_reference_channel_choice(env):
         assert int(rf[0]) == 2 and np.linalg.norm(Xf[0] - Xo2) <= TOL_X * np.linalg.norm(Xo2)
 
 
+@pytest.mark.parametrize("S,F,T", [(1, 3, 1024), (2, 5, 1025), (1, 4, 2049), (3, 200, 1030), (3, 200, 2049)])
+def test_mvdr_frames_per_workgroup(env, S, F, T):
+    """The beamformer's workgroups take 1024 frames of few problems and 2048 of many: lengths around both, a ragged batch."""
+    o = env["o"]
+    D, K = 3, 2
+    rng = np.random.default_rng(S * F + T)
+    Y = _cn(rng, (S, F, T, D)).astype(np.complex64)
+    g = rng.random((S, 1, F, T)).astype(np.float32)
+    g = np.concatenate([g, 1.0 - g], axis=1)
+    T_len = np.array([T, 1023, 1025][:S], dtype=np.int32)
+    Xg, _ = _gpu_mvdr(env, Y, g, T_len, [0] * S, [1] * S)
+    for s in range(S):
+        n = min(int(T_len[s]), T)
+        Xo, _, _ = o.mvdr(Y[s, :, :n], g[s, :, :, :n], 0, ref=1)
+        assert np.linalg.norm(Xg[s, :, :n] - Xo) <= TOL_X * np.linalg.norm(Xo)
+        assert np.all(Xg[s, :, n:] == 0)
+
+
 @pytest.mark.parametrize("F", [1, 31, 33, 224, 225, 256, 257, 480, 513])
 def test_reference_channel_sums_every_bin(env, F):
     """The powers of a candidate are added up over the bins 256 at a time and the rest one by one: one loud bin (the first, one
