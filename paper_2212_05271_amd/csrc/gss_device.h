@@ -429,28 +429,28 @@ constexpr SlotTable<D> make_slot_table() {
 }
 
 // The covariances of a tile: lane (tg, i) accumulates acc[n][k] += w_k[r] * (slot n of lane type i)[r] over the frames r of its group.
-// sY: [64][TileLayout<D>::row] doubles, sW: [64][WS] doubles (KW weights per frame).
-template <int D, int KW, int WS, int UNROLL = 2>
+// sY: [64][TileLayout<D>::row] doubles, sW: [64][WS] doubles (two weights per frame: target and background).
+template <int D, int WS>
 __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, const double* __restrict__ sW,
-                                                int tg, int i, double (&acc)[D][KW]) {
+                                                int tg, int i, double (&acc)[D][2]) {
   using L = TileLayout<D>;
   int o[L::reads];
 #pragma unroll
   for (int n = 0; n < L::reads; ++n) o[n] = tile_operand<D>(i, n);
   auto frame = [&](int r) {
-    double w[KW], e[D];
+    double w[2], e[D];
     double2 y[L::reads];
 #pragma unroll
-    for (int k = 0; k < KW; ++k) w[k] = sW[r * WS + k];
+    for (int k = 0; k < 2; ++k) w[k] = sW[r * WS + k];
 #pragma unroll
     for (int n = 0; n < L::reads; ++n) y[n] = *reinterpret_cast<const double2*>(&sY[r * L::row + o[n]]);
     tile_entries<D>(y, e);
 #pragma unroll
     for (int n = 0; n < D; ++n)
 #pragma unroll
-      for (int k = 0; k < KW; ++k) acc[n][k] = fma(w[k], e[n], acc[n][k]);
+      for (int k = 0; k < 2; ++k) acc[n][k] = fma(w[k], e[n], acc[n][k]);
   };
-#pragma unroll UNROLL
+#pragma unroll 2
   for (int j = 0; j < L::steps; ++j) frame(L::first(tg) + j * L::next);
   if constexpr (L::rest > 0) {
     if (tg < L::rest) frame(tg + L::steps * L::next);
@@ -458,66 +458,42 @@ __device__ __forceinline__ void accumulate_tile(const double* __restrict__ sY, c
 }
 
 // Reduction of the per-lane accumulators of a workgroup of kPassWaves wavefronts into packed partial
-// sums: out[k * E + packed index] for k < KW, matrix size D.  Sums are taken in a fixed order (frame
+// sums: out[k * E + packed index] for both matrices k of size D.  Sums are taken in a fixed order (frame
 // groups ascending, then wavefronts ascending).
 //   wbuf: LDS private to the calling wavefront, reduce_wave_doubles(D) doubles (its tile region);
-//   red:  LDS scratch of the workgroup, kPassWaves * 64 * KW doubles, may overlap the wbuf regions.
+//   red:  LDS scratch of the workgroup, kPassWaves * 128 doubles, may overlap the wbuf regions.
 // The function starts with a barrier (every wavefront is done with its tiles).  First every wavefront
-// sums over its frame groups through its own LDS region, two classes at a time: entry n of all lanes
-// goes out as one contiguous row (lane = D tg + i), and lane o = D n + i reads the values of slot
-// (i, n) back.  Then the wavefronts' sums meet in `red`.
+// sums over its frame groups through its own LDS region: entry n of all lanes goes out as one contiguous
+// row (lane = D tg + i), and lane o = D n + i reads the values of slot (i, n) back (lanes from D * D on: the last
+// slot once more).  Then the wavefronts' sums meet in `red`.
 constexpr int kReduceRow = 72;                         // doubles per row of 64 (+ 8: spreads the banks)
 __host__ __device__ constexpr int reduce_wave_doubles(int D) { return 2 * D * kReduceRow; }
-// The wavefront's sums over the frame groups of the classes k0 and k0 + 1 (as far as they exist): S[c] of lane o = D n + i is
-// slot (i, n) of class k0 + c (lanes from D * D on: a copy of the last slot).
-template <int D, int KW>
-__device__ __forceinline__ void sum_frame_groups(const double (&acc)[D][KW], int k0, double* __restrict__ wbuf, int lane,
-                                                 double (&S)[2]) {
-  using L = TileLayout<D>;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    if (k0 + c < KW) {
-#pragma unroll
-      for (int n = 0; n < D; ++n) wbuf[(c * D + n) * kReduceRow + lane] = acc[n][k0 + c < KW ? k0 + c : 0];
-    }
-  }
-  wave_lds_sync();
-  const int o = lane < D * D ? lane : D * D - 1;
-  const int n = o / D, i = o - n * D;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    double sum = 0.0;
-    if (k0 + c < KW) {
-#pragma unroll
-      for (int tg = 0; tg < L::groups; ++tg) sum += wbuf[(c * D + n) * kReduceRow + tg * D + i];
-    }
-    S[c] = sum;
-  }
-  wave_lds_sync();
-}
-
-template <int D, int KW>
-__device__ __forceinline__ void reduce_and_store_partials(double (&acc)[D][KW], double* wbuf, double* red, double* __restrict__ out,
+template <int D>
+__device__ __forceinline__ void reduce_and_store_partials(const double (&acc)[D][2], double* wbuf, double* red, double* __restrict__ out,
                                                           int lane, int wave) {
   constexpr int E = D * D;
-  double S[KW + 1];
   __syncthreads();
 #pragma unroll
-  for (int k0 = 0; k0 < KW; k0 += 2) {
-    double S2[2];
-    sum_frame_groups<D, KW>(acc, k0, wbuf, lane, S2);
-    S[k0] = S2[0];
-    S[k0 + 1] = S2[1];
-  }
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int n = 0; n < D; ++n) wbuf[(k * D + n) * kReduceRow + lane] = acc[n][k];
+  wave_lds_sync();
+  const int o = lane < E ? lane : E - 1;
+  const int n = o / D, i = o - n * D;
+  double S[2] = {0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int tg = 0; tg < TileLayout<D>::groups; ++tg) S[k] += wbuf[(k * D + n) * kReduceRow + tg * D + i];
   __syncthreads();                           // the private regions are free: `red` may overlap them
 #pragma unroll
-  for (int k = 0; k < KW; ++k) red[(wave * KW + k) * 64 + lane] = S[k];
+  for (int k = 0; k < 2; ++k) red[(wave * 2 + k) * 64 + lane] = S[k];
   __syncthreads();
-  for (int x = threadIdx.x; x < 64 * KW; x += kWave * kPassWaves) {
+  for (int x = threadIdx.x; x < 2 * 64; x += kWave * kPassWaves) {
     const int k = x / 64, slot = x % 64;
     double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kPassWaves; ++w) sum += red[(w * KW + k) * 64 + slot];
+    for (int w = 0; w < kPassWaves; ++w) sum += red[(w * 2 + k) * 64 + slot];
     static constexpr SlotTable<D> kSlots = make_slot_table<D>();
     if (slot < E) out[k * E + kSlots.index[slot]] = kSlots.sign[slot] < 0 ? -sum : sum;
   }

@@ -90,7 +90,6 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 // Grid: blockIdx.x = chunk + C * (f + F * s).  A chunk is `tiles_per_chunk` tiles of 64 frames.
 // ----------------------------------------------------------------------------------------------
 
-constexpr int kPrefetchMaxAcc = 64;            // the whole-EM kernel requests the next tile ahead up to this many
 // Tile layout: the D * D packed entries of the outer product in blocks of 16, which phase 2 takes transposed (lane = entry of a
 // block), and up to 4 entries left over (6 and 7 channels), which a lane adds up for its own frame as in the direct layout.
 template <int D>
@@ -1004,8 +1003,8 @@ __global__ __launch_bounds__(256) void em_order_segments(gss_yview yv, const int
 __host__ __device__ constexpr bool request_ahead(int D, int K) { return D * K < 64; }
 
 // One pass of a wavefront of the whole-EM kernel over its tiles below tile_end: the one resident tile `pre` (ONE_TILE), or
-// tiles wave, wave + NW, ...  With the direct layout and not too many accumulators there are registers to spare, and the frames
-// of the next tile are requested from memory before the current tile is worked on.
+// tiles wave, wave + NW, ...  With the direct layout there are registers to spare (36 accumulators at most), and the frames of
+// the next tile are requested from memory before the current tile is worked on.
 template <int D, int K, int NW, bool ONE_TILE, PassKind KIND, bool RESIDENT, bool DIRECT, class MaskPtr>
 __device__ __forceinline__ void whole_pass(
     const float2* __restrict__ Yrow, const uint8_t* __restrict__ abrow, MaskPtr tmrow,
@@ -1019,7 +1018,7 @@ __device__ __forceinline__ void whole_pass(
       pass_tile<D, K, KIND, RESIDENT, DIRECT, TILE_KEEP>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax,
                                              wave * kWave, lane, __builtin_amdgcn_readfirstlane(my_mask), sY, acc,
                                              nacc, &pre);
-  } else if constexpr (DIRECT && D * D * K <= kPrefetchMaxAcc) {
+  } else if constexpr (DIRECT) {
     constexpr unsigned kmask = (1u << K) - 1u;
     TileRegs<D> cur{};                                   // (replaced below when the first tile is live)
     int tile = wave;
@@ -1044,7 +1043,7 @@ __device__ __forceinline__ void whole_pass(
       m = mn;
       tile = next;
     }
-  } else if constexpr (DIRECT || FINAL || !request_ahead(D, K)) {
+  } else if constexpr (FINAL || !request_ahead(D, K)) {
     for (int tile = wave; tile < tile_end; tile += NW)
       pass_tile<D, K, KIND, RESIDENT, DIRECT>(Yrow, abrow, creg, sC, cc, gamma_row, status, gamma_kstride, T, Tmax, tile * kWave,
                                        lane, tmrow[tile], sY, acc, nacc);

@@ -100,10 +100,10 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
     sW[lane * WS + 1] = valid ? wb : 0.0;
     if (tile + kPassWaves < tile_hi) load_tile(tile + kPassWaves);
     wave_lds_sync();
-    accumulate_tile<D, 2, WS>(sY, sW, tg, eg, acc);
+    accumulate_tile<D, WS>(sY, sW, tg, eg, acc);
     wave_lds_sync();
   }
-  reduce_and_store_partials<D, 2>(acc, sY, lds, part + (sf * C + chunk) * (long)(2 * E), lane, wave);
+  reduce_and_store_partials<D>(acc, sY, lds, part + (sf * C + chunk) * (long)(2 * E), lane, wave);
 }
 
 // ----------------------------------------------------------------------------------------------
