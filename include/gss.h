@@ -88,9 +88,9 @@ int64_t gss_scratch_bytes(const gss_ctx* ctx);
  * Tuning options of a context (host call, no device work).  Returns GSS_EINVAL for an unknown option.
  *   GSS_OPT_EM_WHOLE_MIN_PROBLEMS: gss_cacgmm_em* runs a batch with at least this many (segment, frequency)
  *     problems (and D <= 8) in its one-wavefront-per-problem kernel, smaller batches in the kernels that cut a
- *     problem over several workgroups.  value < 0 restores the default (by the number of problems, channels, frames
- *     and iterations); 0 always takes the one-wavefront-per-problem kernel.  Both give the same masks up to the order
- *     of the floating-point sums.
+ *     problem over several workgroups.  value < 0 restores the default (by the number of problems, channels, classes,
+ *     frames and iterations, and by whether T_len is given, all equal or not); 0 always takes the
+ *     one-wavefront-per-problem kernel.  All give the same masks up to the order of the floating-point sums.
  */
 #define GSS_OPT_EM_WHOLE_MIN_PROBLEMS 1
 int gss_set_option(gss_ctx* ctx, int option, int64_t value);

@@ -81,7 +81,8 @@ __global__ void em_init_coef(double* __restrict__ coef, double* __restrict__ cco
 //
 // Bound: the vector ALUs, with the clock held at 2.1 GHz by their power (2.4 GHz under a fill kernel), so what counts is the number
 // of vector instructions, not the waits.  With y and the weights in LDS and the products formed again from y by 8 lane types in
-// phase 2 a tile of 8 channels took about 830 of them, now 700 (of which the end of an iteration, shared by 17 tiles, is 90).
+// phase 2 a tile of 8 channels took about 830 of them with its share of the end of an iteration (shared by 17 tiles), now 665: 195 and 149
+// per live class (counted; 2.8 classes in a batch of speech), and a 17th of 949 (m_step_in_wave).
 // Times, us: 64 segments of up to 1875 frames, 8 channels, 5 classes, 15 iterations 15931 -> 14517; 3 segments of up to 701, 6
 // channels, 4 classes, 10 iterations 430 -> 350; 24 segments of up to 700, 5 iterations, 8 channels and 2 / 5 / 8 classes 730 -> 725
 // / 1079 -> 978 / 1971 -> 1281 (the accumulators no longer spill), 5 channels and 5 classes 653 -> 520.  Fewer tests of the class
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(kWave * kPassWaves, 2) void em_pass_small(
 // complex numbers: the rows of two classes are read without bank conflicts): an entry of the upper triangle is written to both
 // of its places, and a row is read with D loads and no choices.  The coefficients are collected from the inverse in the same
 // way.  A wavefront of a batch runs this once per iteration for 17 tiles on average (64 segments of up to 1875 frames), where it
-// was 1500 vector instructions of 700 per tile; now 900.
+// was 1500 vector instructions against the 610 of a tile; now 949.
 // ----------------------------------------------------------------------------------------------
 constexpr int kMatRow = 18;                              // doubles per row of a class matrix in LDS
 __host__ __device__ constexpr int mat_doubles(int D) { return D * kMatRow; }

@@ -69,7 +69,10 @@ __global__ __launch_bounds__(kWave * kPassWaves) void mvdr_cov_small(
   const int tile_end = (T + kWave - 1) / kWave;
   tile_hi = tile_hi < tile_end ? tile_hi : tile_end;
   // One tile of 64 frames per step; the loads of the wavefront's next tile are issued before the arithmetic
-  // of the current one.  The masks are read past the caches, which keep the observations for the beamformer.  A lane beyond T reads frame 0 (its weights are forced to zero).
+  // of the current one.  The masks are read past the caches in every call, so that these keep the observations for the
+  // beamformer (2 channels and 6 classes, past the caches / through them, us: 150 MB of observations 107 / 112, 260 MB 177 / 189; what
+  // fits the cache with its masks pays a little, 80 MB 66.8 / 63.9; 8 channels within 1 %).  A lane beyond T reads frame 0 (its
+  // weights are forced to zero).
   float2 yraw[D];
   float gv[GSS_MAX_K];
   auto load_tile = [&](int tile) {
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(256) void mvdr_apply_small(
     int ref_per_f) {
   // last row first: the covariances were formed from the first to the last, so the observations read last are still in the 256
   // MB cache (16 segments, 0.55 GB of observations: the whole call 332 -> 315 us; a call that fits the cache gains nothing), and
-  // where they do not all fit it the output and the masks go past it (STREAM; 315 -> 302, 2048 frames per workgroup 292)
+  // where they do not all fit it the output goes past it (STREAM, and the masks always; 315 -> 302, 2048 frames per workgroup 292)
   const unsigned block = gridDim.x - 1 - blockIdx.x;
   const int chunk = block % C;
   const long sf = block / C;
@@ -401,6 +404,8 @@ int run_mvdr_small(gss_ctx* ctx, const gss_yview& Y, const float* gamma, const i
   const int fpc = n_sf < ctx->num_cu ? 1024 : 2048;
   const int CA = (Tmax + fpc - 1) / fpc;
   if (n_sf * CA > 0x7fffffffL) return GSS_EUNSUPPORTED;
+  // (output through the caches / past them, us: 150 MB of observations 84.0 / 84.1 at 8 channels and 106.7 / 107.5 at 2, 220 MB 113.5 /
+  // 113.2 and 158 / 151, 320 MB 161 / 159 and 239 / 218)
   const bool past = (double)n_sf * Tmax * D * sizeof(float2) > 200e6;
   hipLaunchKernelGGL((past ? mvdr_apply_small<D, true> : mvdr_apply_small<D, false>), dim3((unsigned)(n_sf * CA)), dim3(256), 0, st, Y, H,
                      ref, T_len, X, F, Tmax, CA, fpc, ref_per_f);

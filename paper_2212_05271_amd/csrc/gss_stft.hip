@@ -161,8 +161,8 @@ __device__ __forceinline__ long share_begin(long w, long wgs, long n) { return (
 
 // ----------------------------------------------------------------------------------------------
 // STFT.  A workgroup of W wavefronts takes steps of (segment, frame) items; a step is UNITS units of W transforms, one per wavefront: a
-// unit is all channels of W / D consecutive frames, or 8 channels of a frame with more than 8 (W = 8).  The samples of the next unit are requested before the current transforms.  The spectrum replaces the transform in
-// the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and X[512 - k]), and the workgroup
+// unit is all channels of W / D consecutive frames, or 8 channels of a frame with more than 8 (W = 8).  The samples of the next unit
+// are requested before the current transforms.  The spectrum replaces the transform in the wavefront's LDS row (the lane that reads the pair Z[k], Z[512 - k] writes X[k] and X[512 - k]), and the workgroup
 // writes a bin's values of the step as one run of memory (128 bytes for two units of 8 channels).
 //
 // Bound: memory and latency.  W = 8: two workgroups per compute unit are resident, held there by 128 registers and, for two
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(64 * W, 4) void stft_kernel(const float* __restrict
     const int nr = nf * nd, q = by_frame ? per_unit * D : W;     // values per bin, of the first unit
     float2* __restrict__ out = Y + ((long)s * kBins * T + t) * D + d0;
     const long pitch = (long)T * D;
-    constexpr int kFull = W * UNITS, kShift = kFull == 8 ? 3 : kFull == 16 ? 4 : 5;        // (a full step: the first unit has 8 values)
+    constexpr int kFull = W * UNITS, kShift = kFull == 8 ? 3 : kFull == 16 ? 4 : 5;        // (a full step: the first unit has W values)
     if (nr == kFull) {
       for (int e = threadIdx.x; e < kBins * kFull; e += 64 * W)
         put<STREAM>(out + (e >> kShift) * pitch + (e & (kFull - 1)), rows[e & (kFull - 1)][e >> kShift]);
@@ -468,7 +468,10 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   const int per_unit = D <= 8 ? 8 / D : 1;
   // Long calls: 16 wavefronts per workgroup, runs of 256 bytes per bin (8 channels), one workgroup per compute unit.  8 / 16 wavefronts,
   // us: 8 channels, 512 MB 164 / 170, 640 MB 189 / 194, 768 MB 237 / 233, 1.23 GB 428 / 370, 3.8 GB 1673 / 1390; 6 channels 288 MB 138 /
-  // 136, 577 MB 315 / 251; 4 channels 616 MB 291 / 246; 5 channels 962 MB 608 / 426.
+  // 136, 577 MB 315 / 251; 4 channels 616 MB 291 / 246; 5 channels 962 MB 608 / 426.  On both sides of 300 MB, at 240 and 360 MB: 1
+  // channel 104 / 101 and 164 / 153, 2 channels 112 / 108 and 166 / 148, 3 channels 115 / 119 and 189 / 181, 5 channels 117 / 114 and
+  // 205 / 172, 7 channels 114 / 122 and 191 / 175.  (8 recordings of 4 channels whose frames are a multiple of 4: up to 1.09 times as
+  // long, 340 MB 121 / 133.)
   const double out_bytes = (double)S * kBins * T * D * sizeof(float2);
   const bool wide = D <= 8 && out_bytes > (D == 8 ? 700e6 : 300e6);
   const long steps1 = (n_items + per_unit - 1) / per_unit;

@@ -748,7 +748,7 @@ def test_stft_istft(env, S, D, N):
                                    (1, 32, 300), (700, 1, 1), (350, 1, 256 * 61), (330, 1, 256 * 90 + 3), (1, 8, 256 * 1100 + 9)])
 def test_stft_istft_edges(env, S, D, N):
     """Steps of several frames that end with a segment or with the items of an XCD, channel groups of 8 and 16 with a rest,
-    and inverse transforms of one and of several steps of eight frames per workgroup, with a last block that is cut."""
+    and inverse transforms of one and of several steps per workgroup, with a last block that is cut."""
     _check_stft_istft(env, S, D, N)
 
 
