@@ -1333,7 +1333,7 @@ int run_small(gss_ctx* ctx, const gss_yview& Y, const uint8_t* act, const int32_
       static const int ones_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, true>, kWave * kWholeQuad, 2);
       static const int walks_per_cu = resident_wgs(em_whole_small<D, K, kWholeQuad, false>, kWave * kWholeQuad, 2);
       const int quads_per_cu = tiles <= kWholeQuad ? ones_per_cu : walks_per_cu;
-      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, tiles, iters, T_len != nullptr);
+      tiny = use_quad(D, K, (double)n_sf / ctx->num_cu, tiles, iters, T_len ? S : 1);
       const int row = tiny ? (tiles + kWholeQuad - 1) / kWholeQuad + 1 : tiles;
       if (row <= whole_max_tiles(tiny, quads_per_cu)) whole = true;
     }

@@ -48,12 +48,12 @@ inline bool use_whole(int D, double load, int tiles, bool ragged) {
 // compute unit, the 513 problems of a segment take two rounds (4000 frames of 4 channels and 5 classes 1.2 times as long as in chunks).
 constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_per_cu <= 2 ? 12 : 25; }
 // Four wavefronts per problem instead of one, up to 4 channels: fewer tiles in a row, but barriers, and one of the four adds up and
-// factorises while the others wait, which costs the more the more problems share a compute unit (`load`): 0.85 `load` - 1.5 tiles.
-// Segments of their own lengths save fewer tiles than the longest one says.  A tile per wavefront: a launch goes as well (the
-// activity is read in place), which counts the more the fewer and shorter the iterations; at 2 channels and 7 or 8 classes that
-// kernel keeps 28 and 42 registers in scratch memory, which costs it 1.5 tiles (one tile of one segment 1.27).  The walk with the
-// direct layout: its sums and accumulators cost a tile at 2 channels and two, with two workgroups on a compute unit at most, at 3
-// and 4 (three segments of 6 or 7 tiles 1.25).
+// factorises while the others wait, which costs the more the more problems share a compute unit (`load`): 0.95 `load` - 1.9 tiles,
+// and 1.15 `load` at 2 channels, where one wavefront per problem leaves room for many.  `lengths` segments of their own lengths (1:
+// all alike) save fewer tiles than the longest one says.  A tile per wavefront: a launch goes as well (the activity is read in
+// place), which counts the more the fewer and shorter the iterations; at 2 channels and 7 or 8 classes that kernel keeps 28 and 42
+// registers in scratch memory, which costs it 1.5 tiles (one tile of one segment 1.27).  Of the walks with the direct layout at 3
+// and 4 channels two workgroups fit a compute unit: 2.5 tiles (three segments of 6 or 7 tiles 1.25).
 // Four / one, time of the call, 5 iterations and more, mean over 1 to 4 channels and 2 to 8 classes:
 //   tiles         1     2     3     4     5-6   7-9   10-14 15-22 23-30
 //   1 segment     0.92  0.80  0.75  0.65  0.75  0.68  0.62  0.56  0.53    (513 bins: load 2)
@@ -63,16 +63,17 @@ constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_pe
 //   6             1.73  1.37  1.16  1.12  1.19  1.02  0.96  0.90  0.92
 //   9 to 24       1.98  1.56  1.44  1.27  1.38  1.26  1.14  1.06  0.99
 // and with 1 to 3 iterations one tile of 1, 2, 3, 6 segments 0.82, 0.90, 1.06, 1.48.  Over 4122 calls (1 to 8 classes, 1 to 24 segments
-// of 30 to 1900 frames, 33 to 513 bins, 1 to 15 iterations) the choice takes 0.37 % longer than the better of both on average,
-// and more than a fifth longer in 8 of them.  (By `load` squared and the tiles alone: 1.8 %, more than a fifth in 131.)
+// of 30 to 1900 frames, 33 to 513 bins, 1 to 15 iterations) the choice takes 0.4 % longer than the better of both on average,
+// and more than a tenth longer in 55 of them (by `load` squared and the tiles alone 1.8 % and 300); over 1721 calls of 2 to 4 channels,
+// 125 frames and 5 iterations or more, two thirds of them with lengths of their own, 0.07 % and 3.
 constexpr int kWholeQuad = 4;                 // wavefronts per problem of the variant for few problems
 constexpr int kWholeQuadMaxD = 4;             // ... which is built for up to this many channels
-inline bool use_quad(int D, int K, double load, int tiles, int iters, bool ragged) {
+inline bool use_quad(int D, int K, double load, int tiles, int iters, int lengths) {
   const int row = (tiles + kWholeQuad - 1) / kWholeQuad;
-  double saved = (ragged ? 0.7 : 1.0) * (tiles - row);
+  double saved = (lengths > 1 ? 0.65 + 0.45 / lengths : 1.0) * (tiles - row);
   if (row == 1) saved += 150.0 / ((double)iters * (D + 1) * (K + 2)) - (D == 2 && K >= 7 ? 1.5 : 0.0);
-  else if (direct_layout(D, K, false)) saved -= D < 3 ? D - 1 : 2;
-  return saved >= 0.85 * load - 1.5;
+  else if (D >= 3 && direct_layout(D, K, false)) saved -= 2.5;
+  return saved >= (D == 2 ? 1.15 : 0.95) * load - 1.9;
 }
 
 // ----------------------------------------------------------------------------------------------

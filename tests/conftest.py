@@ -38,7 +38,7 @@ extern "C" void istft_plan(long S, long T, int num_cu, long* out) {
   out[0] = p.waves; out[1] = p.steps; out[2] = p.per_seg;
 }
 extern "C" int em_whole(int D, double load, int tiles, int ragged) { return use_whole(D, load, tiles, ragged != 0); }
-extern "C" int em_quad(int D, int K, double load, int tiles, int iters, int ragged) { return use_quad(D, K, load, tiles, iters, ragged != 0); }
+extern "C" int em_quad(int D, int K, double load, int tiles, int iters, int lengths) { return use_quad(D, K, load, tiles, iters, lengths); }
 """
 
 
@@ -67,6 +67,6 @@ def rules(tmp_path_factory):
         @staticmethod
         def em_four_wavefronts(D, K, S, T, iters, ragged=False, F=513, num_cu=256):
             """Whether gss_cacgmm_em takes four wavefronts per problem (where it runs a problem in one workgroup)."""
-            return bool(lib.em_quad(D, K, ctypes.c_double(S * F / num_cu), (T + 63) // 64, iters, int(ragged)))
+            return bool(lib.em_quad(D, K, ctypes.c_double(S * F / num_cu), (T + 63) // 64, iters, S if ragged else 1))
 
     return Rules
