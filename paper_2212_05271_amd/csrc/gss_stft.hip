@@ -468,10 +468,10 @@ extern "C" int gss_stft(gss_ctx* ctx, const float* x, int S, int D, int64_t N, i
   const int per_unit = D <= 8 ? 8 / D : 1;
   // Long calls: 16 wavefronts per workgroup, runs of 256 bytes per bin (8 channels), one workgroup per compute unit.  8 / 16 wavefronts,
   // us: 8 channels, 512 MB 164 / 170, 640 MB 189 / 194, 768 MB 237 / 233, 1.23 GB 428 / 370, 3.8 GB 1673 / 1390; 6 channels 288 MB 138 /
-  // 136, 577 MB 315 / 251; 4 channels 616 MB 291 / 246; 5 channels 962 MB 608 / 426.  On both sides of 300 MB, at 240 and 360 MB: 1
-  // channel 104 / 101 and 164 / 153, 2 channels 112 / 108 and 166 / 148, 3 channels 115 / 119 and 189 / 181, 5 channels 117 / 114 and
-  // 205 / 172, 7 channels 114 / 122 and 191 / 175.  (8 recordings of 4 channels whose frames are a multiple of 4: up to 1.09 times as
-  // long, 340 MB 121 / 133.)
+  // 136, 577 MB 315 / 251; 4 channels 616 MB 291 / 246; 5 channels 962 MB 608 / 426.  Around 300 MB, at 270, 300, 320 and 360 MB, 16 over
+  // 8: 1 channel 0.99, 0.95, 0.95, 0.89, 2 channels 1.04, 0.95, 0.97, 0.94, 3 channels 1.04, 1.03, 0.99, 0.94, 4 channels 1.12, 1.00, 1.00,
+  // 0.98, 5 channels 0.97, 0.96, 0.95, 0.86, 6 channels 1.02, 0.98, 0.97, 0.92, 7 channels 1.05, 1.00, 0.97, 0.94.  (Single lengths of
+  // 4 channels suit 8 wavefronts far better than their neighbours do: 3 x 6496 frames, 320 MB, 118 / 132.)
   const double out_bytes = (double)S * kBins * T * D * sizeof(float2);
   const bool wide = D <= 8 && out_bytes > (D == 8 ? 700e6 : 300e6);
   const long steps1 = (n_items + per_unit - 1) / per_unit;
