@@ -53,7 +53,7 @@ constexpr int whole_max_tiles(bool quad, int wgs_per_cu) { return quad && wgs_pe
 // all alike) save fewer tiles than the longest one says.  A tile per wavefront: a launch goes as well (the activity is read in
 // place), which counts the more the fewer and shorter the iterations; at 2 channels and 7 or 8 classes that kernel keeps 28 and 42
 // registers in scratch memory, which costs it 1.5 tiles (one tile of one segment 1.27).  Of the walks with the direct layout at 3
-// and 4 channels two workgroups fit a compute unit: 2.5 tiles (three segments of 6 or 7 tiles 1.25).
+// and 4 channels two workgroups fit a compute unit: 1.2 `load` tiles (three segments of 6 or 7 tiles 1.25).
 // Four / one, time of the call, 5 iterations and more, mean over 1 to 4 channels and 2 to 8 classes:
 //   tiles         1     2     3     4     5-6   7-9   10-14 15-22 23-30
 //   1 segment     0.92  0.80  0.75  0.65  0.75  0.68  0.62  0.56  0.53    (513 bins: load 2)
@@ -72,7 +72,7 @@ inline bool use_quad(int D, int K, double load, int tiles, int iters, int length
   const int row = (tiles + kWholeQuad - 1) / kWholeQuad;
   double saved = (lengths > 1 ? 0.65 + 0.45 / lengths : 1.0) * (tiles - row);
   if (row == 1) saved += 150.0 / ((double)iters * (D + 1) * (K + 2)) - (D == 2 && K >= 7 ? 1.5 : 0.0);
-  else if (D >= 3 && direct_layout(D, K, false)) saved -= 2.5;
+  else if (D >= 3 && direct_layout(D, K, false)) return saved >= 1.2 * load;
   return saved >= (D == 2 ? 1.15 : 0.95) * load - 1.9;
 }
 

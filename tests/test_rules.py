@@ -37,7 +37,8 @@ def test_istft_long_calls_keep_16_wavefronts(rules):
     (3, 3, 3, 271, 15, False, 86.4, 118.0), (4, 2, 3, 346, 5, False, 44.3, 55.0), (3, 4, 3, 397, 15, True, 113.2, 145.3),
     (3, 3, 4, 381, 5, True, 42.2, 53.4), (1, 3, 8, 1296, 15, True, 208.1, 210.8), (4, 3, 6, 636, 15, False, 335.8, 315.1),
     (3, 6, 5, 999, 15, False, 452.7, 399.8), (3, 2, 1, 296, 15, True, 54.5, 47.3), (4, 6, 2, 140, 12, True, 99.6, 88.5),
-    (2, 6, 7, 1431, 20, True, 375.3, 433.4), (4, 2, 5, 893, 5, False, 105.1, 118.1)])
+    (2, 6, 7, 1431, 20, True, 375.3, 433.4), (4, 2, 5, 893, 5, False, 105.1, 118.1),
+    (4, 2, 3, 779, 10, True, 103.0, 118.0), (4, 2, 5, 1356, 19, True, 309.1, 349.8)])
 def test_em_four_wavefronts_where_measured(rules, D, K, S, T, iters, ragged, one, four):
     """Calls measured with one and with four wavefronts per problem (us, 513 bins, 256 compute units): the one that is
     chosen takes at most a tenth longer than the other."""
