@@ -224,6 +224,7 @@ __device__ __forceinline__ void pass_tile(
   const double n2c = fmax(n2, GSS_EPS_NORM_SQ);
   const double qfloor = GSS_EPS_Q * n2c;
   const double rq_first = KIND == PASS_FIRST ? rcp_f64_fast(fmax(n2, qfloor)) : 0.0;
+  const double p_first = fma(rq_first, 0.0, 1.0);     // 1, and for an infinite frame not a number, as q^-D is in the passes that follow
   double rq[K], v[K], Z = 0.0;
   static_for<0, K>([&](auto KI) {
     constexpr int k = KI.value;
@@ -231,7 +232,7 @@ __device__ __forceinline__ void pass_tile(
     v[k] = 0.0;
     if constexpr (KIND == PASS_FIRST) {
       rq[k] = rq_first;
-      v[k] = ((abits >> k) & 1u) ? 1.0 : 0.0;
+      v[k] = ((abits >> k) & 1u) ? p_first : 0.0;
       Z += v[k];
     } else if (class_on(tmask, k)) {
       double c[R], q[3] = {0.0, 0.0, 0.0};

@@ -595,6 +595,30 @@ def test_degenerate_frames(env):
     assert np.all(g[:, :, :, 100:] == 0) and env["ctx"].get_status() == 0
 
 
+@pytest.mark.parametrize("D,T", [(1, 40), (2, 300), (3, 200), (4, 700), (5, 100), (8, 100)])
+def test_infinite_samples(env, D, T):
+    """A frame with an infinite sample has no posterior and leaves the classes that are active in it without a count, in the first
+    iteration as in the others: where such a class meets one that is not, it has no weight."""
+    gss, ctx = env["gss"], env["ctx"]
+    rng = np.random.default_rng(D)
+    F, K = 5, 2
+    Y = _cn(rng, (1, F, T, D)).astype(np.complex64)
+    Y[:, :, 10, 0] = np.inf
+    act = np.ones((1, K, T), np.uint8)
+    act[0, 1, 10] = 0
+    for forced in (-1, 0, 1 << 40):
+        ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, forced)
+        try:
+            for iters in (1, 2, 4):
+                g = _gpu_em(env, Y, act, None, iters)
+                sel = np.arange(T) != 10
+                assert np.all(g[0, 1][:, 10] == 0)
+                assert np.max(g[0, 0][:, sel]) <= 1e-6 and np.min(g[0, 1][:, sel]) >= 1 - 1e-6, (forced, iters)
+        finally:
+            ctx.set_option(gss.GSS_OPT_EM_WHOLE_MIN_PROBLEMS, -1)
+    ctx.get_status()
+
+
 @pytest.mark.parametrize("D", [4, 8, 9, 24, 32])
 def test_zero_frame_flag(env, D):
     """A frame without energy is flagged wherever its stretch of 64 frames has an active class, whether or not one is active
